@@ -1299,47 +1299,52 @@ rbc_status rbc_ensemble_get_state(rbc_handle h, int32_t slot, double *x, double 
     return state_slot(h, slot, x, nrm, v, w);
 }
 
+// The single system's pairs: their number (sync), and the first m of them, sorted, to the
+// host through the device buffer `dev`.
+static rbc_status count_pairs(rbc_handle h, int64_t &count) {
+    HostSys &hs = h->sys[0];
+    if (!runs(hs)) return RBC_OK;            // a frozen slot has no descriptor: no pairs
+    Scope sc(h);
+    const int64_t at = launch_pair_count(h->L, 0, (int)hs.n);
+    HIPCHK(hipMemcpyAsync(&count, (const int64_t *)hs.dev.hist + at, sizeof(int64_t), hipMemcpyDeviceToHost, h->st));
+    HIPCHK(hipStreamSynchronize(h->st));
+    return RBC_OK;
+}
+
+static rbc_status fill_pairs(rbc_handle h, int32_t *dev, int64_t m, int32_t *ij) {
+    Scope sc(h);
+    launch_pair_fill(h->L, 0, (int)h->sys[0].n, dev, m);
+    HIPCHK(hipMemcpyAsync(ij, dev, sizeof(int32_t) * 2 * (size_t)m, hipMemcpyDeviceToHost, h->st));
+    HIPCHK(hipStreamSynchronize(h->st));
+    return RBC_OK;
+}
+
 rbc_status rbc_get_pairs(rbc_handle h, int64_t cap, int32_t *ij, int64_t *npairs) {
     if (!h || !npairs || cap < 0 || (cap > 0 && !ij)) return RBC_ERR_INVALID_ARG;
     HostSys &hs = h->sys[0];
     if (!hs.live) return fail(h, RBC_ERR_NOT_READY, "no system loaded");
     if (any_pending(h)) return fail(h, RBC_ERR_NOT_READY, "staged systems wait for rbc_ensemble_commit");
-    int64_t want = std::max<int64_t>(1024, 32 * hs.n);
-    for (int attempt = 0; attempt < 2; ++attempt) {
-        if (hs.pairs_cap < want) {
-            if (hs.pairs_mem) { hipStreamSynchronize(h->st); hipFree(hs.pairs_mem); }
+    int64_t count = 0;
+    const rbc_status r = count_pairs(h, count);
+    if (r != RBC_OK) return r;
+    const int64_t m = std::min(cap, count);
+    if (m > 0) {
+        if (hs.pairs_cap < m) {
+            if (hs.pairs_mem) hipFree(hs.pairs_mem);         // idle: count_pairs waited for the stream
             hs.pairs_mem = nullptr;
-            if (hipMalloc(&hs.pairs_mem, sizeof(int32_t) * 2 * want) != hipSuccess)
+            hs.pairs_cap = 0;
+            const int64_t want = m + m / 8 + 1024;           // room for the pairs of later frames
+            if (hipMalloc(&hs.pairs_mem, sizeof(int32_t) * 2 * want) != hipSuccess) {
+                hs.pairs_mem = nullptr;
                 return fail(h, RBC_ERR_OUT_OF_MEMORY, "pair export buffer");
+            }
             hs.pairs_cap = want;
-            hs.dev.pairs = (int32_t *)hs.pairs_mem;
-            hs.dev.pairs_cap = want;
-            rbc_status r = refresh_tables(h);
-            if (r != RBC_OK) return r;
         }
-        int32_t count = 0;
-        {
-            Scope sc(h);
-            HIPCHK(hipMemsetAsync(&h->d_sc[0].npairs, 0, sizeof(int32_t), h->st));
-            launch_export_pairs(h->L, 0, (int)hs.n, hs.dev.pairs, hs.pairs_cap, &h->d_sc[0].npairs);
-            HIPCHK(hipMemcpyAsync(&count, &h->d_sc[0].npairs, sizeof(int32_t), hipMemcpyDeviceToHost, h->st));
-            HIPCHK(hipStreamSynchronize(h->st));
-        }
-        if (count > hs.pairs_cap) { want = count; continue; }
-        std::vector<int32_t> buf(2 * (size_t)count);
-        if (count > 0) HIPCHK(hipMemcpy(buf.data(), hs.pairs_mem, sizeof(int32_t) * 2 * count, hipMemcpyDeviceToHost));
-        std::vector<int64_t> keys(count);
-        for (int32_t q = 0; q < count; ++q) keys[q] = ((int64_t)buf[2 * q] << 32) | (uint32_t)buf[2 * q + 1];
-        std::sort(keys.begin(), keys.end());
-        const int64_t m = std::min<int64_t>(cap, count);
-        for (int64_t q = 0; q < m; ++q) {
-            ij[2 * q] = (int32_t)(keys[q] >> 32);
-            ij[2 * q + 1] = (int32_t)(keys[q] & 0xffffffff);
-        }
-        *npairs = count;
-        return RBC_OK;
+        const rbc_status e = fill_pairs(h, (int32_t *)hs.pairs_mem, m, ij);
+        if (e != RBC_OK) return e;
     }
-    return fail(h, RBC_ERR_CAPACITY, "pair export overflow");
+    *npairs = count;
+    return RBC_OK;
 }
 
 rbc_status rbc_get_pairs_noalloc(rbc_handle h, int64_t cap, int32_t *ij, int64_t *npairs) {
@@ -1348,28 +1353,16 @@ rbc_status rbc_get_pairs_noalloc(rbc_handle h, int64_t cap, int32_t *ij, int64_t
     if (!hs.live) return fail(h, RBC_ERR_NOT_READY, "no system loaded");
     if (any_pending(h)) return fail(h, RBC_ERR_NOT_READY, "staged systems wait for rbc_ensemble_commit");
     if (!h->pair_scratch) return fail(h, RBC_ERR_HIP, "no staging for the allocation-free export on this device");
-    int32_t *counter = h->pair_scratch;
     int32_t *out = h->pair_scratch + 64;                 // pairs from byte 256
-    int32_t count = 0;
-    {
-        Scope sc(h);
-        launch_zero_counter(h->L, counter);
-        launch_export_pairs(h->L, 0, (int)hs.n, out, PAIR_SCRATCH_PAIRS, counter);
-        HIPCHK(hipMemcpyAsync(&count, counter, sizeof(int32_t), hipMemcpyDeviceToHost, h->st));
-        HIPCHK(hipStreamSynchronize(h->st));
-    }
-    if ((int64_t)count > PAIR_SCRATCH_PAIRS)
+    int64_t count = 0;
+    const rbc_status r = count_pairs(h, count);
+    if (r != RBC_OK) return r;
+    if (count > PAIR_SCRATCH_PAIRS)
         return fail(h, RBC_ERR_CAPACITY, std::to_string(count) + " pairs exceed the allocation-free export's " +
                                              std::to_string(PAIR_SCRATCH_PAIRS));
     *npairs = count;
     if (cap < count || count == 0) return RBC_OK;        // a size query: nothing written
-    HIPCHK(hipMemcpy(ij, out, sizeof(int32_t) * 2 * (size_t)count, hipMemcpyDeviceToHost));
-    struct Pair {
-        int32_t i, j;
-    };
-    Pair *p = reinterpret_cast<Pair *>(ij);               // sorted in the caller's buffer, in place
-    std::sort(p, p + count, [](const Pair &a, const Pair &b) { return a.i != b.i ? a.i < b.i : a.j < b.j; });
-    return RBC_OK;
+    return fill_pairs(h, out, count, ij);
 }
 
 static rbc_status energy_slot(rbc_handle h, int32_t slot, double *out) {

@@ -66,8 +66,7 @@ struct alignas(256) SysScal {
     int32_t nlrows;                   // largest neighbour-list row count of the last build
     int32_t cnbr_total;
     int32_t cnbr_maxrow;
-    int32_t npairs;
-    int32_t pad0, pad1;
+    int32_t pad0, pad1, pad2;
     double slo[3], shi[3];            // seed bounding box (Morton quantisation)
     double glo[3], gh[3];             // seed-grid origin and spacing
     int32_t gdim[3];
@@ -135,8 +134,6 @@ struct SysDev {
     double *epart;                                  // per-chunk energy partials (nchunk x 9)
     double *vpart;                                  // per-chunk lipid sums for the volume (8 x nchunk)
     double *vred;                                   // their first-level reduction (32 x 8)
-    int32_t *pairs;                                 // scratch for exporting the pair set
-    int64_t pairs_cap;
     int32_t *stage, *scount;                        // per 256-particle block: staged slots (SMAX), count (-1: none)
     uint16_t *il16;                                 // pruned lists: indices into the pruned stage (0xffff pads)
     int32_t *ilk;                                   // per chunk: rows of the pruned list
@@ -344,11 +341,13 @@ void launch_volume_partials(const LaunchCtx &L);          // lipid sums of the c
 void launch_volume_reduce(const LaunchCtx &L);            // lipid sums -> V, volume force constants
 void launch_scatter_state(const LaunchCtx &L, int sys, double *x, double *n, double *v, double *w, int count);
 void launch_scatter_forces(const LaunchCtx &L, int sys, double *F, double *T, int count);
-void launch_export_pairs(const LaunchCtx &L, int sys, int count, int32_t *out, int64_t cap, int32_t *counter);
-// the allocation-free export's staging: a counter word, then pairs from byte 256
+// the sorted pairs of a system: count them (the number ends in its hist, as 64 bits, at
+// the index returned), then write the first cap of them
+int64_t launch_pair_count(const LaunchCtx &L, int sys, int count);
+void launch_pair_fill(const LaunchCtx &L, int sys, int count, int32_t *out, int64_t cap);
+// the allocation-free export's staging: pairs from byte 256
 constexpr int64_t PAIR_SCRATCH_PAIRS = ((32ll << 20) - 256) / 8;
 hipError_t pair_scratch_address(int device, void **out);   // this device's copy (it must be current)
-void launch_zero_counter(const LaunchCtx &L, int32_t *p);
 // cell update kernels (each predicated on SysScal::rebuild)
 void launch_set_rebuild(const LaunchCtx &L, const unsigned long long m[4]);
 void launch_restrict_maps(const LaunchCtx &L, int32_t *out);   // 7 x (nsys+1) prefix maps of the rebuilding systems
