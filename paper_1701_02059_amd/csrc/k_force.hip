@@ -513,6 +513,93 @@ __device__ __forceinline__ float lipid_coef(const DevParams &P, float dx, float 
     return U;
 }
 
+// sqrt(r2) and its reciprocal to within an ulp, from the hardware's approximate
+// reciprocal square root by two Goldschmidt steps and a correction of each (10 fused
+// multiply-adds; the library's square root and division take about 35 instructions
+// with their scaling for subnormal and huge arguments, which squared separations are not).
+__device__ __forceinline__ void sqrt_rsqrt(double r2, double &r, double &rinv) {
+    const double y = __builtin_amdgcn_rsq(r2);
+    double g = r2 * y, h = 0.5 * y;
+    const double e = fma(-h, g, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+    r = fma(fma(-g, g, r2), h, g);
+    rinv = 2.0 * h;
+    rinv = fma(fma(-r, rinv, 1.0), rinv, rinv);
+}
+
+// The lipid-lipid law of the FP64 step kernel in the same coefficient form,
+//   force on i  = -(A e + bi n_i + bj n_j),    g_i = cn n_j + ce e,
+// for a pair in range.  Both radial branches are evaluated and selected: a wavefront
+// nearly always holds lanes of both.
+template <bool FAST, bool ENERGY>
+__device__ __forceinline__ double lipid_coef64(const DevParams &P, double dx, double dy, double dz, double r2, double nix,
+                                               double niy, double niz, double njx, double njy, double njz, double &ex,
+                                               double &ey, double &ez, double &A, double &bi, double &bj, double &cn,
+                                               double &ce) {
+    const double eps = P.eps, mu = P.mu, rmin = P.r_min, st0 = FAST ? 0.0 : P.st0;
+    double r, rinv;
+    sqrt_rsqrt(r2, r, rinv);
+    ex = dx * rinv;
+    ey = dy * rinv;
+    ez = dz * rinv;
+    const double s = nix * ex + niy * ey + niz * ez;
+    const double t = njx * ex + njy * ey + njz * ez;
+    const double c = nix * njx + niy * njy + niz * njz;
+    double a = c - s * t;
+    if (!FAST) a += st0 * (t - s) - st0 * st0;
+    const double phi = fma(mu, a, 1.0 - mu);
+    // repulsive core
+    const double q = (rmin * rinv) * (rmin * rinv);
+    const double dUdrR = (4.0 * eps) * ((q - q * q) * rinv);
+    // attractive well: x = (pi/2) u = 2 h with h in [0, pi/4], Taylor series of sin h / h and
+    // cos h (terms through h^14 and h^16; the first omitted ones are below 1e-16), then the
+    // double angle; a core lane's h is a small negative number and its result unused
+    const double h = (0.25 * M_PI * P.inv_w) * (r - rmin), h2 = h * h;
+    double sp = -1.0 / 1307674368000.0;
+    sp = fma(sp, h2, 1.0 / 6227020800.0);
+    sp = fma(sp, h2, -1.0 / 39916800.0);
+    sp = fma(sp, h2, 1.0 / 362880.0);
+    sp = fma(sp, h2, -1.0 / 5040.0);
+    sp = fma(sp, h2, 1.0 / 120.0);
+    sp = fma(sp, h2, -1.0 / 6.0);
+    const double sh = fma(h * h2, sp, h);
+    double cp = 1.0 / 20922789888000.0;
+    cp = fma(cp, h2, -1.0 / 87178291200.0);
+    cp = fma(cp, h2, 1.0 / 479001600.0);
+    cp = fma(cp, h2, -1.0 / 3628800.0);
+    cp = fma(cp, h2, 1.0 / 40320.0);
+    cp = fma(cp, h2, -1.0 / 720.0);
+    cp = fma(cp, h2, 1.0 / 24.0);
+    cp = fma(cp, h2, -0.5);
+    const double ch = fma(cp, h2, 1.0);
+    const double sx = 2.0 * sh * ch, cx = (ch - sh) * (ch + sh);
+    const double c2 = cx * cx;
+    double cz1;                                          // cos^(2 zeta - 2)
+    if (FAST) cz1 = (c2 * c2) * c2;
+    else cz1 = ipow(c2, P.zeta - 1);
+    const double c2z = cz1 * c2;
+    const double dUdrA = (phi * P.dudr_k) * ((sx * cx) * cz1);
+    const bool rep = r < rmin;
+    const double dUdr = rep ? dUdrR : dUdrA;
+    const double dUda = rep ? -mu * eps : (-mu * eps) * c2z;
+    const double k = dUda * rinv;
+    const double kt = k * t, ks = k * s;
+    double ge2 = 2.0 * kt * s;                           // -k g.e
+    if (!FAST) ge2 -= k * st0 * (t - s);
+    A = dUdr + ge2;
+    bi = -kt;
+    bj = -ks;
+    if (!FAST) {
+        bi -= k * st0;
+        bj += k * st0;
+    }
+    cn = -dUda;
+    ce = dUda * (FAST ? t : t + st0);
+    if (!ENERGY) return 0.0;
+    return rep ? eps * (q * q - 2.0 * q) + (1.0 - phi) * eps : -eps * c2z * phi;
+}
+
 // LDS stage per 256-particle block (structure of arrays): FP64 positions, and either
 // FP32 orientations with the type in w (mixed) or FP64 orientations and a type byte.
 // The stage is the block's pruned partner set; entries beyond the LDS part (rare)
@@ -825,6 +912,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
             return c;
         };
         Rec rec = fetch(e_cur);
+        double sbi = 0.0, gx = 0.0, gy = 0.0, gz = 0.0;       // sum of bi; of g_i - cn n_i
         for (int r = 0; r < nr; ++r) {
             const int e = e_cur;
             const Rec c = rec;
@@ -833,7 +921,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
             e_n2 = e_n3;
             e_n3 = (valid && r + 4 < nr) ? (int)ldg(col + (r + 4) * cstep) : 0xffff;
             rec = fetch(e_cur);
-            if (e >= scnt) continue;
             const int tj = c.t;
             double dx, dy, dz, d2;
             if constexpr (PER) {
@@ -841,22 +928,45 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
             } else {
                 d2 = dist2_open(pi.x, pi.y, pi.z, c.x, c.y, c.z, dx, dy, dz);
             }
-            const double rc2 = sel_cut(tj, rcA, rcB, rcC);
-            if (!(d2 < rc2)) continue;
-            T ax = 0, ay = 0, az = 0, u;
-            if ((ti | tj) == 0)
-                u = lipid_pair<T, FAST>(P, (T)dx, (T)dy, (T)dz, nix, niy, niz, c.nx, c.ny, c.nz, ax, ay, az, tx, ty,
-                                        tz);
-            else
-                u = wca_pair<T>(P, (T)dx, (T)dy, (T)dz, ax, ay, az);
-            fx += ax;
-            fy += ay;
-            fz += az;
-            if (ENERGY) {
-                U += 0.5 * (double)u;
-                W += 0.5 * (dx * (double)ax + dy * (double)ay + dz * (double)az);
+            const bool in = e < scnt && d2 < sel_cut(tj, rcA, rcB, rcC);
+            const bool lip = (ti | tj) == 0;
+            if (in && lip) {
+                double ex, ey, ez, A, bi, bj, cn, ce;
+                const double u = lipid_coef64<FAST, ENERGY>(P, dx, dy, dz, d2, nix, niy, niz, c.nx, c.ny, c.nz, ex, ey, ez,
+                                                            A, bi, bj, cn, ce);
+                fx = fma(-bj, c.nx, fma(-A, ex, fx));
+                fy = fma(-bj, c.ny, fma(-A, ey, fy));
+                fz = fma(-bj, c.nz, fma(-A, ez, fz));
+                sbi += bi;
+                gx = fma(ce, ex, fma(cn, c.nx - nix, gx));
+                gy = fma(ce, ey, fma(cn, c.ny - niy, gy));
+                gz = fma(ce, ez, fma(cn, c.nz - niz, gz));
+                if (ENERGY) {
+                    U += 0.5 * u;
+                    W -= 0.5 * (dx * (A * ex + bi * nix + bj * c.nx) + dy * (A * ey + bi * niy + bj * c.ny) +
+                                dz * (A * ez + bi * niz + bj * c.nz));
+                }
+            }
+            if (__builtin_expect(__ballot(in && !lip) != 0ull, 0)) {
+                if (in && !lip) {
+                    T ax = 0, ay = 0, az = 0;
+                    const double u = wca_pair<T>(P, (T)dx, (T)dy, (T)dz, ax, ay, az);
+                    fx += ax;
+                    fy += ay;
+                    fz += az;
+                    if (ENERGY) {
+                        U += 0.5 * u;
+                        W += 0.5 * (dx * ax + dy * ay + dz * az);
+                    }
+                }
             }
         }
+        fx -= sbi * nix;
+        fy -= sbi * niy;
+        fz -= sbi * niz;
+        tx += niy * gz - niz * gy;
+        ty += niz * gx - nix * gz;
+        tz += nix * gy - niy * gx;
     };
 
     if (scnt >= 0) {
