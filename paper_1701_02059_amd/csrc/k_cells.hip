@@ -1323,50 +1323,50 @@ __device__ __forceinline__ int union_cell(const int *ofs, int nsc, int u) {
     return lo;
 }
 
-// Smallest and largest coordinates of each wavefront's particles (FP32 offsets;
-// lanes without a particle pass +inf and -inf), in s_b[6 w .. 6 w + 5].
-__device__ __forceinline__ void chunk_box(const float lo_in[3], const float hi_in[3], float *s_b) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    float mn[3] = {lo_in[0], lo_in[1], lo_in[2]}, mx[3] = {hi_in[0], hi_in[1], hi_in[2]};
-    for (int off = 32; off > 0; off >>= 1)
-        for (int a = 0; a < 3; ++a) {
-            mn[a] = fminf(mn[a], __shfl_xor(mn[a], off));
-            mx[a] = fmaxf(mx[a], __shfl_xor(mx[a], off));
-        }
-    if (lane == 0)
-        for (int a = 0; a < 3; ++a) {
-            s_b[w * 6 + a] = mn[a];
-            s_b[w * 6 + 3 + a] = mx[a];
-        }
-}
+// One block per 256 consecutive cell-sorted particles (four 64-particle chunks), whose
+// cells are consecutive: the block's own cells.
+//  - Candidate cells: the cell-pair entries of the own cells, sorted and deduplicated in
+//    LDS (the union).
+//  - Stage: the union's particles that lie within the list radius of some own cell's
+//    bounding sphere, of those own cells that pair with the particle's cell (a 64-bit
+//    mask per union cell), cell by cell as FP32 offsets from the block's first particle
+//    with slot and type packed in w.  A superset of the block's partners.
+//  - Candidate lists: for each own cell the stage entries within the list radius of its
+//    bounding sphere, written by one wavefront as 16-bit stage indices.  Every particle
+//    of a cell scans the same short list (about 150 entries for 47 partners at skin
+//    0.65), so that the wavefront's lanes run through it together.  The lists are placed
+//    by an upper bound (the staged sizes of the paired cells), as many cells at a time
+//    as fit the buffer; nearly always that is all of them.
+//  - Lists: each lane keeps every partner within the list radius (rc + 2 skin of the
+//    pair's types).  The test runs in FP32 against the radius widened by 1e-3 sigma,
+//    which bounds the offsets' rounding (offsets are limited to 4096 sigma), so the list
+//    is a superset of the FP64 one; the step kernel decides every pair exactly.  The
+//    16-bit lists hold stage indices (0xffff pads).
+// Blocks whose stage does not fit keep 32-bit lists of global slots (stage count -1),
+// built on FP64 positions by a slow serial scan.
+// The kernel is bound by instruction issue and, on small systems, by one block's chain of
+// dependent loads, barriers and LDS reads.
+constexpr int UCELLS = 768;           // candidate (union) cells per block
+constexpr int OWNMAX = 64;            // own cells whose lists are built together
+constexpr int CLIST = 6160;           // candidate-list entries of those cells
 
-// One block per 256 consecutive cell-sorted particles (four 64-particle chunks).
-// Candidates: the cell-pair entries of the block's (consecutive) cells, sorted and
-// deduplicated in LDS; their particles, in cell order, form the block's candidate
-// union.  The union's particles within the largest list radius of the bounding box of
-// the block's own particles form the block's stage (a superset of its partners), held
-// in LDS as FP32 offsets from the block's first particle with slot and type packed in
-// w, cell by cell.  Each lane then collects every partner within the list radius (rc +
-// 2 skin of the pair's types) by scanning the staged particles of the cells paired
-// with its own cell, after culling each cell by its bounding sphere.  The test runs in
-// FP32 against the list radius widened by 1e-3 sigma, which bounds the offsets'
-// rounding (offsets are limited to 4096 sigma), so the list is a superset of the FP64
-// one; the step kernel decides every pair exactly.  The 16-bit lists hold stage
-// indices (0xffff pads), in candidate order.  Blocks whose stage does not fit keep
-// 32-bit lists of global slots (stage count -1), built on FP64 positions.
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) void k_nlist(const SysDev *Sd, Maps L_maps, DevParams P) {
     SYS_FROM(p);
     if (!S.sc->rebuild) return;
-    __shared__ int s_cand[CANDMAX];
-    __shared__ int s_ofs[CANDMAX + 1];
-    static_assert(CANDBITS / 32 <= CANDMAX, "the candidate bitmap and its prefix counts overlay s_ofs and s_kofs");
-    __shared__ int s_kofs[CANDMAX + 1];
-    __shared__ int s_qpos[CANDMAX];
-    __shared__ F4 s_u[USTAGE];
-    __shared__ F4 s_cb[CULLMAX];
-    __shared__ float s_b[24];
+    __shared__ F4 s_u[USTAGE];                              // the stage; before it, the union's sort
+    __shared__ __align__(16) unsigned char s_x[2 * CLIST];  // union cells, offsets, masks; then the candidate lists
+    __shared__ uint16_t s_kofs[UCELLS + 1];                 // first stage entry of each union cell
+    __shared__ __align__(16) unsigned char s_pflag[USTAGE]; // stage entries that a pruned list uses
+    __shared__ uint16_t s_qpos[CANDMAX];                    // union position of every cell-pair entry
+    __shared__ F4 s_sph[OWNMAX];                            // own cells: centroid offset and widened radius
+    __shared__ int s_row[OWNMAX + 1], s_lofs[OWNMAX + 1], s_lcnt[OWNMAX];
     __shared__ int s_w[16];
-    __shared__ int s_rows, s_big;
+    __shared__ int s_rows, s_big, s_nfit;
+    int *s_cand = reinterpret_cast<int *>(s_x);
+    int *s_ofs = s_cand + UCELLS;
+    unsigned long long *s_mask = reinterpret_cast<unsigned long long *>(s_ofs + UCELLS + 2);
+    static_assert(sizeof(s_x) >= (2 * UCELLS + 2) * sizeof(int) + UCELLS * sizeof(unsigned long long), "union arrays");
+    uint16_t *s_list = reinterpret_cast<uint16_t *>(s_x);
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int chunk = lb * (BLOCK / WAVE) + wv;
     const bool chunk_ok = chunk < S.nchunk;
@@ -1378,24 +1378,40 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
         return;
     }
     if (tid == 0) { s_rows = 0; s_big = 0; }
-    // ---- candidate cells, their particle offsets, and the union position of every cell-pair entry
+    // ---- candidate cells and the union position of every cell-pair entry
     const int first = lb * BLOCK;
     const int last = min(S.n - 1, first + BLOCK - 1);
     const int c0 = S.owner[first], c1 = S.owner[last];
+    const int A = valid ? ldg(S.owner + i) : c0;
+    const D4 ref = ld3(S.pos + first);
+    const D4 pi = valid ? ldpos(S, i) : ref;
     const int q0 = S.cnbr_start[c0];
     const int ncand = S.cnbr_start[c1 + 1] - q0;
-    const bool have_union = !(ncand <= 0 || ncand > CANDMAX || c1 < c0);
+    const int nown = c1 - c0 + 1;
+    bool have_union = !(ncand <= 0 || ncand > CANDMAX || c1 < c0);
+    const bool periodic = (S.per[0] | S.per[1] | S.per[2]) != 0;
+    const float Lx = S.per[0] ? (float)S.box[0] : 0.0f, Ly = S.per[1] ? (float)S.box[1] : 0.0f,
+                Lz = S.per[2] ? (float)S.box[2] : 0.0f;
+    const float iLx = S.per[0] ? 1.0f / Lx : 0.0f, iLy = S.per[1] ? 1.0f / Ly : 0.0f, iLz = S.per[2] ? 1.0f / Lz : 0.0f;
     int nsc = 0, ss = 0;
     if (have_union) {
         // the range of the candidate cell ids: where it spans at most CANDBITS ids, a
-        // bitmap over it (in s_ofs, with the words' prefix counts in s_kofs, both free
-        // until the stage) sorts and deduplicates them; otherwise a bitonic sort does
+        // bitmap over it and the words' prefix counts sort and deduplicate them; otherwise
+        // a bitonic sort does (both in the stage's memory)
+        int *s_srt = reinterpret_cast<int *>(s_u);
+        int cv[CANDMAX / BLOCK];         // this thread's entries
         int mn = INT_MAX, mx = INT_MIN;
-        for (int q = tid; q < ncand; q += BLOCK) {
-            const int v = ldg(S.cnbr + q0 + q);
-            mn = min(mn, v);
-            mx = max(mx, v);
+#pragma unroll
+        for (int k = 0; k < CANDMAX / BLOCK; ++k) {
+            const int q = tid + k * BLOCK;
+            cv[k] = q < ncand ? ldg(S.cnbr + q0 + q) : -1;
         }
+#pragma unroll
+        for (int k = 0; k < CANDMAX / BLOCK; ++k)
+            if (cv[k] >= 0) {
+                mn = min(mn, cv[k]);
+                mx = max(mx, cv[k]);
+            }
         for (int o = 32; o > 0; o >>= 1) {
             mn = min(mn, __shfl_xor(mn, o));
             mx = max(mx, __shfl_xor(mx, o));
@@ -1406,243 +1422,327 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
         mx = max(max(s_w[8], s_w[9]), max(s_w[10], s_w[11]));
         __syncthreads();
         if (mx - mn < CANDBITS) {
-            unsigned *bm = reinterpret_cast<unsigned *>(s_ofs);
-            int *wpre = s_kofs;
+            unsigned *bm = reinterpret_cast<unsigned *>(s_srt);
+            int *wpre = s_srt + CANDBITS / 32;
+            static_assert(sizeof(s_u) >= 2 * (CANDBITS / 32) * sizeof(int) && CANDBITS / 32 <= 16 * BLOCK, "the bitmap");
             const int nw = ((mx - mn) >> 5) + 1;
             for (int w = tid; w < nw; w += BLOCK) bm[w] = 0u;
             __syncthreads();
-            for (int q = tid; q < ncand; q += BLOCK) {
-                const int v = ldg(S.cnbr + q0 + q) - mn;
-                atomicOr(&bm[v >> 5], 1u << (v & 31));
-            }
+#pragma unroll
+            for (int k = 0; k < CANDMAX / BLOCK; ++k)
+                if (cv[k] >= 0) atomicOr(&bm[(cv[k] - mn) >> 5], 1u << ((cv[k] - mn) & 31));
             __syncthreads();
-            for (int w = tid; w < nw; w += BLOCK) wpre[w] = __popc(bm[w]);
-            __syncthreads();
-            nsc = block_scan_lds(wpre, nw, s_w);
-            for (int w = tid; w < nw; w += BLOCK) {
+            // prefix counts of the words, a run of consecutive words per thread
+            const int per = (nw + BLOCK - 1) / BLOCK, w0 = tid * per, w1 = min(nw, w0 + per);
+            int cnt = 0;
+            for (int w = w0; w < w1; ++w) cnt += __popc(bm[w]);
+            int r = block_excl_scan(cnt, s_w, nsc);
+            for (int w = w0; w < w1; ++w) {
                 unsigned b = bm[w];
-                int r = wpre[w];
+                wpre[w] = r;
                 while (b) {
-                    s_cand[r++] = mn + (w << 5) + (__ffs(b) - 1);
+                    if (r < UCELLS) s_cand[r] = mn + (w << 5) + (__ffs(b) - 1);
+                    ++r;
                     b &= b - 1u;
                 }
             }
-            for (int q = tid; q < ncand; q += BLOCK) {
-                const int v = ldg(S.cnbr + q0 + q) - mn;
-                s_qpos[q] = wpre[v >> 5] + __popc(bm[v >> 5] & ((1u << (v & 31)) - 1u));
-            }
             __syncthreads();
-            for (int q = tid; q < nsc; q += BLOCK) s_ofs[q] = ldg(S.ccount + s_cand[q]);
+#pragma unroll
+            for (int k = 0; k < CANDMAX / BLOCK; ++k)
+                if (cv[k] >= 0) {
+                    const int v = cv[k] - mn;
+                    s_qpos[tid + k * BLOCK] = (uint16_t)(wpre[v >> 5] + __popc(bm[v >> 5] & ((1u << (v & 31)) - 1u)));
+                }
         } else {
             int pw = 1;
             while (pw < ncand) pw <<= 1;
-            for (int q = tid; q < pw; q += BLOCK) s_cand[q] = (q < ncand) ? ldg(S.cnbr + q0 + q) : INT_MAX;
+#pragma unroll
+            for (int k = 0; k < CANDMAX / BLOCK; ++k) s_srt[tid + k * BLOCK] = cv[k] >= 0 ? cv[k] : INT_MAX;
             __syncthreads();
             for (int kk = 2; kk <= pw; kk <<= 1)
                 for (int jj = kk >> 1; jj > 0; jj >>= 1) {
                     for (int t = tid; t < pw; t += BLOCK) {
                         int ixj = t ^ jj;
                         if (ixj > t) {
-                            int va = s_cand[t], vb = s_cand[ixj];
+                            int va = s_srt[t], vb = s_srt[ixj];
                             bool up = (t & kk) == 0;
-                            if ((va > vb) == up) { s_cand[t] = vb; s_cand[ixj] = va; }
+                            if ((va > vb) == up) { s_srt[t] = vb; s_srt[ixj] = va; }
                         }
                     }
                     __syncthreads();
                 }
-            // deduplicate in place
+            // deduplicate into the union
             int vals[CANDMAX / BLOCK], fl[CANDMAX / BLOCK], loc = 0;
             for (int q = 0; q < CANDMAX / BLOCK; ++q) {
                 const int idx = tid * (CANDMAX / BLOCK) + q;
-                vals[q] = idx < pw ? s_cand[idx] : INT_MAX;
-                const int prev = (idx > 0 && idx < pw) ? s_cand[idx - 1] : INT_MIN;
+                vals[q] = idx < pw ? s_srt[idx] : INT_MAX;
+                const int prev = (idx > 0 && idx < pw) ? s_srt[idx - 1] : INT_MIN;
                 fl[q] = (idx < ncand && (idx == 0 || vals[q] != prev)) ? 1 : 0;
                 loc += fl[q];
             }
             int p = block_excl_scan(loc, s_w, nsc);
             for (int q = 0; q < CANDMAX / BLOCK; ++q)
-                if (fl[q]) s_cand[p++] = vals[q];
+                if (fl[q]) {
+                    if (p < UCELLS) s_cand[p] = vals[q];
+                    ++p;
+                }
             __syncthreads();
-            for (int q = tid; q < nsc; q += BLOCK) s_ofs[q] = ldg(S.ccount + s_cand[q]);
-            for (int q = tid; q < ncand; q += BLOCK) s_qpos[q] = lds_lower_bound(s_cand, nsc, ldg(S.cnbr + q0 + q));
+#pragma unroll
+            for (int k = 0; k < CANDMAX / BLOCK; ++k)
+                if (cv[k] >= 0) s_qpos[tid + k * BLOCK] = (uint16_t)lds_lower_bound(s_cand, min(nsc, UCELLS), cv[k]);
         }
-        __syncthreads();
-        ss = block_scan_lds(s_ofs, nsc, s_w);
-        if (tid == 0) s_ofs[nsc] = ss;
+        have_union = nsc <= UCELLS;                  // block-uniform
         __syncthreads();
     }
-    // ---- the stage: the union's particles near the block, as FP32 offsets, cell by
-    // cell (s_kofs: each candidate cell's first stage entry), with the candidate cells'
-    // centroids and radii (widened by 2e-3 sigma for the offsets' rounding)
-    const bool cull = nsc <= CULLMAX;
-    const D4 ref = ld3(S.pos + first);
-    const D4 pi = valid ? ldpos(S, i) : ref;
+    // ---- the stage
     float oi[3] = {(float)minimg1(pi.x - ref.x, S.per[0], S.box[0]), (float)minimg1(pi.y - ref.y, S.per[1], S.box[1]),
                    (float)minimg1(pi.z - ref.z, S.per[2], S.box[2])};
     if (!valid) oi[0] = oi[1] = oi[2] = 0.0f;
-    int kept = 0;
     // offsets beyond LIST_EXTENT (or not finite) leave the block without a stage
     auto far = [](const float o[3]) {
         return !(fabsf(o[0]) <= LIST_EXTENT && fabsf(o[1]) <= LIST_EXTENT && fabsf(o[2]) <= LIST_EXTENT);
     };
+    auto dist2f = [&](const F4 &a, float x, float y, float z) {
+        float dx = a.x - x, dy = a.y - y, dz = a.z - z;
+        if (periodic) {
+            dx -= Lx * rintf(dx * iLx);
+            dy -= Ly * rintf(dy * iLy);
+            dz -= Lz * rintf(dz * iLz);
+        }
+        return dx * dx + dy * dy + dz * dz;
+    };
+    // the bounding sphere of own cell a (radius widened by 2e-3 sigma for the offsets' rounding)
+    auto own_sphere = [&](int a) {
+        const D4 c = ldg(S.seed + c0 + a);
+        const float o[3] = {(float)minimg1(c.x - ref.x, S.per[0], S.box[0]), (float)minimg1(c.y - ref.y, S.per[1], S.box[1]),
+                            (float)minimg1(c.z - ref.z, S.per[2], S.box[2])};
+        if (far(o)) s_big = 1;
+        return F4{o[0], o[1], o[2], (float)c.w + 2e-3f};
+    };
+    // list radius of a candidate by its type (the largest over the own types)
+    const float rlm0 = P.rlmaxf[0], rlm1 = P.rlmaxf[1], rlm2 = P.rlmaxf[2];
+    int kept = 0;
     if (have_union) {
-        if (cull)
-            for (int q = tid; q < nsc; q += BLOCK) {
-                const D4 c = ldg(S.seed + s_cand[q]);
-                const float ox = (float)minimg1(c.x - ref.x, S.per[0], S.box[0]);
-                const float oy = (float)minimg1(c.y - ref.y, S.per[1], S.box[1]);
-                const float oz = (float)minimg1(c.z - ref.z, S.per[2], S.box[2]);
-                s_cb[q] = F4{ox, oy, oz, (float)c.w + 2e-3f};
-                const float o[3] = {ox, oy, oz};
-                if (far(o)) s_big = 1;
-            }
-        // the boxes of the block's four chunks, widened by the largest list radius (plus
-        // 1e-3 for the rounding of the distance to them): a particle farther from every
-        // box has no partner in the block.  A periodic axis measures the distance to a
-        // box's centre by the minimum image, and keeps every particle where the widened
-        // box spans a quarter of the period or more.  A chunk without particles has no box.
-        {
-            const float lo_in[3] = {valid ? oi[0] : INFINITY, valid ? oi[1] : INFINITY, valid ? oi[2] : INFINITY};
-            const float hi_in[3] = {valid ? oi[0] : -INFINITY, valid ? oi[1] : -INFINITY, valid ? oi[2] : -INFINITY};
-            chunk_box(lo_in, hi_in, s_b);
+        // with more own cells than mask bits, every union particle is kept
+        const bool tight = nown <= OWNMAX;
+        for (int c = tid; c < nsc; c += BLOCK) {
+            s_ofs[c] = ldg(S.ccount + s_cand[c]);
+            s_mask[c] = 0ull;
+        }
+        for (int a = tid; a < nown; a += BLOCK) {
+            const F4 sp = own_sphere(a);
+            if (tight) s_sph[a] = sp;
         }
         __syncthreads();
-        const float rb = fmaxf(P.rlmaxf[0], fmaxf(P.rlmaxf[1], P.rlmaxf[2])) + 1e-3f;
-        constexpr int NB = BLOCK / WAVE;
-        float bc[NB][3], bw[NB][3], L[3], iL[3];
-        for (int a = 0; a < 3; ++a) {
-            L[a] = S.per[a] ? (float)S.box[a] : 0.0f;
-            iL[a] = S.per[a] ? 1.0f / L[a] : 0.0f;
-        }
-        for (int w = 0; w < NB; ++w) {
-            const bool empty = !(s_b[w * 6] <= s_b[w * 6 + 3]);
-            for (int a = 0; a < 3; ++a) {
-                const float lo = s_b[w * 6 + a], hi = s_b[w * 6 + 3 + a];
-                bc[w][a] = empty ? 0.0f : 0.5f * (lo + hi);
-                bw[w][a] = empty ? -INFINITY : 0.5f * (hi - lo) + 1e-3f;   // half width; rounding of bc covered
-                if (!empty && S.per[a] && !(4.0f * (bw[w][a] + rb) < L[a])) bw[w][a] = INFINITY;
+        if (tight)
+            for (int a = wv; a < nown; a += BLOCK / WAVE) {
+                const int b = ldg(S.cnbr_start + c0 + a) - q0, e = ldg(S.cnbr_start + c0 + a + 1) - q0;
+                for (int q = b + lane; q < e; q += WAVE) atomicOr(&s_mask[s_qpos[q]], 1ull << a);
             }
+        // exclusive scan of the cells' particle counts, three cells per thread
+        {
+            constexpr int PER = UCELLS / BLOCK;
+            static_assert(UCELLS == PER * BLOCK, "cells per thread");
+            int v[PER], loc = 0;
+            for (int q = 0; q < PER; ++q) {
+                const int c = tid * PER + q;
+                v[q] = c < nsc ? s_ofs[c] : 0;
+                loc += v[q];
+            }
+            int ex = block_excl_scan(loc, s_w, ss);
+            for (int q = 0; q < PER; ++q) {
+                const int c = tid * PER + q;
+                if (c <= nsc) s_ofs[c] = ex;
+                ex += v[q];
+            }
+            if (tid == 0 && nsc == UCELLS) s_ofs[nsc] = ss;
+            __syncthreads();
         }
-        for (int u0 = 0; u0 < ss; u0 += BLOCK) {
-            const int u = u0 + tid;
-            bool keep = false;
-            F4 rec = F4{0.0f, 0.0f, 0.0f, 0.0f};
-            int c = -1;
-            if (u < ss) {
-                c = union_cell(s_ofs, nsc + 1, u);
-                const int slot = ldg(S.cstart + s_cand[c]) + (u - s_ofs[c]);
-                const D4 pj = ldpos(S, slot);
-                const float o[3] = {(float)minimg1(pj.x - ref.x, S.per[0], S.box[0]),
-                                    (float)minimg1(pj.y - ref.y, S.per[1], S.box[1]),
-                                    (float)minimg1(pj.z - ref.z, S.per[2], S.box[2])};
-                if (far(o)) s_big = 1;
-                float e2min = INFINITY;
-                for (int w = 0; w < NB; ++w) {
-                    float e2 = 0.0f;
-                    for (int a = 0; a < 3; ++a) {
-                        float d = o[a] - bc[w][a];
-                        if (S.per[a]) d -= L[a] * rintf(d * iL[a]);
-                        const float e = bw[w][a] == INFINITY ? 0.0f : fmaxf(fabsf(d) - bw[w][a], 0.0f);
-                        e2 += e * e;
+        constexpr int SB = 4;                       // union particles per thread in flight
+        for (int u0 = 0; u0 < ss; u0 += SB * BLOCK) {
+            int c[SB], slot[SB];
+            bool keep[SB];
+            F4 rec[SB];
+            D4 pj[SB];
+#pragma unroll
+            for (int k = 0; k < SB; ++k) {
+                const int u = u0 + k * BLOCK + tid;
+                c[k] = u < ss ? union_cell(s_ofs, nsc + 1, u) : -1;
+                slot[k] = c[k] >= 0 ? ldg(S.cstart + s_cand[c[k]]) + (u - s_ofs[c[k]]) : first;
+            }
+#pragma unroll
+            for (int k = 0; k < SB; ++k) pj[k] = ldpos(S, slot[k]);
+#pragma unroll
+            for (int k = 0; k < SB; ++k) {
+                keep[k] = false;
+                if (c[k] >= 0) {
+                    const float o[3] = {(float)minimg1(pj[k].x - ref.x, S.per[0], S.box[0]),
+                                        (float)minimg1(pj[k].y - ref.y, S.per[1], S.box[1]),
+                                        (float)minimg1(pj[k].z - ref.z, S.per[2], S.box[2])};
+                    if (far(o)) s_big = 1;
+                    const int t = (int)pj[k].w;
+                    rec[k] = F4{o[0], o[1], o[2], __int_as_float((slot[k] << 2) | (t & 3))};
+                    keep[k] = !tight;
+                    const float rm = sel3f(t, rlm0, rlm1, rlm2);
+                    for (unsigned long long m = s_mask[c[k]]; m; m &= m - 1ull) {
+                        const F4 sp = s_sph[__ffsll(m) - 1];
+                        const float rr = sp.w + rm;
+                        if (dist2f(sp, o[0], o[1], o[2]) <= rr * rr) {
+                            keep[k] = true;
+                            break;
+                        }
                     }
-                    e2min = fminf(e2min, e2);
                 }
-                keep = e2min <= rb * rb;
-                rec = F4{o[0], o[1], o[2], __int_as_float((slot << 2) | ((int)pj.w & 3))};
             }
-            int tot;
-            const int k = kept + block_excl_scan(keep ? 1 : 0, s_w, tot);
-            if (keep && k < USTAGE) s_u[k] = rec;
-            // each cell's first stage entry (cells without particles share the next one's)
-            if (u < ss && u == s_ofs[c])
-                for (int c2 = c; c2 >= 0 && s_ofs[c2] == u; --c2) s_kofs[c2] = k;
-            kept += tot;
+            // places: by round, wavefront and lane (the union's order)
+            int rank[SB];
+#pragma unroll
+            for (int k = 0; k < SB; ++k) {
+                const unsigned long long m = __ballot(keep[k]);
+                rank[k] = __popcll(m & ((1ull << lane) - 1ull));
+                if (lane == 0) s_w[k * (BLOCK / WAVE) + wv] = __popcll(m);
+            }
+            static_assert(SB * (BLOCK / WAVE) == 16, "counts of a pass");
+            __syncthreads();
+            int run = kept;
+#pragma unroll
+            for (int k = 0; k < SB; ++k) {
+#pragma unroll
+                for (int w = 0; w < BLOCK / WAVE; ++w) {
+                    if (w == wv) rank[k] += run;
+                    run += s_w[k * (BLOCK / WAVE) + w];
+                }
+                if (keep[k] && rank[k] < USTAGE) s_u[rank[k]] = rec[k];
+                // each cell's first stage entry (cells without particles share the next one's)
+                const int u = u0 + k * BLOCK + tid;
+                if (c[k] >= 0 && u == s_ofs[c[k]])
+                    for (int c2 = c[k]; c2 >= 0 && s_ofs[c2] == u; --c2) s_kofs[c2] = (uint16_t)rank[k];   // (kept beyond USTAGE: no stage)
+            }
+            kept = run;
+            __syncthreads();
         }
         for (int c = tid; c <= nsc; c += BLOCK)
-            if (s_ofs[c] == ss) s_kofs[c] = kept;
+            if (s_ofs[c] == ss) s_kofs[c] = (uint16_t)kept;
         __syncthreads();
     }
     const bool staged = have_union && kept <= USTAGE && s_big == 0;
     // ---- the lists, and the pruned lists (partners within rc + 2 inner skin) with the
-    // stage entries they use flagged in s_pflag (the candidate cells are done with)
-    unsigned char *s_pflag = reinterpret_cast<unsigned char *>(s_cand);
-    static_assert(sizeof(s_cand) >= USTAGE, "pruned-stage flags overlay the candidate cells");
+    // stage entries they use flagged in s_pflag
     for (int w = tid; w < USTAGE / 4; w += BLOCK) reinterpret_cast<unsigned *>(s_pflag)[w] = 0u;
-    __syncthreads();
     int cnt = 0, pc = 0;
     int32_t *col = S.nl + (size_t)(chunk_ok ? chunk : 0) * MAXNB * CHUNK + lane;
     uint16_t *col16 = S.nl16 + (size_t)(chunk_ok ? chunk : 0) * MAXNB * CHUNK + lane;
     uint16_t *icol = S.il16 + (size_t)(chunk_ok ? chunk : 0) * MAXNB * CHUNK + lane;
-    if (valid && staged) {
-        const int ti = (int)pi.w;
-        const int A = S.owner[i];
+    const int ti = (int)pi.w & 3;
+    if (staged) {
         const float oix = oi[0], oiy = oi[1], oiz = oi[2];
         const float rlA = P.rl2f[ti][0], rlB = P.rl2f[ti][1], rlC = P.rl2f[ti][2];
         const float riA = P.rin2f[ti][0], riB = P.rin2f[ti][1], riC = P.rin2f[ti][2];
-        const float rlmax = P.rlmaxf[ti];
-        const int selfw = (i << 2) | (ti & 3);            // this particle's own stage record
-        const bool periodic = (S.per[0] | S.per[1] | S.per[2]) != 0;
-        const float Lx = S.per[0] ? (float)S.box[0] : 0.0f, Ly = S.per[1] ? (float)S.box[1] : 0.0f,
-                    Lz = S.per[2] ? (float)S.box[2] : 0.0f;
-        const float iLx = S.per[0] ? 1.0f / Lx : 0.0f, iLy = S.per[1] ? 1.0f / Ly : 0.0f,
-                    iLz = S.per[2] ? 1.0f / Lz : 0.0f;
-        const int qa = S.cnbr_start[A] - q0, qb = S.cnbr_start[A + 1] - q0;
-        auto scan_cells = [&](auto per_tag) {
-            constexpr bool PER = decltype(per_tag)::value;
-            for (int q = qa; q < qb; ++q) {
-                const int pos = s_qpos[q];
-                if (cull) {
-                    // skip cells whose bounding sphere lies beyond the list radius
-                    const F4 cb = s_cb[pos];
-                    float dx = cb.x - oix, dy = cb.y - oiy, dz = cb.z - oiz;
-                    if constexpr (PER) {
-                        dx -= Lx * rintf(dx * iLx);
-                        dy -= Ly * rintf(dy * iLy);
-                        dz -= Lz * rintf(dz * iLz);
-                    }
-                    const float rr = cb.w + rlmax;
-                    if (dx * dx + dy * dy + dz * dz > rr * rr) continue;
+        const int selfw = (i << 2) | ti;                  // this particle's own stage record
+        for (int a0 = 0; a0 < nown;) {
+            const int nb = min(nown - a0, OWNMAX);
+            __syncthreads();
+            // the cells' rows and, from their paired cells' staged sizes, the lists' places
+            if (tid <= nb) s_row[tid] = ldg(S.cnbr_start + c0 + a0 + tid) - q0;
+            if (tid < nb && (a0 > 0 || nown > OWNMAX)) s_sph[tid] = own_sphere(a0 + tid);
+            __syncthreads();
+            for (int a = wv; a < nb; a += BLOCK / WAVE) {
+                int sz = 0;
+                for (int q = s_row[a] + lane; q < s_row[a + 1]; q += WAVE) {
+                    const int p = s_qpos[q];
+                    sz += s_kofs[p + 1] - s_kofs[p];
                 }
-                const int ke = s_kofs[pos + 1];
-                auto test = [&](const F4 &c, int k) {
-                    float dx = c.x - oix, dy = c.y - oiy, dz = c.z - oiz;
-                    if constexpr (PER) {
-                        dx -= Lx * rintf(dx * iLx);
-                        dy -= Ly * rintf(dy * iLy);
-                        dz -= Lz * rintf(dz * iLz);
-                    }
-                    const float d2 = dx * dx + dy * dy + dz * dz;
-                    const int w = __float_as_int(c.w);
-                    const float rl = sel3f(w & 3, rlA, rlB, rlC);
-                    if (d2 < rl && w != selfw) {
-                        if (cnt < MAXNB) {
-                            stg(col16 + cnt * CHUNK, (uint16_t)k);
-                            // the pruned list: the entries within the pruned radius
-                            if (d2 < sel3f(w & 3, riA, riB, riC)) {
-                                stg(icol + pc * CHUNK, (uint16_t)k);
-                                ++pc;
-                                s_pflag[k] = 1;
-                            }
-                        }
-                        ++cnt;
-                    }
-                };
-                int k = s_kofs[pos];
-                for (; k + 3 < ke; k += 4) {                      // four candidates per trip
-                    const F4 a0 = s_u[k], a1 = s_u[k + 1], a2 = s_u[k + 2], a3 = s_u[k + 3];
-                    test(a0, k);
-                    test(a1, k + 1);
-                    test(a2, k + 2);
-                    test(a3, k + 3);
-                }
-                for (; k < ke; ++k) test(s_u[k], k);
+                for (int o = 32; o > 0; o >>= 1) sz += __shfl_xor(sz, o);
+                if (lane == 0) s_lcnt[a] = sz;
             }
-        };
-        if (periodic) scan_cells(std::true_type{});
-        else scan_cells(std::false_type{});
+            __syncthreads();
+            if (wv == 0) {
+                const int v = lane < nb ? s_lcnt[lane] : 0;
+                int x = v;
+                for (int o = 1; o < WAVE; o <<= 1) {
+                    const int y = __shfl_up(x, o);
+                    if (lane >= o) x += y;
+                }
+                s_lofs[lane] = x - v;
+                const unsigned long long fit = __ballot(lane < nb && x <= CLIST);
+                if (lane == 0) s_nfit = __popcll(fit);       // x grows with the lane: a prefix
+            }
+            static_assert(CLIST >= USTAGE, "one cell's list always fits");
+            __syncthreads();
+            const int nfit = s_nfit;
+            // one wavefront per cell, sixteen lanes per paired cell
+            for (int a = wv; a < nfit; a += BLOCK / WAVE) {
+                const F4 sp = s_sph[a];
+                const float r0 = sp.w + rlm0, r1 = sp.w + rlm1, r2 = sp.w + rlm2;
+                const float r0s = r0 * r0, r1s = r1 * r1, r2s = r2 * r2;
+                uint16_t *out = s_list + s_lofs[a];
+                int n = 0;
+                for (int q = s_row[a] + (lane >> 4), qe = s_row[a + 1]; __ballot(q < qe) != 0ull; q += 4) {
+                    int k = 0, ke = 0;
+                    if (q < qe) {
+                        const int p = s_qpos[q];
+                        k = s_kofs[p] + (lane & 15);
+                        ke = s_kofs[p + 1];
+                    }
+                    while (__ballot(k < ke) != 0ull) {
+                        bool in = false;
+                        if (k < ke) {
+                            const F4 u = s_u[k];
+                            in = dist2f(u, sp.x, sp.y, sp.z) <= sel3f(__float_as_int(u.w) & 3, r0s, r1s, r2s);
+                        }
+                        const unsigned long long m = __ballot(in);
+                        if (in) out[n + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)k;
+                        n += __popcll(m);
+                        k += 16;
+                    }
+                }
+                if (lane == 0) s_lcnt[a] = n;
+            }
+            __syncthreads();
+            if (valid && A >= c0 + a0 && A < c0 + a0 + nfit) {
+                const uint16_t *lst = s_list + s_lofs[A - c0 - a0];
+                const int n = s_lcnt[A - c0 - a0];
+                auto scan_list = [&](auto per_tag) {
+                    constexpr bool PER = decltype(per_tag)::value;
+                    auto test = [&](const F4 &c, int k) {
+                        float dx = c.x - oix, dy = c.y - oiy, dz = c.z - oiz;
+                        if constexpr (PER) {
+                            dx -= Lx * rintf(dx * iLx);
+                            dy -= Ly * rintf(dy * iLy);
+                            dz -= Lz * rintf(dz * iLz);
+                        }
+                        const float d2 = dx * dx + dy * dy + dz * dz;
+                        const int w = __float_as_int(c.w);
+                        if (d2 < sel3f(w & 3, rlA, rlB, rlC) && w != selfw) {
+                            if (cnt < MAXNB) {
+                                stg(col16 + cnt * CHUNK, (uint16_t)k);
+                                // the pruned list: the entries within the pruned radius
+                                if (d2 < sel3f(w & 3, riA, riB, riC)) {
+                                    stg(icol + pc * CHUNK, (uint16_t)k);
+                                    ++pc;
+                                    s_pflag[k] = 1;
+                                }
+                            }
+                            ++cnt;
+                        }
+                    };
+                    int e = 0;
+                    for (; e + 3 < n; e += 4) {                   // four candidates per trip
+                        const int k0 = lst[e], k1 = lst[e + 1], k2 = lst[e + 2], k3 = lst[e + 3];
+                        const F4 u0 = s_u[k0], u1 = s_u[k1], u2 = s_u[k2], u3 = s_u[k3];
+                        test(u0, k0);
+                        test(u1, k1);
+                        test(u2, k2);
+                        test(u3, k3);
+                    }
+                    for (; e < n; ++e) test(s_u[lst[e]], lst[e]);
+                };
+                if (periodic) scan_list(std::true_type{});
+                else scan_list(std::false_type{});
+            }
+            a0 += nfit;
+        }
     } else if (valid) {
-        const int ti = (int)pi.w;
-        const int A = S.owner[i];
         for (int q = S.cnbr_start[A]; q < S.cnbr_start[A + 1]; ++q) {
             int B = ldg(S.cnbr + q);
             int b = ldg(S.cstart + B), e = b + ldg(S.ccount + B);
@@ -1683,9 +1783,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
     if (!staged) irows = rows;
     if (chunk_ok && lane == 0) S.ilk[chunk] = irows;
     __syncthreads();
-    unsigned *s_bits = reinterpret_cast<unsigned *>(s_ofs);          // the union offsets are done with
-    int *s_pre = s_ofs + USTAGE / 32;
-    static_assert(sizeof(s_ofs) >= 2 * (USTAGE / 32) * sizeof(int), "pruned-stage words overlay the union offsets");
+    unsigned *s_bits = reinterpret_cast<unsigned *>(s_x);            // the candidate lists are done with
+    int *s_pre = reinterpret_cast<int *>(s_x) + USTAGE / 32;
+    static_assert(sizeof(s_x) >= 2 * (USTAGE / 32) * sizeof(int), "pruned-stage words overlay the candidate lists");
     int nkept = -1;
     if (staged) {
         const int nwords = (kept + 31) / 32;

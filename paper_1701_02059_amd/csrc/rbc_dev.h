@@ -25,7 +25,6 @@ constexpr int CANDBITS = 32 * CANDMAX;    // candidate-cell id range the list bu
 constexpr int USTAGE = 2048;           // candidate particles staged in LDS while building a block's lists
 static_assert(USTAGE <= SMAX && USTAGE < 0xffff, "a staged candidate union is the block's stage, indexed in 16 bits");
 constexpr float LIST_EXTENT = 4096.0f; // largest FP32 offset (sigma) allowed in that staging
-constexpr int CULLMAX = 256;           // candidate cells whose bounding spheres are staged for culling
 constexpr int SCAN_TILE = 2048;        // elements per block in the segmented scans
 constexpr int BRED = 12;               // doubles of per-block partial results (3 per chunk in a drift)
 
