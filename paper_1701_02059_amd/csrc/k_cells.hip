@@ -35,32 +35,46 @@ __device__ __forceinline__ void max_if_larger(T *p, T v) {
     if (v > __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(p, v);
 }
 
-__device__ __forceinline__ int wave_max_int(int v) {
-    for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o));
+// Wavefront scans by DPP lane moves (row shifts 1, 2, 4, 8, then each row's last lane into
+// the next rows): seven register instructions, where a shuffle through LDS takes about 130
+// cycles for each of six steps.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_or0(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ int wave_incl_scan(int v) {
+    v += dpp_or0<0x111, 0xf>(v);
+    v += dpp_or0<0x112, 0xf>(v);
+    v += dpp_or0<0x114, 0xf>(v);
+    v += dpp_or0<0x118, 0xf>(v);
+    v += dpp_or0<0x142, 0xa>(v);
+    v += dpp_or0<0x143, 0xc>(v);
     return v;
+}
+
+// The largest of 64 non-negative values, on every lane.
+__device__ __forceinline__ int wave_max_int(int v) {
+    v = max(v, dpp_or0<0x111, 0xf>(v));
+    v = max(v, dpp_or0<0x112, 0xf>(v));
+    v = max(v, dpp_or0<0x114, 0xf>(v));
+    v = max(v, dpp_or0<0x118, 0xf>(v));
+    v = max(v, dpp_or0<0x142, 0xa>(v));
+    v = max(v, dpp_or0<0x143, 0xc>(v));
+    return __builtin_amdgcn_readlane(v, WAVE - 1);
 }
 
 // Exclusive scan across the block (blockDim.x a multiple of 64, <= 1024).
 __device__ int block_excl_scan(int v, int *s_w, int &total) {
-    int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    int x = v;
-    for (int o = 1; o < 64; o <<= 1) {
-        int y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-    }
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const int x = wave_incl_scan(v);
     if (lane == 63) s_w[w] = x;
     __syncthreads();
-    if (w == 0) {
-        int s = (lane < nw) ? s_w[lane] : 0;
-        for (int o = 1; o < 64; o <<= 1) {
-            int y = __shfl_up(s, o);
-            if (lane >= o) s += y;
-        }
-        if (lane < nw) s_w[lane] = s;
+    int base = 0;
+    total = 0;
+    for (int q = 0; q < nw; ++q) {
+        if (q < w) base += s_w[q];
+        total += s_w[q];
     }
-    __syncthreads();
-    int base = (w > 0) ? s_w[w - 1] : 0;
-    total = s_w[nw - 1];
     __syncthreads();
     return base + x - v;
 }
@@ -1299,18 +1313,98 @@ __device__ __forceinline__ float sel3f(int t, float a, float b, float c) {
     return __int_as_float(r);
 }
 
-// 32 byte flags (each 0 or 1, 4-byte aligned in LDS) as one word, flag k in bit k.
-// Marking set members with plain byte stores of 1 avoids serialising many lanes'
-// atomics on a few bitmap words.
-__device__ __forceinline__ unsigned pack_flags(const unsigned char *f) {
+// A block's stage entries in LDS: FP32 offsets from the block's first particle, and a byte
+// with the type and, once a pruned list uses the entry, STAGE_USED.  The used entries are
+// marked with plain byte stores: many lanes' atomics on a few bitmap words would serialise.
+constexpr unsigned char STAGE_USED = 4;
+
+// The USED bits of 32 such bytes (4-byte aligned) as one word, entry k in bit k.
+__device__ __forceinline__ unsigned pack_used(const unsigned char *f) {
     const unsigned *w = reinterpret_cast<const unsigned *>(f);
     unsigned bits = 0u;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-        const unsigned v = w[q];
+        const unsigned v = w[q] >> 2;
         bits |= ((v & 1u) | ((v >> 7) & 2u) | ((v >> 14) & 4u) | ((v >> 21) & 8u)) << (4 * q);
     }
     return bits;
+}
+
+// The pruned stage of a block: the used ones of its scnt stage entries, in stage order
+// (slots to istage), and for every 32 entries their bits and rank in bp.  Returns its size.
+__device__ int pruned_stage(const SysDev &S, int lb, int scnt, const unsigned char *s_tf, uint2 *s_bp, int *s_w) {
+    const int nwords = (scnt + 31) / 32;                 // at most SMAX / 32 = 64: one wavefront's
+    static_assert(SMAX / 32 <= WAVE, "the words of a stage");
+    __syncthreads();
+    if (threadIdx.x < WAVE) {
+        const int w = threadIdx.x;
+        const unsigned bits = w < nwords ? pack_used(s_tf + 32 * w) : 0u;
+        const int c = __popc(bits);
+        const int x = wave_incl_scan(c);
+        s_bp[w] = make_uint2(bits, (unsigned)(x - c));
+        if (w == WAVE - 1) s_w[0] = x;
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < scnt; k += BLOCK) {
+        const uint2 b = s_bp[k >> 5];
+        const unsigned m = 1u << (k & 31);
+        if (b.x & m)
+            stg(S.istage + (size_t)lb * SSTRIDE + b.y + __popc(b.x & (m - 1u)), ldg(S.stage + (size_t)lb * SSTRIDE + k));
+    }
+    return s_w[0];
+}
+
+// The pruned lists of a wavefront's chunk from its full lists (`rows` rows) and the bits
+// of the rows that stay (pm): each lane's entries become indices into the pruned stage,
+// are gathered in its own dwords of an LDS buffer (PAIRS row pairs; entries beyond it go
+// straight to memory) and leave as whole row pairs, padded with 0xffff to the chunk's row
+// count rounded up to even (the step kernel takes rows in pairs).
+template <int PAIRS>
+__device__ void emit_pruned(const SysDev &S, int chunk, int rows, unsigned pm0, unsigned pm1, unsigned pm2,
+                            const uint2 *s_bp, uint16_t *s_buf) {
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+    const int mine = __popc(pm0) + __popc(pm1) + __popc(pm2);
+    const int irows = wave_max_int(mine);
+    if (lane == 0) S.ilk[chunk] = irows;
+    const v4u *src = reinterpret_cast<const v4u *>(S.nl16 + (size_t)chunk * MAXNB * CHUNK) + lane;
+    uint16_t *dst = S.il16 + (size_t)chunk * MAXNB * CHUNK;
+    const int ng = (rows + 7) / 8;
+    int pc = 0;
+    v4u nxt = {0u, 0u, 0u, 0u};
+    if (ng > 0) nxt = ldg(src);
+    for (int g = 0; g < ng; ++g) {
+        const v4u e = nxt;
+        if (g + 1 < ng) nxt = ldg(src + (g + 1) * CHUNK);
+        const unsigned pb = (g < 4 ? pm0 : (g < 8 ? pm1 : pm2)) >> (8 * (g & 3));
+        unsigned local[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {                // the eight ranks side by side
+            unsigned k = (q & 1) ? e[q >> 1] >> 16 : e[q >> 1] & 0xffffu;
+            k = (pb >> q) & 1u ? k : 0u;
+            const uint2 b = s_bp[k >> 5];
+            local[q] = b.y + __popc(b.x & ((1u << (k & 31)) - 1u));
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            if ((pb >> q) & 1u) {
+                if (pc < 2 * PAIRS) s_buf[(pc >> 1) * (2 * BLOCK) + 2 * tid + (pc & 1)] = (uint16_t)local[q];
+                else stg(dst + il_at(pc, lane), (uint16_t)local[q]);
+                ++pc;
+            }
+        }
+    }
+    const unsigned *s_b32 = reinterpret_cast<const unsigned *>(s_buf);
+    for (int p = 0, np = (irows + 1) >> 1; p < np; ++p) {
+        const int r = 2 * p;
+        if (p < PAIRS) {
+            unsigned v = s_b32[p * BLOCK + tid];
+            v = r + 1 < mine ? v : (r < mine ? v | 0xffff0000u : 0xffffffffu);
+            stg(reinterpret_cast<unsigned *>(dst + il_at(r, lane)), v);
+        } else {
+            if (r >= mine) stg(dst + il_at(r, lane), (uint16_t)0xffff);
+            if (r + 1 >= mine) stg(dst + il_at(r + 1, lane), (uint16_t)0xffff);
+        }
+    }
 }
 
 // Last candidate cell whose particle offset is <= u (offsets of empty cells repeat).
@@ -1329,44 +1423,62 @@ __device__ __forceinline__ int union_cell(const int *ofs, int nsc, int u) {
 //    LDS (the union).
 //  - Stage: the union's particles that lie within the list radius of some own cell's
 //    bounding sphere, of those own cells that pair with the particle's cell (a 64-bit
-//    mask per union cell), cell by cell as FP32 offsets from the block's first particle
-//    with slot and type packed in w.  A superset of the block's partners.
-//  - Candidate lists: for each own cell the stage entries within the list radius of its
-//    bounding sphere, written by one wavefront as 16-bit stage indices.  Every particle
-//    of a cell scans the same short list (about 150 entries for 47 partners at skin
-//    0.65), so that the wavefront's lanes run through it together.  The lists are placed
-//    by an upper bound (the staged sizes of the paired cells), as many cells at a time
-//    as fit the buffer; nearly always that is all of them.
-//  - Lists: each lane keeps every partner within the list radius (rc + 2 skin of the
-//    pair's types).  The test runs in FP32 against the radius widened by 1e-3 sigma,
-//    which bounds the offsets' rounding (offsets are limited to 4096 sigma), so the list
-//    is a superset of the FP64 one; the step kernel decides every pair exactly.  The
-//    16-bit lists hold stage indices (0xffff pads).
-// Blocks whose stage does not fit keep 32-bit lists of global slots (stage count -1),
-// built on FP64 positions by a slow serial scan.
-// The kernel is bound by instruction issue and, on small systems, by one block's chain of
-// dependent loads, barriers and LDS reads.
-constexpr int UCELLS = 768;           // candidate (union) cells per block
-constexpr int OWNMAX = 64;            // own cells whose lists are built together
-constexpr int CLIST = 6160;           // candidate-list entries of those cells
+//    mask per union cell), in the union's order, as FP32 offsets from the block's first
+//    particle.  A superset of the block's partners.  Each entry keeps a bit for every own
+//    cell whose sphere test it passed.
+//  - Candidate lists: for each own cell the stage entries with its bit, compacted by one
+//    wavefront's ballots as 16-bit LDS offsets, lipids from the front, proteins from the
+//    back (neighbouring cells share a list where a block has more than 16).  Every
+//    particle of a cell scans the same short list (about 130 entries for 47 partners at
+//    skin 0.65), so that the wavefront's lanes run through it together, each segment with
+//    one radius.  As many lists are built at a time as fit the buffer; nearly always that
+//    is all of them.
+//  - Scan: each lane tests its cell's candidates against the list radius (rc + 2 skin of
+//    the pair's types) and keeps a bit for each, in words in LDS.  The test runs in FP32
+//    against the radius widened by 1e-3 sigma, which bounds the offsets' rounding (offsets
+//    are limited to 4096 sigma), so the list is a superset of the FP64 one; the step
+//    kernel decides every pair exactly.
+//  - Lists: the lanes take their next set bit row by row together, eight rows to a
+//    16-byte store.  The same pass tests the pruned radius (rc + 2 inner skin), marks the
+//    stage entries that pass and keeps a bit per row; emit_pruned then writes the pruned
+//    lists.  Hits beyond the words that fit are appended one by one.
+// What bounds it is latency: three blocks of four wavefronts share a CU, and every phase is
+// a chain of loads, barriers and LDS reads, so each is written with as many of them side
+// by side as it has (four union particles, eight candidates, eight rows at a time).
+// Blocks whose stage does not fit, or with more than 64 own cells, keep 32-bit lists of
+// global slots (stage count -1), built on FP64 positions by a slow serial scan.
+constexpr int UCELLS = 512;           // candidate (union) cells per block
+constexpr int OWNMAX = 64;            // own cells of a staged block
+constexpr int GROUPS = 16;            // candidate lists of a block
+constexpr int CLIST = 5120;           // candidate-list entries of those cells
+constexpr int MWORDS = 11;            // words of hit bits per lane (352 candidates)
 
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) void k_nlist(const SysDev *Sd, Maps L_maps, DevParams P) {
     SYS_FROM(p);
     if (!S.sc->rebuild) return;
-    __shared__ F4 s_u[USTAGE];                              // the stage; before it, the union's sort
-    __shared__ __align__(16) unsigned char s_x[2 * CLIST];  // union cells, offsets, masks; then the candidate lists
-    __shared__ uint16_t s_kofs[UCELLS + 1];                 // first stage entry of each union cell
-    __shared__ __align__(16) unsigned char s_pflag[USTAGE]; // stage entries that a pruned list uses
-    __shared__ uint16_t s_qpos[CANDMAX];                    // union position of every cell-pair entry
+    // 53 KB of LDS, three blocks per CU.  s_raw: the stage's x, y, z; the union arrays, then
+    // the candidate lists; the own particles' stage entries, then the hit words; before the
+    // stage, the union's sort; after the scan, the pruned stage's words and the row buffer.
+    constexpr int RX = 3 * USTAGE * 4, RL = 2 * CLIST, RM = MWORDS * BLOCK * 4;
+    __shared__ __align__(16) unsigned char s_raw[RX + RL + RM];
+    __shared__ __align__(16) unsigned char s_tf[USTAGE];    // type | STAGE_USED of the stage entries
+    __shared__ uint16_t s_q[USTAGE];                        // union position of every cell-pair entry; then the
+                                                            // stage entries' own-list bits
     __shared__ F4 s_sph[OWNMAX];                            // own cells: centroid offset and widened radius
-    __shared__ int s_row[OWNMAX + 1], s_lofs[OWNMAX + 1], s_lcnt[OWNMAX];
+    __shared__ int s_lofs[GROUPS + 1];
+    __shared__ uint16_t s_nl[GROUPS], s_np[GROUPS];         // lipid and protein candidates of each list
     __shared__ int s_w[16];
     __shared__ int s_rows, s_big, s_nfit;
-    int *s_cand = reinterpret_cast<int *>(s_x);
+    uint16_t *s_qpos = s_q, *s_om = s_q;
+    static_assert(CANDMAX <= USTAGE && GROUPS <= 16, "list bits");
+    float *s_ux = reinterpret_cast<float *>(s_raw), *s_uy = s_ux + USTAGE, *s_uz = s_uy + USTAGE;
+    int *s_cand = reinterpret_cast<int *>(s_raw + RX);
     int *s_ofs = s_cand + UCELLS;
     unsigned long long *s_mask = reinterpret_cast<unsigned long long *>(s_ofs + UCELLS + 2);
-    static_assert(sizeof(s_x) >= (2 * UCELLS + 2) * sizeof(int) + UCELLS * sizeof(unsigned long long), "union arrays");
-    uint16_t *s_list = reinterpret_cast<uint16_t *>(s_x);
+    static_assert(RL >= (2 * UCELLS + 2) * (int)sizeof(int) + UCELLS * (int)sizeof(unsigned long long), "union arrays");
+    uint16_t *s_list = reinterpret_cast<uint16_t *>(s_raw + RX);
+    uint16_t *s_self = reinterpret_cast<uint16_t *>(s_raw + RX + RL);
+    unsigned *s_m = reinterpret_cast<unsigned *>(s_raw + RX + RL);
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int chunk = lb * (BLOCK / WAVE) + wv;
     const bool chunk_ok = chunk < S.nchunk;
@@ -1378,6 +1490,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
         return;
     }
     if (tid == 0) { s_rows = 0; s_big = 0; }
+    reinterpret_cast<uint2 *>(s_tf)[tid] = make_uint2(0u, 0u);
+    static_assert(USTAGE == 8 * BLOCK, "type bytes");
     // ---- candidate cells and the union position of every cell-pair entry
     const int first = lb * BLOCK;
     const int last = min(S.n - 1, first + BLOCK - 1);
@@ -1388,17 +1502,23 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
     const int q0 = S.cnbr_start[c0];
     const int ncand = S.cnbr_start[c1 + 1] - q0;
     const int nown = c1 - c0 + 1;
-    bool have_union = !(ncand <= 0 || ncand > CANDMAX || c1 < c0);
+    bool have_union = !(ncand <= 0 || ncand > CANDMAX || c1 < c0 || nown > OWNMAX);
     const bool periodic = (S.per[0] | S.per[1] | S.per[2]) != 0;
     const float Lx = S.per[0] ? (float)S.box[0] : 0.0f, Ly = S.per[1] ? (float)S.box[1] : 0.0f,
                 Lz = S.per[2] ? (float)S.box[2] : 0.0f;
     const float iLx = S.per[0] ? 1.0f / Lx : 0.0f, iLy = S.per[1] ? 1.0f / Ly : 0.0f, iLz = S.per[2] ? 1.0f / Lz : 0.0f;
+    const double iL[3] = {S.per[0] ? 1.0 / S.box[0] : 0.0, S.per[1] ? 1.0 / S.box[1] : 0.0, S.per[2] ? 1.0 / S.box[2] : 0.0};
+    // FP32 offset from the block's first particle (any image: the tests take the nearest)
+    auto offset = [&](int a, double x, double x0) {
+        const double d = x - x0;
+        return (float)(periodic && S.per[a] ? minimg_fast(d, S.box[a], iL[a]) : d);
+    };
     int nsc = 0, ss = 0;
     if (have_union) {
         // the range of the candidate cell ids: where it spans at most CANDBITS ids, a
         // bitmap over it and the words' prefix counts sort and deduplicate them; otherwise
         // a bitonic sort does (both in the stage's memory)
-        int *s_srt = reinterpret_cast<int *>(s_u);
+        int *s_srt = reinterpret_cast<int *>(s_raw);
         int cv[CANDMAX / BLOCK];         // this thread's entries
         int mn = INT_MAX, mx = INT_MIN;
 #pragma unroll
@@ -1424,7 +1544,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
         if (mx - mn < CANDBITS) {
             unsigned *bm = reinterpret_cast<unsigned *>(s_srt);
             int *wpre = s_srt + CANDBITS / 32;
-            static_assert(sizeof(s_u) >= 2 * (CANDBITS / 32) * sizeof(int) && CANDBITS / 32 <= 16 * BLOCK, "the bitmap");
+            static_assert(3 * USTAGE * sizeof(float) >= 2 * (CANDBITS / 32) * sizeof(int), "the bitmap");
             const int nw = ((mx - mn) >> 5) + 1;
             for (int w = tid; w < nw; w += BLOCK) bm[w] = 0u;
             __syncthreads();
@@ -1495,15 +1615,14 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
         __syncthreads();
     }
     // ---- the stage
-    float oi[3] = {(float)minimg1(pi.x - ref.x, S.per[0], S.box[0]), (float)minimg1(pi.y - ref.y, S.per[1], S.box[1]),
-                   (float)minimg1(pi.z - ref.z, S.per[2], S.box[2])};
+    float oi[3] = {offset(0, pi.x, ref.x), offset(1, pi.y, ref.y), offset(2, pi.z, ref.z)};
     if (!valid) oi[0] = oi[1] = oi[2] = 0.0f;
     // offsets beyond LIST_EXTENT (or not finite) leave the block without a stage
     auto far = [](const float o[3]) {
         return !(fabsf(o[0]) <= LIST_EXTENT && fabsf(o[1]) <= LIST_EXTENT && fabsf(o[2]) <= LIST_EXTENT);
     };
-    auto dist2f = [&](const F4 &a, float x, float y, float z) {
-        float dx = a.x - x, dy = a.y - y, dz = a.z - z;
+    auto dist2f = [&](float ax, float ay, float az, float x, float y, float z) {
+        float dx = ax - x, dy = ay - y, dz = az - z;
         if (periodic) {
             dx -= Lx * rintf(dx * iLx);
             dy -= Ly * rintf(dy * iLy);
@@ -1514,8 +1633,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
     // the bounding sphere of own cell a (radius widened by 2e-3 sigma for the offsets' rounding)
     auto own_sphere = [&](int a) {
         const D4 c = ldg(S.seed + c0 + a);
-        const float o[3] = {(float)minimg1(c.x - ref.x, S.per[0], S.box[0]), (float)minimg1(c.y - ref.y, S.per[1], S.box[1]),
-                            (float)minimg1(c.z - ref.z, S.per[2], S.box[2])};
+        const float o[3] = {offset(0, c.x, ref.x), offset(1, c.y, ref.y), offset(2, c.z, ref.z)};
         if (far(o)) s_big = 1;
         return F4{o[0], o[1], o[2], (float)c.w + 2e-3f};
     };
@@ -1523,47 +1641,35 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
     const float rlm0 = P.rlmaxf[0], rlm1 = P.rlmaxf[1], rlm2 = P.rlmaxf[2];
     int kept = 0;
     if (have_union) {
-        // with more own cells than mask bits, every union particle is kept
-        const bool tight = nown <= OWNMAX;
-        for (int c = tid; c < nsc; c += BLOCK) {
-            s_ofs[c] = ldg(S.ccount + s_cand[c]);
+        constexpr int PER = UCELLS / BLOCK;
+        static_assert(UCELLS == PER * BLOCK, "cells per thread");
+        int ccnt[PER], loc = 0;
+        for (int q = 0; q < PER; ++q) {
+            const int c = tid * PER + q;
+            ccnt[q] = c < nsc ? ldg(S.ccount + s_cand[c]) : 0;
+            loc += ccnt[q];
             s_mask[c] = 0ull;
         }
-        for (int a = tid; a < nown; a += BLOCK) {
-            const F4 sp = own_sphere(a);
-            if (tight) s_sph[a] = sp;
+        if (tid < nown) s_sph[tid] = own_sphere(tid);
+        int ex = block_excl_scan(loc, s_w, ss);
+        for (int q = 0; q < PER; ++q) {
+            const int c = tid * PER + q;
+            if (c <= nsc) s_ofs[c] = ex;
+            ex += ccnt[q];
+        }
+        if (tid == 0 && nsc == UCELLS) s_ofs[nsc] = ss;
+        for (int a = wv; a < nown; a += BLOCK / WAVE) {
+            const int b = ldg(S.cnbr_start + c0 + a) - q0, e = ldg(S.cnbr_start + c0 + a + 1) - q0;
+            for (int q = b + lane; q < e; q += WAVE) atomicOr(&s_mask[s_qpos[q]], 1ull << a);
         }
         __syncthreads();
-        if (tight)
-            for (int a = wv; a < nown; a += BLOCK / WAVE) {
-                const int b = ldg(S.cnbr_start + c0 + a) - q0, e = ldg(S.cnbr_start + c0 + a + 1) - q0;
-                for (int q = b + lane; q < e; q += WAVE) atomicOr(&s_mask[s_qpos[q]], 1ull << a);
-            }
-        // exclusive scan of the cells' particle counts, three cells per thread
-        {
-            constexpr int PER = UCELLS / BLOCK;
-            static_assert(UCELLS == PER * BLOCK, "cells per thread");
-            int v[PER], loc = 0;
-            for (int q = 0; q < PER; ++q) {
-                const int c = tid * PER + q;
-                v[q] = c < nsc ? s_ofs[c] : 0;
-                loc += v[q];
-            }
-            int ex = block_excl_scan(loc, s_w, ss);
-            for (int q = 0; q < PER; ++q) {
-                const int c = tid * PER + q;
-                if (c <= nsc) s_ofs[c] = ex;
-                ex += v[q];
-            }
-            if (tid == 0 && nsc == UCELLS) s_ofs[nsc] = ss;
-            __syncthreads();
-        }
         constexpr int SB = 4;                       // union particles per thread in flight
         for (int u0 = 0; u0 < ss; u0 += SB * BLOCK) {
             int c[SB], slot[SB];
-            bool keep[SB];
-            F4 rec[SB];
+            float o[SB][3], rm[SB];
+            int t[SB];
             D4 pj[SB];
+            unsigned lo[SB], hi[SB], om[SB], any = 0u, anyhi = 0u;
 #pragma unroll
             for (int k = 0; k < SB; ++k) {
                 const int u = u0 + k * BLOCK + tid;
@@ -1574,33 +1680,44 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
             for (int k = 0; k < SB; ++k) pj[k] = ldpos(S, slot[k]);
 #pragma unroll
             for (int k = 0; k < SB; ++k) {
-                keep[k] = false;
-                if (c[k] >= 0) {
-                    const float o[3] = {(float)minimg1(pj[k].x - ref.x, S.per[0], S.box[0]),
-                                        (float)minimg1(pj[k].y - ref.y, S.per[1], S.box[1]),
-                                        (float)minimg1(pj[k].z - ref.z, S.per[2], S.box[2])};
-                    if (far(o)) s_big = 1;
-                    const int t = (int)pj[k].w;
-                    rec[k] = F4{o[0], o[1], o[2], __int_as_float((slot[k] << 2) | (t & 3))};
-                    keep[k] = !tight;
-                    const float rm = sel3f(t, rlm0, rlm1, rlm2);
-                    for (unsigned long long m = s_mask[c[k]]; m; m &= m - 1ull) {
-                        const F4 sp = s_sph[__ffsll(m) - 1];
-                        const float rr = sp.w + rm;
-                        if (dist2f(sp, o[0], o[1], o[2]) <= rr * rr) {
-                            keep[k] = true;
-                            break;
-                        }
+                o[k][0] = offset(0, pj[k].x, ref.x);
+                o[k][1] = offset(1, pj[k].y, ref.y);
+                o[k][2] = offset(2, pj[k].z, ref.z);
+                if (c[k] >= 0 && far(o[k])) s_big = 1;
+                t[k] = (int)pj[k].w & 3;
+                rm[k] = sel3f(t[k], rlm0, rlm1, rlm2);
+                const unsigned long long m = c[k] >= 0 ? s_mask[c[k]] : 0ull;
+                lo[k] = (unsigned)m;
+                hi[k] = (unsigned)(m >> 32);
+                om[k] = 0u;
+                any |= lo[k];
+                anyhi |= hi[k];
+            }
+            // the own cells' spheres, the four particles' next ones side by side
+            auto spheres = [&](unsigned (&m)[SB], unsigned more, int base) {
+                while (more) {
+                    more = 0u;
+#pragma unroll
+                    for (int k = 0; k < SB; ++k) {
+                        const int a = base + (m[k] ? __ffs(m[k]) - 1 : 0);
+                        const F4 sp = s_sph[a];
+                        const float rr = sp.w + rm[k];
+                        if (m[k] && dist2f(sp.x, sp.y, sp.z, o[k][0], o[k][1], o[k][2]) <= rr * rr)
+                            om[k] |= 1u << (nown <= GROUPS ? a : a * GROUPS / nown);
+                        m[k] &= m[k] - 1u;
+                        more |= m[k];
                     }
                 }
-            }
+            };
+            spheres(lo, any, 0);
+            spheres(hi, anyhi, 32);
             // places: by round, wavefront and lane (the union's order)
             int rank[SB];
 #pragma unroll
             for (int k = 0; k < SB; ++k) {
-                const unsigned long long m = __ballot(keep[k]);
-                rank[k] = __popcll(m & ((1ull << lane) - 1ull));
-                if (lane == 0) s_w[k * (BLOCK / WAVE) + wv] = __popcll(m);
+                const unsigned long long b = __ballot(om[k] != 0u);
+                rank[k] = __popcll(b & ((1ull << lane) - 1ull));
+                if (lane == 0) s_w[k * (BLOCK / WAVE) + wv] = __popcll(b);
             }
             static_assert(SB * (BLOCK / WAVE) == 16, "counts of a pass");
             __syncthreads();
@@ -1612,137 +1729,248 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
                     if (w == wv) rank[k] += run;
                     run += s_w[k * (BLOCK / WAVE) + w];
                 }
-                if (keep[k] && rank[k] < USTAGE) s_u[rank[k]] = rec[k];
-                // each cell's first stage entry (cells without particles share the next one's)
-                const int u = u0 + k * BLOCK + tid;
-                if (c[k] >= 0 && u == s_ofs[c[k]])
-                    for (int c2 = c[k]; c2 >= 0 && s_ofs[c2] == u; --c2) s_kofs[c2] = (uint16_t)rank[k];   // (kept beyond USTAGE: no stage)
+                if (om[k] && rank[k] < USTAGE) {
+                    s_ux[rank[k]] = o[k][0];
+                    s_uy[rank[k]] = o[k][1];
+                    s_uz[rank[k]] = o[k][2];
+                    s_tf[rank[k]] = (unsigned char)t[k];
+                    s_om[rank[k]] = (uint16_t)om[k];
+                    stg(S.stage + (size_t)lb * SSTRIDE + rank[k], slot[k]);
+                    if ((unsigned)(slot[k] - first) < (unsigned)BLOCK) s_self[slot[k] - first] = (uint16_t)rank[k];
+                }
             }
-            kept = run;
+            kept = run;                              // (beyond USTAGE: no stage)
             __syncthreads();
         }
-        for (int c = tid; c <= nsc; c += BLOCK)
-            if (s_ofs[c] == ss) s_kofs[c] = (uint16_t)kept;
-        __syncthreads();
     }
     const bool staged = have_union && kept <= USTAGE && s_big == 0;
-    // ---- the lists, and the pruned lists (partners within rc + 2 inner skin) with the
-    // stage entries they use flagged in s_pflag
-    for (int w = tid; w < USTAGE / 4; w += BLOCK) reinterpret_cast<unsigned *>(s_pflag)[w] = 0u;
-    int cnt = 0, pc = 0;
-    int32_t *col = S.nl + (size_t)(chunk_ok ? chunk : 0) * MAXNB * CHUNK + lane;
-    uint16_t *col16 = S.nl16 + (size_t)(chunk_ok ? chunk : 0) * MAXNB * CHUNK + lane;
-    uint16_t *icol = S.il16 + (size_t)(chunk_ok ? chunk : 0) * MAXNB * CHUNK + lane;
+    // ---- the lists, and the bits of the rows that the pruned lists keep
+    int cnt = 0, mygroups = 0;                       // this lane's partners, and groups of eight rows written
+    unsigned pm0 = 0u, pm1 = 0u, pm2 = 0u;
+    static_assert(MAXNB == 96, "row bits in three words");
     const int ti = (int)pi.w & 3;
+    uint16_t *row = S.nl16 + (size_t)(chunk_ok ? chunk : 0) * MAXNB * CHUNK;
+    v4u *row8 = reinterpret_cast<v4u *>(row) + lane;
     if (staged) {
         const float oix = oi[0], oiy = oi[1], oiz = oi[2];
         const float rlA = P.rl2f[ti][0], rlB = P.rl2f[ti][1], rlC = P.rl2f[ti][2];
         const float riA = P.rin2f[ti][0], riB = P.rin2f[ti][1], riC = P.rin2f[ti][2];
-        const int selfw = (i << 2) | ti;                  // this particle's own stage record
-        for (int a0 = 0; a0 < nown;) {
-            const int nb = min(nown - a0, OWNMAX);
-            __syncthreads();
-            // the cells' rows and, from their paired cells' staged sizes, the lists' places
-            if (tid <= nb) s_row[tid] = ldg(S.cnbr_start + c0 + a0 + tid) - q0;
-            if (tid < nb && (a0 > 0 || nown > OWNMAX)) s_sph[tid] = own_sphere(a0 + tid);
-            __syncthreads();
-            for (int a = wv; a < nb; a += BLOCK / WAVE) {
-                int sz = 0;
-                for (int q = s_row[a] + lane; q < s_row[a + 1]; q += WAVE) {
-                    const int p = s_qpos[q];
-                    sz += s_kofs[p + 1] - s_kofs[p];
+        const int oself = valid ? 4 * (int)s_self[tid] : -1;     // this particle's own stage entry (LDS offset)
+        const int G = min(nown, GROUPS), mygrp = nown <= GROUPS ? A - c0 : (A - c0) * GROUPS / nown;
+        auto ux = [&](int o) { return *reinterpret_cast<const float *>(s_raw + o); };
+        auto uy = [&](int o) { return *reinterpret_cast<const float *>(s_raw + 4 * USTAGE + o); };
+        auto uz = [&](int o) { return *reinterpret_cast<const float *>(s_raw + 8 * USTAGE + o); };
+        // a wavefront's lists (every fourth): one sweep over the stage entries' bits counts
+        // them, a second one writes those that fit
+        constexpr int LPW = GROUPS / (BLOCK / WAVE);
+        auto sweep = [&](auto write_tag, int g0, int g1, int (&nl)[LPW], int (&np)[LPW], const int (&pf)[LPW], const int (&pb)[LPW]) {
+            constexpr bool WRITE = decltype(write_tag)::value;
+            unsigned nbits = lane < kept ? s_om[lane] : 0u;
+            int ntype = s_tf[lane];
+            for (int k0 = 0; k0 < kept; k0 += WAVE) {
+                const int k = k0 + lane;
+                const unsigned bits = nbits;
+                const bool lip = (ntype & 3) == 0;
+                const int kn = min(k + WAVE, USTAGE - 1);                // the next entries are on their way
+                nbits = k + WAVE < kept ? s_om[kn] : 0u;
+                ntype = s_tf[kn];
+#pragma unroll
+                for (int j = 0; j < LPW; ++j) {
+                    const int g = wv + j * (BLOCK / WAVE);
+                    if (g < g0 || g >= g1) continue;                     // wavefront-uniform
+                    const bool in = (bits >> g) & 1u;
+                    const unsigned long long ml = __ballot(in && lip), mp = __ballot(in && !lip);
+                    if constexpr (WRITE) {
+                        const unsigned long long mine = lip ? ml : mp;
+                        const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(mine >> 32),
+                                                                     __builtin_amdgcn_mbcnt_lo((unsigned)mine, 0u));
+                        const int at = lip ? pf[j] + nl[j] + before : pb[j] - 1 - np[j] - before;
+                        if (in) s_list[at] = (uint16_t)(4 * k);
+                    }
+                    nl[j] += __popcll(ml);
+                    np[j] += __popcll(mp);
                 }
-                for (int o = 32; o > 0; o >>= 1) sz += __shfl_xor(sz, o);
-                if (lane == 0) s_lcnt[a] = sz;
             }
+        };
+        {
+            int nl[LPW] = {0, 0, 0, 0}, np[LPW] = {0, 0, 0, 0};
+            sweep(std::false_type{}, 0, G, nl, np, nl, np);
+#pragma unroll
+            for (int j = 0; j < LPW; ++j) {
+                const int g = wv + j * (BLOCK / WAVE);
+                if (lane == 0 && g < G) {
+                    s_nl[g] = (uint16_t)nl[j];
+                    s_np[g] = (uint16_t)np[j];
+                }
+            }
+        }
+        for (int g0 = 0; g0 < G;) {
             __syncthreads();
+            // the lists' places: whole groups of four entries, with room for both ends' padding
             if (wv == 0) {
-                const int v = lane < nb ? s_lcnt[lane] : 0;
-                int x = v;
-                for (int o = 1; o < WAVE; o <<= 1) {
-                    const int y = __shfl_up(x, o);
-                    if (lane >= o) x += y;
+                const bool has = lane < G - g0;
+                const int x = wave_incl_scan(has ? (((int)s_nl[g0 + lane] + (int)s_np[g0 + lane] + 3) & ~3) + 4 : 0);
+                if (lane < GROUPS) s_lofs[lane + 1] = x;
+                const unsigned long long fit = __ballot(has && x <= CLIST);
+                if (lane == 0) {
+                    s_lofs[0] = 0;
+                    s_nfit = __popcll(fit);                              // x grows with the lane: a prefix
                 }
-                s_lofs[lane] = x - v;
-                const unsigned long long fit = __ballot(lane < nb && x <= CLIST);
-                if (lane == 0) s_nfit = __popcll(fit);       // x grows with the lane: a prefix
             }
-            static_assert(CLIST >= USTAGE, "one cell's list always fits");
+            static_assert(CLIST >= USTAGE + 8, "one list always fits");
             __syncthreads();
             const int nfit = s_nfit;
-            // one wavefront per cell, sixteen lanes per paired cell
-            for (int a = wv; a < nfit; a += BLOCK / WAVE) {
-                const F4 sp = s_sph[a];
-                const float r0 = sp.w + rlm0, r1 = sp.w + rlm1, r2 = sp.w + rlm2;
-                const float r0s = r0 * r0, r1s = r1 * r1, r2s = r2 * r2;
-                uint16_t *out = s_list + s_lofs[a];
-                int n = 0;
-                for (int q = s_row[a] + (lane >> 4), qe = s_row[a + 1]; __ballot(q < qe) != 0ull; q += 4) {
-                    int k = 0, ke = 0;
-                    if (q < qe) {
-                        const int p = s_qpos[q];
-                        k = s_kofs[p] + (lane & 15);
-                        ke = s_kofs[p + 1];
-                    }
-                    while (__ballot(k < ke) != 0ull) {
-                        bool in = false;
-                        if (k < ke) {
-                            const F4 u = s_u[k];
-                            in = dist2f(u, sp.x, sp.y, sp.z) <= sel3f(__float_as_int(u.w) & 3, r0s, r1s, r2s);
-                        }
-                        const unsigned long long m = __ballot(in);
-                        if (in) out[n + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)k;
-                        n += __popcll(m);
-                        k += 16;
+            {
+                int nl[LPW] = {0, 0, 0, 0}, np[LPW] = {0, 0, 0, 0}, pf[LPW], pb[LPW];
+#pragma unroll
+                for (int j = 0; j < LPW; ++j) {
+                    const int g = min(max(wv + j * (BLOCK / WAVE) - g0, 0), nfit - 1);
+                    pf[j] = __builtin_amdgcn_readfirstlane(s_lofs[g]);
+                    pb[j] = __builtin_amdgcn_readfirstlane(s_lofs[g + 1]);
+                }
+                sweep(std::true_type{}, g0, g0 + nfit, nl, np, pf, pb);
+#pragma unroll
+                for (int j = 0; j < LPW; ++j) {
+                    const int g = wv + j * (BLOCK / WAVE);
+                    if (g >= g0 && g < g0 + nfit && lane < 3) {          // the last groups of four end in valid offsets
+                        s_list[pf[j] + nl[j] + lane] = 0;
+                        s_list[pb[j] - 1 - np[j] - lane] = 0;
                     }
                 }
-                if (lane == 0) s_lcnt[a] = n;
             }
             __syncthreads();
-            if (valid && A >= c0 + a0 && A < c0 + a0 + nfit) {
-                const uint16_t *lst = s_list + s_lofs[A - c0 - a0];
-                const int n = s_lcnt[A - c0 - a0];
-                auto scan_list = [&](auto per_tag) {
+            if (valid && mygrp >= g0 && mygrp < g0 + nfit) {
+                const int nl = s_nl[mygrp], np = s_np[mygrp], wl = (nl + 31) >> 5;
+                const int pf = s_lofs[mygrp - g0], pb = s_lofs[mygrp - g0 + 1];    // lipids from pf up, proteins from pb - 1 down
+                auto scan = [&](auto per_tag) {
                     constexpr bool PER = decltype(per_tag)::value;
-                    auto test = [&](const F4 &c, int k) {
-                        float dx = c.x - oix, dy = c.y - oiy, dz = c.z - oiz;
+                    auto dist2 = [&](int o) {
+                        float dx = ux(o) - oix, dy = uy(o) - oiy, dz = uz(o) - oiz;
                         if constexpr (PER) {
                             dx -= Lx * rintf(dx * iLx);
                             dy -= Ly * rintf(dy * iLy);
                             dz -= Lz * rintf(dz * iLz);
                         }
-                        const float d2 = dx * dx + dy * dy + dz * dz;
-                        const int w = __float_as_int(c.w);
-                        if (d2 < sel3f(w & 3, rlA, rlB, rlC) && w != selfw) {
-                            if (cnt < MAXNB) {
-                                stg(col16 + cnt * CHUNK, (uint16_t)k);
-                                // the pruned list: the entries within the pruned radius
-                                if (d2 < sel3f(w & 3, riA, riB, riC)) {
-                                    stg(icol + pc * CHUNK, (uint16_t)k);
-                                    ++pc;
-                                    s_pflag[k] = 1;
-                                }
-                            }
-                            ++cnt;
-                        }
+                        return dx * dx + dy * dy + dz * dz;
                     };
-                    int e = 0;
-                    for (; e + 3 < n; e += 4) {                   // four candidates per trip
-                        const int k0 = lst[e], k1 = lst[e + 1], k2 = lst[e + 2], k3 = lst[e + 3];
-                        const F4 u0 = s_u[k0], u1 = s_u[k1], u2 = s_u[k2], u3 = s_u[k3];
-                        test(u0, k0);
-                        test(u1, k1);
-                        test(u2, k2);
-                        test(u3, k3);
+                    // the hits among 32 candidates of a segment from candidate c on (n in all),
+                    // candidate c + b in bit b, four candidates per trip
+                    auto word = [&](auto lip_tag, int c, int n) {
+                        constexpr bool LIP = decltype(lip_tag)::value;
+                        const int ne = min(32, n - c);
+                        unsigned m = 0u;
+#pragma unroll 2
+                        for (int j = 0; j < ne; j += 4) {
+                            const uint2 l = *reinterpret_cast<const uint2 *>(s_list + (LIP ? pf + c + j : pb - 4 - c - j));
+                            const int o[4] = {(int)(l.x & 0xffffu), (int)(l.x >> 16), (int)(l.y & 0xffffu), (int)(l.y >> 16)};
+                            m >>= 4;
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                const int oq = o[LIP ? q : 3 - q];
+                                const float rl = LIP ? rlA : sel3f(s_tf[oq >> 2] & 3, rlA, rlB, rlC);
+                                const bool hit = dist2(oq) < rl && oq != oself;
+                                m |= hit ? 1u << (28 + q) : 0u;
+                            }
+                        }
+                        m >>= 32 - ((ne + 3) & ~3);
+                        return ne < 32 ? m & ((1u << ne) - 1u) : m;
+                    };
+                    // candidate b of word w in the list
+                    auto at = [&](int w, int b) { return w < wl ? pf + 32 * w + b : pb - 1 - 32 * (w - wl) - b; };
+                    // a row's test against the pruned radius
+                    auto inner = [&](int o, int t) { return dist2(o) < sel3f(t, riA, riB, riC); };
+                    // hit words, the empty ones left out; their numbers, five bits each, in wix
+                    const int nw = wl + ((np + 31) >> 5);
+                    int w = 0, slots = 0;
+                    unsigned long long wix = 0ull;
+                    for (; w < nw && w < 32 && slots < MWORDS; ++w) {
+                        const unsigned m = w < wl ? word(std::true_type{}, 32 * w, nl) : word(std::false_type{}, 32 * (w - wl), np);
+                        if (m) {
+                            s_m[slots * BLOCK + tid] = m;
+                            wix |= (unsigned long long)w << (5 * slots);
+                            ++slots;
+                            cnt += __popc(m);
+                        }
                     }
-                    for (; e < n; ++e) test(s_u[lst[e]], lst[e]);
+                    // rows: every lane's next hit, eight rows to a store
+                    const int n = min(cnt, MAXNB);
+                    // (the next three words wait in registers; a group that uses up more reads on)
+                    int slot = 0;
+                    unsigned cur = n > 0 ? s_m[tid] : 0u;
+                    for (int g = 0; __ballot(8 * g < n) != 0ull; ++g) {
+                        int o[8], t[8];
+                        bool have[8];
+                        unsigned e[8], pbits = 0u;
+                        unsigned n1 = s_m[min(slot + 1, MWORDS - 1) * BLOCK + tid], n2 = s_m[min(slot + 2, MWORDS - 1) * BLOCK + tid],
+                                 n3 = s_m[min(slot + 3, MWORDS - 1) * BLOCK + tid];
+                        const int last3 = slot + 3;
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) {
+                            have[q] = 8 * g + q < n;
+                            const bool next = have[q] && cur == 0u;
+                            slot += next ? 1 : 0;
+                            cur = next ? n1 : cur;
+                            n1 = next ? n2 : n1;
+                            n2 = next ? n3 : n2;
+                            if (__builtin_expect(__ballot(next && slot > last3) != 0ull, 0))
+                                if (next && slot > last3) cur = s_m[slot * BLOCK + tid];
+                            const int cw = (int)(wix >> (5 * slot)) & 31;
+                            o[q] = have[q] ? at(cw, __ffs(cur) - 1) : pf;
+                            cur &= cur - 1u;
+                        }
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) o[q] = s_list[o[q]];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) t[q] = s_tf[o[q] >> 2] & 3;
+                        bool in[8];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) in[q] = have[q] && inner(o[q], t[q]);
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) {
+                            e[q] = have[q] ? (unsigned)(o[q] >> 2) : 0xffffu;
+                            if (in[q]) {
+                                pbits |= 1u << q;
+                                s_tf[o[q] >> 2] = (unsigned char)(t[q] | STAGE_USED);
+                            }
+                        }
+                        const v4u out = {e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
+                        stg(row8 + g * CHUNK, out);
+                        const unsigned pw = pbits << (8 * (g & 3));
+                        if (g < 4) pm0 |= pw;
+                        else if (g < 8) pm1 |= pw;
+                        else pm2 |= pw;
+                        mygroups = g + 1;
+                    }
+                    // the words beyond the slots, hit by hit
+                    for (; w < nw; ++w) {
+                        unsigned m = w < wl ? word(std::true_type{}, 32 * w, nl) : word(std::false_type{}, 32 * (w - wl), np);
+                        for (; m; m &= m - 1u, ++cnt) {
+                            if (cnt >= MAXNB) continue;
+                            const int o1 = s_list[at(w, __ffs(m) - 1)], t1 = s_tf[o1 >> 2] & 3;
+                            if ((cnt & 7) == 0) {
+                                stg(row8 + (cnt >> 3) * CHUNK, v4u{~0u, ~0u, ~0u, ~0u});
+                                mygroups = (cnt >> 3) + 1;
+                            }
+                            stg(row + nl_at(cnt, lane), (uint16_t)(o1 >> 2));
+                            if (inner(o1, t1)) {
+                                const unsigned bit = 1u << (cnt & 31);
+                                if (cnt < 32) pm0 |= bit;
+                                else if (cnt < 64) pm1 |= bit;
+                                else pm2 |= bit;
+                                s_tf[o1 >> 2] = (unsigned char)(t1 | STAGE_USED);
+                            }
+                        }
+                    }
                 };
-                if (periodic) scan_list(std::true_type{});
-                else scan_list(std::false_type{});
+                if (periodic) scan(std::true_type{});
+                else scan(std::false_type{});
             }
-            a0 += nfit;
+            g0 += nfit;
         }
-    } else if (valid) {
+    }
+    int32_t *col = S.nl + (size_t)(chunk_ok ? chunk : 0) * MAXNB * CHUNK + lane;
+    if (!staged && valid) {
+        cnt = 0;
         for (int q = S.cnbr_start[A]; q < S.cnbr_start[A + 1]; ++q) {
             int B = ldg(S.cnbr + q);
             int b = ldg(S.cstart + B), e = b + ldg(S.ccount + B);
@@ -1765,60 +1993,21 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
     }
     if (chunk_ok && lane == 0) S.nlk[chunk] = rows;
     if (lane == 0) atomicMax(&s_rows, rows);
-    // pad every lane to the chunk's row count, and write the stage's slots
-    if (chunk_ok) {
-        const int mycnt = valid ? min(cnt, MAXNB) : 0;
-        if (staged)
-            for (int r = mycnt; r < rows; ++r) stg(col16 + r * CHUNK, (uint16_t)0xffff);
-        else
-            for (int r = mycnt; r < rows; ++r) stg(col + r * CHUNK, (int32_t)-1);
-    }
-    if (staged)
-        for (int k = tid; k < kept; k += BLOCK) stg(S.stage + (size_t)lb * SSTRIDE + k, __float_as_int(s_u[k].w) >> 2);
-    // the pruned stage: the flagged stage entries, in stage order; the pruned lists are
-    // rewritten as indices into it (each lane reads back what it wrote) and padded to
-    // the chunk's row count rounded up to even (the step kernel takes rows in pairs).
-    // A block without a stage walks its 32-bit lists unpruned.
-    int irows = wave_max_int(min(pc, MAXNB));
-    if (!staged) irows = rows;
-    if (chunk_ok && lane == 0) S.ilk[chunk] = irows;
-    __syncthreads();
-    unsigned *s_bits = reinterpret_cast<unsigned *>(s_x);            // the candidate lists are done with
-    int *s_pre = reinterpret_cast<int *>(s_x) + USTAGE / 32;
-    static_assert(sizeof(s_x) >= 2 * (USTAGE / 32) * sizeof(int), "pruned-stage words overlay the candidate lists");
     int nkept = -1;
     if (staged) {
-        const int nwords = (kept + 31) / 32;
-        for (int w = tid; w < nwords; w += BLOCK) {
-            s_bits[w] = pack_flags(s_pflag + 32 * w);
-            s_pre[w] = __popc(s_bits[w]);
-        }
-        __syncthreads();
-        nkept = block_scan_lds(s_pre, nwords, s_w);
-        for (int k = tid; k < kept; k += BLOCK) {
-            const int w = k >> 5;
-            const unsigned m = 1u << (k & 31);
-            if (s_bits[w] & m)
-                stg(S.istage + (size_t)lb * SSTRIDE + s_pre[w] + __popc(s_bits[w] & (m - 1u)), __float_as_int(s_u[k].w) >> 2);
-        }
-        const int prows = (irows + 1) & ~1;
-        const int mine = valid ? min(pc, MAXNB) : 0;
+        // pad every lane to the chunk's groups of rows, then the pruned stage and lists
         if (chunk_ok)
-            for (int r0 = 0; r0 < prows; r0 += 8) {
-                int e[8];
-#pragma unroll
-                for (int q = 0; q < 8; ++q) e[q] = r0 + q < mine ? (int)ldg(icol + (r0 + q) * CHUNK) : -1;
-#pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    if (r0 + q >= prows) break;
-                    int local = 0xffff;
-                    if (e[q] >= 0) {
-                        const int w = e[q] >> 5;
-                        local = s_pre[w] + __popc(s_bits[w] & ((1u << (e[q] & 31)) - 1u));
-                    }
-                    stg(icol + (r0 + q) * CHUNK, (uint16_t)local);
-                }
-            }
+            for (int g = mygroups; 8 * g < rows; ++g) stg(row8 + g * CHUNK, v4u{~0u, ~0u, ~0u, ~0u});
+        uint2 *s_bp = reinterpret_cast<uint2 *>(s_raw);
+        nkept = pruned_stage(S, lb, kept, s_tf, s_bp, s_w);
+        constexpr int PAIRS = (sizeof(s_raw) - 8 * (SMAX / 32)) / (4 * BLOCK);
+        if (chunk_ok)
+            emit_pruned<PAIRS>(S, chunk, rows, pm0, pm1, pm2, s_bp, reinterpret_cast<uint16_t *>(s_raw + 8 * (SMAX / 32)));
+    } else if (chunk_ok) {
+        // a block without a stage walks its 32-bit lists unpruned
+        const int mycnt = valid ? min(cnt, MAXNB) : 0;
+        for (int r = mycnt; r < rows; ++r) stg(col + r * CHUNK, (int32_t)-1);
+        if (lane == 0) S.ilk[chunk] = rows;
     }
     __syncthreads();
     if (tid == 0) {
@@ -1851,14 +2040,12 @@ void launch_nlist(const LaunchCtx &L) {
 // since the prune.
 __global__ __launch_bounds__(BLOCK) void k_prune(const SysDev *Sd, Maps L_maps, DevParams P) {
     SYS_FROM(p);
-    // stage offsets, 12 B each: the type rides in the two low mantissa bits of x (a
-    // change of at most three ulp, far inside the 1e-3 sigma widening of the radius)
-    __shared__ F3 s_o[SMAX];
-    __shared__ __align__(16) unsigned char s_flag[SMAX];   // stage entry kept by some lane (plain stores of 1)
-    __shared__ unsigned s_bits[SMAX / 32];
-    __shared__ int s_pre[SMAX / 32];
-    __shared__ int s_w[16];
+    // the stage's offsets; after the test, the pruned stage's words and the row buffer
+    __shared__ __align__(16) unsigned char s_raw[3 * SMAX * 4];
+    __shared__ __align__(16) unsigned char s_tf[SMAX];     // type | STAGE_USED
+    __shared__ int s_w[4];
     __shared__ int s_big;
+    float *s_x = reinterpret_cast<float *>(s_raw), *s_y = s_x + SMAX, *s_z = s_y + SMAX;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int chunk = lb * (BLOCK / WAVE) + wv;
     const bool chunk_ok = chunk < S.nchunk;
@@ -1868,14 +2055,13 @@ __global__ __launch_bounds__(BLOCK) void k_prune(const SysDev *Sd, Maps L_maps, 
     const D4 pi = valid ? ldpos(S, i) : D4{0.0, 0.0, 0.0, 0.0};
     if (valid) S.xp[i] = F3{(float)pi.x, (float)pi.y, (float)pi.z};
     const int scnt = S.scount[lb];
-    const int rows = chunk_ok ? min(S.nlk[chunk], MAXNB) : 0;
+    const int rows = chunk_ok ? __builtin_amdgcn_readfirstlane(min(S.nlk[chunk], MAXNB)) : 0;
     if (scnt < 0) {
         if (chunk_ok && lane == 0) S.ilk[chunk] = rows;
         if (tid == 0) S.iscount[lb] = -1;
         return;
     }
     if (tid == 0) s_big = 0;
-    for (int w = tid; w < SMAX / 4; w += BLOCK) reinterpret_cast<unsigned *>(s_flag)[w] = 0u;
     const D4 ref = ld3(S.pos + (size_t)lb * BLOCK);
     bool far = false;
     // eight entries per thread in flight: their slots, then their positions
@@ -1894,17 +2080,21 @@ __global__ __launch_bounds__(BLOCK) void k_prune(const SysDev *Sd, Maps L_maps, 
             const float ox = (float)minimg1(pj.x - ref.x, S.per[0], S.box[0]);
             const float oy = (float)minimg1(pj.y - ref.y, S.per[1], S.box[1]);
             const float oz = (float)minimg1(pj.z - ref.z, S.per[2], S.box[2]);
-            s_o[q] = F3{__int_as_float((__float_as_int(ox) & ~3) | ((int)pj.w & 3)), oy, oz};
+            s_x[q] = ox;
+            s_y[q] = oy;
+            s_z[q] = oz;
+            s_tf[q] = (unsigned char)((int)pj.w & 3);
             far = far || !(fabsf(ox) <= LIST_EXTENT && fabsf(oy) <= LIST_EXTENT && fabsf(oz) <= LIST_EXTENT);
         }
     }
+    // the bytes up to the next whole word of flags
+    if (tid < 32 && scnt + tid < ((scnt + 31) & ~31)) s_tf[scnt + tid] = 0;
     if (far) s_big = 1;                              // offsets out of range or not finite
     __syncthreads();
     const bool keep_all = s_big != 0;
-    int cnt = 0;
-    const uint16_t *col = S.nl16 + (size_t)(chunk_ok ? chunk : 0) * MAXNB * CHUNK + lane;
-    uint16_t *icol = S.il16 + (size_t)(chunk_ok ? chunk : 0) * MAXNB * CHUNK + lane;
-    constexpr int BATCH = 32;    // list rows whose entries are loaded together
+    const v4u *src = reinterpret_cast<const v4u *>(S.nl16 + (size_t)(chunk_ok ? chunk : 0) * MAXNB * CHUNK) + lane;
+    unsigned pm0 = 0u, pm1 = 0u, pm2 = 0u;           // the rows that stay
+    static_assert(MAXNB == 96, "row bits in three words");
     if (valid && chunk_ok) {
         const int ti = (int)pi.w;
         const float oix = (float)minimg1(pi.x - ref.x, S.per[0], S.box[0]);
@@ -1918,68 +2108,44 @@ __global__ __launch_bounds__(BLOCK) void k_prune(const SysDev *Sd, Maps L_maps, 
                     Lz = S.per[2] ? (float)S.box[2] : 0.0f;
         const float iLx = S.per[0] ? 1.0f / Lx : 0.0f, iLy = S.per[1] ? 1.0f / Ly : 0.0f,
                     iLz = S.per[2] ? 1.0f / Lz : 0.0f;
-        for (int r0 = 0; r0 < rows; r0 += BATCH) {
-            int e[BATCH];
+        const int ng = (rows + 7) / 8;
+        v4u nx0 = {~0u, ~0u, ~0u, ~0u}, nx1 = nx0;   // the next two groups of eight rows
+        if (ng > 0) nx0 = ldg(src);
+        if (ng > 1) nx1 = ldg(src + CHUNK);
+        for (int g = 0; g < ng; ++g) {
+            const v4u e = nx0;
+            nx0 = nx1;
+            if (g + 2 < ng) nx1 = ldg(src + (g + 2) * CHUNK);
+            unsigned pbits = 0u;
 #pragma unroll
-            for (int q = 0; q < BATCH; ++q) e[q] = (int)ldg(col + min(r0 + q, rows - 1) * CHUNK);
-#pragma unroll
-            for (int q = 0; q < BATCH; ++q) {
-                const int eq = (r0 + q < rows) ? e[q] : 0xffff;
-                const F3 c = s_o[eq < scnt ? eq : 0];
-                float dx = c.x - oix, dy = c.y - oiy, dz = c.z - oiz;
+            for (int q = 0; q < 8; ++q) {
+                const int k = (int)((q & 1) ? e[q >> 1] >> 16 : e[q >> 1] & 0xffffu);
+                const bool real = k < scnt;          // 0xffff pads
+                const int ks = real ? k : 0;
+                float dx = s_x[ks] - oix, dy = s_y[ks] - oiy, dz = s_z[ks] - oiz;
                 if (periodic) {
                     dx -= Lx * rintf(dx * iLx);
                     dy -= Ly * rintf(dy * iLy);
                     dz -= Lz * rintf(dz * iLz);
                 }
                 const float d2 = dx * dx + dy * dy + dz * dz;
-                const float rr = sel3f(__float_as_int(c.x) & 3, rA, rB, rC);
-                if (eq < scnt && (keep_all || d2 < rr)) {
-                    stg(icol + cnt * CHUNK, (uint16_t)eq);
-                    ++cnt;
-                    s_flag[eq] = 1;
+                const int t = s_tf[ks] & 3;
+                if (real && (keep_all || d2 < sel3f(t, rA, rB, rC))) {
+                    pbits |= 1u << q;
+                    s_tf[ks] = (unsigned char)(t | STAGE_USED);
                 }
             }
+            const unsigned pw = pbits << (8 * (g & 3));
+            if (g < 4) pm0 |= pw;
+            else if (g < 8) pm1 |= pw;
+            else pm2 |= pw;
         }
     }
-    const int irows = wave_max_int(cnt);
-    if (chunk_ok && lane == 0) S.ilk[chunk] = irows;
-    __syncthreads();
-    const int nwords = (scnt + 31) / 32;
-    for (int w = tid; w < nwords; w += BLOCK) {
-        s_bits[w] = pack_flags(s_flag + 32 * w);
-        s_pre[w] = __popc(s_bits[w]);
-    }
-    __syncthreads();
-    const int nkept = block_scan_lds(s_pre, nwords, s_w);
-    // the pruned stage: every kept entry's slot at its rank among the kept entries
-    for (int q = tid; q < scnt; q += BLOCK) {
-        const int w = q >> 5;
-        const unsigned m = 1u << (q & 31);
-        if (s_bits[w] & m)
-            stg(S.istage + (size_t)lb * SSTRIDE + s_pre[w] + __popc(s_bits[w] & (m - 1u)),
-                ldg(S.stage + (size_t)lb * SSTRIDE + q));
-    }
-    // rewrite the kept entries as pruned-stage indices (the lane reads back what it
-    // wrote), padding every lane to the chunk's row count rounded up to even (the step
-    // kernel takes rows in pairs)
-    const int prows = (irows + 1) & ~1;
+    uint2 *s_bp = reinterpret_cast<uint2 *>(s_raw);
+    const int nkept = pruned_stage(S, lb, scnt, s_tf, s_bp, s_w);
+    constexpr int PAIRS = (sizeof(s_raw) - 8 * (SMAX / 32)) / (4 * BLOCK);
     if (chunk_ok)
-        for (int r0 = 0; r0 < prows; r0 += BATCH) {
-            int e[BATCH];
-#pragma unroll
-            for (int q = 0; q < BATCH; ++q) e[q] = r0 + q < cnt ? (int)ldg(icol + (r0 + q) * CHUNK) : -1;
-#pragma unroll
-            for (int q = 0; q < BATCH; ++q) {
-                if (r0 + q >= prows) break;
-                int local = 0xffff;
-                if (e[q] >= 0) {
-                    const int w = e[q] >> 5;
-                    local = s_pre[w] + __popc(s_bits[w] & ((1u << (e[q] & 31)) - 1u));
-                }
-                stg(icol + (r0 + q) * CHUNK, (uint16_t)local);
-            }
-        }
+        emit_pruned<PAIRS>(S, chunk, rows, pm0, pm1, pm2, s_bp, reinterpret_cast<uint16_t *>(s_raw + 8 * (SMAX / 32)));
     if (tid == 0) S.iscount[lb] = nkept;
 }
 

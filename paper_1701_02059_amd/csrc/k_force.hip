@@ -432,18 +432,6 @@ __device__ __forceinline__ void swap_drift(SysDev &W) {
 
 // ------------------------------------------------------------------ force kernel
 
-// Minimum-image separation for the step kernel: k = rint(d * (1/L)) instead of
-// rint(d / L).  The two differ only where d / L lies within a few ulp of a
-// half-integer, that is at separations near L / 2, beyond every list radius (a
-// periodic length exceeds twice the largest cutoff plus skin); every pair that can
-// be in range gets the same k, hence the same separation bits, as the exact test.
-__device__ __forceinline__ double minimg_fast(double d, double L, double iL) {
-#pragma clang fp contract(off)
-    const double k = __builtin_rint(d * iL);
-    const double kl = k * L;
-    return d - kl;
-}
-
 // Branch-free FP32 lipid-lipid law for the mixed-precision step kernel, on the
 // separation (dx, dy, dz) = x_i - x_j with r2 = |d|^2 > 0.  Both radial branches are
 // evaluated and selected (the repulsive core below r_min, the cos^(2 zeta) well above
@@ -720,11 +708,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
         constexpr int UNR = 2;          // rows per trip (consecutive), evaluated side by side
         // The pruned lists are padded with 0xffff to an even row count in every lane, so
         // both rows of a trip are always valid entries or padding.
-        const int nrow = (rows + 1) & ~1;
-        const int r0 = SPLIT ? UNR * (tid >> 6) : 0;
-        constexpr int tstride = SPLIT ? UNR * (BLOCK / WAVE) : UNR;
-        const uint16_t *col = S.il16 + (size_t)chunk * MAXNB * CHUNK + r0 * CHUNK + lane;
-        const int ntrip = nrow > r0 ? (nrow - r0 + tstride - 1) / tstride : 0;
+        const int npair = (rows + 1) >> 1;
+        constexpr int tstride = SPLIT ? BLOCK / WAVE : 1;
+        const int p0 = SPLIT ? tid >> 6 : 0;
+        const unsigned *col = reinterpret_cast<const unsigned *>(S.il16 + (size_t)chunk * MAXNB * CHUNK) + p0 * CHUNK + lane;
+        const int ntrip = npair > p0 ? (npair - p0 + tstride - 1) / tstride : 0;
         // this particle's row of the FP32 bounds, chosen by selects (no dynamic indexing
         // of the parameter block, which would go through scratch memory)
         auto row_of = [&](const float (&m)[3][3], int b) {
@@ -764,13 +752,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
         // memory while this trip's rows are evaluated (the lists carry padding rows past
         // the last chunk, so the load after the last trip stays in bounds).
         float sbi = 0.0f, gx = 0.0f, gy = 0.0f, gz = 0.0f;   // sum of bi; of g_i - cn n_i
-        int en[UNR];
-        for (int q = 0; q < UNR; ++q) en[q] = ntrip > 0 ? (int)ldg(col + q * CHUNK) : 0xffff;
+        unsigned en = ntrip > 0 ? ldg(col) : 0xffffffffu;    // a pair of rows
         for (int it = 0; it < ntrip; ++it) {
             Rec c[UNR];
-            for (int q = 0; q < UNR; ++q) c[q] = fetch(en[q]);
-            const uint16_t *nxt = col + (size_t)(it + 1) * tstride * CHUNK;
-            for (int q = 0; q < UNR; ++q) en[q] = (int)ldg(nxt + q * CHUNK);
+            c[0] = fetch((int)(en & 0xffffu));
+            c[1] = fetch((int)(en >> 16));
+            en = ldg(col + (size_t)(it + 1) * tstride * CHUNK);
             // separations and the neighbour test of every row of the trip
             double dx[UNR], dy[UNR], dz[UNR];
             float fdx[UNR], fdy[UNR], fdz[UNR], r2[UNR];
@@ -874,17 +861,17 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
         constexpr bool PER = decltype(per_tag)::value;
         constexpr bool PARTIAL = decltype(part_tag)::value;
         constexpr bool SPLIT = decltype(split_tag)::value;
-        constexpr int rstep = SPLIT ? BLOCK / WAVE : 1;
-        const int r0 = SPLIT ? (tid >> 6) : 0;
-        // Software pipeline: the list entry of row r+4 is fetched from global memory and
-        // the stage record of row r+1 from LDS while row r is evaluated.
-        const uint16_t *col = S.il16 + (size_t)chunk * MAXNB * CHUNK + r0 * CHUNK + lane;
-        const int cstep = rstep * CHUNK;
-        const int nr = rows > r0 ? (rows - r0 + rstep - 1) / rstep : 0;
-        int e_cur = (valid && nr > 0) ? (int)ldg(col) : 0xffff;
-        int e_nxt = (valid && nr > 1) ? (int)ldg(col + cstep) : 0xffff;
-        int e_n2 = (valid && nr > 2) ? (int)ldg(col + 2 * cstep) : 0xffff;
-        int e_n3 = (valid && nr > 3) ? (int)ldg(col + 3 * cstep) : 0xffff;
+        constexpr int tstride = SPLIT ? BLOCK / WAVE : 1;    // pairs of rows, as in mixed mode
+        const int p0 = SPLIT ? tid >> 6 : 0;
+        // Software pipeline: the list entries two pairs of rows ahead are fetched from global
+        // memory and the stage record of the next row from LDS while a row is evaluated (the
+        // lists carry padding rows past the last chunk).
+        const unsigned *col = reinterpret_cast<const unsigned *>(S.il16 + (size_t)chunk * MAXNB * CHUNK) + p0 * CHUNK + lane;
+        constexpr int cstep = tstride * CHUNK;
+        const int npair = (rows + 1) >> 1;
+        const int ntrip = npair > p0 ? (npair - p0 + tstride - 1) / tstride : 0;
+        unsigned w0 = (valid && ntrip > 0) ? ldg(col) : 0xffffffffu;
+        unsigned w1 = (valid && ntrip > 1) ? ldg(col + cstep) : 0xffffffffu;
         struct Rec {
             double x, y, z;
             T nx, ny, nz;
@@ -911,16 +898,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
             c.t = s_t[q];
             return c;
         };
-        Rec rec = fetch(e_cur);
         double sbi = 0.0, gx = 0.0, gy = 0.0, gz = 0.0;       // sum of bi; of g_i - cn n_i
-        for (int r = 0; r < nr; ++r) {
-            const int e = e_cur;
-            const Rec c = rec;
-            e_cur = e_nxt;
-            e_nxt = e_n2;
-            e_n2 = e_n3;
-            e_n3 = (valid && r + 4 < nr) ? (int)ldg(col + (r + 4) * cstep) : 0xffff;
-            rec = fetch(e_cur);
+        auto eval = [&](const Rec &c, int e) {
             const int tj = c.t;
             double dx, dy, dz, d2;
             if constexpr (PER) {
@@ -960,6 +939,16 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
                     }
                 }
             }
+        };
+        Rec ra = fetch((int)(w0 & 0xffffu));
+        for (int it = 0; it < ntrip; ++it) {
+            const int ea = (int)(w0 & 0xffffu), eb = (int)(w0 >> 16);
+            const Rec rb = fetch(eb);
+            w0 = w1;
+            w1 = (valid && it + 2 < ntrip) ? ldg(col + (it + 2) * cstep) : 0xffffffffu;
+            eval(ra, ea);
+            ra = fetch((int)(w0 & 0xffffu));
+            eval(rb, eb);
         }
         fx -= sbi * nix;
         fy -= sbi * niy;
@@ -1426,12 +1415,12 @@ void launch_scatter_forces(const LaunchCtx &L, int sys, double *F, double *T, in
 // Pruned blocks keep indices into their pruned stage in the 16-bit lists (0xffff
 // pads); the others keep global slots in the 32-bit lists (-1 pads).
 __device__ __forceinline__ int entry_slot(const SysDev &S, int blk, int scnt, int chunk, int lane, int r) {
-    const size_t at = (size_t)chunk * MAXNB * CHUNK + (size_t)r * CHUNK + lane;
+    const size_t base = (size_t)chunk * MAXNB * CHUNK;
     if (scnt >= 0) {
-        const int e = S.il16[at];
+        const int e = S.il16[base + il_at(r, lane)];
         return e < scnt ? S.istage[(size_t)blk * SSTRIDE + e] : -1;
     }
-    return S.nl[at];
+    return S.nl[base + r * CHUNK + lane];
 }
 
 // Pairs (gid_i < gid_j) of the pruned lists the step kernel walks that pass the exact

@@ -125,7 +125,7 @@ struct SysDev {
     int32_t *gstart, *gcount, *gseed, *sgcell;      // seed grid (gcap+1, gcap, k, k)
     D4 *gpos;                                       // centroids in grid order, w = seed index (k)
     int32_t *nl, *nlk;                              // neighbour lists (nchunk x MAXNB x 64), rows
-    uint16_t *nl16;                                 // the same lists as stage indices (staged blocks)
+    uint16_t *nl16;                                 // the same lists as stage indices (staged blocks; nl_at)
     F4 *ori32;                                      // FP32 copy of the orientations, w = type bits (staging)
     F4 *ori32b;                                     // its second buffer (fused drift target; pos2 / ori2 likewise)
     int32_t *bstart, *bpart;                        // bonds by caller id (n+1, 2 nbond)
@@ -134,7 +134,7 @@ struct SysDev {
     double *vpart;                                  // per-chunk lipid sums for the volume (8 x nchunk)
     double *vred;                                   // their first-level reduction (32 x 8)
     int32_t *stage, *scount;                        // per 256-particle block: staged slots (SMAX), count (-1: none)
-    uint16_t *il16;                                 // pruned lists: indices into the pruned stage (0xffff pads)
+    uint16_t *il16;                                 // pruned lists: indices into the pruned stage (il_at; 0xffff pads)
     int32_t *ilk;                                   // per chunk: rows of the pruned list
     int32_t *istage, *iscount;                      // per block: the pruned stage (SMAX), count (-1: use nl)
     double *bred;                                   // per particle block: BRED partials (stats, bounding box)
@@ -172,6 +172,14 @@ struct DevParams {
     int32_t pad2;
     double quench_max;
 };
+
+// Places in the lists of a 64-particle chunk.  The full lists keep eight rows of a lane
+// together (the build and the prune read and write them 16 bytes at a time), the pruned
+// ones two (a trip of the step kernel).
+__device__ __forceinline__ int nl_at(int r, int lane) { return (r >> 3) * (8 * CHUNK) + 8 * lane + (r & 7); }
+__device__ __forceinline__ int il_at(int r, int lane) { return (r >> 1) * (2 * CHUNK) + 2 * lane + (r & 1); }
+static_assert(MAXNB % 8 == 0, "whole groups of rows");
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
 // Block -> system maps: off[s] = first block of system s, off[nsys] = total blocks.
 struct Maps {
@@ -222,6 +230,18 @@ __device__ __forceinline__ double minimg1(double d, int per, double L) {
         d = d - kl;
     }
     return d;
+}
+
+// Minimum image by the reciprocal: k = rint(d * (1/L)) instead of rint(d / L).  The two
+// differ only where d / L lies within a few ulp of a half-integer, that is at separations
+// near L / 2, beyond every list radius (a periodic length exceeds twice the largest cutoff
+// plus skin); every pair that can be in range gets the same k, hence the same separation
+// bits, as the exact test.
+__device__ __forceinline__ double minimg_fast(double d, double L, double iL) {
+#pragma clang fp contract(off)
+    const double k = __builtin_rint(d * iL);
+    const double kl = k * L;
+    return d - kl;
 }
 
 __device__ __forceinline__ double dist2_exact(const SysDev &S, double xi, double yi, double zi,
