@@ -194,7 +194,8 @@ __global__ void k_clear_owner(const SysDev *Sd, Maps L_maps) {
 
 // ------------------------------------------------------------------ seed grid
 
-// Per-block bounding boxes of the (wrapped) particle positions: BRED partials 2..7.
+// Per-block bounding boxes of the (wrapped) particle positions: partials 2..7 of bred2
+// (bred holds the statistics of the last drift, which the next step kernel publishes).
 __global__ __launch_bounds__(BLOCK) void k_bbox_partial(const SysDev *Sd, Maps L_maps) {
     SYS_FROM(p);
     if (!S.sc->rebuild) return;
@@ -220,7 +221,7 @@ __global__ __launch_bounds__(BLOCK) void k_bbox_partial(const SysDev *Sd, Maps L
         const int a = threadIdx.x;
         double r = s_v[a][0];
         for (int q = 1; q < BLOCK / WAVE; ++q) r = (a < 3) ? fmin(r, s_v[a][q]) : fmax(r, s_v[a][q]);
-        S.bred[(size_t)lb * BRED + 2 + a] = r;
+        S.bred2[(size_t)lb * BRED + 2 + a] = r;
     }
 }
 
@@ -266,7 +267,7 @@ __global__ void k_grid_setup(const SysDev *Sd, int nsys, double hmin) {
     for (int a = 0; a < 6; ++a) { mn[a] = INFINITY; mx[a] = -INFINITY; }
     const int nblk = (S.n + BLOCK - 1) / BLOCK;
     for (int b = threadIdx.x; b < nblk; b += blockDim.x) {
-        const double *r = S.bred + (size_t)b * BRED + 2;
+        const double *r = S.bred2 + (size_t)b * BRED + 2;
         for (int a = 0; a < 3; ++a) { mn[a] = fmin(mn[a], r[a]); mx[a] = fmax(mx[a], r[3 + a]); }
     }
     const int nsb = (S.k + BLOCK - 1) / BLOCK;
@@ -2051,7 +2052,6 @@ __global__ __launch_bounds__(BLOCK) void k_prune(const SysDev *Sd, Maps L_maps, 
     const bool chunk_ok = chunk < S.nchunk;
     const int i = lb * BLOCK + tid;
     const bool valid = i < S.n;
-    if (lb == 0 && tid == 0) S.sc->maxdisp2p = 0ull;
     const D4 pi = valid ? ldpos(S, i) : D4{0.0, 0.0, 0.0, 0.0};
     if (valid) S.xp[i] = F3{(float)pi.x, (float)pi.y, (float)pi.z};
     const int scnt = S.scount[lb];
@@ -2198,12 +2198,7 @@ __global__ __launch_bounds__(256) void k_finish_sys(const SysDev *Sd, int nsys) 
     const SysDev &S = Sd[blockIdx.x];
     SysScal *sc = S.sc;
     if (!sc->rebuild) return;
-    if (threadIdx.x == 0) {
-        sc->maxdisp2 = 0ull;
-        sc->maxv2 = 0ull;
-        sc->maxdisp2p = 0ull;
-        sc->rebuild = 0;
-    }
+    if (threadIdx.x == 0) sc->rebuild = 0;
 }
 
 void launch_finish_update(const LaunchCtx &L, bool cells_moved) {

@@ -28,10 +28,6 @@ __device__ __forceinline__ T wave_sum(T v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     return v;
 }
-__device__ __forceinline__ double wave_maxd(double v) {
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
-    return v;
-}
 
 template <class T>
 __device__ __forceinline__ T ipow(T c, int e) {
@@ -368,66 +364,72 @@ __device__ __forceinline__ void volume_term(const SysScal *sc, const D4 &x, cons
 
 // Per-wavefront drift statistics: the largest |x - x_build|^2, |v|^2 and
 // |x - x_prune|^2 of the wave's particles (chunk w of the particle block) go to the
-// block's partial slots 3w, 3w+1 and 3w+2; a non-finite state raises the system's
-// error bit.
-__device__ __forceinline__ void drift_stats(const SysDev &S, int blk, int w, double &disp2, double &v2, double &disp2p,
-                                            bool bad) {
+// block's partial slots 3w, 3w+1 and 3w+2 in `out`; a non-finite state raises the
+// system's error bit.
+__device__ __forceinline__ void drift_stats(const SysDev &S, double *out, int blk, int w, double disp2, double v2,
+                                            double disp2p, bool bad) {
     disp2 = wave_max_lane63(disp2);
     v2 = wave_max_lane63(v2);
     disp2p = wave_max_lane63(disp2p);
     const unsigned long long anybad = __ballot(bad);
     if (lane_id_f() == WAVE - 1) {
-        S.bred[(size_t)blk * BRED + 3 * w] = disp2;
-        S.bred[(size_t)blk * BRED + 3 * w + 1] = v2;
-        S.bred[(size_t)blk * BRED + 3 * w + 2] = disp2p;
+        out[(size_t)blk * BRED + 3 * w] = disp2;
+        out[(size_t)blk * BRED + 3 * w + 1] = v2;
+        out[(size_t)blk * BRED + 3 * w + 2] = disp2p;
         if (anybad) atomicOr(&S.sc->err, ERR_NONFINITE);
     }
 }
 
-// The end of a drift's statistics pass over one system, run once by whichever
-// block finishes last: the maxima (every block's atomic max is in) go to the host
-// ring entry of this drift number, tag last, and the drift is counted.
-__device__ __forceinline__ void publish_drift(SysScal *sc, StepStat *hstat) {
-    const unsigned long long st = sc->step;
-    const unsigned long long d = atomicOr(&sc->maxdisp2, 0ull);
-    const unsigned long long v = atomicOr(&sc->maxv2, 0ull);
-    const unsigned long long dp = atomicOr(&sc->maxdisp2p, 0ull);
-    StepStat *e = hstat + st % STAT_RING;
-    e->d2 = bitsd(d);
-    e->v2 = bitsd(v);
-    e->d2p = bitsd(dp);
-    __threadfence_system();
-    e->tag = st + 1;
-    sc->step = st + 1;
-}
-
-__device__ __forceinline__ void swap_drift(SysDev &W);
-
-// A small (split) system publishes its drift statistics from the step kernel itself:
-// lane 63 of each workgroup's wave 0 (which holds the wave's maxima after drift_stats)
-// folds them into the system's running maxima; the last of the system's nwg
-// workgroups (one per chunk) to finish publishes them and swaps the drift buffers, as the statistics
-// kernel does for larger systems.  Atomic maxima of non-negative doubles' bit patterns
-// do not depend on their order.
-__device__ __forceinline__ void publish_split(SysDev &W, int nwg, double disp2, double v2, double disp2p) {
-    if (lane_id_f() != WAVE - 1) return;
-    SysScal *sc = W.sc;
-    atomicMax(&sc->maxdisp2, dbits(disp2));
-    atomicMax(&sc->maxv2, dbits(v2));
-    atomicMax(&sc->maxdisp2p, dbits(disp2p));
-    __threadfence();
-    if (atomicAdd(&sc->parts_done, 1u) == (unsigned)nwg - 1u) {
-        __threadfence();
-        publish_drift(sc, W.hstat);
-        sc->parts_done = 0;
-        swap_drift(W);
+// The statistics of one system's last drift, from the per-wavefront partials (three per
+// 64-particle chunk), published to the host ring by one block: the largest displacements
+// and speed, the error bits, and the drift's number as a tag, written last.  The step
+// kernel runs one such block per system beside the blocks of the next step, so that no
+// kernel of its own (6 us on any system, 8 us at 4M particles, and the gap before it) and
+// no counting of finished blocks (about 4 us at the end of a small system's step) stands
+// between two steps.
+__device__ void publish_stats(const SysDev &S, unsigned long long step, double *s_m) {
+    constexpr int U = 8;                              // chunks per thread in flight
+    const int nb = blockDim.x, lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
+    double d = 0.0, v = 0.0, dp = 0.0;
+    for (int c0 = threadIdx.x; c0 < S.nchunk; c0 += U * nb) {
+        double a[U][3];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const double *r = S.bred + 3 * (size_t)min(c0 + k * nb, S.nchunk - 1);   // (a chunk twice changes no maximum)
+            a[k][0] = ldg(r);
+            a[k][1] = ldg(r + 1);
+            a[k][2] = ldg(r + 2);
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            d = fmax(d, a[k][0]);
+            v = fmax(v, a[k][1]);
+            dp = fmax(dp, a[k][2]);
+        }
     }
-}
-
-__device__ __forceinline__ void swap_drift(SysDev &W) {
-    V3 *u = W.pos; W.pos = W.pos2; W.pos2 = u;
-    u = W.ori; W.ori = W.ori2; W.ori2 = u;
-    F4 *f = W.ori32; W.ori32 = W.ori32b; W.ori32b = f;
+    d = wave_max_lane63(d);
+    v = wave_max_lane63(v);
+    dp = wave_max_lane63(dp);
+    if (lane == WAVE - 1) {
+        s_m[3 * w] = d;
+        s_m[3 * w + 1] = v;
+        s_m[3 * w + 2] = dp;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int q = 1; q < nb / WAVE; ++q) {
+            s_m[0] = fmax(s_m[0], s_m[3 * q]);
+            s_m[1] = fmax(s_m[1], s_m[3 * q + 1]);
+            s_m[2] = fmax(s_m[2], s_m[3 * q + 2]);
+        }
+        StepStat *e = S.hstat + (step - 1) % STAT_RING;
+        e->d2 = s_m[0];
+        e->v2 = s_m[1];
+        e->d2p = s_m[2];
+        e->err = (unsigned long long)(unsigned)S.sc->err;
+        __threadfence_system();
+        e->tag = step;
+    }
 }
 
 // ------------------------------------------------------------------ force kernel
@@ -617,9 +619,11 @@ constexpr int PAD_TYPE = 3;           // the padding entry's type (a periodic wr
 // KICK: 0 stores F and tau; 1 also applies the closing half-kick of the step;
 // 2 applies the closing half-kick and then, with the same force, the opening
 // half-kick and drift of the next step (positions and orientations go to the
-// second buffers, which the stats kernel then swaps in), without storing F, tau.
+// second buffers, which the other descriptor table holds as the current ones),
+// without storing F, tau.  With KICK, the grid's first blocks (one per system)
+// publish the statistics of the drift that led to this step's positions.
 template <int MIXED, int ENERGY, int KICK, int FAST>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5 : 4))) void k_force(const SysDev *Sd, Maps L_maps, DevParams P, double dt) {
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5 : 4))) void k_force(const SysDev *Sd, Maps L_maps, DevParams P, double dt, int par) {
     using T = typename std::conditional<MIXED, float, double>::type;
     constexpr int SL = Stage<MIXED>::lds;
     constexpr int SX = Stage<MIXED>::ext;
@@ -630,7 +634,16 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
     F4 *s_n4 = reinterpret_cast<F4 *>(s_z + SX);                  // mixed
     double *s_nx = s_z + SL, *s_ny = s_nx + SL, *s_nz = s_ny + SL;        // FP64
     unsigned char *s_t = reinterpret_cast<unsigned char *>(s_nz + SL);    // FP64
-    const int gb = xcd_group_block(blockIdx.x, gridDim.x);
+    const int nstat = KICK ? L_maps.nsys : 0;
+    if (KICK && (int)blockIdx.x < nstat) {
+        const SysDev &S = Sd[blockIdx.x];
+        if (S.n <= 0) return;
+        const unsigned long long step = S.sc->step[par];
+        if (KICK == 2 && threadIdx.x == 0) S.sc->step[par ^ 1] = step + 1;       // the fused drift's number
+        publish_stats(S, step, reinterpret_cast<double *>(s_raw));
+        return;
+    }
+    const int gb = xcd_group_block((int)blockIdx.x - nstat, (int)gridDim.x - nstat);
     const int s = find_sys(L_maps.f, L_maps.nsys, gb);
     const SysDev &S = Sd[s];
     const int fb = gb - L_maps.f[s];
@@ -1079,7 +1092,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
             const double hw = 0.5 * dt * P.inv_inertia;
             half_kick(v, h, Fx, Fy, Fz);
             if (ti == 0) half_kick(w, hw, Tq.x, Tq.y, Tq.z);
-            if (P.thermo_on) langevin_update(P, g, S.sc->step, ti, ni, v, w);
+            if (P.thermo_on) langevin_update(P, g, S.sc->step[par], ti, ni, v, w);
             if (P.quench_on) {
                 project_along(v, Fx, Fy, Fz);
                 if (ti == 0) project_along(w, Tq.x, Tq.y, Tq.z);
@@ -1109,9 +1122,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
         }
     }
     if (KICK == 2) {
-        drift_stats(S, lb, csub, disp2, vmax2, disp2p, bad);
+        drift_stats(S, S.bred2, lb, csub, disp2, vmax2, disp2p, bad);
         if (P.vol_on) volume_chunk_store(S, chunk, vsum);
-        if (split) publish_split(const_cast<SysDev &>(S), S.nchunk, disp2, vmax2, disp2p);   // a workgroup per chunk
     }
     if (ENERGY) {
         // per-chunk partials of U, W, KE, sum F and sum (r x F + tau), reduced across
@@ -1142,12 +1154,13 @@ static void launch_force_t(const LaunchCtx &L, double dt) {
     // FAST: the default pair-law constants, and one cutoff for both protein types
     bool fast = L.prm.zeta == 4 && L.prm.st0 == 0.0;
     for (int t = 0; t < 3; ++t) fast = fast && L.prm.rc2[t][1] == L.prm.rc2[t][2];
+    const int nblk = L.nblk_f + (KICK ? L.nsys : 0);
     if (fast)
-        hipLaunchKernelGGL((k_force<MIXED, ENERGY, KICK, 1>), dim3(L.nblk_f), dim3(BLOCK), 0, L.st, L.S, L.maps, L.prm,
-                           dt);
+        hipLaunchKernelGGL((k_force<MIXED, ENERGY, KICK, 1>), dim3(nblk), dim3(BLOCK), 0, L.st, L.S, L.maps, L.prm, dt,
+                           L.par);
     else
-        hipLaunchKernelGGL((k_force<MIXED, ENERGY, KICK, 0>), dim3(L.nblk_f), dim3(BLOCK), 0, L.st, L.S, L.maps, L.prm,
-                           dt);
+        hipLaunchKernelGGL((k_force<MIXED, ENERGY, KICK, 0>), dim3(nblk), dim3(BLOCK), 0, L.st, L.S, L.maps, L.prm, dt,
+                           L.par);
 }
 
 void launch_force(const LaunchCtx &L, int mixed, int energy, int kick, double dt) {
@@ -1173,13 +1186,14 @@ void launch_force(const LaunchCtx &L, int mixed, int energy, int kick, double dt
 // ------------------------------------------------------------------ kick + drift
 
 // v += dt/2m F, omega += dt/2I tau (lipids); x += dt v; n rotated about omega by
-// |omega| dt (Rodrigues) and renormalised.  Tracks the largest displacement since
-// the last cell build and the largest drift speed, per system.
-__global__ __launch_bounds__(BLOCK) void k_kick_drift(const SysDev *Sd, Maps L_maps, DevParams P, double dt) {
+// |omega| dt (Rodrigues) and renormalised, in place; with the drift's statistics and
+// its number.
+__global__ __launch_bounds__(BLOCK) void k_kick_drift(const SysDev *Sd, Maps L_maps, DevParams P, double dt, int par) {
     const int s = find_sys(L_maps.p, L_maps.nsys, blockIdx.x);
     const SysDev &S = Sd[s];
     const int lb = blockIdx.x - L_maps.p[s];
     const int i = lb * BLOCK + threadIdx.x;
+    if (i == 0) S.sc->step[par] += 1;                 // no other block of this kernel reads it
     double disp2 = 0.0, disp2p = 0.0, v2 = 0.0;
     bool bad = false;
     double vsum[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -1207,68 +1221,24 @@ __global__ __launch_bounds__(BLOCK) void k_kick_drift(const SysDev *Sd, Maps L_m
         }
         drift_measures(p, v, S.xb[i], S.xp[i], disp2, disp2p, v2, bad);
     }
-    drift_stats(S, lb, (threadIdx.x >> 6) & 3, disp2, v2, disp2p, bad);
+    drift_stats(S, S.bred, lb, (threadIdx.x >> 6) & 3, disp2, v2, disp2p, bad);
     if (P.vol_on && i / CHUNK < S.nchunk) volume_chunk_store(S, i / CHUNK, vsum);
 }
 
-// Largest displacements since the last build and since the last prune, and the
-// largest drift speed, per system, from the per-wavefront partials of a drift, three
-// per 64-particle chunk.  STATS_BLOCKS blocks per system fold their share with an
-// unsigned atomic max on the bits (non-negative doubles order like their bit
-// patterns); the last one publishes the result.  swap: after the drift fused into
-// the force kernel, which wrote the second position / orientation buffers; the last
-// block swaps them in.
-constexpr int STATS_BLOCKS = 64;
-
-__global__ __launch_bounds__(256) void k_stats_reduce(SysDev *Sd, int nsys, int swap) {
-    SysDev &S = Sd[blockIdx.x / STATS_BLOCKS];
-    if (swap && S.split) return;          // the step kernel published this small system's drift
-    const int part = blockIdx.x % STATS_BLOCKS;
-    const int per = (S.nchunk + STATS_BLOCKS - 1) / STATS_BLOCKS;
-    const int c0 = part * per, c1 = min(S.nchunk, c0 + per);
-    double d = 0.0, v = 0.0, dp = 0.0;
-    for (int c = c0 + (int)threadIdx.x; c < c1; c += blockDim.x) {
-        d = fmax(d, S.bred[3 * c]);
-        v = fmax(v, S.bred[3 * c + 1]);
-        dp = fmax(dp, S.bred[3 * c + 2]);
-    }
-    d = wave_maxd(d);
-    v = wave_maxd(v);
-    dp = wave_maxd(dp);
-    __shared__ double s_m[3][4];
-    if ((threadIdx.x & 63) == 0) {
-        s_m[0][threadIdx.x >> 6] = d;
-        s_m[1][threadIdx.x >> 6] = v;
-        s_m[2][threadIdx.x >> 6] = dp;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0 && S.n > 0) {
-        d = fmax(fmax(s_m[0][0], s_m[0][1]), fmax(s_m[0][2], s_m[0][3]));
-        v = fmax(fmax(s_m[1][0], s_m[1][1]), fmax(s_m[1][2], s_m[1][3]));
-        dp = fmax(fmax(s_m[2][0], s_m[2][1]), fmax(s_m[2][2], s_m[2][3]));
-        SysScal *sc = S.sc;
-        if (c1 > c0) {
-            atomicMax(&sc->maxdisp2, dbits(d));
-            atomicMax(&sc->maxv2, dbits(v));
-            atomicMax(&sc->maxdisp2p, dbits(dp));
-        }
-        __threadfence();
-        if (atomicAdd(&sc->parts_done, 1u) == STATS_BLOCKS - 1) {
-            __threadfence();
-            publish_drift(sc, S.hstat);
-            sc->parts_done = 0;
-            if (swap) swap_drift(S);
-        }
-    }
+// The same statistics at once, for the steps whose list work waits for them.
+__global__ __launch_bounds__(1024) void k_stats(const SysDev *Sd, int par) {
+    const SysDev &S = Sd[blockIdx.x];
+    if (S.n <= 0) return;
+    __shared__ double s_m[3 * 1024 / WAVE];
+    publish_stats(S, S.sc->step[par], s_m);
 }
 
 void launch_kick_drift(const LaunchCtx &L, double dt) {
-    hipLaunchKernelGGL(k_kick_drift, dim3(L.nblk_p), dim3(BLOCK), 0, L.st, L.S, L.maps, L.prm, dt);
-    hipLaunchKernelGGL(k_stats_reduce, dim3(L.nsys * STATS_BLOCKS), dim3(256), 0, L.st, L.Sw, L.nsys, 0);
+    hipLaunchKernelGGL(k_kick_drift, dim3(L.nblk_p), dim3(BLOCK), 0, L.st, L.S, L.maps, L.prm, dt, L.par);
 }
 
-void launch_drift_stats_swap(const LaunchCtx &L) {
-    hipLaunchKernelGGL(k_stats_reduce, dim3(L.nsys * STATS_BLOCKS), dim3(256), 0, L.st, L.Sw, L.nsys, 1);
+void launch_stats(const LaunchCtx &L) {
+    hipLaunchKernelGGL(k_stats, dim3(L.nsys), dim3(1024), 0, L.st, L.S, L.par);
 }
 
 // ------------------------------------------------------------------ energy reduction

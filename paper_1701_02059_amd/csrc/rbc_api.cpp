@@ -4,13 +4,13 @@
 // device allocation carved into its arrays; a device-side table of system
 // descriptors plus block->system prefix maps lets every kernel launch serve all
 // live systems at once.  The time-step loop is driven from the host with one
-// step of lookahead: after each kick-drift the per-system displacement statistics
-// are copied to pinned memory, and while the force kernel of step s runs the
-// host decides which systems need a cell update before the force of step s+1.
-// With graphs enabled (the default for ensembles) the fixed launch sequence of a
-// step -- the force kernel with its fused drift and the drift statistics -- is
-// captured once per system table and time step and replayed as a HIP graph; cell
-// updates launch only the blocks of the systems that rebuild.
+// step of lookahead: the force kernel of step s publishes the displacement statistics
+// of the drift to step s's positions in pinned memory as it starts, and while it runs
+// the host decides which systems need a cell update before the force of step s+1.
+// The fused drift writes the second position and orientation buffers; two descriptor
+// tables, taken in turn, hold either pair as the current one.  With graphs enabled
+// the step's launch is captured once per table, time step and parity and replayed as
+// a HIP graph; cell updates launch only the blocks of the systems that rebuild.
 #include "../../include/rbc.h"
 #include "rbc_dev.h"
 
@@ -26,7 +26,6 @@ using namespace rbc;
 
 namespace {
 
-constexpr int RING = 8;
 // Systems this large decide list rebuilds and prunes from the statistics of the drift to
 // the current positions (exact); the margin covers the FP32 reference positions.
 constexpr int64_t EXACT_MIN_N = 1 << 20;
@@ -54,6 +53,7 @@ struct HostSys {
     bool have_stats = false, rebuilt_last = false, refreshed_last = false;
     double disp2 = 0.0, v2 = 0.0, disp2p = 0.0;
     double cur_d2 = 0.0, cur_v2 = 0.0, cur_d2p = 0.0;   // the latest drift statistics read
+    int cur_err = 0;                 // the error bits published with them
     uint64_t drifts = 0;             // statistics passes since loading (the device's step counter)
     bool pending = false;            // staged: uploaded, cells not built yet
     rbc_status failed = RBC_OK;      // ensemble slot frozen by an error (held until retired)
@@ -96,8 +96,7 @@ struct rbc_ctx {
     const int32_t **d_lip = nullptr;
     SysScal *h_sc = nullptr;          // pinned mirror of the per-system scalars (read after a sync)
     StepStat *h_stat = nullptr, *d_stat = nullptr;   // published drift statistics: host / device view
-    hipEvent_t step_ev[RING] = {};    // one per step in flight: the drift statistics are published
-    int64_t step_pos = 0;
+    int par = 0;                      // the current descriptor table
     LaunchCtx L{};
     int32_t nsys = 0;                 // descriptors in use (highest live slot + 1)
     bool forces_valid = false;
@@ -110,7 +109,7 @@ struct rbc_ctx {
     int64_t table_version = 0;
     int64_t graph_version = -1;
     double graph_dt = 0.0;
-    hipGraphExec_t g_step = nullptr, g_last = nullptr;
+    hipGraphExec_t g_step[2] = {}, g_last[2] = {};       // by table parity
     // per-step timing (events at the end of every step of a call)
     bool step_timing = false;
     std::vector<hipEvent_t> ev_step;
@@ -295,6 +294,7 @@ size_t layout(HostSys &s, char *base) {
     d.istage = c.take<int32_t>((size_t)nblkp * SSTRIDE);
     d.iscount = c.take<int32_t>(nblkp);
     d.bred = c.take<double>((size_t)nblkp * BRED);
+    d.bred2 = c.take<double>((size_t)nblkp * BRED);
     d.tsum = c.take<int32_t>((size_t)std::max((k + SCAN_TILE - 1) / SCAN_TILE, (s.gcap + SCAN_TILE - 1) / SCAN_TILE) + 2);
     s.lip = c.take<int32_t>(s.nlip + s.nsrcp);
     return c.off + 256;
@@ -323,7 +323,20 @@ int key_bits(int32_t k) {
     return b;
 }
 
-// Rebuild the device descriptor table and the block maps after a membership change.
+// A descriptor with the drift's buffers exchanged: the other table's.
+void swap_drift(SysDev &d) {
+    std::swap(d.pos, d.pos2);
+    std::swap(d.ori, d.ori2);
+    std::swap(d.ori32, d.ori32b);
+    std::swap(d.bred, d.bred2);
+}
+
+void use_table(rbc_ctx *h, LaunchCtx &L, int par) {
+    L.S = L.Sw = h->d_sys + (size_t)par * h->max_slots;
+    L.par = par;
+}
+
+// Rebuild the device descriptor tables and the block maps after a membership change.
 rbc_status refresh_tables(rbc_ctx *h) {
     int top = 0;
     for (int s = 0; s < h->max_slots; ++s)
@@ -360,14 +373,17 @@ rbc_status refresh_tables(rbc_ctx *h) {
         msg[s + 1] = msg[s] + (on ? (hs.gcap + SCAN_TILE - 1) / SCAN_TILE : 0);
         mf[s + 1] = mf[s] + (mp[s + 1] - mp[s]) * (d.split ? 4 : 1);
     }
-    HIPCHK(hipMemcpyAsync(h->d_sys, tab.data(), sizeof(SysDev) * ns, hipMemcpyHostToDevice, h->st));
+    std::vector<SysDev> other = tab;
+    for (SysDev &d : other) swap_drift(d);
+    SysDev *cur = h->d_sys + (size_t)h->par * h->max_slots, *nxt = h->d_sys + (size_t)(h->par ^ 1) * h->max_slots;
+    HIPCHK(hipMemcpyAsync(cur, tab.data(), sizeof(SysDev) * ns, hipMemcpyHostToDevice, h->st));
+    HIPCHK(hipMemcpyAsync(nxt, other.data(), sizeof(SysDev) * ns, hipMemcpyHostToDevice, h->st));
     HIPCHK(hipMemcpyAsync(h->d_maps, maps.data(), sizeof(int32_t) * maps.size(), hipMemcpyHostToDevice, h->st));
     HIPCHK(hipMemcpyAsync(h->d_lip, lips.data(), sizeof(void *) * ns, hipMemcpyHostToDevice, h->st));
     HIPCHK(hipStreamSynchronize(h->st));   // host staging vectors go out of scope
     h->table_version++;
     LaunchCtx &L = h->L;
-    L.S = h->d_sys;
-    L.Sw = h->d_sys;
+    use_table(h, L, h->par);
     L.maps.p = h->d_maps;
     L.maps.c = h->d_maps + (ns + 1);
     L.maps.g = h->d_maps + 2 * (ns + 1);
@@ -556,7 +572,7 @@ rbc_status freeze_failed(rbc_ctx *h, const std::vector<std::pair<int, std::strin
     };
     for (int s = 0; s < h->nsys; ++s) {
         if (!runs(h->sys[s])) continue;
-        const rbc_status r = slot_error(h, s, h->h_sc[s].err);
+        const rbc_status r = slot_error(h, s, h->sys[s].cur_err);
         if (r != RBC_OK) freeze(s, r, h->err);
     }
     for (const auto &e : host_err) freeze(e.first, RBC_ERR_SKIN, e.second);
@@ -621,22 +637,12 @@ rbc_status ensure_forces(rbc_ctx *h) {
 }
 
 void drop_graphs(rbc_ctx *h) {
-    for (hipGraphExec_t *g : {&h->g_step, &h->g_last})
+    for (hipGraphExec_t *g : {h->g_step, h->g_step + 1, h->g_last, h->g_last + 1})
         if (*g) {
             hipGraphExecDestroy(*g);
             *g = nullptr;
         }
     h->graph_version = -1;
-}
-
-// Whether some running system needs the statistics kernel after a fused drift (small,
-// split systems publish their statistics from the step kernel).
-bool stats_kernel_needed(const rbc_ctx *h) {
-    for (int s = 0; s < h->nsys; ++s) {
-        const HostSys &hs = h->sys[s];
-        if (runs(hs) && hs.n > 0 && !hs.dev.split) return true;
-    }
-    return false;
 }
 
 template <class F>
@@ -654,16 +660,18 @@ hipGraphExec_t capture(rbc_ctx *h, F body) {
 // Capture the step sequences for the current table and dt.  Returns false (eager
 // launches are used) if capture fails.
 bool ensure_graphs(rbc_ctx *h, double dt) {
-    if (h->graph_version == h->table_version && h->graph_dt == dt && h->g_step && h->g_last) return true;
+    if (h->graph_version == h->table_version && h->graph_dt == dt && h->g_step[0]) return true;
     drop_graphs(h);
     const int mixed = h->prm.precision == RBC_MIXED;
-    const bool stats = stats_kernel_needed(h);
-    h->g_step = capture(h, [&] {
-        launch_force(h->L, mixed, 0, 2, dt);
-        if (stats) launch_drift_stats_swap(h->L);
-    });
-    h->g_last = capture(h, [&] { launch_force(h->L, mixed, 0, 1, dt); });
-    if (!(h->g_step && h->g_last)) {
+    bool ok = true;
+    for (int p = 0; p < 2; ++p) {
+        LaunchCtx L = h->L;
+        use_table(h, L, p);
+        h->g_step[p] = capture(h, [&] { launch_force(L, mixed, 0, 2, dt); });
+        h->g_last[p] = capture(h, [&] { launch_force(L, mixed, 0, 1, dt); });
+        ok = ok && h->g_step[p] && h->g_last[p];
+    }
+    if (!ok) {
         drop_graphs(h);
         hipGetLastError();
         return false;
@@ -674,15 +682,13 @@ bool ensure_graphs(rbc_ctx *h, double dt) {
 }
 
 // The drift of every step but the first is fused into the previous step's force
-// kernel, which wrote the second position / orientation buffers; the statistics
-// kernel swaps them in on the device, and the host mirror follows.
-void swap_drift_buffers(rbc_ctx *h) {
+// kernel, which wrote the second position / orientation buffers: the other table holds
+// them as the current ones, and the host mirror follows.
+void flip_tables(rbc_ctx *h) {
     for (auto &hs : h->sys)
-        if (hs.live) {
-            std::swap(hs.dev.pos, hs.dev.pos2);
-            std::swap(hs.dev.ori, hs.dev.ori2);
-            std::swap(hs.dev.ori32, hs.dev.ori32b);
-        }
+        if (hs.live) swap_drift(hs.dev);
+    h->par ^= 1;
+    use_table(h, h->L, h->par);
 }
 
 // The time-step loop over every live system.
@@ -710,7 +716,6 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
         }
         hipEventRecord(h->ev_call0, h->st);
     }
-    const bool stats_kernel = stats_kernel_needed(h);
     bool exact_any = false;
     for (const auto &hs : h->sys)
         if (runs(hs) && hs.n >= EXACT_MIN_N) exact_any = true;
@@ -727,6 +732,7 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
             hs.cur_d2 = e.d2;
             hs.cur_v2 = e.v2;
             hs.cur_d2p = e.d2p;
+            hs.cur_err = (int)e.err;
             hs.drifts++;
         }
     };
@@ -734,10 +740,10 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
     const auto t_loop0 = clk::now();
     double wait_s = 0.0;
     // Waiting for a step's drift statistics: poll the ring tags in pinned memory (the
-    // device writes them last, after a system-scope fence), checking the event that
-    // follows their publication every 64 polls; the event completing (or failing) ends
-    // the wait too, and read_stats then checks the tags.  Polling answers within about
-    // a microsecond of the publication, where a blocking event wait takes several.
+    // device writes them last, after a system-scope fence).  Polling answers within about
+    // a microsecond of the publication.  A stream that has ended or failed without them
+    // ends the wait too (looked at every 20 ms: an event recorded per step for this cost
+    // the GPU 6 us between two steps), and read_stats then checks the tags.
     auto stats_ready = [&]() {
         for (int s = 0; s < h->nsys; ++s) {
             const HostSys &hs = h->sys[s];
@@ -747,11 +753,15 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
         }
         return true;
     };
-    auto wait_event = [&](hipEvent_t ev) {
+    auto wait_stats = [&]() {
         const auto a = clk::now();
-        for (int k = 1;; ++k) {
-            if (stats_ready()) break;
-            if (k % 64 == 0 && hipEventQuery(ev) != hipErrorNotReady) break;
+        auto asked = a;
+        for (int k = 1; !stats_ready(); ++k) {
+            if (k % 1024) continue;
+            const auto b = clk::now();
+            if (b - asked < std::chrono::milliseconds(20)) continue;
+            asked = b;
+            if (hipStreamQuery(h->st) != hipErrorNotReady) break;
         }
         wait_s += std::chrono::duration<double>(clk::now() - a).count();
     };
@@ -759,11 +769,6 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
     h->vol_fresh = true;              // every drift also writes the volume's lipid sums
     for (int64_t st = 0; st < nsteps; ++st) {
         const bool last = st + 1 == nsteps;
-        const int slot = (int)(h->step_pos % RING);
-        h->step_pos++;
-        // the statistics of the drift to this step's positions are published when
-        // this event completes
-        hipEventRecord(h->step_ev[slot], h->st);
         // Systems of at least EXACT_MIN_N particles decide from the statistics of the drift
         // to this step's positions.  The host waits for them (the GPU idles for the host's
         // reaction time) only when the previous step's statistics plus a bound on one more
@@ -781,7 +786,8 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
                 if (pred_p > din - EXACT_MARGIN) { need = true; break; }
             }
             if (need) {
-                wait_event(h->step_ev[slot]);
+                launch_stats(h->L);
+                wait_stats();
                 read_stats();
                 waited = true;
             }
@@ -829,16 +835,15 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
         run_lists(h, lists);
         run_prunes(h, pruned);
         if (graphs) {
-            hipGraphLaunch(last ? h->g_last : h->g_step, h->st);
+            hipGraphLaunch(last ? h->g_last[h->par] : h->g_step[h->par], h->st);
         } else {
             force_launch(h, 0, last ? 1 : 2, dt);
-            if (!last && stats_kernel) launch_drift_stats_swap(h->L);
         }
-        if (!last) swap_drift_buffers(h);
+        if (!last) flip_tables(h);
         if (timed) hipEventRecord(h->ev_step[st], h->st);
         // while the force runs, read this step's drift statistics (unless read above)
         if (!waited) {
-            wait_event(h->step_ev[slot]);
+            wait_stats();
             read_stats();
         }
         for (int s = 0; s < h->nsys; ++s) {
@@ -875,16 +880,22 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
     }
     h->ens_steps += nsteps;
     if (timed) hipEventRecord(h->ev_prev_end, h->st);
-    rbc_status e;
+    // the last published error bits cover the call's drifts and list builds (the closing
+    // force raises none): nothing is copied back
+    const hipError_t le = hipGetLastError();
+    if (le != hipSuccess) return fail(h, RBC_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(le));
+    HIPCHK(hipStreamSynchronize(h->st));
+    for (int s = 0; s < h->nsys; ++s) {
+        HostSys &hs = h->sys[s];
+        if (runs(hs) && hs.n > 0 && hs.drifts > 0)
+            hs.cur_err = (int)h->h_stat[(size_t)s * STAT_RING + (hs.drifts - 1) % STAT_RING].err;
+    }
+    rbc_status e = RBC_OK;
     if (h->ensemble) {
-        // one slot's error freezes that slot only; the others have advanced nsteps
-        hipError_t le = hipGetLastError();
-        if (le != hipSuccess) return fail(h, RBC_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(le));
-        HIPCHK(hipMemcpyAsync(h->h_sc, h->d_sc, sizeof(SysScal) * h->nsys, hipMemcpyDeviceToHost, h->st));
-        HIPCHK(hipStreamSynchronize(h->st));
-        e = freeze_failed(h, slot_err);
+        e = freeze_failed(h, slot_err);       // one slot's error freezes that slot only; the others have advanced nsteps
     } else {
-        e = sync_and_check(h);
+        for (int s = 0; s < h->nsys && e == RBC_OK; ++s)
+            if (runs(h->sys[s])) e = slot_error(h, s, h->sys[s].cur_err);
     }
     harvest_timing(h);
     if (timed) {
@@ -1115,7 +1126,7 @@ rbc_status create(const rbc_params *params, void *stream, int32_t max_slots, int
     bool ok = hipStreamCreateWithFlags(&h->st, hipStreamNonBlocking) == hipSuccess &&
               hipEventCreateWithFlags(&h->ev_in, hipEventDisableTiming) == hipSuccess &&
               hipEventCreateWithFlags(&h->ev_out, hipEventDisableTiming) == hipSuccess &&
-              hipMalloc(&h->d_sys, sizeof(SysDev) * max_slots) == hipSuccess &&
+              hipMalloc(&h->d_sys, 2 * sizeof(SysDev) * max_slots) == hipSuccess &&
               hipMalloc(&h->d_sc, sizeof(SysScal) * max_slots) == hipSuccess &&
               hipMalloc(&h->d_maps, sizeof(int32_t) * 8 * (max_slots + 1)) == hipSuccess &&
               hipMalloc(&h->d_umaps, sizeof(int32_t) * 7 * (MAX_SLOTS + 1)) == hipSuccess &&
@@ -1126,7 +1137,6 @@ rbc_status create(const rbc_params *params, void *stream, int32_t max_slots, int
                             hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess &&
               hipHostGetDevicePointer((void **)&h->d_stat, h->h_stat, 0) == hipSuccess;
     if (ok) std::memset(h->h_stat, 0, sizeof(StepStat) * MAX_SLOTS * STAT_RING);
-    for (int q = 0; ok && q < RING; ++q) ok = hipEventCreateWithFlags(&h->step_ev[q], hipEventDisableTiming) == hipSuccess;
     if (ok) ok = hipEventCreate(&h->ev_call0) == hipSuccess && hipEventCreate(&h->ev_prev_end) == hipSuccess &&
                  hipEventCreate(&h->ev_prev_end_last) == hipSuccess;
     if (ok) ok = hipMemset(h->d_sc, 0, sizeof(SysScal) * max_slots) == hipSuccess;
@@ -1187,7 +1197,6 @@ rbc_status rbc_destroy(rbc_handle h) {
     for (auto e : h->te) hipEventDestroy(e);
     for (auto e : h->nb) hipEventDestroy(e);
     for (auto e : h->ne) hipEventDestroy(e);
-    for (int q = 0; q < RING; ++q) if (h->step_ev[q]) hipEventDestroy(h->step_ev[q]);
     for (auto e : h->ev_step) hipEventDestroy(e);
     for (hipEvent_t e : {h->ev_call0, h->ev_prev_end, h->ev_prev_end_last})
         if (e) hipEventDestroy(e);

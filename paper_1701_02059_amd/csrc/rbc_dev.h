@@ -56,9 +56,6 @@ struct F3 {
 
 // Per-system scalars living in device memory.
 struct alignas(256) SysScal {
-    unsigned long long maxdisp2;      // bits of the largest |x - x_build|^2 since the last build
-    unsigned long long maxv2;         // bits of the largest |v|^2 used in a drift since the build
-    unsigned long long maxdisp2p;     // bits of the largest |x - x_prune|^2 since the last prune
     unsigned long long rmax;          // bits of the largest cell radius
     int32_t err;
     int32_t rebuild;                  // this system takes part in the running cell update
@@ -77,9 +74,9 @@ struct alignas(256) SysScal {
     double volkap;                    // dU_V/dV a_L/3: the volume force is -volkap (n_i - nbar)
     double volU;                      // U_V
     double xbar[3], nbar[3];          // lipid centroid and mean orientation
-    unsigned long long step;          // drifts done since loading: numbers the thermostat's draws
-    uint32_t parts_done;              // statistics blocks finished in the running pass
-    uint32_t pad3;
+    // drifts done since loading, by table parity: numbers the thermostat's draws and the
+    // published statistics
+    unsigned long long step[2];
 };
 
 // Drift statistics published to pinned host memory, one ring of STAT_RING entries
@@ -90,11 +87,12 @@ constexpr int STAT_RING = 8;
 // per particle block): too small to fill the GPU, their step time is one wave's walk
 // over its rows, which this cuts by four.
 constexpr int SPLIT_MAX_BLOCKS = 32;
-struct alignas(32) StepStat {
-    double d2;                        // largest |x - x_build|^2 since the last build
-    double v2;                        // largest |v|^2 used in a drift since the build
-    double d2p;                       // largest |x - x_prune|^2 since the last prune
-    unsigned long long tag;           // drift number + 1, written last (0: never written)
+struct alignas(64) StepStat {
+    double d2;                        // largest |x - x_build|^2 of this drift
+    double v2;                        // largest |v|^2 used in it
+    double d2p;                       // largest |x - x_prune|^2
+    unsigned long long err;           // the system's error bits when this was published
+    unsigned long long tag;           // drift number, from 1, written last (0: never written)
 };
 
 // One system (slot): sizes and device arrays.  Particle arrays are in cell-sorted
@@ -137,7 +135,8 @@ struct SysDev {
     uint16_t *il16;                                 // pruned lists: indices into the pruned stage (il_at; 0xffff pads)
     int32_t *ilk;                                   // per chunk: rows of the pruned list
     int32_t *istage, *iscount;                      // per block: the pruned stage (SMAX), count (-1: use nl)
-    double *bred;                                   // per particle block: BRED partials (stats, bounding box)
+    double *bred;                                   // per particle block: BRED partials (the last drift's statistics)
+    double *bred2;                                  // the next fused drift's; bounding boxes while cells update
     int32_t *tsum;                                  // segmented-scan tile sums
     SysScal *sc;
     StepStat *hstat;                                // this system's ring in pinned host memory
@@ -342,7 +341,8 @@ namespace rbc {
 
 struct LaunchCtx {
     const SysDev *S;         // device array of systems
-    SysDev *Sw;              // the same array, for the kernel that swaps the drift buffers
+    SysDev *Sw;              // the same array, for the kernel that swaps gathered state in
+    int32_t par;             // which of the two tables it is: they differ in the drift's buffers, current and next
     Maps maps;
     int32_t nblk_p, nblk_c, nblk_g, nblk_tp, nblk_ts, nblk_sc, nblk_sg, nblk_f;   // totals over systems
     int32_t nsys;
@@ -352,8 +352,8 @@ struct LaunchCtx {
 };
 
 // step kernels
-void launch_kick_drift(const LaunchCtx &L, double dt);   // includes the per-system statistics reduction
-void launch_drift_stats_swap(const LaunchCtx &L);         // statistics of a fused drift, then buffer swap
+void launch_kick_drift(const LaunchCtx &L, double dt);
+void launch_stats(const LaunchCtx &L);                    // publish the last drift's statistics now
 void launch_force(const LaunchCtx &L, int mixed, int energy, int kick, double dt);
 void launch_reduce_energy(const LaunchCtx &L);
 void launch_volume_partials(const LaunchCtx &L);          // lipid sums of the current state, per chunk
