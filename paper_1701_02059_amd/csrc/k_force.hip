@@ -382,7 +382,7 @@ __device__ __forceinline__ void drift_stats(const SysDev &S, double *out, int bl
 
 // The statistics of one system's last drift, from the per-wavefront partials (three per
 // 64-particle chunk), published to the host ring by one block: the largest displacements
-// and speed, the error bits, and the drift's number as a tag, written last.  The step
+// and speed, the error bits, and a tag of the drift's number and these words.  The step
 // kernel runs one such block per system beside the blocks of the next step, so that no
 // kernel of its own (6 us on any system, 8 us at 4M particles, and the gap before it) and
 // no counting of finished blocks (about 4 us at the end of a small system's step) stands
@@ -423,12 +423,16 @@ __device__ void publish_stats(const SysDev &S, unsigned long long step, double *
             s_m[2] = fmax(s_m[2], s_m[3 * q + 2]);
         }
         StepStat *e = S.hstat + (step - 1) % STAT_RING;
-        e->d2 = s_m[0];
-        e->v2 = s_m[1];
-        e->d2p = s_m[2];
-        e->err = (unsigned long long)(unsigned)S.sc->err;
-        __threadfence_system();
-        e->tag = step;
+        const unsigned long long err = (unsigned long long)(unsigned)S.sc->err;
+        const unsigned long long d2 = dbits(s_m[0]), v2 = dbits(s_m[1]), d2p = dbits(s_m[2]);
+        auto put = [](void *p, unsigned long long v) {
+            __hip_atomic_store((unsigned long long *)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        };
+        put(&e->d2, d2);
+        put(&e->v2, v2);
+        put(&e->d2p, d2p);
+        put(&e->err, err);
+        put(&e->tag, stat_tag(step, d2, v2, d2p, err));
     }
 }
 

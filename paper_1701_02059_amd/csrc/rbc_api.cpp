@@ -691,6 +691,20 @@ void flip_tables(rbc_ctx *h) {
     use_table(h, h->L, h->par);
 }
 
+// Slot s's published statistics of its drift number `step` (from 1); false while they have
+// not arrived whole.
+bool ring_entry(const rbc_ctx *h, int s, uint64_t step, StepStat &out) {
+    const volatile StepStat &e = h->h_stat[(size_t)s * STAT_RING + (step - 1) % STAT_RING];
+    out.tag = e.tag;
+    out.d2 = e.d2;
+    out.v2 = e.v2;
+    out.d2p = e.d2p;
+    out.err = e.err;
+    unsigned long long w[3];
+    std::memcpy(w, &out.d2, sizeof w);                // d2, v2, d2p
+    return out.tag == stat_tag(step, w[0], w[1], w[2], out.err);
+}
+
 // The time-step loop over every live system.
 rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
     if (!any_live(h)) return RBC_OK;
@@ -726,8 +740,8 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
             if (!runs(hs)) continue;
             hs.cur_d2 = hs.cur_v2 = hs.cur_d2p = 0.0;
             if (hs.n == 0) continue;
-            const volatile StepStat &e = h->h_stat[(size_t)s * STAT_RING + hs.drifts % STAT_RING];
-            if (e.tag != hs.drifts + 1 && out == RBC_OK)
+            StepStat e;
+            if (!ring_entry(h, s, hs.drifts + 1, e) && out == RBC_OK)
                 out = fail(h, RBC_ERR_HIP, "drift statistics out of sequence (slot " + std::to_string(s) + ")");
             hs.cur_d2 = e.d2;
             hs.cur_v2 = e.v2;
@@ -739,17 +753,16 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
     using clk = std::chrono::steady_clock;
     const auto t_loop0 = clk::now();
     double wait_s = 0.0;
-    // Waiting for a step's drift statistics: poll the ring tags in pinned memory (the
-    // device writes them last, after a system-scope fence).  Polling answers within about
-    // a microsecond of the publication.  A stream that has ended or failed without them
+    // Waiting for a step's drift statistics: poll the ring entries in pinned memory until
+    // their tags match their words.  Polling answers within about a microsecond.  A stream that has ended or failed without them
     // ends the wait too (looked at every 20 ms: an event recorded per step for this cost
     // the GPU 6 us between two steps), and read_stats then checks the tags.
     auto stats_ready = [&]() {
         for (int s = 0; s < h->nsys; ++s) {
             const HostSys &hs = h->sys[s];
             if (!runs(hs) || hs.n == 0) continue;
-            const volatile StepStat &e = h->h_stat[(size_t)s * STAT_RING + hs.drifts % STAT_RING];
-            if (e.tag != hs.drifts + 1) return false;
+            StepStat e;
+            if (!ring_entry(h, s, hs.drifts + 1, e)) return false;
         }
         return true;
     };
@@ -887,8 +900,8 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
     HIPCHK(hipStreamSynchronize(h->st));
     for (int s = 0; s < h->nsys; ++s) {
         HostSys &hs = h->sys[s];
-        if (runs(hs) && hs.n > 0 && hs.drifts > 0)
-            hs.cur_err = (int)h->h_stat[(size_t)s * STAT_RING + (hs.drifts - 1) % STAT_RING].err;
+        StepStat last;
+        if (runs(hs) && hs.n > 0 && hs.drifts > 0 && ring_entry(h, s, hs.drifts, last)) hs.cur_err = (int)last.err;
     }
     rbc_status e = RBC_OK;
     if (h->ensemble) {

@@ -82,6 +82,19 @@ struct alignas(256) SysScal {
 // Drift statistics published to pinned host memory, one ring of STAT_RING entries
 // per system indexed by the drift number: the host reads them without a copy.
 constexpr int STAT_RING = 8;
+// The tag of a published entry: the drift's number (from 1) mixed with the entry's words,
+// so that an entry whose stores have not all arrived does not match.  The device then
+// needs no fence between the words and the tag: a system-scope fence writes the L2 back,
+// with the other blocks' data in it, before the host may see the step's statistics.
+__host__ __device__ constexpr unsigned long long stat_mix(unsigned long long h, unsigned long long w) {
+    h = (h ^ w) * 0x9E3779B97F4A7C15ull;              // odd multiplier: every step is a bijection
+    return h ^ (h >> 29);
+}
+__host__ __device__ inline unsigned long long stat_tag(unsigned long long step, unsigned long long d2, unsigned long long v2,
+                                                       unsigned long long d2p, unsigned long long err) {
+    return stat_mix(stat_mix(stat_mix(stat_mix(stat_mix(0x243F6A8885A308D3ull, step), d2), v2), d2p), err);
+}
+
 // Systems of at most this many 256-particle blocks run the step kernel with each
 // 64-particle chunk's list rows spread over the four waves of a block (four blocks
 // per particle block): too small to fill the GPU, their step time is one wave's walk
@@ -92,7 +105,7 @@ struct alignas(64) StepStat {
     double v2;                        // largest |v|^2 used in it
     double d2p;                       // largest |x - x_prune|^2
     unsigned long long err;           // the system's error bits when this was published
-    unsigned long long tag;           // drift number, from 1, written last (0: never written)
+    unsigned long long tag;           // stat_tag of the drift's number and the words above
 };
 
 // One system (slot): sizes and device arrays.  Particle arrays are in cell-sorted
