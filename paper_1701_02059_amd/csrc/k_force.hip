@@ -666,7 +666,14 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
     // this lane's own particle, loaded while the stage is read
     const int traw = valid ? ldg(S.typ + i) : 0;
     const D4 pi = valid ? ld3(S.pos + i) : D4{0.0, 0.0, 0.0, 0.0};
-    const D4 ni = valid ? ld3(S.ori + i) : D4{0.0, 0.0, 0.0, 0.0};
+    // (mixed mode's rows take the FP32 copy of the orientation, which the stage reads too; the
+    // FP64 one would be spilled over them and is read in the epilogue)
+    D4 ni = {0.0, 0.0, 0.0, 0.0};
+    F4 ni32 = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (valid) {
+        if constexpr (MIXED) ni32 = ldg(S.ori32 + i);
+        else ni = ld3(S.ori + i);
+    }
     // the stage: every thread's (at most three) slots first, then their records
     constexpr int SPT = (SL + BLOCK - 1) / BLOCK;
     for (int q0 = tid; q0 < nlds; q0 += SPT * BLOCK) {
@@ -704,7 +711,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
     __syncthreads();
     if (chunk >= S.nchunk) return;
     const int ti = traw & TYP_MASK;
-    const T nix = (T)ni.x, niy = (T)ni.y, niz = (T)ni.z;
+    const T nix = MIXED ? (T)ni32.x : (T)ni.x, niy = MIXED ? (T)ni32.y : (T)ni.y, niz = MIXED ? (T)ni32.z : (T)ni.z;
     T fx = 0, fy = 0, fz = 0, tx = 0, ty = 0, tz = 0;
     double U = 0.0, W = 0.0;
     const int rows = __builtin_amdgcn_readfirstlane(min(S.ilk[chunk], MAXNB));   // wave-uniform
@@ -1059,6 +1066,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
     double vsum[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (valid) {
         // the own-state loads first, so that they are in flight during the bond lookups
+        if constexpr (MIXED) ni = ld3(S.ori + i);
         if (KICK || ENERGY) {
             v = ld3(S.vel + i);
             if (ti == 0) w = ld3(S.angv + i);        // zero for protein beads
