@@ -20,6 +20,7 @@
 #include "rbc_dev.h"
 
 #include <climits>
+#include <type_traits>
 
 namespace rbc {
 
@@ -112,19 +113,43 @@ __device__ void block_scan_array(int *a, int n, int *s_w) {
 
 // ------------------------------------------------------------------ rebuild flags
 
-__global__ void k_set_rebuild(const SysDev *Sd, int nsys, unsigned long long m0, unsigned long long m1,
-                              unsigned long long m2, unsigned long long m3) {
-    int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= nsys) return;
-    unsigned long long w = (s < 64) ? m0 : (s < 128) ? m1 : (s < 192) ? m2 : m3;
-    int bit = (int)((w >> (s & 63)) & 1ull);
-    SysScal *sc = Sd[s].sc;
-    sc->rebuild = bit;
-    if (bit) {
-        sc->rmax = 0ull;
-        sc->nlrows = 0;
-        sc->cnbr_maxrow = 0;
-        sc->err &= ~(ERR_NLIST | ERR_CNBR | ERR_ASSIGN);
+// The rebuild flags of every system from the mask, and the block maps restricted to the
+// systems that rebuild (the others get no blocks), so that an update launches only the
+// rebuilding systems' blocks.  The block counts per system match the full maps built on
+// the host; one block of MAX_SLOTS threads.
+__global__ __launch_bounds__(MAX_SLOTS) void k_set_rebuild(const SysDev *Sd, int nsys, unsigned long long m0,
+                                                           unsigned long long m1, unsigned long long m2,
+                                                           unsigned long long m3, int32_t *out) {
+    __shared__ int s_w[16];
+    const int s = threadIdx.x;
+    int cnt[7] = {0, 0, 0, 0, 0, 0, 0};
+    if (s < nsys) {
+        const unsigned long long w = (s < 64) ? m0 : (s < 128) ? m1 : (s < 192) ? m2 : m3;
+        const int bit = (int)((w >> (s & 63)) & 1ull);
+        const SysDev &S = Sd[s];
+        SysScal *sc = S.sc;
+        sc->rebuild = bit;
+        if (bit) {
+            sc->rmax = 0ull;
+            sc->nlrows = 0;
+            sc->cnbr_maxrow = 0;
+            sc->err &= ~(ERR_NLIST | ERR_CNBR | ERR_ASSIGN);
+            if (S.n > 0) {
+                cnt[0] = (S.n + BLOCK - 1) / BLOCK;
+                cnt[1] = (S.k + BLOCK - 1) / BLOCK;
+                cnt[2] = (S.gcap + BLOCK - 1) / BLOCK;
+                cnt[3] = S.ntile_p;
+                cnt[4] = S.ntile_s;
+                cnt[5] = (S.k + SCAN_TILE - 1) / SCAN_TILE;
+                cnt[6] = (S.gcap + SCAN_TILE - 1) / SCAN_TILE;
+            }
+        }
+    }
+    for (int m = 0; m < 7; ++m) {
+        int tot;
+        const int ex = block_excl_scan(cnt[m], s_w, tot);
+        if (s <= nsys) out[m * (nsys + 1) + s] = ex;     // entry nsys receives the total
+        if (s == 0 && nsys == MAX_SLOTS) out[m * (nsys + 1) + nsys] = tot;
     }
 }
 
@@ -444,8 +469,47 @@ __global__ __launch_bounds__(BLOCK) void k_scan_c(const SysDev *Sd, Maps L_maps)
     if (tile == ntile - 1 && threadIdx.x == 0) dst[len] = S.tsum[ntile];
 }
 
+// The whole scan of a system by one block, up to SCAN_ONE elements (32 per thread): one
+// launch of 7.4 us instead of three of 14.2 us together (eight systems of 6250 cells).
+// Beyond that one block's rounds take longer than the three launches.
+constexpr int SCAN_ONE = 32768;
+
+template <int WHICH>
+__global__ __launch_bounds__(1024) void k_scan_one(const SysDev *Sd) {
+    const SysDev &S = Sd[blockIdx.x];
+    if (S.n <= 0 || !S.sc->rebuild) return;
+    __shared__ int s_w[16];
+    const int *src = scan_src<WHICH>(S);
+    int *dst = scan_dst<WHICH>(S);
+    const int len = scan_len<WHICH>(S);
+    constexpr int PER = 8;                            // consecutive elements per thread and round
+    int carry = 0;
+    for (int base = 0; base < len; base += 1024 * PER) {
+        const int i0 = base + (int)threadIdx.x * PER;
+        int v[PER], loc = 0;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            v[q] = i0 + q < len ? src[i0 + q] : 0;
+            loc += v[q];
+        }
+        int tot;
+        int run = carry + block_excl_scan(loc, s_w, tot);
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            if (i0 + q < len) dst[i0 + q] = run;
+            run += v[q];
+        }
+        carry += tot;
+    }
+    if (threadIdx.x == 0) dst[len] = carry;
+}
+
 template <int WHICH>
 static void launch_scan_t(const LaunchCtx &L) {
+    if ((WHICH == 0 ? L.gmax : L.kmax) <= SCAN_ONE) {
+        hipLaunchKernelGGL(k_scan_one<WHICH>, dim3(L.nsys), dim3(1024), 0, L.st, L.S);
+        return;
+    }
     const int nblk = WHICH == 0 ? L.nblk_sg : L.nblk_sc;
     hipLaunchKernelGGL(k_scan_a<WHICH>, dim3(nblk), dim3(BLOCK), 0, L.st, L.S, L.maps);
     hipLaunchKernelGGL(k_scan_b<WHICH>, dim3(L.nsys), dim3(1024), 0, L.st, L.S);
@@ -999,25 +1063,51 @@ void launch_block_permute(const LaunchCtx &L) {
 
 // ------------------------------------------------------------------ cell radii and cell pairs
 
-__global__ void k_cell_bounds(const SysDev *Sd, Maps L_maps) {
-    SYS_FROM(c);
+// The radius of each cell about its centroid.  CELL_LANES lanes per cell read its members
+// (about 18) side by side; one thread's walk through them is a chain of dependent loads
+// (14.3 us at 125k particles; side by side 10.9 us, most of it the launch's own chain of
+// map, descriptor, flag and cell loads).
+constexpr int CELL_LANES = 16;
+constexpr int CB_BLOCKS = CELL_LANES;      // blocks per 256-cell block of the cell map
+
+// The largest of 16 lanes' non-negative values, on the last of them.
+__device__ __forceinline__ double row_max(double v) {
+    auto step = [](double x, auto ctrl) {
+        constexpr int C = decltype(ctrl)::value;
+        const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), C, 0xf, 0xf, false);
+        const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), C, 0xf, 0xf, false);
+        return fmax(x, __hiloint2double(hi, lo));
+    };
+    v = step(v, std::integral_constant<int, 0x111>{});
+    v = step(v, std::integral_constant<int, 0x112>{});
+    v = step(v, std::integral_constant<int, 0x114>{});
+    return step(v, std::integral_constant<int, 0x118>{});
+}
+
+__global__ __launch_bounds__(BLOCK) void k_cell_bounds(const SysDev *Sd, Maps L_maps) {
+    const int cbk = blockIdx.x / CB_BLOCKS;
+    const int s = find_sys(L_maps.c, L_maps.nsys, cbk);
+    const SysDev &S = Sd[s];
     if (!S.sc->rebuild) return;
-    int c = lb * BLOCK + threadIdx.x;
+    const int c = (cbk - L_maps.c[s]) * BLOCK + (blockIdx.x % CB_BLOCKS) * (BLOCK / CELL_LANES) + (int)threadIdx.x / CELL_LANES;
+    const int l = threadIdx.x % CELL_LANES;
     double R = 0.0;
     if (c < S.k) {
-        D4 sd = S.seed[c];
+        const D4 sd = S.seed[c];
         double r2 = 0.0;
-        int b = S.cstart[c], e = b + S.ccount[c];
-        for (int i = b; i < e; ++i) {
-            D4 p = ld3(S.pos + i);
+        const int b = S.cstart[c], e = b + S.ccount[c];
+        for (int i = b + l; i < e; i += CELL_LANES) {
+            const D4 p = ld3(S.pos + i);
             double dx, dy, dz;
             r2 = fmax(r2, dist2_exact(S, p.x, p.y, p.z, sd.x, sd.y, sd.z, dx, dy, dz));
         }
+        r2 = row_max(r2);
         R = sqrt(r2);
-        S.seed[c].w = R;
+        if (l == CELL_LANES - 1) S.seed[c].w = R;
     }
+    if (l != CELL_LANES - 1) R = 0.0;
     for (int o = 32; o > 0; o >>= 1) R = fmax(R, __shfl_xor(R, o));
-    if ((threadIdx.x & 63) == 0 && c - (int)(threadIdx.x & 63) < S.k) max_if_larger(&S.sc->rmax, dbits(R));
+    if ((threadIdx.x & 63) == 0 && R > 0.0) max_if_larger(&S.sc->rmax, dbits(R));
 }
 
 // The query window of cell A on the seed grid: per axis the grid rows within
@@ -1089,8 +1179,8 @@ __device__ __forceinline__ bool cell_pair_test(const SysDev &S, const D4 &ca, co
 }
 
 // Cells B paired with A (as below), one thread per cell: the serial walk of the
-// window, a column's z runs at a time.  mode 0 counts, mode 1 writes (grid-scan order).
-__device__ int cell_query_serial(const SysDev &S, const SysScal *sc, int A, double search, int mode, int *out, int cap) {
+// window, a column's z runs at a time.  The first cap hits are written, in grid-scan order.
+__device__ int cell_query_serial(const SysDev &S, const SysScal *sc, int A, double search, int *out, int cap) {
     const D4 ca = S.seed[A];
     const QWin w = query_window(S, sc, ca, search);
     int cnt = 0;
@@ -1102,7 +1192,7 @@ __device__ int cell_query_serial(const SysDev &S, const SysScal *sc, int A, doub
                 for (int q = ldg(S.gstart + base + w.za[r]); q < qe; ++q) {
                     const int B = ldg(S.gseed + q);
                     if (cell_pair_test(S, ca, ldg(S.seed + B), search)) {
-                        if (mode && cnt < cap) out[cnt] = B;
+                        if (cnt < cap) out[cnt] = B;
                         ++cnt;
                     }
                 }
@@ -1114,9 +1204,9 @@ __device__ int cell_query_serial(const SysDev &S, const SysScal *sc, int A, doub
 // Cells B paired with A: |minimg(c_A - c_B)| <= R_A + R_B + search + 1e-9 with
 // search = largest (rc + 2 skin).  One wavefront per cell A: the window's grid columns
 // (x slowest) are taken 64 at a time, lane l scanning the seeds of the l-th one's z
-// runs.  With `out`, the hits are written in that scan order (an exclusive scan of the
-// lanes' counts places each lane's hits), so the row is the same as a serial walk of
-// the window would give.  Returns the row's length on every lane.
+// runs.  The first cap hits are written in that scan order: each lane keeps its first
+// hits (a column holds few) until a scan of the lanes' counts places them, and walks its
+// column again only if there are more.  Returns the row's length on every lane.
 __device__ int cell_query_wave(const SysDev &S, const SysScal *sc, int A, double search, int32_t *out, int cap) {
     const int lane = threadIdx.x & (WAVE - 1);
     const D4 ca = S.seed[A];
@@ -1133,18 +1223,24 @@ __device__ int cell_query_wave(const SysDev &S, const SysScal *sc, int A, double
                 qe[r] = ldg(S.gstart + base + w.zb[r] + 1);
             }
         }
-        int cnt = 0;
+        int cnt = 0, hit[4] = {0, 0, 0, 0};
         for (int r = 0; r < 2; ++r)
-            for (int q = qb[r]; q < qe[r]; ++q)
-                if (cell_pair_test(S, ca, ldg(S.seed + ldg(S.gseed + q)), search)) ++cnt;
-        // inclusive scan of the lanes' counts
-        int inc = cnt;
-        for (int o = 1; o < WAVE; o <<= 1) {
-            const int y = __shfl_up(inc, o);
-            if (lane >= o) inc += y;
-        }
-        if (out && cnt > 0) {
-            int k = total + inc - cnt;
+            for (int q = qb[r]; q < qe[r]; ++q) {
+                const int B = ldg(S.gseed + q);
+                if (cell_pair_test(S, ca, ldg(S.seed + B), search)) {
+                    if (cnt == 0) hit[0] = B;
+                    else if (cnt == 1) hit[1] = B;
+                    else if (cnt == 2) hit[2] = B;
+                    else if (cnt == 3) hit[3] = B;
+                    ++cnt;
+                }
+            }
+        const int inc = wave_incl_scan(cnt);
+        int k = total + inc - cnt;
+        if (cnt <= 4) {
+            for (int h = 0; h < 4; ++h)
+                if (h < cnt && k + h < cap) out[k + h] = hit[h];
+        } else {
             for (int r = 0; r < 2; ++r)
                 for (int q = qb[r]; q < qe[r]; ++q) {
                     const int B = ldg(S.gseed + q);
@@ -1154,72 +1250,56 @@ __device__ int cell_query_wave(const SysDev &S, const SysScal *sc, int A, double
                     }
                 }
         }
-        total += __shfl(inc, WAVE - 1);
+        total += __builtin_amdgcn_readlane(inc, WAVE - 1);
     }
     return total;
 }
 
 // Cell-pair kernels.  Systems of at least CQ_SERIAL_MIN cells take one thread per
 // cell (there are enough threads to hide the serial walk's latency); smaller ones
-// give each cell a wavefront, CQ_WAVE consecutive cells per wavefront in turn and
-// CQ_BLOCKS blocks per 256-cell block of the cell map.  Both write the same rows.
-constexpr int CQ_WAVE = 1;
-constexpr int CQ_BLOCKS = BLOCK / ((BLOCK / WAVE) * CQ_WAVE);
+// give each cell a wavefront, CQ_BLOCKS blocks per 256-cell block of the cell map.  Both
+// find the same rows.  The query writes a cell's first CROW hits to a scratch row (in the
+// memory of the 32-bit fallback lists, idle until the list build) and its row's length;
+// once a scan has placed the rows they are copied, and only a longer row is queried again.
+// (Querying every cell a second time to fill its row took longer than the first time:
+// 41 after 32 us at 125k particles; the copy takes 5 us.)
+constexpr int CQ_BLOCKS = BLOCK / (BLOCK / WAVE);
 constexpr int CQ_SERIAL_MIN = 20000;
+constexpr int CROW = 64;
+__device__ __forceinline__ int32_t *scratch_row(const SysDev &S, int c) { return S.nl + (size_t)c * CROW; }
 
-__global__ __launch_bounds__(BLOCK) void k_cnbr_count_serial(const SysDev *Sd, Maps L_maps, double search) {
+// A cell's row length as counted; 0 and an error where it would let the scanned total
+// leave int32.
+__device__ __forceinline__ int checked_row(const SysDev &S, int c, int n, bool lead) {
+    if (n > CNBR_ROW_MAX) {
+        if (lead) atomicOr(&S.sc->err, ERR_CNBR);
+        n = 0;
+    }
+    if (lead) S.cnbr_start[c] = n;
+    return n;
+}
+
+__global__ __launch_bounds__(BLOCK) void k_cnbr_query_serial(const SysDev *Sd, Maps L_maps, double search) {
     SYS_FROM(c);
     if (!S.sc->rebuild || S.k < CQ_SERIAL_MIN) return;
     const int c = lb * BLOCK + threadIdx.x;
     int n = 0;
-    if (c < S.k) {
-        n = cell_query_serial(S, S.sc, c, search, 0, nullptr, 0);
-        if (n > CNBR_ROW_MAX) {          // keeps the scanned total inside int32
-            atomicOr(&S.sc->err, ERR_CNBR);
-            n = 0;
-        }
-        S.cnbr_start[c] = n;
-    }
+    if (c < S.k) n = checked_row(S, c, cell_query_serial(S, S.sc, c, search, scratch_row(S, c), CROW), true);
     const int m = wave_max_int(n);
     if ((threadIdx.x & 63) == 0 && m > 0) max_if_larger(&S.sc->cnbr_maxrow, m);
 }
 
-__global__ __launch_bounds__(BLOCK) void k_cnbr_fill_serial(const SysDev *Sd, Maps L_maps, double search) {
-    SYS_FROM(c);
-    if (!S.sc->rebuild || S.k < CQ_SERIAL_MIN) return;
-    const int c = lb * BLOCK + threadIdx.x;
-    if (c >= S.k) return;
-    const int total = S.cnbr_start[S.k];
-    if (c == 0) S.sc->cnbr_total = total;
-    if (total > S.cnbr_cap || (S.sc->err & ERR_CNBR)) {
-        if (c == 0) atomicOr(&S.sc->err, ERR_CNBR);
-        return;
-    }
-    const int b = S.cnbr_start[c];
-    (void)cell_query_serial(S, S.sc, c, search, 1, S.cnbr + b, S.cnbr_start[c + 1] - b);
-}
-
-__global__ __launch_bounds__(BLOCK) void k_cnbr_count(const SysDev *Sd, Maps L_maps, double search) {
+__global__ __launch_bounds__(BLOCK) void k_cnbr_query(const SysDev *Sd, Maps L_maps, double search) {
     const int cbk = blockIdx.x / CQ_BLOCKS;
     if (cbk >= L_maps.c[L_maps.nsys]) return;
     const int s = find_sys(L_maps.c, L_maps.nsys, cbk);
     const SysDev &S = Sd[s];
     if (!S.sc->rebuild || S.k >= CQ_SERIAL_MIN) return;
-    const int lb = cbk - L_maps.c[s];
     const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
-    const int c0 = lb * BLOCK + ((blockIdx.x % CQ_BLOCKS) * (BLOCK / WAVE) + wv) * CQ_WAVE;
+    const int c = (cbk - L_maps.c[s]) * BLOCK + (blockIdx.x % CQ_BLOCKS) * (BLOCK / WAVE) + wv;
     int m = 0;
-    for (int k = 0; k < CQ_WAVE; ++k) {
-        const int c = c0 + k;
-        if (c >= S.k) break;                       // wavefront-uniform
-        int n = cell_query_wave(S, S.sc, c, search, nullptr, 0);
-        if (n > CNBR_ROW_MAX) {                    // keeps the scanned total inside int32
-            if (lane == 0) atomicOr(&S.sc->err, ERR_CNBR);
-            n = 0;
-        }
-        if (lane == 0) S.cnbr_start[c] = n;
-        m = max(m, n);
-    }
+    if (c < S.k)                                   // wavefront-uniform
+        m = checked_row(S, c, cell_query_wave(S, S.sc, c, search, scratch_row(S, c), CROW), lane == 0);
     __shared__ int s_m[BLOCK / WAVE];
     if (lane == 0) s_m[wv] = m;
     __syncthreads();
@@ -1229,50 +1309,45 @@ __global__ __launch_bounds__(BLOCK) void k_cnbr_count(const SysDev *Sd, Maps L_m
     }
 }
 
-__global__ __launch_bounds__(BLOCK) void k_cnbr_fill(const SysDev *Sd, Maps L_maps, double search) {
-    const int cbk = blockIdx.x / CQ_BLOCKS;
-    if (cbk >= L_maps.c[L_maps.nsys]) return;
+// The rows to their places, CELL_LANES lanes per cell.
+__global__ __launch_bounds__(BLOCK) void k_cnbr_place(const SysDev *Sd, Maps L_maps, double search) {
+    const int cbk = blockIdx.x / CB_BLOCKS;
     const int s = find_sys(L_maps.c, L_maps.nsys, cbk);
     const SysDev &S = Sd[s];
-    if (!S.sc->rebuild || S.k >= CQ_SERIAL_MIN) return;
-    const int lb = cbk - L_maps.c[s];
-    const int wv = threadIdx.x / WAVE;
-    const bool first = lb == 0 && blockIdx.x % CQ_BLOCKS == 0 && threadIdx.x == 0;
+    if (!S.sc->rebuild) return;
+    const int c = (cbk - L_maps.c[s]) * BLOCK + (blockIdx.x % CB_BLOCKS) * (BLOCK / CELL_LANES) + (int)threadIdx.x / CELL_LANES;
+    const int l = threadIdx.x % CELL_LANES;
+    const bool lead = c == 0 && l == 0;
     const int total = S.cnbr_start[S.k];
-    if (first) S.sc->cnbr_total = total;
+    if (lead) S.sc->cnbr_total = total;
     if (total > S.cnbr_cap || (S.sc->err & ERR_CNBR)) {
-        if (first) atomicOr(&S.sc->err, ERR_CNBR);
+        if (lead) atomicOr(&S.sc->err, ERR_CNBR);
         return;
     }
-    const int c0 = lb * BLOCK + ((blockIdx.x % CQ_BLOCKS) * (BLOCK / WAVE) + wv) * CQ_WAVE;
-    for (int k = 0; k < CQ_WAVE; ++k) {
-        const int c = c0 + k;
-        if (c >= S.k) break;
-        const int b = S.cnbr_start[c];
-        const int room = S.cnbr_start[c + 1] - b;
-        (void)cell_query_wave(S, S.sc, c, search, S.cnbr + b, room);
+    if (c >= S.k) return;
+    const int b = S.cnbr_start[c], n = S.cnbr_start[c + 1] - b;
+    if (n > CROW) {
+        if (l == 0) (void)cell_query_serial(S, S.sc, c, search, S.cnbr + b, n);
+        return;
     }
+    const int32_t *row = scratch_row(S, c);
+    for (int q = l; q < n; q += CELL_LANES) S.cnbr[b + q] = row[q];
 }
 
 void launch_cell_bounds(const LaunchCtx &L) {
-    hipLaunchKernelGGL(k_cell_bounds, dim3(L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps);
+    hipLaunchKernelGGL(k_cell_bounds, dim3(CB_BLOCKS * L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps);
 }
 
 void launch_cell_pairs(const LaunchCtx &L) {
     if (L.nblk_c == 0) return;
-    // each size class's kernels only where the launch holds a system of that class
-    const bool large = L.kmax >= CQ_SERIAL_MIN, small = L.kmin < CQ_SERIAL_MIN;
-    if (large)
-        hipLaunchKernelGGL(k_cnbr_count_serial, dim3(L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps, L.prm.cell_search);
-    if (small)
-        hipLaunchKernelGGL(k_cnbr_count, dim3(CQ_BLOCKS * L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps,
+    // each size class's query only where the launch holds a system of that class
+    if (L.kmax >= CQ_SERIAL_MIN)
+        hipLaunchKernelGGL(k_cnbr_query_serial, dim3(L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps, L.prm.cell_search);
+    if (L.kmin < CQ_SERIAL_MIN)
+        hipLaunchKernelGGL(k_cnbr_query, dim3(CQ_BLOCKS * L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps,
                            L.prm.cell_search);
     launch_scan(L, 3);
-    if (large)
-        hipLaunchKernelGGL(k_cnbr_fill_serial, dim3(L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps, L.prm.cell_search);
-    if (small)
-        hipLaunchKernelGGL(k_cnbr_fill, dim3(CQ_BLOCKS * L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps,
-                           L.prm.cell_search);
+    hipLaunchKernelGGL(k_cnbr_place, dim3(CB_BLOCKS * L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps, L.prm.cell_search);
 }
 
 // ------------------------------------------------------------------ neighbour lists
@@ -1454,7 +1529,7 @@ constexpr int GROUPS = 16;            // candidate lists of a block
 constexpr int CLIST = 5120;           // candidate-list entries of those cells
 constexpr int MWORDS = 11;            // words of hit bits per lane (352 candidates)
 
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) void k_nlist(const SysDev *Sd, Maps L_maps, DevParams P) {
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) void k_nlist(const SysDev *Sd, Maps L_maps, DevParams P, int cells_moved) {
     SYS_FROM(p);
     if (!S.sc->rebuild) return;
     // 53 KB of LDS, three blocks per CU.  s_raw: the stage's x, y, z; the union arrays, then
@@ -1485,6 +1560,20 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
     const bool chunk_ok = chunk < S.nchunk;
     const int i = lb * BLOCK + tid;
     const bool valid = i < S.n;
+    const int first = lb * BLOCK;
+    const D4 ref = ld3(S.pos + first);
+    const D4 pi = valid ? ldpos(S, i) : ref;
+    if (valid) {
+        // the drift references of the new lists, and after a cell update (the particles have
+        // moved to new slots) the FP32 orientation copies, which the step kernel keeps current
+        const F3 b = {(float)pi.x, (float)pi.y, (float)pi.z};
+        S.xb[i] = b;
+        S.xp[i] = b;
+        if (cells_moved) {
+            const V3 o = ldg(S.ori + i);
+            S.ori32[i] = F4{(float)o.x, (float)o.y, (float)o.z, __int_as_float((int)pi.w)};
+        }
+    }
     if (S.sc->err & ERR_CNBR) {          // no valid cell pairs: publish empty lists (block-uniform)
         if (lane == 0 && chunk_ok) { S.nlk[chunk] = 0; S.ilk[chunk] = 0; }
         if (tid == 0) { S.scount[lb] = 0; S.iscount[lb] = 0; }
@@ -1494,12 +1583,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
     reinterpret_cast<uint2 *>(s_tf)[tid] = make_uint2(0u, 0u);
     static_assert(USTAGE == 8 * BLOCK, "type bytes");
     // ---- candidate cells and the union position of every cell-pair entry
-    const int first = lb * BLOCK;
     const int last = min(S.n - 1, first + BLOCK - 1);
     const int c0 = S.owner[first], c1 = S.owner[last];
     const int A = valid ? ldg(S.owner + i) : c0;
-    const D4 ref = ld3(S.pos + first);
-    const D4 pi = valid ? ldpos(S, i) : ref;
     const int q0 = S.cnbr_start[c0];
     const int ncand = S.cnbr_start[c1 + 1] - q0;
     const int nown = c1 - c0 + 1;
@@ -2018,8 +2104,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
     }
 }
 
-void launch_nlist(const LaunchCtx &L) {
-    hipLaunchKernelGGL(k_nlist, dim3(L.nblk_p), dim3(BLOCK), 0, L.st, L.S, L.maps, L.prm);
+void launch_nlist(const LaunchCtx &L, bool cells_moved) {
+    hipLaunchKernelGGL(k_nlist, dim3(L.nblk_p), dim3(BLOCK), 0, L.st, L.S, L.maps, L.prm, cells_moved ? 1 : 0);
 }
 
 // ------------------------------------------------------------------ pruned lists
@@ -2174,73 +2260,10 @@ void launch_mask_maps(const LaunchCtx &L, const unsigned long long m[4], int32_t
     hipLaunchKernelGGL(k_mask_maps, dim3(1), dim3(MAX_SLOTS), 0, L.st, L.S, L.nsys, m[0], m[1], m[2], m[3], out);
 }
 
-// ------------------------------------------------------------------ finish
-
-// The drift references of the new lists, and after a cell update (the particles have
-// moved to new slots) the FP32 orientation copies; between updates the step kernel
-// keeps those current.
-__global__ void k_finish_particles(const SysDev *Sd, Maps L_maps, int cells_moved) {
-    SYS_FROM(p);
-    if (!S.sc->rebuild) return;
-    int i = lb * BLOCK + threadIdx.x;
-    if (i < S.n) {
-        const V3 p = S.pos[i];
-        S.xb[i] = F3{(float)p.x, (float)p.y, (float)p.z};
-        S.xp[i] = F3{(float)p.x, (float)p.y, (float)p.z};
-        if (cells_moved) {
-            const V3 o = S.ori[i];
-            S.ori32[i] = F4{(float)o.x, (float)o.y, (float)o.z, __int_as_float((int)S.typ[i] & TYP_MASK)};
-        }
-    }
-}
-
-__global__ __launch_bounds__(256) void k_finish_sys(const SysDev *Sd, int nsys) {
-    const SysDev &S = Sd[blockIdx.x];
-    SysScal *sc = S.sc;
-    if (!sc->rebuild) return;
-    if (threadIdx.x == 0) sc->rebuild = 0;
-}
-
-void launch_finish_update(const LaunchCtx &L, bool cells_moved) {
-    hipLaunchKernelGGL(k_finish_particles, dim3(L.nblk_p), dim3(BLOCK), 0, L.st, L.S, L.maps, cells_moved ? 1 : 0);
-    hipLaunchKernelGGL(k_finish_sys, dim3(L.nsys), dim3(256), 0, L.st, L.S, L.nsys);
-}
-
 // ------------------------------------------------------------------ entry points used by the runtime
 
-// Block maps restricted to the systems that rebuild (the others get no blocks), so
-// an update launches only the rebuilding systems' blocks.  The block counts per
-// system match the full maps built on the host; one block of MAX_SLOTS threads.
-__global__ __launch_bounds__(MAX_SLOTS) void k_restrict_maps(const SysDev *Sd, int nsys, int32_t *out) {
-    __shared__ int s_w[16];
-    const int s = threadIdx.x;
-    int cnt[7] = {0, 0, 0, 0, 0, 0, 0};
-    if (s < nsys) {
-        const SysDev &S = Sd[s];
-        if (S.n > 0 && S.sc->rebuild) {
-            cnt[0] = (S.n + BLOCK - 1) / BLOCK;
-            cnt[1] = (S.k + BLOCK - 1) / BLOCK;
-            cnt[2] = (S.gcap + BLOCK - 1) / BLOCK;
-            cnt[3] = S.ntile_p;
-            cnt[4] = S.ntile_s;
-            cnt[5] = (S.k + SCAN_TILE - 1) / SCAN_TILE;
-            cnt[6] = (S.gcap + SCAN_TILE - 1) / SCAN_TILE;
-        }
-    }
-    for (int m = 0; m < 7; ++m) {
-        int tot;
-        const int ex = block_excl_scan(cnt[m], s_w, tot);
-        if (s <= nsys) out[m * (nsys + 1) + s] = ex;     // entry nsys receives the total
-    }
-}
-
-void launch_restrict_maps(const LaunchCtx &L, int32_t *out) {
-    hipLaunchKernelGGL(k_restrict_maps, dim3(1), dim3(MAX_SLOTS), 0, L.st, L.S, L.nsys, out);
-}
-
-void launch_set_rebuild(const LaunchCtx &L, const unsigned long long m[4]) {
-    hipLaunchKernelGGL(k_set_rebuild, dim3((L.nsys + 63) / 64), dim3(64), 0, L.st, L.S, L.nsys, m[0], m[1], m[2],
-                       m[3]);
+void launch_set_rebuild(const LaunchCtx &L, const unsigned long long m[4], int32_t *out) {
+    hipLaunchKernelGGL(k_set_rebuild, dim3(1), dim3(MAX_SLOTS), 0, L.st, L.S, L.nsys, m[0], m[1], m[2], m[3], out);
 }
 
 void launch_init_seeds(const LaunchCtx &L, const int32_t *const *lipids) {

@@ -347,7 +347,7 @@ rbc_status refresh_tables(rbc_ctx *h) {
     std::vector<SysDev> tab(ns);
     std::vector<const int32_t *> lips(ns, nullptr);
     std::vector<int32_t> maps(8 * (ns + 1), 0);
-    int32_t kmin = INT32_MAX, kmax = 0;
+    int32_t kmin = INT32_MAX, kmax = 0, gmax = 0;
     int32_t *mp = maps.data(), *mc = mp + (ns + 1), *mg = mc + (ns + 1), *mtp = mg + (ns + 1), *mts = mtp + (ns + 1);
     int32_t *msc = mts + (ns + 1), *msg = msc + (ns + 1), *mf = msg + (ns + 1);
     for (int s = 0; s < ns; ++s) {
@@ -363,7 +363,7 @@ rbc_status refresh_tables(rbc_ctx *h) {
         const bool on = runs(hs);
         const int64_t n = on ? hs.n : 0;
         const int32_t k = on ? hs.k : 0;
-        if (on) { kmin = std::min(kmin, k); kmax = std::max(kmax, k); }
+        if (on) { kmin = std::min(kmin, k); kmax = std::max(kmax, k); gmax = std::max(gmax, hs.gcap); }
         mp[s + 1] = mp[s] + (int32_t)((n + BLOCK - 1) / BLOCK);
         mc[s + 1] = mc[s] + (k + BLOCK - 1) / BLOCK;
         mg[s + 1] = mg[s] + (on ? (hs.gcap + BLOCK - 1) / BLOCK : 0);
@@ -395,6 +395,7 @@ rbc_status refresh_tables(rbc_ctx *h) {
     L.maps.nsys = ns;
     L.kmin = kmin;
     L.kmax = kmax;
+    L.gmax = gmax;
     L.nblk_p = mp[ns];
     L.nblk_c = mc[ns];
     L.nblk_g = mg[ns];
@@ -425,8 +426,7 @@ LaunchCtx restricted(rbc_ctx *h, const std::vector<int> &which) {
     unsigned long long m[4] = {0, 0, 0, 0};
     for (int s : which) m[s >> 6] |= 1ull << (s & 63);
     const LaunchCtx &L = h->L;
-    launch_set_rebuild(L, m);
-    launch_restrict_maps(L, h->d_umaps);
+    launch_set_rebuild(L, m, h->d_umaps);
     LaunchCtx U = L;
     const int ns = h->nsys;
     U.maps.p = h->d_umaps;
@@ -439,10 +439,12 @@ LaunchCtx restricted(rbc_ctx *h, const std::vector<int> &which) {
     U.nblk_p = U.nblk_c = U.nblk_g = U.nblk_tp = U.nblk_ts = U.nblk_sc = U.nblk_sg = 0;
     U.kmin = INT32_MAX;
     U.kmax = 0;
+    U.gmax = 0;
     for (int s : which) {
         const HostSys &hs = h->sys[s];
         U.kmin = std::min(U.kmin, hs.k);
         U.kmax = std::max(U.kmax, hs.k);
+        U.gmax = std::max(U.gmax, hs.gcap);
         U.nblk_p += (int32_t)((hs.n + BLOCK - 1) / BLOCK);
         U.nblk_c += (hs.k + BLOCK - 1) / BLOCK;
         U.nblk_g += (hs.gcap + BLOCK - 1) / BLOCK;
@@ -532,9 +534,8 @@ void lists_body(rbc_ctx *h, const LaunchCtx &L, bool cells_moved) {
     launch_cell_pairs(L);
     const bool t = h->timing && h->ncount < (int)h->nb.size();
     if (t) hipEventRecord(h->nb[h->ncount], L.st);
-    launch_nlist(L);
+    launch_nlist(L, cells_moved);
     if (t) hipEventRecord(h->ne[h->ncount++], L.st);
-    launch_finish_update(L, cells_moved);
 }
 
 // The status and message of one slot's error bits.

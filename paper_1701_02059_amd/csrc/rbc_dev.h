@@ -360,6 +360,7 @@ struct LaunchCtx {
     int32_t nblk_p, nblk_c, nblk_g, nblk_tp, nblk_ts, nblk_sc, nblk_sg, nblk_f;   // totals over systems
     int32_t nsys;
     int32_t kmin, kmax;      // fewest and most cells of a system in the launch
+    int32_t gmax;            // most seed-grid cells (capacity) of one
     DevParams prm;
     hipStream_t st;
 };
@@ -381,8 +382,8 @@ void launch_pair_fill(const LaunchCtx &L, int sys, int count, int32_t *out, int6
 constexpr int64_t PAIR_SCRATCH_PAIRS = ((32ll << 20) - 256) / 8;
 hipError_t pair_scratch_address(int device, void **out);   // this device's copy (it must be current)
 // cell update kernels (each predicated on SysScal::rebuild)
-void launch_set_rebuild(const LaunchCtx &L, const unsigned long long m[4]);
-void launch_restrict_maps(const LaunchCtx &L, int32_t *out);   // 7 x (nsys+1) prefix maps of the rebuilding systems
+void launch_set_rebuild(const LaunchCtx &L, const unsigned long long m[4],
+                        int32_t *out);                    // flags, and 7 x (nsys+1) prefix maps of the rebuilding systems
 void launch_init_seeds(const LaunchCtx &L, const int32_t *const *lipids);
 void launch_grid_build(const LaunchCtx &L);
 void launch_assign(const LaunchCtx &L, int warm);
@@ -394,10 +395,9 @@ void launch_morton_sort_seeds(const LaunchCtx &L);
 void launch_block_permute(const LaunchCtx &L);
 void launch_cell_bounds(const LaunchCtx &L);
 void launch_cell_pairs(const LaunchCtx &L);
-void launch_nlist(const LaunchCtx &L);
+void launch_nlist(const LaunchCtx &L, bool cells_moved);
 void launch_prune(const LaunchCtx &L);                    // pruned lists of the systems in L's particle map
 void launch_mask_maps(const LaunchCtx &L, const unsigned long long m[4], int32_t *out);   // particle map of a mask
-void launch_finish_update(const LaunchCtx &L, bool cells_moved);
 void launch_pack(const LaunchCtx &L, int sys, const double *x, const double *n, const int32_t *type,
                  const double *v, const double *w, int count);
 
