@@ -1501,7 +1501,11 @@ __device__ __forceinline__ int union_cell(const int *ofs, int nsc, int u) {
 //    bounding sphere, of those own cells that pair with the particle's cell (a 64-bit
 //    mask per union cell), in the union's order, as FP32 offsets from the block's first
 //    particle.  A superset of the block's partners.  Each entry keeps a bit for every own
-//    cell whose sphere test it passed.
+//    cell whose sphere test it passed.  A wide cell (one with a member far off) would pass
+//    thousands of particles that are near none of its members: it is tested as one small
+//    sphere per member instead, where the block's spheres still fit 64 in all.  (One such
+//    cell had left its block of a deformed 125k-particle vesicle without a stage: 6.4 ms
+//    instead of 1.5 ms per 20 steps.)
 //  - Candidate lists: for each own cell the stage entries with its bit, compacted by one
 //    wavefront's ballots as 16-bit LDS offsets, lipids from the front, proteins from the
 //    back (neighbouring cells share a list where a block has more than 16).  Every
@@ -1528,6 +1532,9 @@ constexpr int OWNMAX = 64;            // own cells of a staged block
 constexpr int GROUPS = 16;            // candidate lists of a block
 constexpr int CLIST = 5120;           // candidate-list entries of those cells
 constexpr int MWORDS = 11;            // words of hit bits per lane (352 candidates)
+// A cell is wide from this many list radii on: its sphere covers (1 + 1.5)^2 = 6 times the
+// area in which one of its members can have partners; compact cells have 0.5 to 1.
+constexpr float WIDE = 1.5f;
 
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) void k_nlist(const SysDev *Sd, Maps L_maps, DevParams P, int cells_moved) {
     SYS_FROM(p);
@@ -1540,7 +1547,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
     __shared__ __align__(16) unsigned char s_tf[USTAGE];    // type | STAGE_USED of the stage entries
     __shared__ uint16_t s_q[USTAGE];                        // union position of every cell-pair entry; then the
                                                             // stage entries' own-list bits
-    __shared__ F4 s_sph[OWNMAX];                            // own cells: centroid offset and widened radius
+    __shared__ F4 s_sph[OWNMAX];                            // spheres of the own cells: offset and widened radius
+    __shared__ uint16_t s_ibeg[OWNMAX];                     // an own cell's first sphere and their number
     __shared__ int s_lofs[GROUPS + 1];
     __shared__ uint16_t s_nl[GROUPS], s_np[GROUPS];         // lipid and protein candidates of each list
     __shared__ int s_w[16];
@@ -1724,6 +1732,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
         if (far(o)) s_big = 1;
         return F4{o[0], o[1], o[2], (float)c.w + 2e-3f};
     };
+    // a sphere with its candidate list's number in the radius' last bits (rounded up)
+    auto tagged = [](F4 s, int g) {
+        static_assert(GROUPS == 16, "four bits");
+        s.w = __int_as_float(((__float_as_int(s.w) + 16) & ~15) | g);
+        return s;
+    };
+    auto group_of = [&](int a) { return nown <= GROUPS ? a : a * GROUPS / nown; };
     // list radius of a candidate by its type (the largest over the own types)
     const float rlm0 = P.rlmaxf[0], rlm1 = P.rlmaxf[1], rlm2 = P.rlmaxf[2];
     int kept = 0;
@@ -1737,8 +1752,33 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
             loc += ccnt[q];
             s_mask[c] = 0ull;
         }
-        if (tid < nown) s_sph[tid] = own_sphere(tid);
+        if (wv == 0) {
+            // own cell `lane`: its first sphere, the number beyond one, and whether they are
+            // its members'
+            F4 sp = {0.0f, 0.0f, 0.0f, 0.0f};
+            int m = 0;
+            if (lane < nown) {
+                sp = own_sphere(lane);
+                if (sp.w > WIDE * fmaxf(fmaxf(rlm0, rlm1), rlm2)) {
+                    const int b = ldg(S.cstart + c0 + lane), e = b + ldg(S.ccount + c0 + lane);
+                    m = max(min(e, last + 1) - max(b, first), 0);
+                }
+            }
+            const int room = wave_incl_scan(max(m - 1, 0));
+            const bool wide = m > 0 && room <= OWNMAX - nown;
+            const int more = wide ? m - 1 : 0;
+            const int at = wave_incl_scan(more) - more + lane;
+            if (lane < nown) {
+                s_ibeg[lane] = (uint16_t)(at | (more << 8) | (wide ? 0x8000 : 0));
+                if (!wide) s_sph[at] = tagged(sp, group_of(lane));
+            }
+        }
         int ex = block_excl_scan(loc, s_w, ss);
+        if (valid) {
+            const int v = s_ibeg[A - c0];
+            if (v & 0x8000)
+                s_sph[(v & 255) + i - max(ldg(S.cstart + A), first)] = tagged(F4{oi[0], oi[1], oi[2], 2e-3f}, group_of(A - c0));
+        }
         for (int q = 0; q < PER; ++q) {
             const int c = tid * PER + q;
             if (c <= nsc) s_ofs[c] = ex;
@@ -1747,7 +1787,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
         if (tid == 0 && nsc == UCELLS) s_ofs[nsc] = ss;
         for (int a = wv; a < nown; a += BLOCK / WAVE) {
             const int b = ldg(S.cnbr_start + c0 + a) - q0, e = ldg(S.cnbr_start + c0 + a + 1) - q0;
-            for (int q = b + lane; q < e; q += WAVE) atomicOr(&s_mask[s_qpos[q]], 1ull << a);
+            const int v = s_ibeg[a];
+            const unsigned long long bits = (~0ull >> (63 - ((v >> 8) & 127))) << (v & 255);
+            for (int q = b + lane; q < e; q += WAVE) atomicOr(&s_mask[s_qpos[q]], bits);
         }
         __syncthreads();
         constexpr int SB = 4;                       // union particles per thread in flight
@@ -1790,7 +1832,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
                         const F4 sp = s_sph[a];
                         const float rr = sp.w + rm[k];
                         if (m[k] && dist2f(sp.x, sp.y, sp.z, o[k][0], o[k][1], o[k][2]) <= rr * rr)
-                            om[k] |= 1u << (nown <= GROUPS ? a : a * GROUPS / nown);
+                            om[k] |= 1u << (__float_as_int(sp.w) & 15);
                         m[k] &= m[k] - 1u;
                         more |= m[k];
                     }
@@ -1843,7 +1885,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
         const float rlA = P.rl2f[ti][0], rlB = P.rl2f[ti][1], rlC = P.rl2f[ti][2];
         const float riA = P.rin2f[ti][0], riB = P.rin2f[ti][1], riC = P.rin2f[ti][2];
         const int oself = valid ? 4 * (int)s_self[tid] : -1;     // this particle's own stage entry (LDS offset)
-        const int G = min(nown, GROUPS), mygrp = nown <= GROUPS ? A - c0 : (A - c0) * GROUPS / nown;
+        const int G = min(nown, GROUPS), mygrp = group_of(A - c0);
         auto ux = [&](int o) { return *reinterpret_cast<const float *>(s_raw + o); };
         auto uy = [&](int o) { return *reinterpret_cast<const float *>(s_raw + 4 * USTAGE + o); };
         auto uz = [&](int o) { return *reinterpret_cast<const float *>(s_raw + 8 * USTAGE + o); };
@@ -2058,19 +2100,39 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
     int32_t *col = S.nl + (size_t)(chunk_ok ? chunk : 0) * MAXNB * CHUNK + lane;
     if (!staged && valid) {
         cnt = 0;
-        for (int q = S.cnbr_start[A]; q < S.cnbr_start[A + 1]; ++q) {
-            int B = ldg(S.cnbr + q);
-            int b = ldg(S.cstart + B), e = b + ldg(S.ccount + B);
-            for (int j = b; j < e; ++j) {
-                if (j == i) continue;
-                D4 pj = ldpos(S, j);
+        // the paired cells whose sphere reaches this particle, four side by side, and their
+        // members likewise
+        constexpr int SB = 4;
+        const int qe = S.cnbr_start[A + 1];
+        for (int q0 = S.cnbr_start[A]; q0 < qe; q0 += SB) {
+            int b[SB], e[SB];
+#pragma unroll
+            for (int k = 0; k < SB; ++k) {
+                const int B = ldg(S.cnbr + min(q0 + k, qe - 1));
+                const D4 c = ldg(S.seed + B);
+                b[k] = ldg(S.cstart + B);
+                e[k] = b[k] + ldg(S.ccount + B);
                 double dx, dy, dz;
-                double d2 = dist2_exact(S, pi.x, pi.y, pi.z, pj.x, pj.y, pj.z, dx, dy, dz);
-                if (d2 < P.rl2[ti][(int)pj.w]) {
-                    if (cnt < MAXNB) stg(col + cnt * CHUNK, (int32_t)j);
-                    ++cnt;
-                }
+                const double d2 = dist2_exact(S, pi.x, pi.y, pi.z, c.x, c.y, c.z, dx, dy, dz);
+                const double reach = c.w + P.cell_search + 1e-9;
+                if (q0 + k >= qe || d2 > reach * reach) e[k] = b[k];
             }
+            for (int k = 0; k < SB; ++k)
+                for (int j0 = b[k]; j0 < e[k]; j0 += SB) {
+                    D4 pj[SB];
+#pragma unroll
+                    for (int h = 0; h < SB; ++h) pj[h] = ldpos(S, min(j0 + h, e[k] - 1));
+#pragma unroll
+                    for (int h = 0; h < SB; ++h) {
+                        const int j = j0 + h;
+                        double dx, dy, dz;
+                        const double d2 = dist2_exact(S, pi.x, pi.y, pi.z, pj[h].x, pj[h].y, pj[h].z, dx, dy, dz);
+                        if (j < e[k] && j != i && d2 < P.rl2[ti][(int)pj[h].w]) {
+                            if (cnt < MAXNB) stg(col + cnt * CHUNK, (int32_t)j);
+                            ++cnt;
+                        }
+                    }
+                }
         }
     }
     int rows = wave_max_int(cnt);

@@ -1002,13 +1002,33 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
             else dispatch(std::false_type{}, std::false_type{});
         }
     } else {
-        // block whose partners did not fit a stage: its (unpruned) lists hold global slots
+        // block whose partners did not fit a stage: its (unpruned) lists hold global slots.  A
+        // row's records and the entry of the row after it are loaded while the row before is
+        // evaluated (each row's entry, position and orientation in turn were three waits).
         const int32_t *col = S.nl + (size_t)chunk * MAXNB * CHUNK + lane;
         const int r0 = split ? (tid >> 6) : 0, rstep = split ? BLOCK / WAVE : 1;
+        struct Row {
+            D4 p;
+            V3 n;
+            bool real;
+        };
+        auto entry = [&](int r) { return valid && r < rows ? ldg(col + r * CHUNK) : -1; };
+        auto record = [&](int j) {
+            Row c;
+            c.real = j >= 0 && j < S.n;
+            const int js = c.real ? j : lb * BLOCK;
+            c.p = ldpos(S, js);
+            c.n = ldg(S.ori + js);
+            return c;
+        };
+        Row nxt = record(entry(r0));
+        int jn = entry(r0 + rstep);
         for (int r = r0; r < rows; r += rstep) {
-            const int j = valid ? col[r * CHUNK] : -1;
-            if (j < 0 || j >= S.n) continue;
-            const D4 pj = ldpos(S, j);
+            const Row cur = nxt;
+            nxt = record(jn);
+            jn = entry(r + 2 * rstep);
+            if (!cur.real) continue;
+            const D4 pj = cur.p;
             const int tj = (int)pj.w;
             double dx, dy, dz;
             const double d2 = dist2_exact(S, pi.x, pi.y, pi.z, pj.x, pj.y, pj.z, dx, dy, dz);
@@ -1016,7 +1036,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
             T ax = 0, ay = 0, az = 0;
             T u;
             if ((ti | tj) == 0) {
-                const V3 nj = S.ori[j];
+                const V3 nj = cur.n;
                 u = lipid_pair<T, FAST>(P, (T)dx, (T)dy, (T)dz, nix, niy, niz, (T)nj.x, (T)nj.y, (T)nj.z, ax, ay, az,
                                         tx, ty, tz);
             } else {
