@@ -64,6 +64,37 @@ __device__ __forceinline__ int wave_max_int(int v) {
     return __builtin_amdgcn_readlane(v, WAVE - 1);
 }
 
+// Smallest and largest of 64 values by the same lane moves, in the last lane (of 16 in each
+// row's last lane with four steps).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_or(double old, double v) {
+    const int lo = __builtin_amdgcn_update_dpp(__double2loint(old), __double2loint(v), CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(__double2hiint(old), __double2hiint(v), CTRL, ROWS, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double row_max(double v) {
+    v = fmax(v, dpp_or<0x111, 0xf>(-INFINITY, v));
+    v = fmax(v, dpp_or<0x112, 0xf>(-INFINITY, v));
+    v = fmax(v, dpp_or<0x114, 0xf>(-INFINITY, v));
+    return fmax(v, dpp_or<0x118, 0xf>(-INFINITY, v));
+}
+__device__ __forceinline__ double row_min(double v) {
+    v = fmin(v, dpp_or<0x111, 0xf>(INFINITY, v));
+    v = fmin(v, dpp_or<0x112, 0xf>(INFINITY, v));
+    v = fmin(v, dpp_or<0x114, 0xf>(INFINITY, v));
+    return fmin(v, dpp_or<0x118, 0xf>(INFINITY, v));
+}
+__device__ __forceinline__ double wave_max(double v) {
+    v = row_max(v);
+    v = fmax(v, dpp_or<0x142, 0xa>(-INFINITY, v));
+    return fmax(v, dpp_or<0x143, 0xc>(-INFINITY, v));
+}
+__device__ __forceinline__ double wave_min(double v) {
+    v = row_min(v);
+    v = fmin(v, dpp_or<0x142, 0xa>(INFINITY, v));
+    return fmin(v, dpp_or<0x143, 0xc>(INFINITY, v));
+}
+
 // Exclusive scan across the block (blockDim.x a multiple of 64, <= 1024).
 __device__ int block_excl_scan(int v, int *s_w, int &total) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
@@ -122,7 +153,7 @@ __global__ __launch_bounds__(MAX_SLOTS) void k_set_rebuild(const SysDev *Sd, int
                                                            unsigned long long m3, int32_t *out) {
     __shared__ int s_w[16];
     const int s = threadIdx.x;
-    int cnt[7] = {0, 0, 0, 0, 0, 0, 0};
+    int cnt[5] = {0, 0, 0, 0, 0};
     if (s < nsys) {
         const unsigned long long w = (s < 64) ? m0 : (s < 128) ? m1 : (s < 192) ? m2 : m3;
         const int bit = (int)((w >> (s & 63)) & 1ull);
@@ -137,15 +168,13 @@ __global__ __launch_bounds__(MAX_SLOTS) void k_set_rebuild(const SysDev *Sd, int
             if (S.n > 0) {
                 cnt[0] = (S.n + BLOCK - 1) / BLOCK;
                 cnt[1] = (S.k + BLOCK - 1) / BLOCK;
-                cnt[2] = (S.gcap + BLOCK - 1) / BLOCK;
-                cnt[3] = S.ntile_p;
-                cnt[4] = S.ntile_s;
-                cnt[5] = (S.k + SCAN_TILE - 1) / SCAN_TILE;
-                cnt[6] = (S.gcap + SCAN_TILE - 1) / SCAN_TILE;
+                cnt[2] = S.ntile_s;
+                cnt[3] = (S.k + SCAN_TILE - 1) / SCAN_TILE;
+                cnt[4] = (S.gcap + SCAN_TILE - 1) / SCAN_TILE;
             }
         }
     }
-    for (int m = 0; m < 7; ++m) {
+    for (int m = 0; m < 5; ++m) {
         int tot;
         const int ex = block_excl_scan(cnt[m], s_w, tot);
         if (s <= nsys) out[m * (nsys + 1) + s] = ex;     // entry nsys receives the total
@@ -209,14 +238,6 @@ __global__ void k_init_seeds(const SysDev *Sd, Maps L_maps, const int32_t *const
     }
 }
 
-// no warm start for the first assignment after seeding
-__global__ void k_clear_owner(const SysDev *Sd, Maps L_maps) {
-    SYS_FROM(p);
-    if (!S.sc->rebuild) return;
-    int i = lb * BLOCK + threadIdx.x;
-    if (i < S.n) S.owner[i] = -1;
-}
-
 // ------------------------------------------------------------------ seed grid
 
 // Per-block bounding boxes of the (wrapped) particle positions: partials 2..7 of bred2
@@ -233,13 +254,12 @@ __global__ __launch_bounds__(BLOCK) void k_bbox_partial(const SysDev *Sd, Maps L
                        wrap_coord(p.z, S.per[2], S.box[2])};
         for (int a = 0; a < 3; ++a) { mn[a] = v[a]; mx[a] = v[a]; }
     }
-    for (int a = 0; a < 3; ++a)
-        for (int o = 32; o > 0; o >>= 1) {
-            mn[a] = fmin(mn[a], __shfl_xor(mn[a], o));
-            mx[a] = fmax(mx[a], __shfl_xor(mx[a], o));
-        }
+    for (int a = 0; a < 3; ++a) {
+        mn[a] = wave_min(mn[a]);
+        mx[a] = wave_max(mx[a]);
+    }
     const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0)
+    if ((threadIdx.x & 63) == WAVE - 1)
         for (int a = 0; a < 3; ++a) { s_v[a][w] = mn[a]; s_v[3 + a][w] = mx[a]; }
     __syncthreads();
     if (threadIdx.x < 6) {
@@ -262,13 +282,12 @@ __global__ __launch_bounds__(BLOCK) void k_seed_bbox_partial(const SysDev *Sd, M
         const double v[3] = {p.x, p.y, p.z};
         for (int a = 0; a < 3; ++a) { mn[a] = v[a]; mx[a] = v[a]; }
     }
-    for (int a = 0; a < 3; ++a)
-        for (int o = 32; o > 0; o >>= 1) {
-            mn[a] = fmin(mn[a], __shfl_xor(mn[a], o));
-            mx[a] = fmax(mx[a], __shfl_xor(mx[a], o));
-        }
+    for (int a = 0; a < 3; ++a) {
+        mn[a] = wave_min(mn[a]);
+        mx[a] = wave_max(mx[a]);
+    }
     const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0)
+    if ((threadIdx.x & 63) == WAVE - 1)
         for (int a = 0; a < 3; ++a) { s_v[a][w] = mn[a]; s_v[3 + a][w] = mx[a]; }
     __syncthreads();
     if (threadIdx.x < 6) {
@@ -283,8 +302,9 @@ __global__ __launch_bounds__(BLOCK) void k_seed_bbox_partial(const SysDev *Sd, M
 // Uniform grid over the seeds: cubic cells holding about one eighth of a seed each,
 // but no smaller than hmin (twice the cell-pair search radius).  A cell-pair query
 // walks every grid cell within its reach; on small systems a finer grid would make
-// each query a long chain of dependent loads over mostly empty cells.
-__global__ void k_grid_setup(const SysDev *Sd, int nsys, double hmin) {
+// each query a long chain of dependent loads over mostly empty cells.  The seeds' boxes are
+// sper to a 256-cell block of the cell map.
+__global__ __launch_bounds__(1024) void k_grid_setup(const SysDev *Sd, int nsys, double hmin, int sper) {
     const SysDev &S = Sd[blockIdx.x];
     if (!S.sc->rebuild) return;
     __shared__ double s_mn[6][16], s_mx[6][16];
@@ -295,23 +315,24 @@ __global__ void k_grid_setup(const SysDev *Sd, int nsys, double hmin) {
         const double *r = S.bred2 + (size_t)b * BRED + 2;
         for (int a = 0; a < 3; ++a) { mn[a] = fmin(mn[a], r[a]); mx[a] = fmax(mx[a], r[3 + a]); }
     }
-    const int nsb = (S.k + BLOCK - 1) / BLOCK;
+    const int nsb = sper * ((S.k + BLOCK - 1) / BLOCK);
     for (int b = threadIdx.x; b < nsb; b += blockDim.x) {
         const double *r = S.sbox + (size_t)b * 6;
         for (int a = 0; a < 3; ++a) { mn[3 + a] = fmin(mn[3 + a], r[a]); mx[3 + a] = fmax(mx[3 + a], r[3 + a]); }
     }
-    for (int a = 0; a < 6; ++a)
-        for (int o = 32; o > 0; o >>= 1) {
-            mn[a] = fmin(mn[a], __shfl_xor(mn[a], o));
-            mx[a] = fmax(mx[a], __shfl_xor(mx[a], o));
-        }
-    int w = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
-    if (lane == 0)
-        for (int a = 0; a < 6; ++a) { s_mn[a][w] = mn[a]; s_mx[a][w] = mx[a]; }
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (int a = 0; a < 6; ++a) {
+        mn[a] = wave_min(mn[a]);
+        mx[a] = wave_max(mx[a]);
+        if (lane == WAVE - 1) { s_mn[a][w] = mn[a]; s_mx[a][w] = mx[a]; }
+    }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int a = 0; a < 6; ++a)
-            for (int q = 1; q < nw; ++q) { mn[a] = fmin(mn[a], s_mn[a][q]); mx[a] = fmax(mx[a], s_mx[a][q]); }
+    if (w != 0) return;
+    for (int a = 0; a < 6; ++a) {                    // sixteen wavefronts: a row of lanes
+        mn[a] = row_min(s_mn[a][lane & 15]);
+        mx[a] = row_max(s_mx[a][lane & 15]);
+    }
+    if (lane == 15) {
         SysScal *sc = S.sc;
         double ext[3];
         for (int a = 0; a < 3; ++a) {
@@ -363,13 +384,7 @@ __device__ __forceinline__ int grid_coord(const SysScal *sc, const SysDev &S, in
     return c;
 }
 
-__global__ void k_grid_clear(const SysDev *Sd, Maps L_maps) {
-    SYS_FROM(g);
-    if (!S.sc->rebuild) return;
-    int g = lb * BLOCK + threadIdx.x;
-    if (g < S.gcap) S.gcount[g] = 0;
-}
-
+// (gcount is zero between grid builds: the fill takes back what the count adds.)
 __global__ void k_grid_count(const SysDev *Sd, Maps L_maps) {
     SYS_FROM(c);
     if (!S.sc->rebuild) return;
@@ -386,13 +401,13 @@ __global__ void k_grid_count(const SysDev *Sd, Maps L_maps) {
 
 // Segmented exclusive scans, three launches (tile sums, per-system scan of the
 // tile sums, tile scans), specialised at compile time per array.  WHICH: 0 = seed
-// grid (gcount -> gstart over gtot cells), 1 = ccount2 -> cstart2, 2 = ccount ->
-// cstart, 3 = cnbr_start in place (k cells).  dst[len] receives the total.
+// grid (gcount -> gstart over gtot cells), 1 = ccount2 -> cstart2, 2 = ccount2 ->
+// cstart, the counts moving to ccount, 3 = cnbr_start in place (k cells).  dst[len]
+// receives the total.
 template <int WHICH>
 __device__ __forceinline__ const int *scan_src(const SysDev &S) {
     if constexpr (WHICH == 0) return S.gcount;
-    else if constexpr (WHICH == 1) return S.ccount2;
-    else if constexpr (WHICH == 2) return S.ccount;
+    else if constexpr (WHICH == 1 || WHICH == 2) return S.ccount2;
     else return S.cnbr_start;
 }
 template <int WHICH>
@@ -463,16 +478,22 @@ __global__ __launch_bounds__(BLOCK) void k_scan_c(const SysDev *Sd, Maps L_maps)
     int run = S.tsum[tile] + block_excl_scan(loc, s_w, tot);
     for (int q = 0; q < per; ++q) {
         const int idx = tile * SCAN_TILE + threadIdx.x * per + q;
-        if (idx < len) dst[idx] = run;
+        if (idx < len) {
+            dst[idx] = run;
+            if constexpr (WHICH == 2) {
+                S.ccount[idx] = v[q];
+                S.ccount2[idx] = 0;
+            }
+        }
         run += v[q];
     }
     if (tile == ntile - 1 && threadIdx.x == 0) dst[len] = S.tsum[ntile];
 }
 
-// The whole scan of a system by one block, up to SCAN_ONE elements (32 per thread): one
+// The whole scan of a system by one block, up to SCAN_ONE elements (64 per thread): one
 // launch of 7.4 us instead of three of 14.2 us together (eight systems of 6250 cells).
 // Beyond that one block's rounds take longer than the three launches.
-constexpr int SCAN_ONE = 32768;
+constexpr int SCAN_ONE = 65536;
 
 template <int WHICH>
 __global__ __launch_bounds__(1024) void k_scan_one(const SysDev *Sd) {
@@ -496,7 +517,13 @@ __global__ __launch_bounds__(1024) void k_scan_one(const SysDev *Sd) {
         int run = carry + block_excl_scan(loc, s_w, tot);
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
-            if (i0 + q < len) dst[i0 + q] = run;
+            if (i0 + q < len) {
+                dst[i0 + q] = run;
+                if constexpr (WHICH == 2) {
+                    S.ccount[i0 + q] = v[q];
+                    S.ccount2[i0 + q] = 0;
+                }
+            }
             run += v[q];
         }
         carry += tot;
@@ -531,41 +558,37 @@ __global__ void k_grid_fill(const SysDev *Sd, Maps L_maps) {
     int c = lb * BLOCK + threadIdx.x;
     if (c >= S.k) return;
     int g = S.sgcell[c];
-    int p = S.gstart[g] + atomicAdd(&S.gcount[g], 1);
-    S.gseed[p] = c;
+    int p = S.gstart[g] + atomicAdd(&S.gcount[g], -1) - 1;
+    S.val2[p] = (uint32_t)c;
 }
 
-// Seeds inside a grid cell in ascending index order (deterministic scans).
-__global__ void k_grid_sortcells(const SysDev *Sd, Maps L_maps) {
-    SYS_FROM(g);
+// Seeds inside a grid cell in ascending index order (deterministic scans): each seed's place
+// is the number of smaller ones in its cell.  With the centroid positions in grid order,
+// seed index in w (one load per candidate in the E-step).
+__global__ void k_grid_place(const SysDev *Sd, Maps L_maps) {
+    SYS_FROM(c);
     if (!S.sc->rebuild) return;
-    int g = lb * BLOCK + threadIdx.x;
-    if (g >= S.sc->gtot) return;
-    int b = S.gstart[g], e = S.gstart[g + 1];
-    for (int i = b + 1; i < e; ++i) {
-        int v = S.gseed[i];
-        int j = i - 1;
-        while (j >= b && S.gseed[j] > v) { S.gseed[j + 1] = S.gseed[j]; --j; }
-        S.gseed[j + 1] = v;
-    }
-    // centroid positions in grid order, seed index in w (one load per candidate in the E-step)
-    for (int q = b; q < e; ++q) {
-        const int sd = S.gseed[q];
-        const D4 c = S.seed[sd];
-        S.gpos[q] = D4{c.x, c.y, c.z, (double)sd};
-    }
+    const int c = lb * BLOCK + threadIdx.x;
+    if (c >= S.k) return;
+    const int g = S.sgcell[c], b = S.gstart[g], e = S.gstart[g + 1];
+    int at = b;
+    for (int q = b; q < e; ++q) at += (int)ldg(reinterpret_cast<const int32_t *>(S.val2) + q) < c ? 1 : 0;
+    const D4 p = S.seed[c];
+    S.gseed[at] = c;
+    S.gpos[at] = D4{p.x, p.y, p.z, (double)c};
 }
 
-void launch_grid_build(const LaunchCtx &L) {
+// The particles do not move while the cells update: their boxes serve all of its grids.
+void launch_particle_boxes(const LaunchCtx &L) {
     hipLaunchKernelGGL(k_bbox_partial, dim3(L.nblk_p), dim3(BLOCK), 0, L.st, L.S, L.maps);
-    hipLaunchKernelGGL(k_seed_bbox_partial, dim3(L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps);
-    hipLaunchKernelGGL(k_grid_setup, dim3(L.nsys), dim3(1024), 0, L.st, L.S, L.nsys, 2.0 * L.prm.cell_search);
-    hipLaunchKernelGGL(k_grid_clear, dim3(L.nblk_g), dim3(BLOCK), 0, L.st, L.S, L.maps);
+}
+
+static void grid_build(const LaunchCtx &L, int sper) {
+    hipLaunchKernelGGL(k_grid_setup, dim3(L.nsys), dim3(1024), 0, L.st, L.S, L.nsys, 2.0 * L.prm.cell_search, sper);
     hipLaunchKernelGGL(k_grid_count, dim3(L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps);
     launch_scan(L, 0);
-    hipLaunchKernelGGL(k_grid_clear, dim3(L.nblk_g), dim3(BLOCK), 0, L.st, L.S, L.maps);
     hipLaunchKernelGGL(k_grid_fill, dim3(L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps);
-    hipLaunchKernelGGL(k_grid_sortcells, dim3(L.nblk_g), dim3(BLOCK), 0, L.st, L.S, L.maps);
+    hipLaunchKernelGGL(k_grid_place, dim3(L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps);
 }
 
 // ------------------------------------------------------------------ E-step
@@ -602,7 +625,84 @@ __device__ int nearest_seed(const SysDev &S, const SysScal *sc, double xi, doubl
     cc[2] = grid_coord(sc, S, 2, zi, u[2]);
     int plo[3] = {1, 1, 1}, phi[3] = {-1, -1, -1};
     int rmax = max(sc->gdim[0], max(sc->gdim[1], sc->gdim[2]));
-    for (int r = 0; r <= rmax; ++r) {
+    // whether every seed outside the window [lo, hi] is farther than the best one: compares it
+    // with the distance from the particle to the nearest cell not yet visited
+    auto done = [&](const int (&lo)[3], const int (&hi)[3]) {
+        double m = INFINITY;
+        for (int a = 0; a < 3; ++a) {
+            int dim = sc->gdim[a];
+            bool full = S.per[a] ? (hi[a] - lo[a] + 1 >= dim) : false;
+            if (full) continue;
+            bool lo_open = S.per[a] ? true : (cc[a] + lo[a] > 0);
+            bool hi_open = S.per[a] ? true : (cc[a] + hi[a] < dim - 1);
+            if (lo_open) m = fmin(m, u[a] - (double)(cc[a] + lo[a]) * sc->gh[a]);
+            if (hi_open) m = fmin(m, (double)(cc[a] + hi[a] + 1) * sc->gh[a] - u[a]);
+        }
+        if (m == INFINITY) return true;
+        if (best >= 0 && m > 0.0) {
+            double mm = m * (1.0 - 1e-9);
+            if (bestd2 < mm * mm) return true;
+        }
+        return false;
+    };
+    // The cells around the particle's own first, at once: nine columns of three grid cells,
+    // whose seed ranges are all loaded together; then the columns' seeds, own column first,
+    // leaving out columns farther away than the best seed so far (a warm start leaves one to
+    // four).  Nearly every particle ends here.  The widening search below takes what does
+    // not (it is a chain of dependent loads), and the windows that wrap along z or cover a
+    // whole periodic axis.
+    int r0 = 0;
+    {
+        const bool zin = !S.per[2] || (cc[2] >= 1 && cc[2] + 1 < sc->gdim[2]);
+        if (zin && !(S.per[0] && sc->gdim[0] < 3) && !(S.per[1] && sc->gdim[1] < 3)) {
+            int lo[3], hi[3];
+            for (int a = 0; a < 3; ++a) axis_window(cc[a], sc->gdim[a], S.per[a], 1, lo[a], hi[a]);
+            double gap2[2][3];                       // squared distance to the rows at -1, 0, 1 along x and y
+            for (int a = 0; a < 2; ++a) {
+                const double gl = fmax(u[a] - (double)cc[a] * sc->gh[a] - 1e-9, 0.0);
+                const double gr = fmax((double)(cc[a] + 1) * sc->gh[a] - u[a] - 1e-9, 0.0);
+                gap2[a][0] = gl * gl * (1.0 - 1e-9);
+                gap2[a][1] = 0.0;
+                gap2[a][2] = gr * gr * (1.0 - 1e-9);
+            }
+            constexpr int NC = 9;
+            constexpr int ord[NC] = {4, 1, 3, 5, 7, 0, 2, 6, 8};
+            int qb[NC], qe[NC];
+#pragma unroll
+            for (int k = 0; k < NC; ++k) {
+                const int ox = ord[k] / 3 - 1, oy = ord[k] % 3 - 1;
+                const bool in = ox >= lo[0] && ox <= hi[0] && oy >= lo[1] && oy <= hi[1] &&
+                                !(gap2[0][ox + 1] + gap2[1][oy + 1] > bestd2);
+                int gx = cc[0] + ox, gy = cc[1] + oy;
+                if (S.per[0]) gx = gx < 0 ? gx + sc->gdim[0] : (gx >= sc->gdim[0] ? gx - sc->gdim[0] : gx);
+                if (S.per[1]) gy = gy < 0 ? gy + sc->gdim[1] : (gy >= sc->gdim[1] ? gy - sc->gdim[1] : gy);
+                const int base = (gx * sc->gdim[1] + gy) * sc->gdim[2] + cc[2];
+                qb[k] = in ? ldg(S.gstart + base + lo[2]) : 0;
+                qe[k] = in ? ldg(S.gstart + base + hi[2] + 1) : 0;
+            }
+#pragma unroll
+            for (int k = 0; k < NC; ++k) {
+                if (gap2[0][ord[k] / 3] + gap2[1][ord[k] % 3] > bestd2) continue;
+                constexpr int SB = 3;                // seeds side by side
+                for (int q0 = qb[k]; q0 < qe[k]; q0 += SB) {
+                    D4 c[SB];
+#pragma unroll
+                    for (int h = 0; h < SB; ++h) c[h] = ldg(S.gpos + min(q0 + h, qe[k] - 1));
+#pragma unroll
+                    for (int h = 0; h < SB; ++h) {
+                        const int sd = (int)c[h].w;
+                        if ((unsigned)(sd - slo) >= span) continue;   // the other particle set's cells
+                        const double d2 = dist2_exact(S, xi, yi, zi, c[h].x, c[h].y, c[h].z, dx, dy, dz);
+                        if (d2 < bestd2 || (d2 == bestd2 && sd < best)) { bestd2 = d2; best = sd; }
+                    }
+                }
+            }
+            if (done(lo, hi)) return best;
+            for (int a = 0; a < 3; ++a) { plo[a] = lo[a]; phi[a] = hi[a]; }
+            r0 = 2;
+        }
+    }
+    for (int r = r0; r <= rmax; ++r) {
         int lo[3], hi[3];
         bool grew = false;
         for (int a = 0; a < 3; ++a) {
@@ -658,56 +758,255 @@ __device__ int nearest_seed(const SysDev &S, const SysScal *sc, double xi, doubl
             }
         }
         for (int a = 0; a < 3; ++a) { plo[a] = lo[a]; phi[a] = hi[a]; }
-        // distance from the particle to the nearest cell not yet visited
-        double m = INFINITY;
-        for (int a = 0; a < 3; ++a) {
-            int dim = sc->gdim[a];
-            bool full = S.per[a] ? (hi[a] - lo[a] + 1 >= dim) : false;
-            if (full) continue;
-            bool lo_open = S.per[a] ? true : (cc[a] + lo[a] > 0);
-            bool hi_open = S.per[a] ? true : (cc[a] + hi[a] < dim - 1);
-            if (lo_open) m = fmin(m, u[a] - (double)(cc[a] + lo[a]) * sc->gh[a]);
-            if (hi_open) m = fmin(m, (double)(cc[a] + hi[a] + 1) * sc->gh[a] - u[a]);
-        }
-        if (m == INFINITY) break;
-        if (best >= 0 && m > 0.0) {
-            double mm = m * (1.0 - 1e-9);
-            if (bestd2 < mm * mm) break;
-        }
+        if (done(lo, hi)) break;
     }
     return best;
 }
 
-__global__ void k_assign(const SysDev *Sd, Maps L_maps, int warm) {
+// The order in which iteration `it` of an update goes through the particles: their slots
+// at first, then cell by cell.  The iterations reorder only what they need (positions,
+// types and slots), in memory that is idle until the update moves the particles.
+struct Order {
+    V3 *pos;
+    uint8_t *typ;
+    uint32_t *idx;                                  // slots (null: the order is the slots')
+};
+__device__ __forceinline__ Order order_of(const SysDev &S, int it) {
+    if (it == 0) return Order{S.pos, S.typ, nullptr};
+    if (it & 1) return Order{S.vel2, S.typ2, reinterpret_cast<uint32_t *>(S.frc)};
+    return Order{S.ori2, reinterpret_cast<uint8_t *>(S.angv2), reinterpret_cast<uint32_t *>(S.trq)};
+}
+
+// The nearest centroid of each particle, and its place among the cell's members: one atomic
+// per run of neighbouring lanes with the same cell.  (Places within a cell are put in order
+// by k_centroids.)
+__global__ __launch_bounds__(BLOCK) void k_assign(const SysDev *Sd, Maps L_maps, int it, int warm) {
     SYS_FROM(p);
     if (!S.sc->rebuild) return;
-    int i = lb * BLOCK + threadIdx.x;
-    if (i >= S.n) return;
-    D4 p = ldpos(S, i);
-    double d2;
-    // lipids search cells [0, kl), protein beads [kl, k) (all cells when kl == k)
-    const bool lipid_set = (p.w == 0.0) || S.kl == S.k;
-    const int slo = lipid_set ? 0 : S.kl, shi = lipid_set ? S.kl : S.k;
-    int best = nearest_seed(S, S.sc, p.x, p.y, p.z, warm ? S.owner[i] : -1, slo, shi, d2);
-    if (best < 0) { atomicOr(&S.sc->err, ERR_ASSIGN); best = 0; }
-    S.key[i] = (uint64_t)best;
-    S.val[i] = (uint32_t)i;
+    const int j = lb * BLOCK + threadIdx.x, lane = threadIdx.x & (WAVE - 1);
+    int best = -1;
+    if (j < S.n) {
+        const Order o = order_of(S, it);
+        const V3 p = ldg(o.pos + j);
+        double d2;
+        // lipids search cells [0, kl), protein beads [kl, k) (all cells when kl == k)
+        const bool lipid_set = (ldg(o.typ + j) & TYP_MASK) == 0 || S.kl == S.k;
+        const int slo = lipid_set ? 0 : S.kl, shi = lipid_set ? S.kl : S.k;
+        best = nearest_seed(S, S.sc, p.x, p.y, p.z, warm ? S.owner[j] : -1, slo, shi, d2);
+        if (best < 0) { atomicOr(&S.sc->err, ERR_ASSIGN); best = 0; }
+    }
+    const int prev = __shfl_up(best, 1);
+    const unsigned long long heads = __ballot(lane == 0 || best != prev);
+    const int head = 63 - __clzll(heads & (~0ull >> (63 - lane)));
+    const unsigned long long later = lane == 63 ? 0ull : heads & (~0ull << (lane + 1));
+    int base = 0;
+    if (lane == head && best >= 0) base = atomicAdd(S.ccount2 + best, (later ? __ffsll(later) - 1 : WAVE) - lane);
+    base = __shfl(base, head);
+    if (best >= 0) S.key[j] = (uint64_t)(unsigned)best | (uint64_t)(unsigned)(base + lane - head) << 32;
 }
 
-void launch_assign(const LaunchCtx &L, int warm) {
-    hipLaunchKernelGGL(k_assign, dim3(L.nblk_p), dim3(BLOCK), 0, L.st, L.S, L.maps, warm);
+__global__ __launch_bounds__(BLOCK) void k_cell_place(const SysDev *Sd, Maps L_maps) {
+    SYS_FROM(p);
+    if (!S.sc->rebuild) return;
+    const int j = lb * BLOCK + threadIdx.x;
+    if (j >= S.n) return;
+    const uint64_t key = S.key[j];
+    S.val[S.cstart[(int)(key & 0xffffffffu)] + (int)(key >> 32)] = (uint32_t)j;
 }
 
-// ------------------------------------------------------------------ segmented stable radix sort
+// ------------------------------------------------------------------ M-step
 
-// kind 0: particles (S.n keys, tiles map tp); kind 1: seeds (S.k keys, map ts).
-__global__ __launch_bounds__(BLOCK) void k_sort_hist(const SysDev *Sd, Maps L_maps, int kind, int pass) {
-    const int32_t *map = kind ? L_maps.ts : L_maps.tp;
+// CELL_LANES lanes per cell, CB_BLOCKS blocks per 256-cell block of the cell map.  The
+// members are put in the iteration's order by counting, among a cell's, those before each;
+// their offsets from the centroid wait in LDS for the sum, which is taken in that order.
+// Each centroid with lipid members moves by the mean min-image offset of those members;
+// centroids without lipids stay; periodic axes wrap.  Cells of a separate protein set
+// (index >= kl) average their protein members.  The members go on in their new order
+// (k_assign's next iteration), and each block leaves its centroids' box.
+//  What bounds it is the latency of one chain (members, their positions, the sum).  This and
+// the assignment's counts replaced a radix sort of the particles by cell (two passes of three
+// launches), the gather of the whole state, the cell ranges and a serial sum per thread.
+//  A cell of more than CMEM members is left to the whole block: up to BIGS members are
+// counted in LDS; the members of a larger one are collected by going through all particles.
+constexpr int CB_BLOCKS = CELL_LANES;
+constexpr int CPB = BLOCK / CELL_LANES;            // cells per block
+constexpr int CMEM = 64;
+constexpr int BIGS = 2048;
+
+// LDS written by one lane and read by others of its wavefront
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+__global__ __launch_bounds__(BLOCK) void k_centroids(const SysDev *Sd, Maps L_maps, int it, int last) {
+#pragma clang fp contract(off)
+    const int cbk = blockIdx.x / CB_BLOCKS;
+    const int s = find_sys(L_maps.c, L_maps.nsys, cbk);
+    const SysDev &S = Sd[s];
+    if (!S.sc->rebuild) return;
+    __shared__ double s_d[3][CPB * CMEM];           // offsets; a big cell's members, then its offsets
+    __shared__ uint32_t s_j[CPB][CMEM];
+    __shared__ int s_big[CPB];
+    __shared__ double s_c[3][CPB];
+    static_assert(sizeof(s_d) >= 2 * BIGS * sizeof(uint32_t), "a big cell's members");
+    const int tid = threadIdx.x, g = tid / CELL_LANES, l = tid % CELL_LANES;
+    const int sb = (cbk - L_maps.c[s]) * CB_BLOCKS + blockIdx.x % CB_BLOCKS;     // this block among its system's
+    const int c = sb * CPB + g;
+    const bool have = c < S.k;
+    const Order o = order_of(S, it), w = order_of(S, it + 1);
+    const int b = have ? S.cstart[c] : 0, m = have ? S.ccount[c] : 0;
+    const D4 sd = S.seed[have ? c : 0];
+    // member j in place q of cell `cell`: its offset from the centroid, 0 if it does not count
+    auto member = [&](uint32_t j, int at, int cell, const D4 &sdc, double (&d)[3]) {
+        const V3 p = ldg(o.pos + j);
+        const uint8_t t = ldg(o.typ + j);
+        w.idx[at] = o.idx ? o.idx[j] : j;
+        if (!last) {
+            w.pos[at] = p;
+            w.typ[at] = t;
+        }
+        S.owner[at] = cell;
+        const bool use = ((t & TYP_MASK) == 0) == (cell < S.kl);
+        (void)dist2_exact(S, p.x, p.y, p.z, sdc.x, sdc.y, sdc.z, d[0], d[1], d[2]);
+        if (!use) d[0] = d[1] = d[2] = 0.0;
+        return use ? 1 : 0;
+    };
+    // the centroid's coordinate a from the sum
+    auto moved = [&](double x, double sum, int cnt, int a) {
+        if (cnt > 0) {
+            x = x + sum / (double)cnt;
+            if (S.per[a]) x = x - S.box[a] * floor(x / S.box[a]);
+        }
+        return x;
+    };
+    if (l == 0) s_big[g] = m > CMEM ? m : 0;
+    double mine = l == 0 ? sd.x : (l == 1 ? sd.y : sd.z);      // lanes 0 to 2: the centroid
+    if (m <= CMEM) {
+        constexpr int R = CMEM / CELL_LANES;
+        uint32_t j[R];
+        int rk[R] = {0, 0, 0, 0}, cnt = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int q = l + r * CELL_LANES;
+            j[r] = q < m ? S.val[b + q] : 0u;
+            if (q < m) s_j[g][q] = j[r];
+        }
+        wave_fence();
+        for (int q = 0; q < m; ++q) {
+            const uint32_t v = s_j[g][q];
+#pragma unroll
+            for (int r = 0; r < R; ++r) rk[r] += v < j[r] ? 1 : 0;
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (l + r * CELL_LANES < m) {
+                double d[3];
+                cnt += member(j[r], b + rk[r], c, sd, d);
+                for (int a = 0; a < 3; ++a) s_d[a][g * CMEM + rk[r]] = d[a];
+            }
+        wave_fence();
+        for (int x = 1; x < CELL_LANES; x <<= 1) cnt += __shfl_xor(cnt, x);
+        if (l < 3) {
+            double sum = 0.0;
+#pragma unroll 4
+            for (int q = 0; q < m; ++q) sum += s_d[l][g * CMEM + q];
+            mine = moved(mine, sum, cnt, l);
+        }
+    }
+    if (l < 3) {
+        s_c[l][g] = mine;
+        if (have && m <= CMEM) reinterpret_cast<double *>(S.seed + c)[l] = mine;
+    }
+    __syncthreads();
+    for (int h = 0; h < CPB; ++h) {
+        const int mb = s_big[h];
+        if (mb == 0) continue;                      // block-uniform
+        __shared__ int s_w[16];
+        __shared__ int s_cnt;
+        const int cb = sb * CPB + h, bb = S.cstart[cb];
+        const D4 sdb = S.seed[cb];
+        if (tid == 0) s_cnt = 0;
+        if (mb <= BIGS) {
+            uint32_t *s_v = reinterpret_cast<uint32_t *>(s_d);
+            for (int q = tid; q < mb; q += BLOCK) s_v[q] = S.val[bb + q];
+            __syncthreads();
+            for (int q = tid; q < mb; q += BLOCK) {
+                const uint32_t v = s_v[q];
+                int r = 0;
+                for (int x = 0; x < mb; ++x) r += s_v[x] < v ? 1 : 0;
+                s_v[BIGS + r] = v;
+            }
+            __syncthreads();
+            for (int q = tid; q < mb; q += BLOCK) S.val[bb + q] = s_v[BIGS + q];
+        } else {
+            int at = bb;
+            for (int j0 = 0; j0 < S.n; j0 += BLOCK) {
+                const int j = j0 + tid;
+                const int in = j < S.n && (int)(S.key[j] & 0xffffffffu) == cb ? 1 : 0;
+                int tot;
+                const int ex = block_excl_scan(in, s_w, tot);
+                if (in) S.val[at + ex] = (uint32_t)j;
+                at += tot;
+            }
+        }
+        __syncthreads();
+        double sum = 0.0;
+        int cnt = 0;
+        for (int q0 = 0; q0 < mb; q0 += BLOCK) {
+            if (q0 + tid < mb) {
+                double d[3];
+                cnt += member(S.val[bb + q0 + tid], bb + q0 + tid, cb, sdb, d);
+                for (int a = 0; a < 3; ++a) s_d[a][tid] = d[a];
+            }
+            __syncthreads();
+            if (tid < 3)
+                for (int q = 0; q < min(BLOCK, mb - q0); ++q) sum += s_d[tid][q];
+            __syncthreads();
+        }
+        atomicAdd(&s_cnt, cnt);
+        __syncthreads();
+        if (tid < 3) {
+            const double v = moved(tid == 0 ? sdb.x : (tid == 1 ? sdb.y : sdb.z), sum, s_cnt, tid);
+            s_c[tid][h] = v;
+            reinterpret_cast<double *>(S.seed + cb)[tid] = v;
+        }
+        __syncthreads();
+    }
+    // the block's box (16 centroids: the first row of lanes)
+    if (tid < WAVE) {
+        const bool in = sb * CPB + (tid & 15) < S.k;
+        for (int a = 0; a < 3; ++a) {
+            const double lo = row_min(in ? s_c[a][tid & 15] : INFINITY), hi = row_max(in ? s_c[a][tid & 15] : -INFINITY);
+            if (tid == 15) {
+                S.sbox[(size_t)sb * 6 + a] = lo;
+                S.sbox[(size_t)sb * 6 + 3 + a] = hi;
+            }
+        }
+    }
+}
+
+// One k-means iteration: the seed grid (unless it stands), the particles' cells and the
+// centroids' means.
+void launch_iteration(const LaunchCtx &L, int it, bool warm, bool last) {
+    if (it > 0) grid_build(L, CB_BLOCKS);
+    hipLaunchKernelGGL(k_assign, dim3(L.nblk_p), dim3(BLOCK), 0, L.st, L.S, L.maps, it, warm ? 1 : 0);
+    launch_scan(L, 2);
+    hipLaunchKernelGGL(k_cell_place, dim3(L.nblk_p), dim3(BLOCK), 0, L.st, L.S, L.maps);
+    hipLaunchKernelGGL(k_centroids, dim3(CB_BLOCKS * L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps, it, last ? 1 : 0);
+}
+
+// ------------------------------------------------------------------ Morton order of centroids
+
+// Segmented stable radix sort of the seeds' 64-bit keys, for launches that hold a system of
+// more than RANK_MAX cells.
+__global__ __launch_bounds__(BLOCK) void k_sort_hist(const SysDev *Sd, Maps L_maps, int pass) {
+    const int32_t *map = L_maps.ts;
     const int s = find_sys(map, L_maps.nsys, blockIdx.x);
     const SysDev &S = Sd[s];
     if (!S.sc->rebuild) return;
     const int tile = blockIdx.x - map[s];
-    const int cnt = kind ? S.k : S.n;
+    const int cnt = S.k;
     const uint64_t *keys = (pass & 1) ? S.key2 : S.key;
     const int shift = 8 * pass;
     __shared__ int h[256];
@@ -725,11 +1024,11 @@ __global__ __launch_bounds__(BLOCK) void k_sort_hist(const SysDev *Sd, Maps L_ma
 // Column scan of the tile histograms: one block per (system, digit) turns the
 // digit's per-tile counts into exclusive tile offsets within the digit and leaves
 // the digit's total after the last tile row (the scatter adds the digit bases).
-__global__ __launch_bounds__(256) void k_sort_scan(const SysDev *Sd, int kind) {
+__global__ __launch_bounds__(256) void k_sort_scan(const SysDev *Sd) {
     const SysDev &S = Sd[blockIdx.x >> 8];
     if (!S.sc->rebuild) return;
     const int d = blockIdx.x & 255;
-    const int cnt = kind ? S.k : S.n;
+    const int cnt = S.k;
     const int ntile = (cnt + SORT_TILE - 1) / SORT_TILE;
     __shared__ int s_w[16];
     int carry = 0;
@@ -744,13 +1043,13 @@ __global__ __launch_bounds__(256) void k_sort_scan(const SysDev *Sd, int kind) {
     if (threadIdx.x == 0) S.hist[ntile * 256 + d] = carry;
 }
 
-__global__ __launch_bounds__(BLOCK) void k_sort_scatter(const SysDev *Sd, Maps L_maps, int kind, int pass) {
-    const int32_t *map = kind ? L_maps.ts : L_maps.tp;
+__global__ __launch_bounds__(BLOCK) void k_sort_scatter(const SysDev *Sd, Maps L_maps, int pass) {
+    const int32_t *map = L_maps.ts;
     const int s = find_sys(map, L_maps.nsys, blockIdx.x);
     const SysDev &S = Sd[s];
     if (!S.sc->rebuild) return;
     const int tile = blockIdx.x - map[s];
-    const int cnt = kind ? S.k : S.n;
+    const int cnt = S.k;
     const uint64_t *kin = (pass & 1) ? S.key2 : S.key;
     const uint32_t *vin = (pass & 1) ? S.val2 : S.val;
     uint64_t *kout = (pass & 1) ? S.key : S.key2;
@@ -798,177 +1097,36 @@ __global__ __launch_bounds__(BLOCK) void k_sort_scatter(const SysDev *Sd, Maps L
     }
 }
 
-static void sort_segments(const LaunchCtx &L, int kind, int key_bits) {
-    int passes = (key_bits + 7) / 8;
-    if (passes & 1) ++passes;           // even: the result lands back in key/val
-    int nblk = kind ? L.nblk_ts : L.nblk_tp;
-    for (int p = 0; p < passes; ++p) {
-        hipLaunchKernelGGL(k_sort_hist, dim3(nblk), dim3(BLOCK), 0, L.st, L.S, L.maps, kind, p);
-        hipLaunchKernelGGL(k_sort_scan, dim3(L.nsys * 256), dim3(256), 0, L.st, L.S, kind);
-        hipLaunchKernelGGL(k_sort_scatter, dim3(nblk), dim3(BLOCK), 0, L.st, L.S, L.maps, kind, p);
+static void radix_sort_seeds(const LaunchCtx &L) {
+    static_assert(64 % 16 == 0, "an even number of passes: the result lands back in key/val");
+    for (int p = 0; p < 64 / 8; ++p) {
+        hipLaunchKernelGGL(k_sort_hist, dim3(L.nblk_ts), dim3(BLOCK), 0, L.st, L.S, L.maps, p);
+        hipLaunchKernelGGL(k_sort_scan, dim3(L.nsys * 256), dim3(256), 0, L.st, L.S);
+        hipLaunchKernelGGL(k_sort_scatter, dim3(L.nblk_ts), dim3(BLOCK), 0, L.st, L.S, L.maps, p);
     }
 }
 
-void launch_sort_particles(const LaunchCtx &L, int key_bits) { sort_segments(L, 0, key_bits); }
-
-// ------------------------------------------------------------------ gather / commit
-
-// new slot j takes old slot val[j]; owner of j is key[j]
-__global__ void k_gather(const SysDev *Sd, Maps L_maps) {
-    SYS_FROM(p);
-    if (!S.sc->rebuild) return;
-    int j = lb * BLOCK + threadIdx.x;
-    if (j >= S.n) return;
-    int src = (int)S.val[j];
-    S.pos2[j] = S.pos[src];
-    S.typ2[j] = S.typ[src];
-    S.vel2[j] = S.vel[src];
-    S.ori2[j] = S.ori[src];
-    S.angv2[j] = S.angv[src];
-    S.gid2[j] = S.gid[src];
-}
-
-// copy the gathered state back; owner from key (mode 0) or val (mode 1)
-__global__ void k_commit(const SysDev *Sd, Maps L_maps, int mode) {
-    SYS_FROM(p);
-    if (!S.sc->rebuild) return;
-    int j = lb * BLOCK + threadIdx.x;
-    if (j >= S.n) return;
-    S.pos[j] = S.pos2[j];
-    S.typ[j] = S.typ2[j];
-    S.vel[j] = S.vel2[j];
-    S.ori[j] = S.ori2[j];
-    S.angv[j] = S.angv2[j];
-    int g = S.gid2[j];
-    S.gid[j] = g;
-    S.slot[g] = j;
-    S.owner[j] = mode ? (int)S.val[j] : (int)S.key[j];
-}
-
-// The gathered state becomes current by swapping the buffer pointers of the
-// rebuilding systems in the descriptor table (each update swaps twice, so the
-// host's copy of the table stays valid); only the id maps and owners are written.
-__global__ void k_swap_state(SysDev *Sd, int nsys) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= nsys) return;
-    SysDev &S = Sd[s];
-    if (S.n <= 0 || !S.sc->rebuild) return;
-    V3 *u;
-    u = S.pos; S.pos = S.pos2; S.pos2 = u;
-    uint8_t *y = S.typ; S.typ = S.typ2; S.typ2 = y;
-    u = S.vel; S.vel = S.vel2; S.vel2 = u;
-    u = S.ori; S.ori = S.ori2; S.ori2 = u;
-    u = S.angv; S.angv = S.angv2; S.angv2 = u;
-    int32_t *g = S.gid; S.gid = S.gid2; S.gid2 = g;
-}
-
-__global__ void k_commit_ids(const SysDev *Sd, Maps L_maps, int mode) {
-    SYS_FROM(p);
-    if (!S.sc->rebuild) return;
-    int j = lb * BLOCK + threadIdx.x;
-    if (j >= S.n) return;
-    S.slot[S.gid[j]] = j;
-    S.owner[j] = mode ? (int)S.val[j] : (int)S.key[j];
-}
-
-static void swap_and_commit(const LaunchCtx &L, int mode) {
-    hipLaunchKernelGGL(k_swap_state, dim3((L.nsys + 63) / 64), dim3(64), 0, L.st, L.Sw, L.nsys);
-    hipLaunchKernelGGL(k_commit_ids, dim3(L.nblk_p), dim3(BLOCK), 0, L.st, L.S, L.maps, mode);
-}
-
-void launch_gather_particles(const LaunchCtx &L, int swap) {
-    hipLaunchKernelGGL(k_gather, dim3(L.nblk_p), dim3(BLOCK), 0, L.st, L.S, L.maps);
-    if (swap) swap_and_commit(L, 0);
-    else hipLaunchKernelGGL(k_commit, dim3(L.nblk_p), dim3(BLOCK), 0, L.st, L.S, L.maps, 0);
-}
-
-// ------------------------------------------------------------------ cell ranges
-
-// Cell ranges from the owners, which the sort left in ascending order: where the
-// owner changes between slots j-1 and j, every cell in between starts at j.
-__global__ void k_cell_starts(const SysDev *Sd, Maps L_maps) {
-    SYS_FROM(p);
-    if (!S.sc->rebuild) return;
-    const int j = lb * BLOCK + threadIdx.x;
-    if (j >= S.n) return;
-    const int o = S.owner[j];
-    const int prev = j > 0 ? S.owner[j - 1] : -1;
-    for (int c = prev + 1; c <= o; ++c) S.cstart[c] = j;
-    if (j == S.n - 1)
-        for (int c = o + 1; c <= S.k; ++c) S.cstart[c] = S.n;
-}
-
-__global__ void k_cell_counts(const SysDev *Sd, Maps L_maps) {
-    SYS_FROM(c);
-    if (!S.sc->rebuild) return;
-    const int c = lb * BLOCK + threadIdx.x;
-    if (c < S.k) S.ccount[c] = S.cstart[c + 1] - S.cstart[c];
-}
-
-void launch_cell_ranges(const LaunchCtx &L) {
-    hipLaunchKernelGGL(k_cell_starts, dim3(L.nblk_p), dim3(BLOCK), 0, L.st, L.S, L.maps);
-    hipLaunchKernelGGL(k_cell_counts, dim3(L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps);
-}
-
-// ------------------------------------------------------------------ M-step
-
-// Each centroid with lipid members moves by the mean min-image offset of those
-// members (summed in slot order); centroids without lipids stay; periodic axes wrap.
-// Cells of a separate protein set (index >= kl) average their protein members.
-__global__ void k_mstep(const SysDev *Sd, Maps L_maps) {
-#pragma clang fp contract(off)
-    SYS_FROM(c);
-    if (!S.sc->rebuild) return;
-    int c = lb * BLOCK + threadIdx.x;
-    if (c >= S.k) return;
-    D4 sd = S.seed[c];
-    double sx = 0, sy = 0, sz = 0;
-    int cnt = 0;
-    const bool lipid_cell = c < S.kl;
-    int b = S.cstart[c], e = b + S.ccount[c];
-    for (int i = b; i < e; ++i) {
-        D4 p = ldpos(S, i);
-        if ((p.w == 0.0) != lipid_cell) continue;
-        double dx, dy, dz;
-        (void)dist2_exact(S, p.x, p.y, p.z, sd.x, sd.y, sd.z, dx, dy, dz);
-        sx += dx; sy += dy; sz += dz;
-        ++cnt;
-    }
-    if (cnt > 0) {
-        double inv = (double)cnt;
-        double v[3] = {sd.x + sx / inv, sd.y + sy / inv, sd.z + sz / inv};
-        for (int a = 0; a < 3; ++a)
-            if (S.per[a]) v[a] = v[a] - S.box[a] * floor(v[a] / S.box[a]);
-        sd.x = v[0]; sd.y = v[1]; sd.z = v[2];
-        S.seed[c] = sd;
-    }
-}
-
-void launch_mstep(const LaunchCtx &L) {
-    hipLaunchKernelGGL(k_mstep, dim3(L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps);
-}
-
-// ------------------------------------------------------------------ Morton order of centroids
-
+// The seeds' boxes into the Morton keys' frame (the centroid kernel leaves one box per
+// CELL_LANES-lane block).
 __global__ void k_seed_bbox(const SysDev *Sd, int nsys) {
     const SysDev &S = Sd[blockIdx.x];
     if (!S.sc->rebuild) return;
     __shared__ double s_mn[3][16], s_mx[3][16];
     double mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
-    const int nsb = (S.k + BLOCK - 1) / BLOCK;
+    const int nsb = CB_BLOCKS * ((S.k + BLOCK - 1) / BLOCK);
     for (int b = threadIdx.x; b < nsb; b += blockDim.x) {
         const double *r = S.sbox + (size_t)b * 6;
         for (int a = 0; a < 3; ++a) { mn[a] = fmin(mn[a], r[a]); mx[a] = fmax(mx[a], r[3 + a]); }
     }
-    for (int a = 0; a < 3; ++a)
-        for (int o = 32; o > 0; o >>= 1) {
-            mn[a] = fmin(mn[a], __shfl_xor(mn[a], o));
-            mx[a] = fmax(mx[a], __shfl_xor(mx[a], o));
-        }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        mn[a] = wave_min(mn[a]);
+        mx[a] = wave_max(mx[a]);
+    }
     int w = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
-    if (lane == 0) for (int a = 0; a < 3; ++a) { s_mn[a][w] = mn[a]; s_mx[a][w] = mx[a]; }
+    if (lane == WAVE - 1) for (int a = 0; a < 3; ++a) { s_mn[a][w] = mn[a]; s_mx[a][w] = mx[a]; }
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == WAVE - 1) {
         for (int a = 0; a < 3; ++a) {
             for (int q = 1; q < nw; ++q) { mn[a] = fmin(mn[a], s_mn[a][q]); mx[a] = fmax(mx[a], s_mx[a][q]); }
             S.sc->slo[a] = S.per[a] ? 0.0 : mn[a];
@@ -1003,87 +1161,155 @@ __global__ void k_morton(const SysDev *Sd, Maps L_maps) {
     if (c >= S.kl) key |= 1ull << 63;
     S.key[c] = key;
     S.val[c] = (uint32_t)c;
+    S.val2[c] = 0u;
 }
 
-// new cell c' takes old cell val[c']; cmap[old] = new
-__global__ void k_seed_permute(const SysDev *Sd, Maps L_maps) {
+// The keys' ranks by comparison, for small systems: each block counts for 256 seeds the
+// smaller keys (and the equal ones before them) in one of RANK_SEGS segments.  All k^2
+// comparisons take less time than eight radix passes of three launches, whose latency does
+// not shrink with the system: RANK_US at 6250 seeds.  The work grows with the square, so
+// beyond RANK_MAX seeds the radix sort is used.
+constexpr int RANK_SEGS = 16;
+constexpr int RANK_MAX = 32768;
+
+__global__ __launch_bounds__(BLOCK) void k_rank_seeds(const SysDev *Sd, Maps L_maps) {
+    const int cbk = blockIdx.x / RANK_SEGS, seg = blockIdx.x % RANK_SEGS;
+    const int s = find_sys(L_maps.c, L_maps.nsys, cbk);
+    const SysDev &S = Sd[s];
+    if (!S.sc->rebuild) return;
+    __shared__ uint64_t s_k[BLOCK];
+    const int c = (cbk - L_maps.c[s]) * BLOCK + threadIdx.x;
+    const uint64_t mine = c < S.k ? S.key[c] : 0ull;
+    const int per = (S.k + RANK_SEGS - 1) / RANK_SEGS, b = seg * per, e = min(S.k, b + per);
+    int cnt = 0;
+    for (int t0 = b; t0 < e; t0 += BLOCK) {
+        __syncthreads();
+        s_k[threadIdx.x] = t0 + (int)threadIdx.x < e ? S.key[t0 + threadIdx.x] : ~0ull;
+        __syncthreads();
+        const int m = min(BLOCK, e - t0);
+#pragma unroll 8
+        for (int q = 0; q < m; ++q) {
+            const uint64_t o = s_k[q];
+            cnt += (o < mine || (o == mine && t0 + q < c)) ? 1 : 0;
+        }
+    }
+    if (c < S.k && cnt > 0) atomicAdd(S.val2 + c, (uint32_t)cnt);
+}
+
+// The cells' new numbers: old cell val[c] becomes c (radix sort), or c becomes val2[c] (ranks).
+// cmap[old] = new.
+__global__ void k_seed_permute(const SysDev *Sd, Maps L_maps, int ranks) {
     SYS_FROM(c);
     if (!S.sc->rebuild) return;
     int c = lb * BLOCK + threadIdx.x;
     if (c >= S.k) return;
-    int old = (int)S.val[c];
-    S.seed2[c] = S.seed[old];
-    S.ccount2[c] = S.ccount[old];
-    S.cmap[old] = c;
+    const int old = ranks ? c : (int)S.val[c], cn = ranks ? (int)S.val2[c] : c;
+    S.seed2[cn] = S.seed[old];
+    S.ccount2[cn] = S.ccount[old];
+    S.cmap[old] = cn;
 }
 
-void launch_morton_sort_seeds(const LaunchCtx &L) {
-    hipLaunchKernelGGL(k_seed_bbox_partial, dim3(L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps);
-    hipLaunchKernelGGL(k_seed_bbox, dim3(L.nsys), dim3(1024), 0, L.st, L.S, L.nsys);
-    hipLaunchKernelGGL(k_morton, dim3(L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps);
-    sort_segments(L, 1, 64);
-    hipLaunchKernelGGL(k_seed_permute, dim3(L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps);
-    launch_scan(L, 1);
-}
-
-// particles move with their renumbered cells, keeping their order inside a cell
-__global__ void k_block_permute(const SysDev *Sd, Maps L_maps) {
-    SYS_FROM(p);
+// The particles move to their renumbered cells, in the last iteration's order within a cell,
+// CELL_LANES lanes per cell (the whole block for cells of more than CMEM members).  With the
+// members at hand, each cell's radius about its new centroid.
+__global__ __launch_bounds__(BLOCK) void k_move(const SysDev *Sd, Maps L_maps, int iters) {
+    const int cbk = blockIdx.x / CB_BLOCKS;
+    const int s = find_sys(L_maps.c, L_maps.nsys, cbk);
+    const SysDev &S = Sd[s];
     if (!S.sc->rebuild) return;
-    int j = lb * BLOCK + threadIdx.x;
-    if (j >= S.n) return;
-    int c = S.owner[j];
-    int cn = S.cmap[c];
-    int dst = S.cstart2[cn] + (j - S.cstart[c]);
-    S.pos2[dst] = S.pos[j];
-    S.typ2[dst] = S.typ[j];
-    S.vel2[dst] = S.vel[j];
-    S.ori2[dst] = S.ori[j];
-    S.angv2[dst] = S.angv[j];
-    S.gid2[dst] = S.gid[j];
-    S.val[dst] = (uint32_t)cn;
+    __shared__ int s_big[CPB];
+    __shared__ double s_r[BLOCK / WAVE];
+    const int tid = threadIdx.x, g = tid / CELL_LANES, l = tid % CELL_LANES;
+    const int c0 = ((cbk - L_maps.c[s]) * CB_BLOCKS + blockIdx.x % CB_BLOCKS) * CPB, c = c0 + g;
+    const bool have = c < S.k;
+    const uint32_t *idx = order_of(S, iters).idx;
+    auto one = [&](int from, int to, int cn, const D4 &sd) {
+        const uint32_t i = ldg(idx + from);
+        const V3 p = ldg(S.pos + i), v = ldg(S.vel + i), n = ldg(S.ori + i), a = ldg(S.angv + i);
+        const uint8_t t = ldg(S.typ + i);
+        const int32_t id = ldg(S.gid + i);
+        S.pos2[to] = p;
+        S.vel2[to] = v;
+        S.ori2[to] = n;
+        S.angv2[to] = a;
+        S.typ2[to] = t;
+        S.gid2[to] = id;
+        S.slot[id] = to;
+        S.owner[to] = cn;
+        double dx, dy, dz;
+        return dist2_exact(S, p.x, p.y, p.z, sd.x, sd.y, sd.z, dx, dy, dz);
+    };
+    const int b = have ? S.cstart[c] : 0, m = have ? S.ccount[c] : 0;
+    const int cn = have ? S.cmap[c] : 0;
+    if (l == 0) s_big[g] = m > CMEM ? m : 0;
+    double r2 = 0.0;
+    if (m <= CMEM && have) {
+        const D4 sd = S.seed[c];
+        const int to = S.cstart2[cn];
+        for (int q = l; q < m; q += CELL_LANES) r2 = fmax(r2, one(b + q, to + q, cn, sd));
+        r2 = row_max(r2);
+        if (l == CELL_LANES - 1) S.seed2[cn].w = sqrt(r2);
+    }
+    __syncthreads();
+    for (int h = 0; h < CPB; ++h) {
+        const int mb = s_big[h];
+        if (mb == 0) continue;                      // block-uniform
+        const int cb = c0 + h, cnb = S.cmap[cb], from = S.cstart[cb], to = S.cstart2[cnb];
+        const D4 sd = S.seed[cb];
+        double rb = 0.0;
+        for (int q = tid; q < mb; q += BLOCK) rb = fmax(rb, one(from + q, to + q, cnb, sd));
+        rb = wave_max(rb);
+        if ((tid & 63) == WAVE - 1) s_r[tid >> 6] = rb;
+        __syncthreads();
+        rb = fmax(fmax(s_r[0], s_r[1]), fmax(s_r[2], s_r[3]));
+        if (tid == 0) S.seed2[cnb].w = sqrt(rb);
+        if (tid % CELL_LANES == CELL_LANES - 1) r2 = fmax(r2, rb);
+        __syncthreads();
+    }
+    if (l != CELL_LANES - 1) r2 = 0.0;
+    r2 = wave_max(r2);
+    if ((tid & 63) == WAVE - 1 && r2 > 0.0) max_if_larger(&S.sc->rmax, dbits(sqrt(r2)));
 }
 
-__global__ void k_cell_commit(const SysDev *Sd, Maps L_maps) {
+// The renumbered cells become current, and the moved state by swapping its buffer pointers in
+// both descriptor tables (the host swaps its copies).
+__global__ void k_cell_commit(const SysDev *Sd, Maps L_maps, SysDev *t0, SysDev *t1) {
     SYS_FROM(c);
     if (!S.sc->rebuild) return;
     int c = lb * BLOCK + threadIdx.x;
     if (c >= S.k) return;
     S.seed[c] = S.seed2[c];
     S.ccount[c] = S.ccount2[c];
+    S.ccount2[c] = 0;                               // the next assignment counts here
     S.cstart[c] = S.cstart2[c];
     if (c == S.k - 1) S.cstart[S.k] = S.cstart2[S.k];
+    if (c < 2) {
+        swap_state(c == 0 ? t0[s] : t1[s]);
+        if (c == 0 && S.k == 1) swap_state(t1[s]);
+    }
 }
 
-void launch_block_permute(const LaunchCtx &L) {
-    hipLaunchKernelGGL(k_block_permute, dim3(L.nblk_p), dim3(BLOCK), 0, L.st, L.S, L.maps);
-    swap_and_commit(L, 1);
-    hipLaunchKernelGGL(k_cell_commit, dim3(L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps);
+// Renumber the cells along the Morton curve of their centroids, move the particles, and build
+// the new centroids' grid.
+void launch_renumber(const LaunchCtx &L, int iters) {
+    const bool ranks = L.kmax <= RANK_MAX;
+    hipLaunchKernelGGL(k_seed_bbox, dim3(L.nsys), dim3(1024), 0, L.st, L.S, L.nsys);
+    hipLaunchKernelGGL(k_morton, dim3(L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps);
+    if (ranks) hipLaunchKernelGGL(k_rank_seeds, dim3(RANK_SEGS * L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps);
+    else radix_sort_seeds(L);
+    hipLaunchKernelGGL(k_seed_permute, dim3(L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps, ranks ? 1 : 0);
+    launch_scan(L, 1);
+    hipLaunchKernelGGL(k_move, dim3(CB_BLOCKS * L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps, iters);
+    hipLaunchKernelGGL(k_cell_commit, dim3(L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps, L.tables[0], L.tables[1]);
+    grid_build(L, CB_BLOCKS);
 }
 
 // ------------------------------------------------------------------ cell radii and cell pairs
 
-// The radius of each cell about its centroid.  CELL_LANES lanes per cell read its members
-// (about 18) side by side; one thread's walk through them is a chain of dependent loads
-// (14.3 us at 125k particles; side by side 10.9 us, most of it the launch's own chain of
-// map, descriptor, flag and cell loads).
-constexpr int CELL_LANES = 16;
-constexpr int CB_BLOCKS = CELL_LANES;      // blocks per 256-cell block of the cell map
-
-// The largest of 16 lanes' non-negative values, on the last of them.
-__device__ __forceinline__ double row_max(double v) {
-    auto step = [](double x, auto ctrl) {
-        constexpr int C = decltype(ctrl)::value;
-        const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), C, 0xf, 0xf, false);
-        const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), C, 0xf, 0xf, false);
-        return fmax(x, __hiloint2double(hi, lo));
-    };
-    v = step(v, std::integral_constant<int, 0x111>{});
-    v = step(v, std::integral_constant<int, 0x112>{});
-    v = step(v, std::integral_constant<int, 0x114>{});
-    return step(v, std::integral_constant<int, 0x118>{});
-}
-
+// The radius of each cell about its centroid, CELL_LANES lanes per cell, for lists rebuilt
+// between cell updates (an update's move leaves the radii).  One thread's walk through a
+// cell's members is a chain of dependent loads (14.3 us at 125k particles; side by side 10.9
+// us, most of it the launch's own chain of map, descriptor, flag and cell loads).
 __global__ __launch_bounds__(BLOCK) void k_cell_bounds(const SysDev *Sd, Maps L_maps) {
     const int cbk = blockIdx.x / CB_BLOCKS;
     const int s = find_sys(L_maps.c, L_maps.nsys, cbk);
@@ -2328,9 +2554,11 @@ void launch_set_rebuild(const LaunchCtx &L, const unsigned long long m[4], int32
     hipLaunchKernelGGL(k_set_rebuild, dim3(1), dim3(MAX_SLOTS), 0, L.st, L.S, L.nsys, m[0], m[1], m[2], m[3], out);
 }
 
+// Seeds from the lipids, and their grid.
 void launch_init_seeds(const LaunchCtx &L, const int32_t *const *lipids) {
     hipLaunchKernelGGL(k_init_seeds, dim3(L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps, lipids);
-    hipLaunchKernelGGL(k_clear_owner, dim3(L.nblk_p), dim3(BLOCK), 0, L.st, L.S, L.maps);
+    hipLaunchKernelGGL(k_seed_bbox_partial, dim3(L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps);
+    grid_build(L, 1);
 }
 
 void launch_pack(const LaunchCtx &L, int s, const double *x, const double *n, const int32_t *type,

@@ -270,7 +270,7 @@ size_t layout(HostSys &s, char *base) {
     d.val = c.take<uint32_t>(n); d.val2 = c.take<uint32_t>(n);
     d.hist = c.take<int32_t>((size_t)256 * (std::max(s.ntile_p, s.ntile_s) + 1));   // + digit totals
     d.seed = c.take<D4>(k); d.seed2 = c.take<D4>(k);
-    d.sbox = c.take<double>((size_t)((k + BLOCK - 1) / BLOCK) * 6);
+    d.sbox = c.take<double>((size_t)CELL_LANES * ((k + BLOCK - 1) / BLOCK) * 6);
     d.cstart = c.take<int32_t>(k + 1); d.ccount = c.take<int32_t>(k); d.cstart2 = c.take<int32_t>(k + 1);
     d.ccount2 = c.take<int32_t>(k); d.cmap = c.take<int32_t>(k);
     d.cnbr_start = c.take<int32_t>(k + 1); d.cnbr = c.take<int32_t>(s.cnbr_cap);
@@ -317,12 +317,6 @@ void size_system(const rbc_ctx *h, HostSys &s, int64_t n, int64_t nlip, int64_t 
     s.ntile_s = (s.k + SORT_TILE - 1) / SORT_TILE;
 }
 
-int key_bits(int32_t k) {
-    int b = 1;
-    while ((1ll << b) < (int64_t)k) ++b;
-    return b;
-}
-
 // A descriptor with the drift's buffers exchanged: the other table's.
 void swap_drift(SysDev &d) {
     std::swap(d.pos, d.pos2);
@@ -332,7 +326,9 @@ void swap_drift(SysDev &d) {
 }
 
 void use_table(rbc_ctx *h, LaunchCtx &L, int par) {
-    L.S = L.Sw = h->d_sys + (size_t)par * h->max_slots;
+    L.S = h->d_sys + (size_t)par * h->max_slots;
+    L.tables[0] = h->d_sys;
+    L.tables[1] = h->d_sys + h->max_slots;
     L.par = par;
 }
 
@@ -346,9 +342,9 @@ rbc_status refresh_tables(rbc_ctx *h) {
     const int ns = h->nsys;
     std::vector<SysDev> tab(ns);
     std::vector<const int32_t *> lips(ns, nullptr);
-    std::vector<int32_t> maps(8 * (ns + 1), 0);
+    std::vector<int32_t> maps(6 * (ns + 1), 0);
     int32_t kmin = INT32_MAX, kmax = 0, gmax = 0;
-    int32_t *mp = maps.data(), *mc = mp + (ns + 1), *mg = mc + (ns + 1), *mtp = mg + (ns + 1), *mts = mtp + (ns + 1);
+    int32_t *mp = maps.data(), *mc = mp + (ns + 1), *mts = mc + (ns + 1);
     int32_t *msc = mts + (ns + 1), *msg = msc + (ns + 1), *mf = msg + (ns + 1);
     for (int s = 0; s < ns; ++s) {
         HostSys &hs = h->sys[s];
@@ -366,8 +362,6 @@ rbc_status refresh_tables(rbc_ctx *h) {
         if (on) { kmin = std::min(kmin, k); kmax = std::max(kmax, k); gmax = std::max(gmax, hs.gcap); }
         mp[s + 1] = mp[s] + (int32_t)((n + BLOCK - 1) / BLOCK);
         mc[s + 1] = mc[s] + (k + BLOCK - 1) / BLOCK;
-        mg[s + 1] = mg[s] + (on ? (hs.gcap + BLOCK - 1) / BLOCK : 0);
-        mtp[s + 1] = mtp[s] + (on ? hs.ntile_p : 0);
         mts[s + 1] = mts[s] + (on ? hs.ntile_s : 0);
         msc[s + 1] = msc[s] + (k + SCAN_TILE - 1) / SCAN_TILE;
         msg[s + 1] = msg[s] + (on ? (hs.gcap + SCAN_TILE - 1) / SCAN_TILE : 0);
@@ -386,20 +380,16 @@ rbc_status refresh_tables(rbc_ctx *h) {
     use_table(h, L, h->par);
     L.maps.p = h->d_maps;
     L.maps.c = h->d_maps + (ns + 1);
-    L.maps.g = h->d_maps + 2 * (ns + 1);
-    L.maps.tp = h->d_maps + 3 * (ns + 1);
-    L.maps.ts = h->d_maps + 4 * (ns + 1);
-    L.maps.sc = h->d_maps + 5 * (ns + 1);
-    L.maps.sg = h->d_maps + 6 * (ns + 1);
-    L.maps.f = h->d_maps + 7 * (ns + 1);
+    L.maps.ts = h->d_maps + 2 * (ns + 1);
+    L.maps.sc = h->d_maps + 3 * (ns + 1);
+    L.maps.sg = h->d_maps + 4 * (ns + 1);
+    L.maps.f = h->d_maps + 5 * (ns + 1);
     L.maps.nsys = ns;
     L.kmin = kmin;
     L.kmax = kmax;
     L.gmax = gmax;
     L.nblk_p = mp[ns];
     L.nblk_c = mc[ns];
-    L.nblk_g = mg[ns];
-    L.nblk_tp = mtp[ns];
     L.nblk_ts = mts[ns];
     L.nblk_sc = msc[ns];
     L.nblk_sg = msg[ns];
@@ -416,7 +406,7 @@ bool any_live(const rbc_ctx *h) {
     return false;
 }
 
-void update_body(rbc_ctx *h, const LaunchCtx &L, int bits, int lloyd);
+void update_body(rbc_ctx *h, const LaunchCtx &L, int lloyd);
 void lists_body(rbc_ctx *h, const LaunchCtx &L, bool cells_moved);
 
 // Launch context whose block maps cover only the systems in `which`, with their
@@ -431,12 +421,10 @@ LaunchCtx restricted(rbc_ctx *h, const std::vector<int> &which) {
     const int ns = h->nsys;
     U.maps.p = h->d_umaps;
     U.maps.c = h->d_umaps + (ns + 1);
-    U.maps.g = h->d_umaps + 2 * (ns + 1);
-    U.maps.tp = h->d_umaps + 3 * (ns + 1);
-    U.maps.ts = h->d_umaps + 4 * (ns + 1);
-    U.maps.sc = h->d_umaps + 5 * (ns + 1);
-    U.maps.sg = h->d_umaps + 6 * (ns + 1);
-    U.nblk_p = U.nblk_c = U.nblk_g = U.nblk_tp = U.nblk_ts = U.nblk_sc = U.nblk_sg = 0;
+    U.maps.ts = h->d_umaps + 2 * (ns + 1);
+    U.maps.sc = h->d_umaps + 3 * (ns + 1);
+    U.maps.sg = h->d_umaps + 4 * (ns + 1);
+    U.nblk_p = U.nblk_c = U.nblk_ts = U.nblk_sc = U.nblk_sg = 0;
     U.kmin = INT32_MAX;
     U.kmax = 0;
     U.gmax = 0;
@@ -447,8 +435,6 @@ LaunchCtx restricted(rbc_ctx *h, const std::vector<int> &which) {
         U.gmax = std::max(U.gmax, hs.gcap);
         U.nblk_p += (int32_t)((hs.n + BLOCK - 1) / BLOCK);
         U.nblk_c += (hs.k + BLOCK - 1) / BLOCK;
-        U.nblk_g += (hs.gcap + BLOCK - 1) / BLOCK;
-        U.nblk_tp += hs.ntile_p;
         U.nblk_ts += hs.ntile_s;
         U.nblk_sc += (hs.k + SCAN_TILE - 1) / SCAN_TILE;
         U.nblk_sg += (hs.gcap + SCAN_TILE - 1) / SCAN_TILE;
@@ -460,12 +446,10 @@ LaunchCtx restricted(rbc_ctx *h, const std::vector<int> &which) {
 // run that many k-means iterations first.
 void run_update(rbc_ctx *h, const std::vector<int> &which, int lloyd) {
     if (which.empty()) return;
-    int32_t kmax = 1;
-    for (int s : which) kmax = std::max(kmax, h->sys[s].k);
-    const LaunchCtx U = restricted(h, which);
-    update_body(h, U, key_bits(kmax), lloyd);
+    update_body(h, restricted(h, which), lloyd);
     for (int s : which) {
         HostSys &hs = h->sys[s];
+        swap_state(hs.dev);
         hs.updates++;
         hs.rebuilds++;
         hs.steps_since = 0;
@@ -504,33 +488,19 @@ void run_prunes(rbc_ctx *h, const std::vector<int> &which) {
 
 // The cell-update launches for the systems whose rebuild flag is set (L carries
 // block maps restricted to them).
-void update_body(rbc_ctx *h, const LaunchCtx &L, int bits, int lloyd) {
-    auto estep_msteps = [&](int iters) {
-        for (int it = 0; it < iters; ++it) {
-            if (it > 0) launch_grid_build(L);
-            launch_assign(L, 1);
-            launch_sort_particles(L, bits);
-            launch_gather_particles(L, it == iters - 1);   // the update swaps buffers exactly twice
-            launch_cell_ranges(L);
-            launch_mstep(L);
-        }
-    };
-    if (lloyd > 0) {
-        launch_init_seeds(L, h->d_lip);
-        launch_grid_build(L);
-        estep_msteps(lloyd);
-    } else {
-        estep_msteps(1);    // the seed grid of the current centroids is still valid
-    }
-    launch_morton_sort_seeds(L);
-    launch_block_permute(L);
-    launch_grid_build(L);
+void update_body(rbc_ctx *h, const LaunchCtx &L, int lloyd) {
+    launch_particle_boxes(L);
+    if (lloyd > 0) launch_init_seeds(L, h->d_lip);
+    // without seeding the grid of the current centroids is still valid
+    const int iters = std::max(lloyd, 1);
+    for (int it = 0; it < iters; ++it) launch_iteration(L, it, it > 0 || lloyd <= 0, it == iters - 1);
+    launch_renumber(L, iters);
     lists_body(h, L, true);
 }
 
 // Cell radii, cell pairs and neighbour lists on the current cells.
 void lists_body(rbc_ctx *h, const LaunchCtx &L, bool cells_moved) {
-    launch_cell_bounds(L);
+    if (!cells_moved) launch_cell_bounds(L);
     launch_cell_pairs(L);
     const bool t = h->timing && h->ncount < (int)h->nb.size();
     if (t) hipEventRecord(h->nb[h->ncount], L.st);
@@ -1016,7 +986,6 @@ rbc_status stage(rbc_ctx *h, int32_t slot, int64_t n, const double *x, const dou
     d.split = (n + BLOCK - 1) / BLOCK <= SPLIT_MAX_BLOCKS;
     d.gcap = fresh.gcap;
     d.cnbr_cap = fresh.cnbr_cap;
-    d.ntile_p = fresh.ntile_p;
     d.ntile_s = fresh.ntile_s;
     for (int a = 0; a < 3; ++a) { d.per[a] = fresh.per[a]; d.box[a] = fresh.box[a]; }
     // bond CSR by caller id
@@ -1142,8 +1111,8 @@ rbc_status create(const rbc_params *params, void *stream, int32_t max_slots, int
               hipEventCreateWithFlags(&h->ev_out, hipEventDisableTiming) == hipSuccess &&
               hipMalloc(&h->d_sys, 2 * sizeof(SysDev) * max_slots) == hipSuccess &&
               hipMalloc(&h->d_sc, sizeof(SysScal) * max_slots) == hipSuccess &&
-              hipMalloc(&h->d_maps, sizeof(int32_t) * 8 * (max_slots + 1)) == hipSuccess &&
-              hipMalloc(&h->d_umaps, sizeof(int32_t) * 7 * (MAX_SLOTS + 1)) == hipSuccess &&
+              hipMalloc(&h->d_maps, sizeof(int32_t) * 6 * (max_slots + 1)) == hipSuccess &&
+              hipMalloc(&h->d_umaps, sizeof(int32_t) * 5 * (MAX_SLOTS + 1)) == hipSuccess &&
               hipMalloc(&h->d_pmaps, sizeof(int32_t) * (MAX_SLOTS + 1)) == hipSuccess &&
               hipMalloc((void **)&h->d_lip, sizeof(void *) * max_slots) == hipSuccess &&
               hipHostMalloc((void **)&h->h_sc, sizeof(SysScal) * MAX_SLOTS, hipHostMallocDefault) == hipSuccess &&

@@ -100,6 +100,7 @@ __host__ __device__ inline unsigned long long stat_tag(unsigned long long step, 
 // per particle block): too small to fill the GPU, their step time is one wave's walk
 // over its rows, which this cuts by four.
 constexpr int SPLIT_MAX_BLOCKS = 32;
+constexpr int CELL_LANES = 16;          // lanes per cell in the kernels that go through cells' members
 struct alignas(64) StepStat {
     double d2;                        // largest |x - x_build|^2 of this drift
     double v2;                        // largest |v|^2 used in it
@@ -111,7 +112,7 @@ struct alignas(64) StepStat {
 // One system (slot): sizes and device arrays.  Particle arrays are in cell-sorted
 // slot order; `gid` maps a slot to the caller's particle id, `slot` the inverse.
 struct SysDev {
-    int32_t n, nlip, k, nchunk, gcap, cnbr_cap, ntile_p, ntile_s;
+    int32_t n, nlip, k, nchunk, gcap, cnbr_cap, ntile_s;
     int32_t per[3];
     int32_t kl;                                     // lipid cells: seeds [0, kl); protein cells: [kl, k)
     int32_t nsrcp;                                  // protein seed sources after the lipid ids in `lip`
@@ -130,7 +131,7 @@ struct SysDev {
     uint32_t *val, *val2;
     int32_t *hist;                                  // sort histograms: tiles x 256
     D4 *seed, *seed2;                               // centroid xyz, w = cell radius
-    double *sbox;                                   // per 256-seed block: the seeds' min xyz, max xyz
+    double *sbox;                                   // boxes of groups of seeds: min xyz, max xyz
     int32_t *cstart, *ccount, *cstart2, *ccount2, *cmap;
     int32_t *cnbr_start, *cnbr;                     // full cell-pair CSR (k+1, cnbr_cap)
     int32_t *gstart, *gcount, *gseed, *sgcell;      // seed grid (gcap+1, gcap, k, k)
@@ -154,6 +155,21 @@ struct SysDev {
     SysScal *sc;
     StepStat *hstat;                                // this system's ring in pinned host memory
 };
+
+// Exchange the buffers between which a cell update moves the particles.
+inline __host__ __device__ void swap_state(SysDev &d) {
+    auto sw = [](auto &a, auto &b) {
+        auto t = a;
+        a = b;
+        b = t;
+    };
+    sw(d.pos, d.pos2);
+    sw(d.typ, d.typ2);
+    sw(d.vel, d.vel2);
+    sw(d.ori, d.ori2);
+    sw(d.angv, d.angv2);
+    sw(d.gid, d.gid2);
+}
 
 // Model constants, passed by value to kernels.
 struct DevParams {
@@ -197,8 +213,6 @@ typedef unsigned v4u __attribute__((ext_vector_type(4)));
 struct Maps {
     const int32_t *p;      // particle blocks (BLOCK particles, also 4 chunks)
     const int32_t *c;      // cell blocks
-    const int32_t *g;      // seed-grid cell blocks
-    const int32_t *tp;     // particle sort tiles
     const int32_t *ts;     // seed sort tiles
     const int32_t *sc;     // scan tiles over cells
     const int32_t *sg;     // scan tiles over seed-grid cells
@@ -354,10 +368,10 @@ namespace rbc {
 
 struct LaunchCtx {
     const SysDev *S;         // device array of systems
-    SysDev *Sw;              // the same array, for the kernel that swaps gathered state in
+    SysDev *tables[2];       // both, for the kernel that swaps moved state in
     int32_t par;             // which of the two tables it is: they differ in the drift's buffers, current and next
     Maps maps;
-    int32_t nblk_p, nblk_c, nblk_g, nblk_tp, nblk_ts, nblk_sc, nblk_sg, nblk_f;   // totals over systems
+    int32_t nblk_p, nblk_c, nblk_ts, nblk_sc, nblk_sg, nblk_f;   // totals over systems
     int32_t nsys;
     int32_t kmin, kmax;      // fewest and most cells of a system in the launch
     int32_t gmax;            // most seed-grid cells (capacity) of one
@@ -383,16 +397,11 @@ constexpr int64_t PAIR_SCRATCH_PAIRS = ((32ll << 20) - 256) / 8;
 hipError_t pair_scratch_address(int device, void **out);   // this device's copy (it must be current)
 // cell update kernels (each predicated on SysScal::rebuild)
 void launch_set_rebuild(const LaunchCtx &L, const unsigned long long m[4],
-                        int32_t *out);                    // flags, and 7 x (nsys+1) prefix maps of the rebuilding systems
+                        int32_t *out);                    // flags, and 5 x (nsys+1) prefix maps of the rebuilding systems
+void launch_particle_boxes(const LaunchCtx &L);           // before the update's first grid
 void launch_init_seeds(const LaunchCtx &L, const int32_t *const *lipids);
-void launch_grid_build(const LaunchCtx &L);
-void launch_assign(const LaunchCtx &L, int warm);
-void launch_sort_particles(const LaunchCtx &L, int key_bits);
-void launch_gather_particles(const LaunchCtx &L, int swap);   // swap: make the gathered buffers current
-void launch_cell_ranges(const LaunchCtx &L);
-void launch_mstep(const LaunchCtx &L);
-void launch_morton_sort_seeds(const LaunchCtx &L);
-void launch_block_permute(const LaunchCtx &L);
+void launch_iteration(const LaunchCtx &L, int it, bool warm, bool last);
+void launch_renumber(const LaunchCtx &L, int iters);
 void launch_cell_bounds(const LaunchCtx &L);
 void launch_cell_pairs(const LaunchCtx &L);
 void launch_nlist(const LaunchCtx &L, bool cells_moved);
