@@ -491,8 +491,8 @@ __global__ __launch_bounds__(BLOCK) void k_scan_c(const SysDev *Sd, Maps L_maps)
 }
 
 // The whole scan of a system by one block, up to SCAN_ONE elements (64 per thread): one
-// launch of 7.4 us instead of three of 14.2 us together (eight systems of 6250 cells).
-// Beyond that one block's rounds take longer than the three launches.
+// launch of 4.5 us instead of three of 10 us together at 50 thousand grid cells.  Beyond
+// SCAN_ONE one block's rounds take longer than the three launches.
 constexpr int SCAN_ONE = 65536;
 
 template <int WHICH>
@@ -503,28 +503,55 @@ __global__ __launch_bounds__(1024) void k_scan_one(const SysDev *Sd) {
     const int *src = scan_src<WHICH>(S);
     int *dst = scan_dst<WHICH>(S);
     const int len = scan_len<WHICH>(S);
-    constexpr int PER = 8;                            // consecutive elements per thread and round
+    // eight consecutive elements per thread and round, in 16-byte accesses (the arrays start
+    // on 256 bytes); the next round's are on their way while this one is scanned
+    constexpr int PER = 8, Q = PER / 4;
+    typedef int v4i __attribute__((ext_vector_type(4)));
+    auto load = [&](int i0, v4i (&v)[Q]) {
+#pragma unroll
+        for (int h = 0; h < Q; ++h) {
+            const int i = i0 + 4 * h;
+            if (i + 3 < len) v[h] = ldg(reinterpret_cast<const v4i *>(src + i));
+            else v[h] = v4i{i < len ? ldg(src + i) : 0, i + 1 < len ? ldg(src + i + 1) : 0, i + 2 < len ? ldg(src + i + 2) : 0, 0};
+        }
+    };
+    auto store = [&](int *p, int i0, const v4i (&v)[Q]) {
+#pragma unroll
+        for (int h = 0; h < Q; ++h) {
+            const int i = i0 + 4 * h;
+            if (i + 3 < len) stg(reinterpret_cast<v4i *>(p + i), v[h]);
+            else
+                for (int q = 0; q < 3; ++q)
+                    if (i + q < len) stg(p + i + q, q == 0 ? v[h].x : (q == 1 ? v[h].y : v[h].z));
+        }
+    };
     int carry = 0;
+    v4i nx[Q];
+    load((int)threadIdx.x * PER, nx);
     for (int base = 0; base < len; base += 1024 * PER) {
         const int i0 = base + (int)threadIdx.x * PER;
-        int v[PER], loc = 0;
+        v4i v[Q], out[Q];
+        int loc = 0;
 #pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            v[q] = i0 + q < len ? src[i0 + q] : 0;
-            loc += v[q];
+        for (int h = 0; h < Q; ++h) {
+            v[h] = nx[h];
+            loc += v[h].x + v[h].y + v[h].z + v[h].w;
         }
+        load(i0 + 1024 * PER, nx);
         int tot;
         int run = carry + block_excl_scan(loc, s_w, tot);
 #pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            if (i0 + q < len) {
-                dst[i0 + q] = run;
-                if constexpr (WHICH == 2) {
-                    S.ccount[i0 + q] = v[q];
-                    S.ccount2[i0 + q] = 0;
-                }
+        for (int h = 0; h < Q; ++h)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                out[h][q] = run;
+                run += v[h][q];
             }
-            run += v[q];
+        store(dst, i0, out);
+        if constexpr (WHICH == 2) {
+            const v4i zero[Q] = {};
+            store(S.ccount, i0, v);
+            store(S.ccount2, i0, zero);
         }
         carry += tot;
     }
@@ -606,9 +633,10 @@ __device__ __forceinline__ void axis_window(int c, int dim, int per, int r, int 
     }
 }
 
-// Nearest centroid among seeds [slo, shi) (ties: lower index).
-__device__ int nearest_seed(const SysDev &S, const SysScal *sc, double xi, double yi, double zi, int warm,
-                            int slo, int shi, double &bestd2) {
+// Nearest centroid among seeds [slo, shi) (ties: lower index).  ranges: nine entries of LDS
+// for this thread, BLOCK apart.
+__device__ __forceinline__ int nearest_seed(const SysDev &S, const SysScal *sc, double xi, double yi, double zi, int warm,
+                                            int slo, int shi, int2 *ranges, double &bestd2) {
     int best = -1;
     bestd2 = INFINITY;
     double dx, dy, dz;
@@ -646,28 +674,28 @@ __device__ int nearest_seed(const SysDev &S, const SysScal *sc, double xi, doubl
         return false;
     };
     // The cells around the particle's own first, at once: nine columns of three grid cells,
-    // whose seed ranges are all loaded together; then the columns' seeds, own column first,
-    // leaving out columns farther away than the best seed so far (a warm start leaves one to
-    // four).  Nearly every particle ends here.  The widening search below takes what does
-    // not (it is a chain of dependent loads), and the windows that wrap along z or cover a
-    // whole periodic axis.
+    // less what is farther away than the warm start (which leaves one to four), whose seed
+    // ranges are all loaded together; then their seeds, own column first.  Nearly every
+    // particle ends here.  The widening search below takes what does not (it is a chain of
+    // dependent loads), and the windows that wrap along z or cover a whole periodic axis.
     int r0 = 0;
     {
         const bool zin = !S.per[2] || (cc[2] >= 1 && cc[2] + 1 < sc->gdim[2]);
         if (zin && !(S.per[0] && sc->gdim[0] < 3) && !(S.per[1] && sc->gdim[1] < 3)) {
             int lo[3], hi[3];
-            for (int a = 0; a < 3; ++a) axis_window(cc[a], sc->gdim[a], S.per[a], 1, lo[a], hi[a]);
-            double gap2[2][3];                       // squared distance to the rows at -1, 0, 1 along x and y
-            for (int a = 0; a < 2; ++a) {
+            double gap2[3][3];                       // squared distance to the rows at -1, 0, 1 along each axis
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                axis_window(cc[a], sc->gdim[a], S.per[a], 1, lo[a], hi[a]);
                 const double gl = fmax(u[a] - (double)cc[a] * sc->gh[a] - 1e-9, 0.0);
                 const double gr = fmax((double)(cc[a] + 1) * sc->gh[a] - u[a] - 1e-9, 0.0);
                 gap2[a][0] = gl * gl * (1.0 - 1e-9);
                 gap2[a][1] = 0.0;
                 gap2[a][2] = gr * gr * (1.0 - 1e-9);
             }
+            const int zlo = gap2[2][0] > bestd2 ? 0 : lo[2], zhi = gap2[2][2] > bestd2 ? 0 : hi[2];
             constexpr int NC = 9;
             constexpr int ord[NC] = {4, 1, 3, 5, 7, 0, 2, 6, 8};
-            int qb[NC], qe[NC];
 #pragma unroll
             for (int k = 0; k < NC; ++k) {
                 const int ox = ord[k] / 3 - 1, oy = ord[k] % 3 - 1;
@@ -677,26 +705,33 @@ __device__ int nearest_seed(const SysDev &S, const SysScal *sc, double xi, doubl
                 if (S.per[0]) gx = gx < 0 ? gx + sc->gdim[0] : (gx >= sc->gdim[0] ? gx - sc->gdim[0] : gx);
                 if (S.per[1]) gy = gy < 0 ? gy + sc->gdim[1] : (gy >= sc->gdim[1] ? gy - sc->gdim[1] : gy);
                 const int base = (gx * sc->gdim[1] + gy) * sc->gdim[2] + cc[2];
-                qb[k] = in ? ldg(S.gstart + base + lo[2]) : 0;
-                qe[k] = in ? ldg(S.gstart + base + hi[2] + 1) : 0;
+                ranges[k * BLOCK] = in ? make_int2(ldg(S.gstart + base + zlo), ldg(S.gstart + base + zhi + 1)) : make_int2(0, 0);
             }
+            auto columns = [&](auto per_tag) {
+                constexpr bool PER = decltype(per_tag)::value;
+                for (int k = 0; k < NC; ++k) {
+                    const int2 r = ranges[k * BLOCK];
+                    constexpr int SB = 2;            // seeds side by side
+                    for (int q0 = r.x; q0 < r.y; q0 += SB) {
+                        D4 c[SB];
 #pragma unroll
-            for (int k = 0; k < NC; ++k) {
-                if (gap2[0][ord[k] / 3] + gap2[1][ord[k] % 3] > bestd2) continue;
-                constexpr int SB = 3;                // seeds side by side
-                for (int q0 = qb[k]; q0 < qe[k]; q0 += SB) {
-                    D4 c[SB];
+                        for (int h = 0; h < SB; ++h) c[h] = ldg(S.gpos + min(q0 + h, r.y - 1));
 #pragma unroll
-                    for (int h = 0; h < SB; ++h) c[h] = ldg(S.gpos + min(q0 + h, qe[k] - 1));
-#pragma unroll
-                    for (int h = 0; h < SB; ++h) {
-                        const int sd = (int)c[h].w;
-                        if ((unsigned)(sd - slo) >= span) continue;   // the other particle set's cells
-                        const double d2 = dist2_exact(S, xi, yi, zi, c[h].x, c[h].y, c[h].z, dx, dy, dz);
-                        if (d2 < bestd2 || (d2 == bestd2 && sd < best)) { bestd2 = d2; best = sd; }
+                        for (int h = 0; h < SB; ++h) {
+                            const int sd = (int)c[h].w;
+                            const double d2 = PER ? dist2_exact(S, xi, yi, zi, c[h].x, c[h].y, c[h].z, dx, dy, dz)
+                                                  : dist2_open(xi, yi, zi, c[h].x, c[h].y, c[h].z, dx, dy, dz);
+                            // (not the other particle set's cells)
+                            if ((unsigned)(sd - slo) < span && (d2 < bestd2 || (d2 == bestd2 && sd < best))) {
+                                bestd2 = d2;
+                                best = sd;
+                            }
+                        }
                     }
                 }
-            }
+            };
+            if ((S.per[0] | S.per[1] | S.per[2]) != 0) columns(std::true_type{});
+            else columns(std::false_type{});
             if (done(lo, hi)) return best;
             for (int a = 0; a < 3; ++a) { plo[a] = lo[a]; phi[a] = hi[a]; }
             r0 = 2;
@@ -783,6 +818,7 @@ __device__ __forceinline__ Order order_of(const SysDev &S, int it) {
 __global__ __launch_bounds__(BLOCK) void k_assign(const SysDev *Sd, Maps L_maps, int it, int warm) {
     SYS_FROM(p);
     if (!S.sc->rebuild) return;
+    __shared__ int2 s_r[9 * BLOCK];
     const int j = lb * BLOCK + threadIdx.x, lane = threadIdx.x & (WAVE - 1);
     int best = -1;
     if (j < S.n) {
@@ -792,7 +828,7 @@ __global__ __launch_bounds__(BLOCK) void k_assign(const SysDev *Sd, Maps L_maps,
         // lipids search cells [0, kl), protein beads [kl, k) (all cells when kl == k)
         const bool lipid_set = (ldg(o.typ + j) & TYP_MASK) == 0 || S.kl == S.k;
         const int slo = lipid_set ? 0 : S.kl, shi = lipid_set ? S.kl : S.k;
-        best = nearest_seed(S, S.sc, p.x, p.y, p.z, warm ? S.owner[j] : -1, slo, shi, d2);
+        best = nearest_seed(S, S.sc, p.x, p.y, p.z, warm ? S.owner[j] : -1, slo, shi, s_r + threadIdx.x, d2);
         if (best < 0) { atomicOr(&S.sc->err, ERR_ASSIGN); best = 0; }
     }
     const int prev = __shfl_up(best, 1);
@@ -1167,9 +1203,9 @@ __global__ void k_morton(const SysDev *Sd, Maps L_maps) {
 // The keys' ranks by comparison, for small systems: each block counts for 256 seeds the
 // smaller keys (and the equal ones before them) in one of RANK_SEGS segments.  All k^2
 // comparisons take less time than eight radix passes of three launches, whose latency does
-// not shrink with the system: RANK_US at 6250 seeds.  The work grows with the square, so
-// beyond RANK_MAX seeds the radix sort is used.
-constexpr int RANK_SEGS = 16;
+// not shrink with the system: 16 us against 230 at 6250 seeds, 80 against 234 at 28 thousand.
+// The work grows with the square, so beyond RANK_MAX seeds the radix sort is used.
+constexpr int RANK_SEGS = 32;
 constexpr int RANK_MAX = 32768;
 
 __global__ __launch_bounds__(BLOCK) void k_rank_seeds(const SysDev *Sd, Maps L_maps) {
@@ -1177,8 +1213,8 @@ __global__ __launch_bounds__(BLOCK) void k_rank_seeds(const SysDev *Sd, Maps L_m
     const int s = find_sys(L_maps.c, L_maps.nsys, cbk);
     const SysDev &S = Sd[s];
     if (!S.sc->rebuild) return;
-    __shared__ uint64_t s_k[BLOCK];
-    const int c = (cbk - L_maps.c[s]) * BLOCK + threadIdx.x;
+    __shared__ __align__(16) uint64_t s_k[BLOCK];
+    const int c0 = (cbk - L_maps.c[s]) * BLOCK, c = c0 + threadIdx.x;
     const uint64_t mine = c < S.k ? S.key[c] : 0ull;
     const int per = (S.k + RANK_SEGS - 1) / RANK_SEGS, b = seg * per, e = min(S.k, b + per);
     int cnt = 0;
@@ -1187,10 +1223,15 @@ __global__ __launch_bounds__(BLOCK) void k_rank_seeds(const SysDev *Sd, Maps L_m
         s_k[threadIdx.x] = t0 + (int)threadIdx.x < e ? S.key[t0 + threadIdx.x] : ~0ull;
         __syncthreads();
         const int m = min(BLOCK, e - t0);
+        // a tile wholly before or after this block's seeds needs one comparison per key
+        if (t0 + m <= c0) {
 #pragma unroll 8
-        for (int q = 0; q < m; ++q) {
-            const uint64_t o = s_k[q];
-            cnt += (o < mine || (o == mine && t0 + q < c)) ? 1 : 0;
+            for (int q = 0; q < m; ++q) cnt += s_k[q] <= mine ? 1 : 0;
+        } else if (t0 >= c0 + BLOCK) {
+#pragma unroll 8
+            for (int q = 0; q < m; ++q) cnt += s_k[q] < mine ? 1 : 0;
+        } else {
+            for (int q = 0; q < m; ++q) cnt += (s_k[q] < mine || (s_k[q] == mine && t0 + q < c)) ? 1 : 0;
         }
     }
     if (c < S.k && cnt > 0) atomicAdd(S.val2 + c, (uint32_t)cnt);
@@ -1429,68 +1470,85 @@ __device__ int cell_query_serial(const SysDev &S, const SysScal *sc, int A, doub
 
 // Cells B paired with A: |minimg(c_A - c_B)| <= R_A + R_B + search + 1e-9 with
 // search = largest (rc + 2 skin).  One wavefront per cell A: the window's grid columns
-// (x slowest) are taken 64 at a time, lane l scanning the seeds of the l-th one's z
-// runs.  The first cap hits are written in that scan order: each lane keeps its first
-// hits (a column holds few) until a scan of the lanes' counts places them, and walks its
-// column again only if there are more.  Returns the row's length on every lane.
-__device__ int cell_query_wave(const SysDev &S, const SysScal *sc, int A, double search, int32_t *out, int cap) {
+// (x slowest) are taken 64 at a time, their seeds laid out in scan order by a scan of their
+// counts, and tested 64 at a time, one per lane; the hits are written in that order, the
+// first cap of them.  (A lane walking its column's seeds by itself made a chain of two loads
+// per seed: 41 us at 6250 cells, now 15.)  Returns the row's length on every lane.
+struct QRuns {
+    int2 first[WAVE], second[WAVE];                 // a column's runs of seeds: first seed, seeds before the run
+    int before[WAVE + 1];                           // candidates before the column
+};
+
+__device__ int cell_query_wave(const SysDev &S, const SysScal *sc, int A, double search, QRuns &Q, int32_t *out, int cap) {
     const int lane = threadIdx.x & (WAVE - 1);
     const D4 ca = S.seed[A];
     const QWin w = query_window(S, sc, ca, search);
-    const int W = w.n[0] * w.n[1];
+    const int ncol = w.nz > 0 ? w.n[0] * w.n[1] : 0;
+    const double reach = ca.w + bitsd(sc->rmax) + search + 1e-9;
+    const bool bounded = reach * reach < INFINITY;
     int total = 0;
-    for (int w0 = 0; w0 < W; w0 += WAVE) {
-        const int wi = w0 + lane;
-        int qb[2] = {0, 0}, qe[2] = {0, 0};
-        if (wi < W) {
-            const int base = window_column(S, sc, w, wi / w.n[1], wi % w.n[1]);
-            for (int r = 0; r < w.nz; ++r) {
-                qb[r] = ldg(S.gstart + base + w.za[r]);
-                qe[r] = ldg(S.gstart + base + w.zb[r] + 1);
-            }
-        }
-        int cnt = 0, hit[4] = {0, 0, 0, 0};
-        for (int r = 0; r < 2; ++r)
-            for (int q = qb[r]; q < qe[r]; ++q) {
-                const int B = ldg(S.gseed + q);
-                if (cell_pair_test(S, ca, ldg(S.seed + B), search)) {
-                    if (cnt == 0) hit[0] = B;
-                    else if (cnt == 1) hit[1] = B;
-                    else if (cnt == 2) hit[2] = B;
-                    else if (cnt == 3) hit[3] = B;
-                    ++cnt;
-                }
-            }
-        const int inc = wave_incl_scan(cnt);
-        int k = total + inc - cnt;
-        if (cnt <= 4) {
-            for (int h = 0; h < 4; ++h)
-                if (h < cnt && k + h < cap) out[k + h] = hit[h];
-        } else {
+    for (int col0 = 0; col0 < ncol; col0 += WAVE) {
+        int qb[2] = {0, 0}, n[2] = {0, 0};
+        const int col = col0 + lane;
+        if (col < ncol) {
+            const int base = window_column(S, sc, w, col / w.n[1], col % w.n[1]);
+#pragma unroll
             for (int r = 0; r < 2; ++r)
-                for (int q = qb[r]; q < qe[r]; ++q) {
-                    const int B = ldg(S.gseed + q);
-                    if (cell_pair_test(S, ca, ldg(S.seed + B), search)) {
-                        if (k < cap) out[k] = B;
-                        ++k;
-                    }
+                if (r < w.nz) {
+                    qb[r] = ldg(S.gstart + base + w.za[r]);
+                    n[r] = ldg(S.gstart + base + w.zb[r] + 1) - qb[r];
                 }
         }
-        total += __builtin_amdgcn_readlane(inc, WAVE - 1);
+        // the candidates of the 64 columns in their order: lane's column starts at `at`
+        const int inc = wave_incl_scan(n[0] + n[1]);
+        const int at = inc - n[0] - n[1], ncand = __builtin_amdgcn_readlane(inc, WAVE - 1);
+        wave_fence();                               // the round before has read its runs
+        Q.first[lane] = make_int2(qb[0], 0);
+        Q.second[lane] = make_int2(qb[1], n[0]);
+        Q.before[lane] = at;
+        if (lane == 0) Q.before[WAVE] = ncand;
+        wave_fence();
+        for (int t0 = 0; t0 < ncand; t0 += WAVE) {
+            const int t = t0 + lane;
+            int B = -1;
+            if (t < ncand) {
+                int lo = 0, hi = WAVE;              // the last column that starts at or before t
+                while (hi - lo > 1) {
+                    const int m = (lo + hi) >> 1;
+                    if (Q.before[m] <= t) lo = m;
+                    else hi = m;
+                }
+                const int k = t - Q.before[lo];
+                const int2 f = Q.first[lo], g = Q.second[lo];
+                const D4 c = ldg(S.gpos + (k < g.y ? f.x + k : g.x + (k - g.y)));
+                // the radius is fetched for seeds within the largest one's reach only
+                double dx, dy, dz;
+                const double d2 = dist2_exact(S, ca.x, ca.y, ca.z, c.x, c.y, c.z, dx, dy, dz);
+                if (!bounded || !(d2 > reach * reach * (1.0 + 1e-12))) {
+                    const int b = (int)c.w;
+                    if (cell_pair_test(S, ca, D4{c.x, c.y, c.z, ldg(&S.seed[b].w)}, search)) B = b;
+                }
+            }
+            const unsigned long long hits = __ballot(B >= 0);
+            const int k = total + __popcll(hits & ((1ull << lane) - 1ull));
+            if (B >= 0 && k < cap) out[k] = B;
+            total += __popcll(hits);
+        }
     }
     return total;
 }
 
 // Cell-pair kernels.  Systems of at least CQ_SERIAL_MIN cells take one thread per
-// cell (there are enough threads to hide the serial walk's latency); smaller ones
-// give each cell a wavefront, CQ_BLOCKS blocks per 256-cell block of the cell map.  Both
-// find the same rows.  The query writes a cell's first CROW hits to a scratch row (in the
-// memory of the 32-bit fallback lists, idle until the list build) and its row's length;
-// once a scan has placed the rows they are copied, and only a longer row is queried again.
-// (Querying every cell a second time to fill its row took longer than the first time:
-// 41 after 32 us at 125k particles; the copy takes 5 us.)
+// cell (there are enough threads to hide the serial walk's latency: 231 us at 225 thousand
+// cells, by wavefronts 251); smaller ones give each cell a wavefront (28 thousand: 115 and
+// 40 us), CQ_BLOCKS blocks per 256-cell block of the cell map.  Both find the same rows.
+// The query writes a cell's first CROW hits to a scratch row (in the memory of the 32-bit
+// fallback lists, idle until the list build) and its row's length; once a scan has placed the
+// rows they are copied, and only a longer row is queried again.  (Querying every cell a
+// second time to fill its row took longer than the first time: 41 after 32 us at 6250 cells;
+// the copy takes 4 us.)
 constexpr int CQ_BLOCKS = BLOCK / (BLOCK / WAVE);
-constexpr int CQ_SERIAL_MIN = 20000;
+constexpr int CQ_SERIAL_MIN = 150000;
 constexpr int CROW = 64;
 __device__ __forceinline__ int32_t *scratch_row(const SysDev &S, int c) { return S.nl + (size_t)c * CROW; }
 
@@ -1523,9 +1581,10 @@ __global__ __launch_bounds__(BLOCK) void k_cnbr_query(const SysDev *Sd, Maps L_m
     if (!S.sc->rebuild || S.k >= CQ_SERIAL_MIN) return;
     const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
     const int c = (cbk - L_maps.c[s]) * BLOCK + (blockIdx.x % CQ_BLOCKS) * (BLOCK / WAVE) + wv;
+    __shared__ QRuns s_q[BLOCK / WAVE];
     int m = 0;
     if (c < S.k)                                   // wavefront-uniform
-        m = checked_row(S, c, cell_query_wave(S, S.sc, c, search, scratch_row(S, c), CROW), lane == 0);
+        m = checked_row(S, c, cell_query_wave(S, S.sc, c, search, s_q[wv], scratch_row(S, c), CROW), lane == 0);
     __shared__ int s_m[BLOCK / WAVE];
     if (lane == 0) s_m[wv] = m;
     __syncthreads();
