@@ -94,6 +94,15 @@ struct rbc_ctx {
     int32_t *d_pmaps = nullptr;       // particle-block map of the systems pruned at this step
     int32_t *pair_scratch = nullptr;  // this device's static staging of the allocation-free pair export
     const int32_t **d_lip = nullptr;
+    char *h_tab = nullptr;            // pinned copy of d_sys, d_maps and d_lip, which are one allocation
+    size_t tab_bytes = 0;
+    // memory of released systems, kept for the next ones (keep_block)
+    struct Block {
+        void *mem;
+        size_t bytes;
+    };
+    std::vector<Block> spare;
+    size_t spare_bytes = 0, held = 0, peak = 0;      // in blocks: kept, of live systems, the most of live systems
     SysScal *h_sc = nullptr;          // pinned mirror of the per-system scalars (read after a sync)
     StepStat *h_stat = nullptr, *d_stat = nullptr;   // published drift statistics: host / device view
     int par = 0;                      // the current descriptor table
@@ -340,15 +349,19 @@ rbc_status refresh_tables(rbc_ctx *h) {
     h->nsys = std::max(top, 1);
     // frozen slots keep their memory but get an empty descriptor: no kernel touches them
     const int ns = h->nsys;
-    std::vector<SysDev> tab(ns);
-    std::vector<const int32_t *> lips(ns, nullptr);
-    std::vector<int32_t> maps(6 * (ns + 1), 0);
+    HIPCHK(hipStreamSynchronize(h->st));   // the pinned copy may still be on its way
+    auto pinned = [&](const void *dev) { return h->h_tab + ((const char *)dev - (const char *)h->d_sys); };
+    SysDev *tab = (SysDev *)pinned(h->d_sys + (size_t)h->par * h->max_slots);
+    SysDev *other = (SysDev *)pinned(h->d_sys + (size_t)(h->par ^ 1) * h->max_slots);
+    const int32_t **lips = (const int32_t **)pinned(h->d_lip);
     int32_t kmin = INT32_MAX, kmax = 0, gmax = 0;
-    int32_t *mp = maps.data(), *mc = mp + (ns + 1), *mts = mc + (ns + 1);
+    int32_t *mp = (int32_t *)pinned(h->d_maps), *mc = mp + (ns + 1), *mts = mc + (ns + 1);
     int32_t *msc = mts + (ns + 1), *msg = msc + (ns + 1), *mf = msg + (ns + 1);
+    for (int32_t *m : {mp, mc, mts, msc, msg, mf}) m[0] = 0;
     for (int s = 0; s < ns; ++s) {
         HostSys &hs = h->sys[s];
         SysDev d{};
+        lips[s] = nullptr;
         if (runs(hs)) {
             d = hs.dev;
             lips[s] = hs.lip;
@@ -356,6 +369,8 @@ rbc_status refresh_tables(rbc_ctx *h) {
         d.sc = h->d_sc + s;
         d.hstat = h->d_stat + (size_t)s * STAT_RING;
         tab[s] = d;
+        other[s] = d;
+        swap_drift(other[s]);
         const bool on = runs(hs);
         const int64_t n = on ? hs.n : 0;
         const int32_t k = on ? hs.k : 0;
@@ -367,14 +382,7 @@ rbc_status refresh_tables(rbc_ctx *h) {
         msg[s + 1] = msg[s] + (on ? (hs.gcap + SCAN_TILE - 1) / SCAN_TILE : 0);
         mf[s + 1] = mf[s] + (mp[s + 1] - mp[s]) * (d.split ? 4 : 1);
     }
-    std::vector<SysDev> other = tab;
-    for (SysDev &d : other) swap_drift(d);
-    SysDev *cur = h->d_sys + (size_t)h->par * h->max_slots, *nxt = h->d_sys + (size_t)(h->par ^ 1) * h->max_slots;
-    HIPCHK(hipMemcpyAsync(cur, tab.data(), sizeof(SysDev) * ns, hipMemcpyHostToDevice, h->st));
-    HIPCHK(hipMemcpyAsync(nxt, other.data(), sizeof(SysDev) * ns, hipMemcpyHostToDevice, h->st));
-    HIPCHK(hipMemcpyAsync(h->d_maps, maps.data(), sizeof(int32_t) * maps.size(), hipMemcpyHostToDevice, h->st));
-    HIPCHK(hipMemcpyAsync(h->d_lip, lips.data(), sizeof(void *) * ns, hipMemcpyHostToDevice, h->st));
-    HIPCHK(hipStreamSynchronize(h->st));   // host staging vectors go out of scope
+    HIPCHK(hipMemcpyAsync(h->d_sys, h->h_tab, h->tab_bytes, hipMemcpyHostToDevice, h->st));
     h->table_version++;
     LaunchCtx &L = h->L;
     use_table(h, L, h->par);
@@ -905,7 +913,67 @@ size_t footprint(const rbc_ctx *h, int64_t n, int64_t nlip, int64_t nbond) {
     return layout(tmp, nullptr);
 }
 
-void release(rbc_ctx *h, int32_t slot);
+void release(rbc_ctx *h, int32_t slot, bool refresh = true);
+
+// Systems come and go (frames of one system loaded in turn, requests served in bursts), and
+// an allocation and its release take 350 us of the host's time for a 125k-particle system,
+// most of it the release.  The memory of a released system is kept for the next one of the
+// same size: the driver hands memory out in units of BLOCK_UNIT, so a block is used again by
+// systems whose footprint rounds to the same number of units, and nothing is wasted in it.
+// The handle never holds more in all than its live systems held at one time, nor more than
+// SPARE_MAX beside them, nor more than the admission budget; rbc_destroy returns it, and
+// rbc_set_system without particles.  A block is kept only after the handle's stream, which
+// alone uses it, is idle.
+constexpr size_t BLOCK_UNIT = size_t(2) << 20;
+constexpr size_t SPARE_MAX = size_t(16) << 30;
+size_t block_bytes(size_t bytes) { return (bytes + BLOCK_UNIT - 1) / BLOCK_UNIT * BLOCK_UNIT; }
+
+// Free kept blocks, the oldest first, until `room` bytes of them remain at most.
+void trim_spare(rbc_ctx *h, size_t room) {
+    size_t q = 0;
+    for (; q < h->spare.size() && h->spare_bytes > room; ++q) {
+        hipFree(h->spare[q].mem);
+        h->spare_bytes -= h->spare[q].bytes;
+    }
+    h->spare.erase(h->spare.begin(), h->spare.begin() + (ptrdiff_t)q);
+}
+
+size_t spare_room(const rbc_ctx *h) {
+    size_t room = std::min(SPARE_MAX, h->peak > h->held ? h->peak - h->held : 0);
+    if (h->budget > 0) room = std::min(room, (size_t)std::max<int64_t>(0, h->budget - (int64_t)h->held));
+    return room;
+}
+
+// Memory for a system of `bytes`: a kept block of its size, or a new one (nullptr: none left).
+void *take_block(rbc_ctx *h, size_t bytes) {
+    const size_t want = block_bytes(bytes);
+    void *mem = nullptr;
+    for (size_t q = h->spare.size(); q-- > 0 && !mem;)
+        if (h->spare[q].bytes == want) {
+            mem = h->spare[q].mem;
+            h->spare_bytes -= want;
+            h->spare.erase(h->spare.begin() + (ptrdiff_t)q);
+        }
+    h->held += want;
+    h->peak = std::max(h->peak, h->held);
+    if (mem) return mem;
+    trim_spare(h, spare_room(h));
+    if (hipMalloc(&mem, want) == hipSuccess) return mem;
+    hipGetLastError();
+    trim_spare(h, 0);
+    if (hipMalloc(&mem, want) == hipSuccess) return mem;
+    hipGetLastError();
+    h->held -= want;
+    return nullptr;
+}
+
+void keep_block(rbc_ctx *h, void *mem, size_t bytes) {
+    const size_t want = block_bytes(bytes);
+    h->held -= want;
+    h->spare.push_back({mem, want});
+    h->spare_bytes += want;
+    trim_spare(h, spare_room(h));
+}
 
 // Everything of an admission but the cell build: validation, allocation, uploads and
 // the packed state.  The slot is live and pending.
@@ -936,38 +1004,45 @@ rbc_status stage(rbc_ctx *h, int32_t slot, int64_t n, const double *x, const dou
         HIPCHK(hipMemcpy(hb.data(), bonds, sizeof(int32_t) * 2 * nbond, hipMemcpyDeviceToHost));
         HIPCHK(hipMemcpy(hr.data(), r0, sizeof(double) * nbond, hipMemcpyDeviceToHost));
     }
-    std::vector<int32_t> lip;
+    // the lipids' ids, then the others'
+    std::vector<int32_t> lip(n);
+    int64_t nlip_real = 0, nbad = 0;
     for (int64_t i = 0; i < n; ++i) {
-        if (ht[i] < 0 || ht[i] > 2) return fail(h, RBC_ERR_INVALID_ARG, "particle type must be 0, 1 or 2");
-        if (ht[i] == 0) lip.push_back((int32_t)i);
+        lip[nlip_real] = (int32_t)i;
+        nlip_real += ht[i] == 0;
+        nbad += (uint32_t)ht[i] > 2u;
     }
-    const int64_t nlip_real = (int64_t)lip.size();
-    if (lip.empty())
-        for (int64_t i = 0; i < n; ++i) lip.push_back((int32_t)i);   // no lipids: seed from every particle
+    if (nbad > 0) return fail(h, RBC_ERR_INVALID_ARG, "particle type must be 0, 1 or 2");
+    if (nlip_real == 0)
+        for (int64_t i = 0; i < n; ++i) lip[i] = (int32_t)i;          // no lipids: seed from every particle
     for (int64_t e = 0; e < nbond; ++e)
         if (hb[2 * e] < 0 || hb[2 * e] >= n || hb[2 * e + 1] < 0 || hb[2 * e + 1] >= n || hb[2 * e] == hb[2 * e + 1])
             return fail(h, RBC_ERR_INVALID_ARG, "bond index out of range");
     HostSys fresh;
     size_system(h, fresh, n, nlip_real, nbond);
-    if (fresh.nsrcp > 0)                    // the protein set's seeds come from protein beads
+    if (fresh.nsrcp > 0) {                  // the protein set's seeds come from protein beads
+        int64_t at = nlip_real;
         for (int64_t i = 0; i < n; ++i)
-            if (ht[i] != 0) lip.push_back((int32_t)i);
+            if (ht[i] != 0) lip[at++] = (int32_t)i;
+    }
     const size_t bytes = layout(fresh, nullptr);
     if (h->budget > 0 && h->used + (int64_t)bytes > h->budget)
         return fail(h, RBC_ERR_CAPACITY, "footprint exceeds the remaining device-memory budget");
-    void *mem = nullptr;
-    if (hipMalloc(&mem, bytes) != hipSuccess) return fail(h, RBC_ERR_OUT_OF_MEMORY, "device allocation failed");
-    if (hipMemset(mem, 0, bytes) != hipSuccess) {
-        hipFree(mem);
-        return fail(h, RBC_ERR_HIP, "hipMemset of a new system failed");
-    }
-    // from here on every error path must free the allocation: the slot does not own it yet
-    struct FreeOnError {
+    void *mem = take_block(h, bytes);
+    if (!mem) return fail(h, RBC_ERR_OUT_OF_MEMORY, "device allocation failed");
+    // from here on every error path must give the allocation back: the slot does not own it yet
+    struct ReturnOnError {
+        rbc_ctx *h;
         void *p;
-        ~FreeOnError() {
-            if (p) hipFree(p);
+        size_t bytes;
+        ~ReturnOnError() {
+            if (!p) return;
+            hipStreamSynchronize(h->st);
+            keep_block(h, p, bytes);
         }
-    } guard{mem};
+    } guard{h, mem, bytes};
+    if (hipMemsetAsync(mem, 0, bytes, h->st) != hipSuccess)
+        return fail(h, RBC_ERR_HIP, "hipMemset of a new system failed");
     fresh.mem = mem;
     fresh.bytes = bytes;
     layout(fresh, (char *)mem);
@@ -988,29 +1063,28 @@ rbc_status stage(rbc_ctx *h, int32_t slot, int64_t n, const double *x, const dou
     d.cnbr_cap = fresh.cnbr_cap;
     d.ntile_s = fresh.ntile_s;
     for (int a = 0; a < 3; ++a) { d.per[a] = fresh.per[a]; d.box[a] = fresh.box[a]; }
-    // bond CSR by caller id
-    std::vector<int32_t> bst(n + 1, 0), bpa(2 * nbond);
+    // bond CSR by caller id (without bonds, the zeros that the memory holds)
+    std::vector<int32_t> bst, bpa(2 * nbond);
     std::vector<double> br(2 * nbond);
-    for (int64_t e = 0; e < nbond; ++e) { bst[hb[2 * e] + 1]++; bst[hb[2 * e + 1] + 1]++; }
-    for (int64_t i = 0; i < n; ++i) bst[i + 1] += bst[i];
-    std::vector<int32_t> fill(n, 0);
-    for (int64_t e = 0; e < nbond; ++e) {
-        int32_t a = hb[2 * e], b = hb[2 * e + 1];
-        int32_t pa = bst[a] + fill[a]++, pb = bst[b] + fill[b]++;
-        bpa[pa] = b; br[pa] = hr[e];
-        bpa[pb] = a; br[pb] = hr[e];
-    }
-    HIPCHK(hipMemcpy(d.bstart, bst.data(), sizeof(int32_t) * (n + 1), hipMemcpyHostToDevice));
     if (nbond > 0) {
-        HIPCHK(hipMemcpy(d.bpart, bpa.data(), sizeof(int32_t) * 2 * nbond, hipMemcpyHostToDevice));
-        HIPCHK(hipMemcpy(d.br0, br.data(), sizeof(double) * 2 * nbond, hipMemcpyHostToDevice));
+        bst.assign(n + 2, 0);              // shifted by one: the fill advances each start to the next one's
+        for (int64_t e = 0; e < nbond; ++e) { bst[hb[2 * e] + 2]++; bst[hb[2 * e + 1] + 2]++; }
+        for (int64_t i = 0; i < n; ++i) bst[i + 2] += bst[i + 1];
+        for (int64_t e = 0; e < nbond; ++e) {
+            const int32_t a = hb[2 * e], b = hb[2 * e + 1];
+            const int32_t pa = bst[a + 1]++, pb = bst[b + 1]++;
+            bpa[pa] = b; br[pa] = hr[e];
+            bpa[pb] = a; br[pb] = hr[e];
+        }
+        HIPCHK(hipMemcpyAsync(d.bstart, bst.data(), sizeof(int32_t) * (n + 1), hipMemcpyHostToDevice, h->st));
+        HIPCHK(hipMemcpyAsync(d.bpart, bpa.data(), sizeof(int32_t) * 2 * nbond, hipMemcpyHostToDevice, h->st));
+        HIPCHK(hipMemcpyAsync(d.br0, br.data(), sizeof(double) * 2 * nbond, hipMemcpyHostToDevice, h->st));
     }
-    HIPCHK(hipMemcpy(fresh.lip, lip.data(), sizeof(int32_t) * lip.size(), hipMemcpyHostToDevice));
-    SysScal zero{};
-    HIPCHK(hipMemcpy(h->d_sc + slot, &zero, sizeof(SysScal), hipMemcpyHostToDevice));
+    HIPCHK(hipMemcpyAsync(fresh.lip, lip.data(), sizeof(int32_t) * (fresh.nlip + fresh.nsrcp), hipMemcpyHostToDevice, h->st));
+    HIPCHK(hipMemsetAsync(h->d_sc + slot, 0, sizeof(SysScal), h->st));
     std::memset(h->h_stat + (size_t)slot * STAT_RING, 0, sizeof(StepStat) * STAT_RING);
     hs = fresh;
-    guard.p = nullptr;                     // the slot owns the allocation now (release() frees it)
+    guard.p = nullptr;                     // the slot owns the allocation now (release() takes it back)
     h->vol_fresh = false;
     h->used += (int64_t)bytes;
     hs.pending = true;
@@ -1060,7 +1134,7 @@ rbc_status build_pending(rbc_ctx *h, const std::vector<int> &which, std::vector<
     }
     for (int s : failed) {
         release(h, s);
-        if (h->d_sc) hipMemset(h->d_sc + s, 0, sizeof(SysScal));
+        hipMemsetAsync(h->d_sc + s, 0, sizeof(SysScal), h->st);
     }
     if (first != RBC_OK) h->err = why;
     return first;
@@ -1075,15 +1149,15 @@ rbc_status admit(rbc_ctx *h, int32_t slot, int64_t n, const double *x, const dou
     return build_pending(h, std::vector<int>{slot}, failed);
 }
 
-void release(rbc_ctx *h, int32_t slot) {
+void release(rbc_ctx *h, int32_t slot, bool refresh) {
     HostSys &hs = h->sys[slot];
     if (!hs.live) return;
     hipStreamSynchronize(h->st);
-    if (hs.mem) hipFree(hs.mem);
+    if (hs.mem) keep_block(h, hs.mem, hs.bytes);
     if (hs.pairs_mem) hipFree(hs.pairs_mem);
     h->used -= (int64_t)hs.bytes;
     hs = HostSys{};
-    refresh_tables(h);
+    if (refresh) refresh_tables(h);
 }
 
 rbc_status create(const rbc_params *params, void *stream, int32_t max_slots, int64_t budget, bool ensemble,
@@ -1106,20 +1180,26 @@ rbc_status create(const rbc_params *params, void *stream, int32_t max_slots, int
     h->sys.resize(max_slots);
     h->user = (hipStream_t)stream;
     hipGetDevice(&h->device);
+    const size_t lip_at = 2 * sizeof(SysDev) * max_slots, map_at = lip_at + sizeof(void *) * max_slots;
+    h->tab_bytes = map_at + sizeof(int32_t) * 6 * (max_slots + 1);
     bool ok = hipStreamCreateWithFlags(&h->st, hipStreamNonBlocking) == hipSuccess &&
               hipEventCreateWithFlags(&h->ev_in, hipEventDisableTiming) == hipSuccess &&
               hipEventCreateWithFlags(&h->ev_out, hipEventDisableTiming) == hipSuccess &&
-              hipMalloc(&h->d_sys, 2 * sizeof(SysDev) * max_slots) == hipSuccess &&
+              hipMalloc((void **)&h->d_sys, h->tab_bytes) == hipSuccess &&
+              hipHostMalloc((void **)&h->h_tab, h->tab_bytes, hipHostMallocDefault) == hipSuccess &&
               hipMalloc(&h->d_sc, sizeof(SysScal) * max_slots) == hipSuccess &&
-              hipMalloc(&h->d_maps, sizeof(int32_t) * 6 * (max_slots + 1)) == hipSuccess &&
               hipMalloc(&h->d_umaps, sizeof(int32_t) * 5 * (MAX_SLOTS + 1)) == hipSuccess &&
               hipMalloc(&h->d_pmaps, sizeof(int32_t) * (MAX_SLOTS + 1)) == hipSuccess &&
-              hipMalloc((void **)&h->d_lip, sizeof(void *) * max_slots) == hipSuccess &&
               hipHostMalloc((void **)&h->h_sc, sizeof(SysScal) * MAX_SLOTS, hipHostMallocDefault) == hipSuccess &&
               hipHostMalloc((void **)&h->h_stat, sizeof(StepStat) * MAX_SLOTS * STAT_RING,
                             hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess &&
               hipHostGetDevicePointer((void **)&h->d_stat, h->h_stat, 0) == hipSuccess;
-    if (ok) std::memset(h->h_stat, 0, sizeof(StepStat) * MAX_SLOTS * STAT_RING);
+    if (ok) {
+        std::memset(h->h_stat, 0, sizeof(StepStat) * MAX_SLOTS * STAT_RING);
+        std::memset(h->h_tab, 0, h->tab_bytes);
+        h->d_lip = (const int32_t **)((char *)h->d_sys + lip_at);
+        h->d_maps = (int32_t *)((char *)h->d_sys + map_at);
+    }
     if (ok) ok = hipEventCreate(&h->ev_call0) == hipSuccess && hipEventCreate(&h->ev_prev_end) == hipSuccess &&
                  hipEventCreate(&h->ev_prev_end_last) == hipSuccess;
     if (ok) ok = hipMemset(h->d_sc, 0, sizeof(SysScal) * max_slots) == hipSuccess;
@@ -1176,6 +1256,7 @@ rbc_status rbc_destroy(rbc_handle h) {
         if (h->sys[s].mem) hipFree(h->sys[s].mem);
         if (h->sys[s].pairs_mem) hipFree(h->sys[s].pairs_mem);
     }
+    trim_spare(h, 0);
     for (auto e : h->tb) hipEventDestroy(e);
     for (auto e : h->te) hipEventDestroy(e);
     for (auto e : h->nb) hipEventDestroy(e);
@@ -1185,10 +1266,9 @@ rbc_status rbc_destroy(rbc_handle h) {
         if (e) hipEventDestroy(e);
     if (h->d_sys) hipFree(h->d_sys);
     if (h->d_sc) hipFree(h->d_sc);
-    if (h->d_maps) hipFree(h->d_maps);
     if (h->d_umaps) hipFree(h->d_umaps);
     if (h->d_pmaps) hipFree(h->d_pmaps);
-    if (h->d_lip) hipFree(h->d_lip);
+    if (h->h_tab) hipHostFree(h->h_tab);
     if (h->h_sc) hipHostFree(h->h_sc);
     if (h->h_stat) hipHostFree(h->h_stat);
     if (h->ev_in) hipEventDestroy(h->ev_in);
@@ -1203,11 +1283,14 @@ rbc_status rbc_set_system(rbc_handle h, int64_t n, const double *x, const double
                           const double *box, const int32_t *periodic) {
     if (!h) return RBC_ERR_INVALID_ARG;
     if (h->ensemble) return fail(h, RBC_ERR_INVALID_ARG, "use rbc_ensemble_admit on an ensemble context");
-    release(h, 0);
+    release(h, 0, false);
     h->forces_valid = false;
     h->sticky = RBC_OK;
-    if (n == 0) return RBC_OK;
-    return admit(h, 0, n, x, nrm, type, v, w, nbond, bonds, r0, box, periodic);
+    rbc_status r = RBC_OK;
+    if (n == 0) trim_spare(h, 0);
+    else r = admit(h, 0, n, x, nrm, type, v, w, nbond, bonds, r0, box, periodic);
+    if (!h->sys[0].live) refresh_tables(h);       // nothing took the released system's place
+    return r;
 }
 
 rbc_status rbc_update_cells(rbc_handle h, int32_t lloyd_iters) {
