@@ -1743,7 +1743,7 @@ __device__ void emit_pruned(const SysDev &S, int chunk, int rows, unsigned pm0, 
             unsigned k = (q & 1) ? e[q >> 1] >> 16 : e[q >> 1] & 0xffffu;
             k = (pb >> q) & 1u ? k : 0u;
             const uint2 b = s_bp[k >> 5];
-            local[q] = b.y + __popc(b.x & ((1u << (k & 31)) - 1u));
+            local[q] = il_entry(b.y + __popc(b.x & ((1u << (k & 31)) - 1u)));
         }
 #pragma unroll
         for (int q = 0; q < 8; ++q) {

@@ -149,38 +149,52 @@ __device__ __forceinline__ T wca_pair(const DevParams &P, T dx, T dy, T dz, T &f
     return U;
 }
 
+// sqrt(r2) and its reciprocal to within an ulp, from the hardware's approximate
+// reciprocal square root by two Goldschmidt steps and a correction of each (10 fused
+// multiply-adds; the library's square root and division take about 35 instructions
+// with their scaling for subnormal and huge arguments, which squared separations are not).
+__device__ __forceinline__ void sqrt_rsqrt(double r2, double &r, double &rinv) {
+    const double y = __builtin_amdgcn_rsq(r2);
+    double g = r2 * y, h = 0.5 * y;
+    const double e = fma(-h, g, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+    r = fma(fma(-g, g, r2), h, g);
+    rinv = 2.0 * h;
+    rinv = fma(fma(-r, rinv, 1.0), rinv, rinv);
+}
+
 // ------------------------------------------------------------------ integrator pieces
 
-// Free linear-rotor drift: n rotated about omega by |omega| dt (Rodrigues), then
-// renormalised.
+// Free linear-rotor drift: n rotated about omega by the angle a = |omega| dt (Rodrigues), then
+// renormalised:  n + S omega x n + C (omega (omega.n) - |omega|^2 n)  with S = sin a / |omega|
+// and C = (1 - cos a) / |omega|^2, whose series need neither |omega| nor a division.
 __device__ __forceinline__ D4 rotor_drift(D4 n, const D4 &w, double dt) {
 #pragma clang fp contract(off)
-    const double wn = sqrt(w.x * w.x + w.y * w.y + w.z * w.z);
-    if (wn > 0.0) {
-        const double iw = 1.0 / wn;
-        const double kx = w.x * iw, ky = w.y * iw, kz = w.z * iw;
-        const double a = wn * dt;
-        double sn, cs;
-        if (a < 0.05) {
+    const double w2 = fma(w.z, w.z, fma(w.y, w.y, w.x * w.x));
+    if (w2 > 0.0) {
+        const double a2 = w2 * (dt * dt);
+        double S, C;
+        if (a2 < 0.0025) {
             // Taylor series; the first omitted terms are below 1e-18 relative here
-            const double a2 = a * a;
-            sn = a * (1.0 - a2 * (1.0 / 6.0) * (1.0 - a2 * (1.0 / 20.0) * (1.0 - a2 * (1.0 / 42.0) *
-                 (1.0 - a2 * (1.0 / 72.0)))));
-            cs = 1.0 - a2 * 0.5 * (1.0 - a2 * (1.0 / 12.0) * (1.0 - a2 * (1.0 / 30.0) * (1.0 - a2 * (1.0 / 56.0) *
-                 (1.0 - a2 * (1.0 / 90.0)))));
+            S = dt * fma(a2, fma(a2, fma(a2, fma(a2, 1.0 / 362880.0, -1.0 / 5040.0), 1.0 / 120.0), -1.0 / 6.0), 1.0);
+            C = (dt * dt) * fma(a2, fma(a2, fma(a2, fma(a2, 1.0 / 3628800.0, -1.0 / 40320.0), 1.0 / 720.0), -1.0 / 24.0), 0.5);
         } else {
-            sincos(a, &sn, &cs);
+            const double wn = sqrt(w2);
+            double sn, cs;
+            sincos(wn * dt, &sn, &cs);
+            S = sn / wn;
+            C = (1.0 - cs) / w2;
         }
-        const double kn = kx * n.x + ky * n.y + kz * n.z;
-        const double cx = ky * n.z - kz * n.y, cy = kz * n.x - kx * n.z, cz = kx * n.y - ky * n.x;
-        const double ox = n.x * cs + cx * sn + kx * kn * (1.0 - cs);
-        const double oy = n.y * cs + cy * sn + ky * kn * (1.0 - cs);
-        const double oz = n.z * cs + cz * sn + kz * kn * (1.0 - cs);
-        n.x = ox; n.y = oy; n.z = oz;
+        const double kn = fma(w.z, n.z, fma(w.y, n.y, w.x * n.x));
+        const double cx = fma(w.y, n.z, -(w.z * n.y)), cy = fma(w.z, n.x, -(w.x * n.z)), cz = fma(w.x, n.y, -(w.y * n.x));
+        n = D4{fma(S, cx, fma(C, fma(w.x, kn, -(w2 * n.x)), n.x)), fma(S, cy, fma(C, fma(w.y, kn, -(w2 * n.y)), n.y)),
+               fma(S, cz, fma(C, fma(w.z, kn, -(w2 * n.z)), n.z)), n.w};
     }
-    const double nn = sqrt(n.x * n.x + n.y * n.y + n.z * n.z);
-    if (nn > 0.0) {
-        const double in = 1.0 / nn;
+    const double nn2 = fma(n.z, n.z, fma(n.y, n.y, n.x * n.x));
+    if (nn2 > 0.0) {
+        double r, in;
+        sqrt_rsqrt(nn2, r, in);
         n.x *= in; n.y *= in; n.z *= in;
     }
     return n;
@@ -507,21 +521,6 @@ __device__ __forceinline__ float lipid_coef(const DevParams &P, float dx, float 
     return U;
 }
 
-// sqrt(r2) and its reciprocal to within an ulp, from the hardware's approximate
-// reciprocal square root by two Goldschmidt steps and a correction of each (10 fused
-// multiply-adds; the library's square root and division take about 35 instructions
-// with their scaling for subnormal and huge arguments, which squared separations are not).
-__device__ __forceinline__ void sqrt_rsqrt(double r2, double &r, double &rinv) {
-    const double y = __builtin_amdgcn_rsq(r2);
-    double g = r2 * y, h = 0.5 * y;
-    const double e = fma(-h, g, 0.5);
-    g = fma(g, e, g);
-    h = fma(h, e, h);
-    r = fma(fma(-g, g, r2), h, g);
-    rinv = 2.0 * h;
-    rinv = fma(fma(-r, rinv, 1.0), rinv, rinv);
-}
-
 // The lipid-lipid law of the FP64 step kernel in the same coefficient form,
 //   force on i  = -(A e + bi n_i + bj n_j),    g_i = cn n_j + ce e,
 // for a pair in range.  Both radial branches are evaluated and selected: a wavefront
@@ -603,12 +602,15 @@ __device__ __forceinline__ double lipid_coef64(const DevParams &P, double dx, do
 template <int MIXED>
 struct Stage {
     static constexpr int lds = MIXED ? 640 : 800;
-    static constexpr int ext = MIXED ? lds + 2 : lds;   // LDS entries (mixed: the sentinel and one pad)
+    static constexpr int ext = MIXED ? lds + 1 : lds;   // LDS entries (mixed: the sentinel)
     static constexpr int bytes = MIXED ? ext * (3 * 8 + 16) : lds * (6 * 8 + 1);
 };
-static_assert(Stage<1>::lds < SMAX && (Stage<1>::ext * 24) % 16 == 0, "mixed stage layout");
+static_assert(Stage<1>::lds < SMAX, "lists reach beyond the LDS part");
 constexpr double SENTINEL = 1.0e8;    // sigma: the padding entry's coordinates (finite FP32 squares)
 constexpr int PAD_TYPE = 3;           // the padding entry's type (a periodic wrap may bring it into range)
+struct alignas(16) D2 {
+    double x, y;
+};
 
 // One workgroup per 256 consecutive cell-sorted particles.  The block's pruned
 // partners (its stage) are read once from HBM into LDS; lane i then walks column i of
@@ -632,12 +634,14 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
     constexpr int SL = Stage<MIXED>::lds;
     constexpr int SX = Stage<MIXED>::ext;
     __shared__ __align__(16) unsigned char s_raw[Stage<MIXED>::bytes];
-    double *s_x = reinterpret_cast<double *>(s_raw);
-    double *s_y = s_x + SX;
-    double *s_z = s_y + SX;
-    F4 *s_n4 = reinterpret_cast<F4 *>(s_z + SX);                  // mixed
-    double *s_nx = s_z + SL, *s_ny = s_nx + SL, *s_nz = s_ny + SL;        // FP64
-    unsigned char *s_t = reinterpret_cast<unsigned char *>(s_nz + SL);    // FP64
+    // mixed: records of x, y; of orientation and type; z
+    D2 *s_xy = reinterpret_cast<D2 *>(s_raw);
+    F4 *s_n4 = reinterpret_cast<F4 *>(s_xy + SX);
+    double *s_zm = reinterpret_cast<double *>(s_n4 + SX);
+    // FP64
+    double *s_x = reinterpret_cast<double *>(s_raw), *s_y = s_x + SX, *s_z = s_y + SX;
+    double *s_nx = s_z + SL, *s_ny = s_nx + SL, *s_nz = s_ny + SL;
+    unsigned char *s_t = reinterpret_cast<unsigned char *>(s_nz + SL);
     const int nstat = KICK ? L_maps.nsys : 0;
     if (KICK && (int)blockIdx.x < nstat) {
         const SysDev &S = Sd[blockIdx.x];
@@ -674,6 +678,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
         if constexpr (MIXED) ni32 = ldg(S.ori32 + i);
         else ni = ld3(S.ori + i);
     }
+    // FP32 orientations carry the type's bits; FAST rows take 0 for a lipid and 1 for a protein
+    // (and NaN, which passes no test, for the sentinel)
+    auto with_kind = [](F4 n) {
+        if constexpr (FAST) n.w = __float_as_int(n.w) == 0 ? 0.0f : 1.0f;
+        return n;
+    };
     // the stage: every thread's (at most three) slots first, then their records
     constexpr int SPT = (SL + BLOCK - 1) / BLOCK;
     for (int q0 = tid; q0 < nlds; q0 += SPT * BLOCK) {
@@ -688,12 +698,14 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
             const int q = q0 + k * BLOCK;
             if (slot[k] < 0) break;
             const V3 p = ldg(S.pos + slot[k]);
-            s_x[q] = p.x;
-            s_y[q] = p.y;
-            s_z[q] = p.z;
             if constexpr (MIXED) {
-                s_n4[q] = ldg(S.ori32 + slot[k]);       // w: the type's bits
+                s_xy[q] = D2{p.x, p.y};
+                s_zm[q] = p.z;
+                s_n4[q] = with_kind(ldg(S.ori32 + slot[k]));
             } else {
+                s_x[q] = p.x;
+                s_y[q] = p.y;
+                s_z[q] = p.z;
                 const V3 o = S.ori[slot[k]];
                 s_nx[q] = o.x;
                 s_ny[q] = o.y;
@@ -703,10 +715,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
         }
     }
     if (MIXED && tid == 0) {
-        s_x[SL] = SENTINEL;
-        s_y[SL] = SENTINEL;
-        s_z[SL] = SENTINEL;
-        s_n4[SL] = F4{0.0f, 0.0f, 1.0f, __int_as_float(PAD_TYPE)};
+        s_xy[SL] = D2{SENTINEL, SENTINEL};
+        s_zm[SL] = SENTINEL;
+        s_n4[SL] = F4{0.0f, 0.0f, 1.0f, FAST ? __builtin_nanf("") : __int_as_float(PAD_TYPE)};
     }
     __syncthreads();
     if (chunk >= S.nchunk) return;
@@ -744,32 +755,34 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
         };
         const float loA = row_of(P.rc2lo, 0), loB = row_of(P.rc2lo, 1), loC = row_of(P.rc2lo, 2);
         const float hiA = row_of(P.rc2hi, 0), hiB = row_of(P.rc2hi, 1), hiC = row_of(P.rc2hi, 2);
+        auto own = [&](const float (&m)[3]) { return ti == 0 ? m[0] : (ti == 1 ? m[1] : m[2]); };
+        const float cutd = own(P.cutd), cutlo = own(P.cutlo), cuthi = own(P.cuthi);
+        // wavefront masks: the lanes with a particle, and those with a lipid
+        const unsigned long long lanes = __ballot(valid), lipids = __ballot(ti == 0);
         struct Rec {
             double x, y, z;
-            float nx, ny, nz;
-            int t;
+            float nx, ny, nz, w;
         };
-        auto fetch = [&](int e) {
+        auto fetch = [&](unsigned e) {                  // e: a list entry (16 times the stage index)
             Rec c;
             if constexpr (PARTIAL) {
-                if (e >= nlds && e < scnt) {            // stage entry beyond the LDS part
-                    const int slot = ldg(S.istage + (size_t)lb * SSTRIDE + e);
+                const int k = (int)(e >> 4);
+                if (k >= nlds && k < scnt) {            // stage entry beyond the LDS part
+                    const int slot = ldg(S.istage + (size_t)lb * SSTRIDE + k);
                     const V3 p = ldg(S.pos + slot);
-                    const F4 o = ldg(S.ori32 + slot);
+                    const F4 o = with_kind(ldg(S.ori32 + slot));
                     c.x = p.x; c.y = p.y; c.z = p.z;
-                    c.nx = o.x; c.ny = o.y; c.nz = o.z;
-                    c.t = __float_as_int(o.w);
+                    c.nx = o.x; c.ny = o.y; c.nz = o.z; c.w = o.w;
                     return c;
                 }
             }
             // padding -> the sentinel (every entry below the LDS part when not PARTIAL)
-            const int q = PARTIAL ? (e < nlds ? e : SL) : min(e, SL);
-            c.x = s_x[q];
-            c.y = s_y[q];
-            c.z = s_z[q];
-            const F4 nj = s_n4[q];
-            c.nx = nj.x; c.ny = nj.y; c.nz = nj.z;
-            c.t = __float_as_int(nj.w);
+            const unsigned q = PARTIAL ? (e < 16u * (unsigned)nlds ? e : 16u * SL) : min(e, 16u * SL);
+            const D2 xy = *reinterpret_cast<const D2 *>(s_raw + q);
+            const F4 nj = *reinterpret_cast<const F4 *>(s_raw + 16 * SX + q);
+            c.x = xy.x; c.y = xy.y;
+            c.z = *reinterpret_cast<const double *>(s_raw + 32 * SX + (q >> 1));
+            c.nx = nj.x; c.ny = nj.y; c.nz = nj.z; c.w = nj.w;
             return c;
         };
         // Software pipeline: the list entries of the next trip are loaded from global
@@ -779,14 +792,14 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
         unsigned en = ntrip > 0 ? ldg(col) : 0xffffffffu;    // a pair of rows
         for (int it = 0; it < ntrip; ++it) {
             Rec c[UNR];
-            c[0] = fetch((int)(en & 0xffffu));
-            c[1] = fetch((int)(en >> 16));
+            c[0] = fetch(en & 0xffffu);
+            c[1] = fetch(en >> 16);
             en = ldg(col + (size_t)(it + 1) * tstride * CHUNK);
             // separations and the neighbour test of every row of the trip
             double dx[UNR], dy[UNR], dz[UNR];
             float fdx[UNR], fdy[UNR], fdz[UNR], r2[UNR];
-            bool in[UNR], band[UNR], lip[UNR];
-            bool anyband = false;
+            // (wavefront masks: scalar registers and instructions beside the vector ones)
+            unsigned long long in[UNR], band[UNR], lip[UNR];
             for (int q = 0; q < UNR; ++q) {
                 dx[q] = pi.x - c[q].x;
                 dy[q] = pi.y - c[q].y;
@@ -800,34 +813,41 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
                 fdy[q] = (float)dy[q];
                 fdz[q] = (float)dz[q];
                 r2[q] = fdx[q] * fdx[q] + fdy[q] * fdy[q] + fdz[q] * fdz[q];
-                const int tj = c[q].t;
-                const float lo = FAST ? (tj == 0 ? loA : loB) : sel_cutf(tj, loA, loB, loC);
-                const float hi = FAST ? (tj == 0 ? hiA : hiB) : sel_cutf(tj, hiA, hiB, hiC);
-                in[q] = r2[q] < lo;
-                band[q] = !in[q] && r2[q] < hi;
-                if constexpr (PER) {            // the wrapped sentinel may land anywhere
-                    in[q] = in[q] && tj != PAD_TYPE;
-                    band[q] = band[q] && tj != PAD_TYPE;
+                if constexpr (FAST) {
+                    const float r2s = fmaf(c[q].w, cutd, r2[q]);
+                    in[q] = __ballot(r2s < cutlo);
+                    band[q] = in[q] ^ __ballot(r2s < cuthi);
+                    lip[q] = __ballot(c[q].w == 0.0f) & lipids;
+                } else {
+                    const int tj = __float_as_int(c[q].w);
+                    in[q] = __ballot(r2[q] < sel_cutf(tj, loA, loB, loC));
+                    band[q] = in[q] ^ __ballot(r2[q] < sel_cutf(tj, hiA, hiB, hiC));
+                    lip[q] = __ballot(tj == 0) & lipids;
+                    if constexpr (PER) {        // the wrapped sentinel may land anywhere
+                        const unsigned long long real = __ballot(tj != PAD_TYPE);
+                        in[q] &= real;
+                        band[q] &= real;
+                    }
                 }
-                anyband = anyband || band[q];
-                lip[q] = (ti | tj) == 0;
             }
-            if (__builtin_expect(__ballot(anyband) != 0ull, 0)) {
+            if (__builtin_expect((band[0] | band[1]) != 0ull, 0)) {
 #pragma clang fp contract(off)
                 // FP32 rounding cannot decide: the exact test of the neighbour-set definition
                 for (int q = 0; q < UNR; ++q) {
                     const double d2 = (dx[q] * dx[q] + dy[q] * dy[q]) + dz[q] * dz[q];
-                    if (band[q]) in[q] = d2 < sel_cut(c[q].t, rcA, rcB, rcC);
+                    const double cut = FAST ? (c[q].w == 0.0f ? rcA : rcB) : sel_cut(__float_as_int(c[q].w), rcA, rcB, rcC);
+                    in[q] |= band[q] & __ballot(d2 < cut);
                 }
             }
+            for (int q = 0; q < UNR; ++q) in[q] &= lanes;
             // the pair law of every row, in one block of straight-line code, as coefficients
             float ex[UNR], ey[UNR], ez[UNR], A[UNR], bi[UNR], bj[UNR], cn[UNR], ce[UNR], u[UNR];
-            bool anywca = false;
+            unsigned long long anywca = 0ull;
             for (int q = 0; q < UNR; ++q) {
-                in[q] = in[q] && valid;
                 u[q] = lipid_coef<FAST>(P, fdx[q], fdy[q], fdz[q], r2[q], nix, niy, niz, c[q].nx, c[q].ny, c[q].nz,
-                                        in[q] && lip[q], ex[q], ey[q], ez[q], A[q], bi[q], bj[q], cn[q], ce[q]);
-                anywca = anywca || (in[q] && !lip[q]);
+                                        __builtin_amdgcn_inverse_ballot_w64(in[q] & lip[q]), ex[q], ey[q], ez[q], A[q],
+                                        bi[q], bj[q], cn[q], ce[q]);
+                anywca |= in[q] & ~lip[q];
             }
             for (int q = 0; q < UNR; ++q) {
                 fx = fmaf(-A[q], ex[q], fx);
@@ -854,9 +874,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
                     W -= 0.5 * (dx[q] * (double)ax + dy[q] * (double)ay + dz[q] * (double)az);
                 }
             }
-            if (__builtin_expect(__ballot(anywca) != 0ull, 0)) {
+            if (__builtin_expect(anywca != 0ull, 0)) {
                 for (int q = 0; q < UNR; ++q) {
-                    const bool wca = in[q] && !lip[q];
+                    const bool wca = __builtin_amdgcn_inverse_ballot_w64(in[q] & ~lip[q]);
                     float bx = 0.0f, by = 0.0f, bz = 0.0f;
                     const float uw = wca_pair<float>(P, wca ? fdx[q] : 2.0f, fdy[q], fdz[q], bx, by, bz);
                     if (wca) {
@@ -964,14 +984,15 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
                 }
             }
         };
-        Rec ra = fetch((int)(w0 & 0xffffu));
+        auto index = [](unsigned e) { return (int)(e >> 4); };       // (padding: beyond every stage)
+        Rec ra = fetch(index(w0 & 0xffffu));
         for (int it = 0; it < ntrip; ++it) {
-            const int ea = (int)(w0 & 0xffffu), eb = (int)(w0 >> 16);
+            const int ea = index(w0 & 0xffffu), eb = index(w0 >> 16);
             const Rec rb = fetch(eb);
             w0 = w1;
             w1 = (valid && it + 2 < ntrip) ? ldg(col + (it + 2) * cstep) : 0xffffffffu;
             eval(ra, ea);
-            ra = fetch((int)(w0 & 0xffffu));
+            ra = fetch(index(w0 & 0xffffu));
             eval(rb, eb);
         }
         fx -= sbi * nix;
@@ -1419,7 +1440,7 @@ void launch_scatter_forces(const LaunchCtx &L, int sys, double *F, double *T, in
 __device__ __forceinline__ int entry_slot(const SysDev &S, int blk, int scnt, int chunk, int lane, int r) {
     const size_t base = (size_t)chunk * MAXNB * CHUNK;
     if (scnt >= 0) {
-        const int e = S.il16[base + il_at(r, lane)];
+        const int e = S.il16[base + il_at(r, lane)] >> 4;
         return e < scnt ? S.istage[(size_t)blk * SSTRIDE + e] : -1;
     }
     return S.nl[base + r * CHUNK + lane];

@@ -223,6 +223,13 @@ void make_dev_params(rbc_ctx *h) {
             d.rc2hi[a][b] = std::nextafter((float)(d.rc2[a][b] * (1.0 + 4e-6)), INFINITY);
             search = std::max(search, rl);
         }
+    for (int a = 0; a < 3; ++a) {
+        // the shift adds rounding of 2e-7 of the larger cutoff
+        const double lip = d.rc2[a][0], pro = d.rc2[a][1], half = 5e-6 * std::max(lip, pro);
+        d.cutd[a] = (float)(lip - pro);
+        d.cutlo[a] = (float)(lip - half);
+        d.cuthi[a] = (float)(lip + half);
+    }
     d.rc_lipid = p.rc[0][0];
     d.r_min = p.r_min;
     d.eps = p.eps;

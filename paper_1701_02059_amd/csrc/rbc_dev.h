@@ -146,7 +146,7 @@ struct SysDev {
     double *vpart;                                  // per-chunk lipid sums for the volume (8 x nchunk)
     double *vred;                                   // their first-level reduction (32 x 8)
     int32_t *stage, *scount;                        // per 256-particle block: staged slots (SMAX), count (-1: none)
-    uint16_t *il16;                                 // pruned lists: indices into the pruned stage (il_at; 0xffff pads)
+    uint16_t *il16;                                 // pruned lists of the pruned stage's entries (il_at, il_entry; 0xffff pads)
     int32_t *ilk;                                   // per chunk: rows of the pruned list
     int32_t *istage, *iscount;                      // per block: the pruned stage (SMAX), count (-1: use nl)
     double *bred;                                   // per particle block: BRED partials (the last drift's statistics)
@@ -180,6 +180,9 @@ struct DevParams {
     float rin2f[3][3];     // (rc + 2 inner skin + 1e-3)^2 rounded up: pruned-list radius for FP32 offsets
     float rc2lo[3][3];     // FP32 squared distances below this are inside fl(rc^2) in the exact test
     float rc2hi[3][3];     // ... and at or above this outside it; between, the FP64 test decides
+    // the same per own type where all proteins have one cutoff: a protein partner's squared
+    // distance is shifted to the lipids' cutoff, and one pair of bounds serves both
+    float cutd[3], cutlo[3], cuthi[3];
     double rc_lipid, r_min, eps, mu, st0, wca_eps, wca_sig2, k_bond;
     double inv_mass[3];
     double inv_inertia;
@@ -205,6 +208,9 @@ struct DevParams {
 // together (the build and the prune read and write them 16 bytes at a time), the pruned
 // ones two (a trip of the step kernel).
 __device__ __forceinline__ int nl_at(int r, int lane) { return (r >> 3) * (8 * CHUNK) + 8 * lane + (r & 7); }
+// A pruned list's entry: 16 times the stage index, the LDS offset of a 16-byte record.
+__device__ __forceinline__ unsigned il_entry(unsigned k) { return k << 4; }
+static_assert(16 * SMAX <= 0xffff, "pruned list entries");
 __device__ __forceinline__ int il_at(int r, int lane) { return (r >> 1) * (2 * CHUNK) + 2 * lane + (r & 1); }
 static_assert(MAXNB % 8 == 0, "whole groups of rows");
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
