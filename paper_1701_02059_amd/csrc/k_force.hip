@@ -361,16 +361,55 @@ __device__ __forceinline__ void langevin_update(const DevParams &P, int gid, uns
     }
 }
 
+// The volume's lipid sums of the whole system from their first-level reduction (VR1 partials
+// of eight sums), one partial per thread of a 256-thread block: a fixed tree over the 32
+// lanes of each sum.  The totals arrive in `tot` (LDS) with the next barrier.
+constexpr int VR1 = 32;
+__device__ __forceinline__ void volume_totals(double part, double *tot) {
+    static_assert(VR1 == 32 && 8 * VR1 == BLOCK, "a partial per thread, 32 lanes per sum");
+    part = dpp_add<0x111, 0xf>(part);
+    part = dpp_add<0x112, 0xf>(part);
+    part = dpp_add<0x114, 0xf>(part);
+    part = dpp_add<0x118, 0xf>(part);
+    part = dpp_add<0x142, 0xa>(part);
+    if ((threadIdx.x & 31) == 31) tot[threadIdx.x >> 5] = part;
+}
+__device__ __forceinline__ double volume_partial(const SysDev &S) {
+    return ldg(S.vred + (threadIdx.x & 31) * 8 + (threadIdx.x >> 5));
+}
+
+// V = a_L/3 (sum x.n - (sum x).(sum n) / N_L), U_V = k_V/2 (V - V0)^2 / V0 and the force
+// constant dU_V/dV a_L/3.  V0 is the given target, else the first V (vol0, 0 before it).
+struct Volume {
+    double V, V0, kap, U, xbar[3], nbar[3];
+};
+__device__ __forceinline__ Volume volume_of(const DevParams &P, const double *t, double vol0) {
+#pragma clang fp contract(off)
+    Volume r{0.0, vol0, 0.0, 0.0, {0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
+    const double cnt = t[7];
+    if (cnt == 0.0) return r;
+    const double inv = 1.0 / cnt;
+    r.V = P.vol_a3 * (t[0] - (t[1] * t[4] + t[2] * t[5] + t[3] * t[6]) * inv);
+    for (int a = 0; a < 3; ++a) { r.xbar[a] = t[1 + a] * inv; r.nbar[a] = t[4 + a] * inv; }
+    if (vol0 == 0.0) r.V0 = P.vol_target > 0.0 ? P.vol_target : r.V;
+    if (P.vol_on && r.V0 > 0.0) {
+        const double dv = (r.V - r.V0) / r.V0;
+        r.kap = P.vol_k * dv * P.vol_a3;
+        r.U = 0.5 * P.vol_k * (r.V - r.V0) * dv;
+    }
+    return r;
+}
+
 // Volume term on a lipid: F -= kap (n - nbar), tau += n x (-kap (x - xbar)), each
 // operation rounded on its own (the same bits in every kernel variant).
-__device__ __forceinline__ void volume_term(const SysScal *sc, const D4 &x, const D4 &n, double &Fx, double &Fy,
+__device__ __forceinline__ void volume_term(const Volume &c, const D4 &x, const D4 &n, double &Fx, double &Fy,
                                             double &Fz, D4 &Tq) {
 #pragma clang fp contract(off)
-    const double kap = sc->volkap;
-    Fx -= kap * (n.x - sc->nbar[0]);
-    Fy -= kap * (n.y - sc->nbar[1]);
-    Fz -= kap * (n.z - sc->nbar[2]);
-    const double gx = -kap * (x.x - sc->xbar[0]), gy = -kap * (x.y - sc->xbar[1]), gz = -kap * (x.z - sc->xbar[2]);
+    const double kap = c.kap;
+    Fx -= kap * (n.x - c.nbar[0]);
+    Fy -= kap * (n.y - c.nbar[1]);
+    Fz -= kap * (n.z - c.nbar[2]);
+    const double gx = -kap * (x.x - c.xbar[0]), gy = -kap * (x.y - c.xbar[1]), gz = -kap * (x.z - c.xbar[2]);
     Tq.x += n.y * gz - n.z * gy;
     Tq.y += n.z * gx - n.x * gz;
     Tq.z += n.x * gy - n.y * gx;
@@ -401,15 +440,15 @@ __device__ __forceinline__ void drift_stats(const SysDev &S, double *out, int bl
 // kernel of its own (6 us on any system, 8 us at 4M particles, and the gap before it) and
 // no counting of finished blocks (about 4 us at the end of a small system's step) stands
 // between two steps.
-__device__ void publish_stats(const SysDev &S, unsigned long long step, double *s_m) {
+__device__ void stats_of(const double *part, int n, double *s_m) {       // into s_m[0..2], for thread 0
     constexpr int U = 8;                              // chunks per thread in flight
     const int nb = blockDim.x, lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
     double d = 0.0, v = 0.0, dp = 0.0;
-    for (int c0 = threadIdx.x; c0 < S.nchunk; c0 += U * nb) {
+    for (int c0 = threadIdx.x; c0 < n; c0 += U * nb) {
         double a[U][3];
 #pragma unroll
         for (int k = 0; k < U; ++k) {
-            const double *r = S.bred + 3 * (size_t)min(c0 + k * nb, S.nchunk - 1);   // (a chunk twice changes no maximum)
+            const double *r = part + 3 * (size_t)min(c0 + k * nb, n - 1);    // (a chunk twice changes no maximum)
             a[k][0] = ldg(r);
             a[k][1] = ldg(r + 1);
             a[k][2] = ldg(r + 2);
@@ -436,6 +475,12 @@ __device__ void publish_stats(const SysDev &S, unsigned long long step, double *
             s_m[1] = fmax(s_m[1], s_m[3 * q + 1]);
             s_m[2] = fmax(s_m[2], s_m[3 * q + 2]);
         }
+    }
+}
+
+__device__ void publish_stats(const SysDev &S, const double *part, int n, unsigned long long step, double *s_m) {
+    stats_of(part, n, s_m);
+    if (threadIdx.x == 0) {
         StepStat *e = S.hstat + (step - 1) % STAT_RING;
         const unsigned long long err = (unsigned long long)(unsigned)S.sc->err;
         const unsigned long long d2 = dbits(s_m[0]), v2 = dbits(s_m[1]), d2p = dbits(s_m[2]);
@@ -634,6 +679,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
     constexpr int SL = Stage<MIXED>::lds;
     constexpr int SX = Stage<MIXED>::ext;
     __shared__ __align__(16) unsigned char s_raw[Stage<MIXED>::bytes];
+    __shared__ double s_vol[8];                                   // the volume's lipid sums
     // mixed: records of x, y; of orientation and type; z
     D2 *s_xy = reinterpret_cast<D2 *>(s_raw);
     F4 *s_n4 = reinterpret_cast<F4 *>(s_xy + SX);
@@ -648,7 +694,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
         if (S.n <= 0) return;
         const unsigned long long step = S.sc->step[par];
         if (KICK == 2 && threadIdx.x == 0) S.sc->step[par ^ 1] = step + 1;       // the fused drift's number
-        publish_stats(S, step, reinterpret_cast<double *>(s_raw));
+        publish_stats(S, S.bred, S.nchunk, step, reinterpret_cast<double *>(s_raw));
         return;
     }
     const int gb = xcd_group_block((int)blockIdx.x - nstat, (int)gridDim.x - nstat);
@@ -667,6 +713,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
     const bool valid = i < S.n;
     const int scnt = __builtin_amdgcn_readfirstlane(S.iscount[lb]);
     const int nlds = min(scnt, SL);                 // stage entries held in LDS
+    const double vpart = P.vol_on ? volume_partial(S) : 0.0;
     // this lane's own particle, loaded while the stage is read
     const int traw = valid ? ldg(S.typ + i) : 0;
     const D4 pi = valid ? ld3(S.pos + i) : D4{0.0, 0.0, 0.0, 0.0};
@@ -719,6 +766,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
         s_zm[SL] = SENTINEL;
         s_n4[SL] = F4{0.0f, 0.0f, 1.0f, FAST ? __builtin_nanf("") : __int_as_float(PAD_TYPE)};
     }
+    // (each block sums the 32 partials for itself: a launch between the steps took 6 us)
+    if (P.vol_on) volume_totals(vpart, s_vol);
     __syncthreads();
     if (chunk >= S.nchunk) return;
     const int ti = traw & TYP_MASK;
@@ -1135,7 +1184,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
                 W += 0.5 * f * d2;
             }
         }
-        if (P.vol_on && ti == 0) volume_term(S.sc, pi, ni, Fx, Fy, Fz, Tq);
+        if (P.vol_on && ti == 0) volume_term(volume_of(P, s_vol, S.sc->vol0), pi, ni, Fx, Fy, Fz, Tq);
         if (KICK != 2) {
             S.frc[i] = V3{Fx, Fy, Fz};
             st3(S.trq + i, Tq);
@@ -1217,7 +1266,7 @@ static void launch_force_t(const LaunchCtx &L, double dt) {
 }
 
 void launch_force(const LaunchCtx &L, int mixed, int energy, int kick, double dt) {
-    if (L.prm.vol_on) launch_volume_reduce(L);   // V of the current state from its lipid sums
+    if (L.prm.vol_on) launch_volume_reduce(L, kick == 0 || energy);   // V of the current state from its lipid sums
     if (kick == 2) {
         if (mixed) launch_force_t<1, 0, 2>(L, dt);
         else launch_force_t<0, 0, 2>(L, dt);
@@ -1278,12 +1327,26 @@ __global__ __launch_bounds__(BLOCK) void k_kick_drift(const SysDev *Sd, Maps L_m
     if (P.vol_on && i / CHUNK < S.nchunk) volume_chunk_store(S, i / CHUNK, vsum);
 }
 
-// The same statistics at once, for the steps whose list work waits for them.
-__global__ __launch_bounds__(1024) void k_stats(const SysDev *Sd, int par) {
+// The statistics by themselves, for the steps whose decisions wait for them.  Two levels: one
+// block alone reads a 4M-particle system's 1.5 MB of partials in 30 us.
+constexpr int SR1 = 32;
+
+__global__ __launch_bounds__(BLOCK) void k_stats_part(const SysDev *Sd) {
+    const SysDev &S = Sd[blockIdx.x / SR1];
+    if (S.n <= 0) return;
+    __shared__ double s_m[3 * BLOCK / WAVE];
+    const int part = blockIdx.x % SR1, per = (S.nchunk + SR1 - 1) / SR1;
+    const int c0 = part * per, n = min(S.nchunk - c0, per);
+    stats_of(S.bred + 3 * (size_t)c0, n, s_m);       // (none: zeros)
+    if (threadIdx.x == 0)
+        for (int q = 0; q < 3; ++q) S.sred[3 * part + q] = s_m[q];
+}
+
+__global__ __launch_bounds__(WAVE) void k_stats(const SysDev *Sd, int par) {
     const SysDev &S = Sd[blockIdx.x];
     if (S.n <= 0) return;
-    __shared__ double s_m[3 * 1024 / WAVE];
-    publish_stats(S, S.sc->step[par], s_m);
+    __shared__ double s_m[3];
+    publish_stats(S, S.sred, SR1, S.sc->step[par], s_m);
 }
 
 void launch_kick_drift(const LaunchCtx &L, double dt) {
@@ -1291,7 +1354,8 @@ void launch_kick_drift(const LaunchCtx &L, double dt) {
 }
 
 void launch_stats(const LaunchCtx &L) {
-    hipLaunchKernelGGL(k_stats, dim3(L.nsys), dim3(1024), 0, L.st, L.S, L.par);
+    hipLaunchKernelGGL(k_stats_part, dim3(L.nsys * SR1), dim3(BLOCK), 0, L.st, L.S);
+    hipLaunchKernelGGL(k_stats, dim3(L.nsys), dim3(WAVE), 0, L.st, L.S, L.par);
 }
 
 // ------------------------------------------------------------------ energy reduction
@@ -1336,12 +1400,8 @@ __global__ __launch_bounds__(BLOCK) void k_volume_partials(const SysDev *Sd, Map
     volume_chunk_store(S, i / CHUNK, v);
 }
 
-// Two fixed-order levels: VR1 blocks per system each sum a contiguous range of
-// chunk totals into vred[b * 8 + q]; one block per system then sums those and
-// derives V = a_L/3 (sum x.n - (sum x).(sum n) / N_L), U_V = k_V/2 (V - V0)^2 / V0
-// and the force constant dU_V/dV a_L/3.  V0 is the given target, else the first V.
-constexpr int VR1 = 32;
-
+// First level of two: VR1 blocks per system each sum a contiguous range of chunk totals
+// into vred[b * 8 + q].  The step kernel's blocks each take the second level themselves.
 __global__ __launch_bounds__(256) void k_volume_reduce1(const SysDev *Sd, int nsys) {
     const SysDev &S = Sd[blockIdx.x / VR1];
     const int part = blockIdx.x % VR1;
@@ -1362,43 +1422,28 @@ __global__ __launch_bounds__(256) void k_volume_reduce1(const SysDev *Sd, int ns
     }
 }
 
-__global__ __launch_bounds__(64) void k_volume_reduce2(const SysDev *Sd, int nsys, DevParams P) {
+// The second level into the system's record, for force evaluations outside the step loop
+// (the first fixes V0, which the step kernel reads; the energy takes U_V).
+__global__ __launch_bounds__(BLOCK) void k_volume_record(const SysDev *Sd, int nsys, DevParams P) {
     const SysDev &S = Sd[blockIdx.x];
-    if (threadIdx.x != 0 || S.n == 0) return;
-    double t[8];
-    for (int q = 0; q < 8; ++q) {
-        double a = 0.0;
-        for (int b = 0; b < VR1; ++b) a += S.vred[b * 8 + q];
-        t[q] = a;
-    }
-    SysScal *sc = S.sc;
-    const double cnt = t[7];
-    if (cnt == 0.0) {
-        sc->volV = 0.0; sc->volkap = 0.0; sc->volU = 0.0;
-        for (int a = 0; a < 3; ++a) { sc->xbar[a] = 0.0; sc->nbar[a] = 0.0; }
-        return;
-    }
-    const double V = P.vol_a3 * (t[0] - (t[1] * t[4] + t[2] * t[5] + t[3] * t[6]) / cnt);
-    sc->volV = V;
-    for (int a = 0; a < 3; ++a) { sc->xbar[a] = t[1 + a] / cnt; sc->nbar[a] = t[4 + a] / cnt; }
-    if (sc->vol0 == 0.0) sc->vol0 = P.vol_target > 0.0 ? P.vol_target : V;
-    const double V0 = sc->vol0;
-    if (P.vol_on && V0 > 0.0) {
-        sc->volkap = P.vol_k * (V - V0) / V0 * P.vol_a3;
-        sc->volU = 0.5 * P.vol_k * (V - V0) * (V - V0) / V0;
-    } else {
-        sc->volkap = 0.0;
-        sc->volU = 0.0;
-    }
+    if (S.n == 0) return;
+    __shared__ double s_vol[8];
+    volume_totals(volume_partial(S), s_vol);
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    const Volume r = volume_of(P, s_vol, S.sc->vol0);
+    S.sc->vol0 = r.V0;
+    S.sc->volV = r.V;
+    S.sc->volU = r.U;
 }
 
 void launch_volume_partials(const LaunchCtx &L) {
     hipLaunchKernelGGL(k_volume_partials, dim3(L.nblk_p), dim3(BLOCK), 0, L.st, L.S, L.maps);
 }
 
-void launch_volume_reduce(const LaunchCtx &L) {
+void launch_volume_reduce(const LaunchCtx &L, bool record) {
     hipLaunchKernelGGL(k_volume_reduce1, dim3(L.nsys * VR1), dim3(256), 0, L.st, L.S, L.nsys);
-    hipLaunchKernelGGL(k_volume_reduce2, dim3(L.nsys), dim3(64), 0, L.st, L.S, L.nsys, L.prm);
+    if (record) hipLaunchKernelGGL(k_volume_record, dim3(L.nsys), dim3(BLOCK), 0, L.st, L.S, L.nsys, L.prm);
 }
 
 // ------------------------------------------------------------------ outputs in caller order

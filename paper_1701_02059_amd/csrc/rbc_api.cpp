@@ -301,7 +301,7 @@ size_t layout(HostSys &s, char *base) {
     d.bstart = c.take<int32_t>(n + 1); d.bpart = c.take<int32_t>(2 * s.nbond); d.br0 = c.take<double>(2 * s.nbond);
     d.epart = c.take<double>((size_t)s.nchunk * 9);
     d.vpart = c.take<double>((size_t)s.nchunk * 8);
-    d.vred = c.take<double>(32 * 8);
+    d.vred = c.take<double>(32 * 8); d.sred = c.take<double>(32 * 3);
     const int64_t nblkp = (n + BLOCK - 1) / BLOCK;
     d.stage = c.take<int32_t>((size_t)nblkp * SSTRIDE);
     d.scount = c.take<int32_t>(nblkp);
@@ -1455,7 +1455,7 @@ static rbc_status energy_slot(rbc_handle h, int32_t slot, double *out) {
         Scope sc(h);
         if (!h->dprm.vol_on) {                        // V is reported with or without the constraint
             launch_volume_partials(h->L);
-            launch_volume_reduce(h->L);
+            launch_volume_reduce(h->L, true);
         }
         force_launch(h, 1, 0, 0.0);
         h->forces_valid = true;

@@ -68,12 +68,10 @@ struct alignas(256) SysScal {
     int32_t gdim[3];
     int32_t gtot;
     double energy[9];                 // U, W, KE, sum F (3), sum r x F + tau (3)
-    // volume term, from the lipid sums of the current state
+    // volume term, from the lipid sums at the last force evaluation outside the step loop
     double volV;                      // V = a_L/3 sum (x_i - xbar).n_i
     double vol0;                      // V0 (set at the first evaluation when no target is given)
-    double volkap;                    // dU_V/dV a_L/3: the volume force is -volkap (n_i - nbar)
     double volU;                      // U_V
-    double xbar[3], nbar[3];          // lipid centroid and mean orientation
     // drifts done since loading, by table parity: numbers the thermostat's draws and the
     // published statistics
     unsigned long long step[2];
@@ -150,6 +148,7 @@ struct SysDev {
     int32_t *ilk;                                   // per chunk: rows of the pruned list
     int32_t *istage, *iscount;                      // per block: the pruned stage (SMAX), count (-1: use nl)
     double *bred;                                   // per particle block: BRED partials (the last drift's statistics)
+    double *sred;                                   // first level of the statistics' own reduction (32 x 3)
     double *bred2;                                  // the next fused drift's; bounding boxes while cells update
     int32_t *tsum;                                  // segmented-scan tile sums
     SysScal *sc;
@@ -391,7 +390,7 @@ void launch_stats(const LaunchCtx &L);                    // publish the last dr
 void launch_force(const LaunchCtx &L, int mixed, int energy, int kick, double dt);
 void launch_reduce_energy(const LaunchCtx &L);
 void launch_volume_partials(const LaunchCtx &L);          // lipid sums of the current state, per chunk
-void launch_volume_reduce(const LaunchCtx &L);            // lipid sums -> V, volume force constants
+void launch_volume_reduce(const LaunchCtx &L, bool record);   // lipid sums -> V (record: into the system's record)
 void launch_gather_state(const LaunchCtx &L, int sys, double *x, double *n, double *v, double *w, int count);
 void launch_gather_forces(const LaunchCtx &L, int sys, double *F, double *T, int count);
 // the sorted pairs of a system: count them (the number ends in its hist, as 64 bits, at
