@@ -570,6 +570,15 @@ __device__ __forceinline__ float lipid_coef(const DevParams &P, float dx, float 
 //   force on i  = -(A e + bi n_i + bj n_j),    g_i = cn n_j + ce e,
 // for a pair in range.  Both radial branches are evaluated and selected: a wavefront
 // nearly always holds lanes of both.
+//  A Horner step a b + c with the coefficient c in scalar registers: the compiler's own form
+// adds into a copy of it, which costs a move per step and registers to keep the coefficients
+// (15 moves and 22 registers per row).
+__device__ __forceinline__ double horner(double a, double b, double c) {
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(c));
+    return r;
+}
+
 template <bool FAST, bool ENERGY>
 __device__ __forceinline__ double lipid_coef64(const DevParams &P, double dx, double dy, double dz, double r2, double nix,
                                                double niy, double niz, double njx, double njy, double njz, double &ex,
@@ -595,21 +604,21 @@ __device__ __forceinline__ double lipid_coef64(const DevParams &P, double dx, do
     // double angle; a core lane's h is a small negative number and its result unused
     const double h = (0.25 * M_PI * P.inv_w) * (r - rmin), h2 = h * h;
     double sp = -1.0 / 1307674368000.0;
-    sp = fma(sp, h2, 1.0 / 6227020800.0);
-    sp = fma(sp, h2, -1.0 / 39916800.0);
-    sp = fma(sp, h2, 1.0 / 362880.0);
-    sp = fma(sp, h2, -1.0 / 5040.0);
-    sp = fma(sp, h2, 1.0 / 120.0);
-    sp = fma(sp, h2, -1.0 / 6.0);
+    sp = horner(sp, h2, 1.0 / 6227020800.0);
+    sp = horner(sp, h2, -1.0 / 39916800.0);
+    sp = horner(sp, h2, 1.0 / 362880.0);
+    sp = horner(sp, h2, -1.0 / 5040.0);
+    sp = horner(sp, h2, 1.0 / 120.0);
+    sp = horner(sp, h2, -1.0 / 6.0);
     const double sh = fma(h * h2, sp, h);
     double cp = 1.0 / 20922789888000.0;
-    cp = fma(cp, h2, -1.0 / 87178291200.0);
-    cp = fma(cp, h2, 1.0 / 479001600.0);
-    cp = fma(cp, h2, -1.0 / 3628800.0);
-    cp = fma(cp, h2, 1.0 / 40320.0);
-    cp = fma(cp, h2, -1.0 / 720.0);
-    cp = fma(cp, h2, 1.0 / 24.0);
-    cp = fma(cp, h2, -0.5);
+    cp = horner(cp, h2, -1.0 / 87178291200.0);
+    cp = horner(cp, h2, 1.0 / 479001600.0);
+    cp = horner(cp, h2, -1.0 / 3628800.0);
+    cp = horner(cp, h2, 1.0 / 40320.0);
+    cp = horner(cp, h2, -1.0 / 720.0);
+    cp = horner(cp, h2, 1.0 / 24.0);
+    cp = horner(cp, h2, -0.5);
     const double ch = fma(cp, h2, 1.0);
     const double sx = 2.0 * sh * ch, cx = (ch - sh) * (ch + sh);
     const double c2 = cx * cx;
@@ -647,8 +656,8 @@ __device__ __forceinline__ double lipid_coef64(const DevParams &P, double dx, do
 template <int MIXED>
 struct Stage {
     static constexpr int lds = MIXED ? 640 : 800;
-    static constexpr int ext = MIXED ? lds + 1 : lds;   // LDS entries (mixed: the sentinel)
-    static constexpr int bytes = MIXED ? ext * (3 * 8 + 16) : lds * (6 * 8 + 1);
+    static constexpr int ext = lds + 1;                  // LDS entries, with the sentinel
+    static constexpr int bytes = MIXED ? ext * (3 * 8 + 16) : ext * (6 * 8 + 1);
 };
 static_assert(Stage<1>::lds < SMAX, "lists reach beyond the LDS part");
 constexpr double SENTINEL = 1.0e8;    // sigma: the padding entry's coordinates (finite FP32 squares)
@@ -684,10 +693,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
     D2 *s_xy = reinterpret_cast<D2 *>(s_raw);
     F4 *s_n4 = reinterpret_cast<F4 *>(s_xy + SX);
     double *s_zm = reinterpret_cast<double *>(s_n4 + SX);
-    // FP64
-    double *s_x = reinterpret_cast<double *>(s_raw), *s_y = s_x + SX, *s_z = s_y + SX;
-    double *s_nx = s_z + SL, *s_ny = s_nx + SL, *s_nz = s_ny + SL;
-    unsigned char *s_t = reinterpret_cast<unsigned char *>(s_nz + SL);
+    // FP64: records of x, y; of z, n_x; of n_y, n_z; type
+    D2 *s_zn = s_xy + SX, *s_nn = s_zn + SX;
+    unsigned char *s_t = reinterpret_cast<unsigned char *>(s_nn + SX);
     const int nstat = KICK ? L_maps.nsys : 0;
     if (KICK && (int)blockIdx.x < nstat) {
         const SysDev &S = Sd[blockIdx.x];
@@ -750,16 +758,19 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
                 s_zm[q] = p.z;
                 s_n4[q] = with_kind(ldg(S.ori32 + slot[k]));
             } else {
-                s_x[q] = p.x;
-                s_y[q] = p.y;
-                s_z[q] = p.z;
-                const V3 o = S.ori[slot[k]];
-                s_nx[q] = o.x;
-                s_ny[q] = o.y;
-                s_nz[q] = o.z;
+                const V3 o = ldg(S.ori + slot[k]);
+                s_xy[q] = D2{p.x, p.y};
+                s_zn[q] = D2{p.z, o.x};
+                s_nn[q] = D2{o.y, o.z};
                 s_t[q] = ldg(S.typ + slot[k]) & TYP_MASK;
             }
         }
+    }
+    if (!MIXED && tid == 0) {                        // a separation that passes no test
+        s_xy[SL] = D2{__builtin_nan(""), 0.0};
+        s_zn[SL] = D2{0.0, 0.0};
+        s_nn[SL] = D2{0.0, 0.0};
+        s_t[SL] = 0;
     }
     if (MIXED && tid == 0) {
         s_xy[SL] = D2{SENTINEL, SENTINEL};
@@ -963,18 +974,19 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
         constexpr int cstep = tstride * CHUNK;
         const int npair = (rows + 1) >> 1;
         const int ntrip = npair > p0 ? (npair - p0 + tstride - 1) / tstride : 0;
-        unsigned w0 = (valid && ntrip > 0) ? ldg(col) : 0xffffffffu;
-        unsigned w1 = (valid && ntrip > 1) ? ldg(col + cstep) : 0xffffffffu;
+        unsigned w0 = ldg(col), w1 = ldg(col + cstep);
+        const unsigned long long lipids = __ballot(ti == 0);
         struct Rec {
             double x, y, z;
             T nx, ny, nz;
             int t;
         };
-        auto fetch = [&](int e) {
+        auto fetch = [&](unsigned e) {                  // e: a list entry (16 times the stage index)
             Rec c;
             if constexpr (PARTIAL) {
-                if (e >= nlds && e < scnt) {
-                    const int slot = ldg(S.istage + (size_t)lb * SSTRIDE + e);
+                const int k = (int)(e >> 4);
+                if (k >= nlds && k < scnt) {
+                    const int slot = ldg(S.istage + (size_t)lb * SSTRIDE + k);
                     const V3 p = ldg(S.pos + slot);
                     const V3 o = ldg(S.ori + slot);
                     c.x = p.x; c.y = p.y; c.z = p.z;
@@ -983,16 +995,18 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
                     return c;
                 }
             }
-            const int q = e < nlds ? e : 0;             // in-bounds dummy for padding entries
-            c.x = s_x[q];
-            c.y = s_y[q];
-            c.z = s_z[q];
-            c.nx = s_nx[q]; c.ny = s_ny[q]; c.nz = s_nz[q];
-            c.t = s_t[q];
+            // padding -> the sentinel
+            const unsigned q = PARTIAL ? (e < 16u * (unsigned)nlds ? e : 16u * SL) : min(e, 16u * SL);
+            const D2 xy = *reinterpret_cast<const D2 *>(s_raw + q);
+            const D2 zn = *reinterpret_cast<const D2 *>(s_raw + 16 * SX + q);
+            const D2 nn = *reinterpret_cast<const D2 *>(s_raw + 32 * SX + q);
+            c.x = xy.x; c.y = xy.y; c.z = zn.x;
+            c.nx = zn.y; c.ny = nn.x; c.nz = nn.y;
+            c.t = s_raw[48 * SX + (q >> 4)];
             return c;
         };
         double sbi = 0.0, gx = 0.0, gy = 0.0, gz = 0.0;       // sum of bi; of g_i - cn n_i
-        auto eval = [&](const Rec &c, int e) {
+        auto eval = [&](const Rec &c) {
             const int tj = c.t;
             double dx, dy, dz, d2;
             if constexpr (PER) {
@@ -1000,9 +1014,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
             } else {
                 d2 = dist2_open(pi.x, pi.y, pi.z, c.x, c.y, c.z, dx, dy, dz);
             }
-            const bool in = e < scnt && d2 < sel_cut(tj, rcA, rcB, rcC);
-            const bool lip = (ti | tj) == 0;
-            if (in && lip) {
+            // (wavefront masks, as in mixed mode; lanes without a particle hold only padding)
+            const unsigned long long in = __ballot(d2 < (FAST ? (tj == 0 ? rcA : rcB) : sel_cut(tj, rcA, rcB, rcC)));
+            const unsigned long long lip = __ballot(tj == 0) & lipids, wca = in & ~lip;
+            if (__builtin_amdgcn_inverse_ballot_w64(in & lip)) {
                 double ex, ey, ez, A, bi, bj, cn, ce;
                 const double u = lipid_coef64<FAST, ENERGY>(P, dx, dy, dz, d2, nix, niy, niz, c.nx, c.ny, c.nz, ex, ey, ez,
                                                             A, bi, bj, cn, ce);
@@ -1019,8 +1034,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
                                 dz * (A * ez + bi * niz + bj * c.nz));
                 }
             }
-            if (__builtin_expect(__ballot(in && !lip) != 0ull, 0)) {
-                if (in && !lip) {
+            if (__builtin_expect(wca != 0ull, 0)) {
+                if (__builtin_amdgcn_inverse_ballot_w64(wca)) {
                     T ax = 0, ay = 0, az = 0;
                     const double u = wca_pair<T>(P, (T)dx, (T)dy, (T)dz, ax, ay, az);
                     fx += ax;
@@ -1033,16 +1048,14 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
                 }
             }
         };
-        auto index = [](unsigned e) { return (int)(e >> 4); };       // (padding: beyond every stage)
-        Rec ra = fetch(index(w0 & 0xffffu));
+        Rec ra = fetch(w0 & 0xffffu);
         for (int it = 0; it < ntrip; ++it) {
-            const int ea = index(w0 & 0xffffu), eb = index(w0 >> 16);
-            const Rec rb = fetch(eb);
+            const Rec rb = fetch(w0 >> 16);
             w0 = w1;
-            w1 = (valid && it + 2 < ntrip) ? ldg(col + (it + 2) * cstep) : 0xffffffffu;
-            eval(ra, ea);
-            ra = fetch(index(w0 & 0xffffu));
-            eval(rb, eb);
+            w1 = ldg(col + (it + 2) * cstep);
+            eval(ra);
+            ra = fetch(w0 & 0xffffu);
+            eval(rb);
         }
         fx -= sbi * nix;
         fy -= sbi * niy;
