@@ -1544,13 +1544,17 @@ __device__ int cell_query_wave(const SysDev &S, const SysScal *sc, int A, double
 // 40 us), CQ_BLOCKS blocks per 256-cell block of the cell map.  Both find the same rows.
 // The query writes a cell's first CROW hits to a scratch row (in the memory of the 32-bit
 // fallback lists, idle until the list build) and its row's length; once a scan has placed the
-// rows they are copied, and only a longer row is queried again.  (Querying every cell a
+// rows they are copied, and only a longer row (a cell with a far member reaches many) is
+// queried again, by a wavefront.  (Querying every cell a
 // second time to fill its row took longer than the first time: 41 after 32 us at 6250 cells;
 // the copy takes 4 us.)
 constexpr int CQ_BLOCKS = BLOCK / (BLOCK / WAVE);
 constexpr int CQ_SERIAL_MIN = 150000;
-constexpr int CROW = 64;
-__device__ __forceinline__ int32_t *scratch_row(const SysDev &S, int c) { return S.nl + (size_t)c * CROW; }
+constexpr int CROW = 256;             // (less where cells hold fewer than three particles on average)
+__device__ __forceinline__ int crow_of(const SysDev &S) {
+    return (int)min((long long)CROW, (long long)S.nchunk * (MAXNB * CHUNK) / S.k);
+}
+__device__ __forceinline__ int32_t *scratch_row(const SysDev &S, int c) { return S.nl + (size_t)c * crow_of(S); }
 
 // A cell's row length as counted; 0 and an error where it would let the scanned total
 // leave int32.
@@ -1568,7 +1572,7 @@ __global__ __launch_bounds__(BLOCK) void k_cnbr_query_serial(const SysDev *Sd, M
     if (!S.sc->rebuild || S.k < CQ_SERIAL_MIN) return;
     const int c = lb * BLOCK + threadIdx.x;
     int n = 0;
-    if (c < S.k) n = checked_row(S, c, cell_query_serial(S, S.sc, c, search, scratch_row(S, c), CROW), true);
+    if (c < S.k) n = checked_row(S, c, cell_query_serial(S, S.sc, c, search, scratch_row(S, c), crow_of(S)), true);
     const int m = wave_max_int(n);
     if ((threadIdx.x & 63) == 0 && m > 0) max_if_larger(&S.sc->cnbr_maxrow, m);
 }
@@ -1584,7 +1588,7 @@ __global__ __launch_bounds__(BLOCK) void k_cnbr_query(const SysDev *Sd, Maps L_m
     __shared__ QRuns s_q[BLOCK / WAVE];
     int m = 0;
     if (c < S.k)                                   // wavefront-uniform
-        m = checked_row(S, c, cell_query_wave(S, S.sc, c, search, s_q[wv], scratch_row(S, c), CROW), lane == 0);
+        m = checked_row(S, c, cell_query_wave(S, S.sc, c, search, s_q[wv], scratch_row(S, c), crow_of(S)), lane == 0);
     __shared__ int s_m[BLOCK / WAVE];
     if (lane == 0) s_m[wv] = m;
     __syncthreads();
@@ -1609,14 +1613,21 @@ __global__ __launch_bounds__(BLOCK) void k_cnbr_place(const SysDev *Sd, Maps L_m
         if (lead) atomicOr(&S.sc->err, ERR_CNBR);
         return;
     }
-    if (c >= S.k) return;
-    const int b = S.cnbr_start[c], n = S.cnbr_start[c + 1] - b;
-    if (n > CROW) {
-        if (l == 0) (void)cell_query_serial(S, S.sc, c, search, S.cnbr + b, n);
-        return;
+    __shared__ QRuns s_q[BLOCK / WAVE];
+    __shared__ int s_long[CPB];
+    const int cap = crow_of(S), g = threadIdx.x / CELL_LANES;
+    const int b = c < S.k ? S.cnbr_start[c] : 0, n = c < S.k ? S.cnbr_start[c + 1] - b : 0;
+    if (l == 0) s_long[g] = n > cap ? n : 0;
+    if (n <= cap && n > 0) {
+        const int32_t *row = scratch_row(S, c);
+        for (int q = l; q < n; q += CELL_LANES) S.cnbr[b + q] = row[q];
     }
-    const int32_t *row = scratch_row(S, c);
-    for (int q = l; q < n; q += CELL_LANES) S.cnbr[b + q] = row[q];
+    __syncthreads();
+    for (int h = threadIdx.x / WAVE; h < CPB; h += BLOCK / WAVE)           // wavefront-uniform
+        if (s_long[h]) {
+            const int cl = c - g + h;
+            (void)cell_query_wave(S, S.sc, cl, search, s_q[threadIdx.x / WAVE], S.cnbr + S.cnbr_start[cl], s_long[h]);
+        }
 }
 
 void launch_cell_bounds(const LaunchCtx &L) {

@@ -61,6 +61,14 @@ def _make(kind):
         g = g[rng.permutation(len(g))[:int(kind[3:])]] + rng.normal(0, 0.1, (int(kind[3:]), 3))
         x = np.r_[x, g]
         return _system(x, np.zeros(len(x)), rng)
+    if kind == "pillar":                    # one cell, with a far member on each side, pairs with every other
+        x = _sheet(70, rng) * [1.0, 1.0, 0.0]
+        x = np.r_[x, [[38.0, 38.0, 60.0], [38.0, 38.0, -60.0]]]
+        s = _system(x, np.zeros(len(x)), rng)
+        # neither of the two seeds a cell: their ids become the last ones
+        far = np.flatnonzero(np.abs(s.x[:, 2]) > 50.0)
+        order = np.r_[np.delete(np.arange(s.N), far), far]
+        return dataclasses.replace(s, x=s.x[order], n=s.n[order], v=s.v[order])
     g = np.stack(np.meshgrid(*[np.arange(13)] * 3, indexing="ij"), axis=-1).reshape(-1, 3) * 1.2
     x = g + rng.normal(0, 0.01, g.shape)    # a solid: 80 partners per particle, 400 candidates per cell
     return _system(x, (rng.random(len(x)) < 0.2).astype(int), rng, (15.6, 15.6, 15.6) if kind == "solid-periodic" else (0, 0, 0))
@@ -70,7 +78,7 @@ CASES = [("sheet", dict()), ("sheet", dict(cell_target=9)), ("sheet", dict(cell_
          ("sheet", dict(cell_target=1)), ("sheet", dict(cell_target=200)), ("sheet", dict(protein_cells=1, skin=0.65)),
          ("periodic", dict()), ("periodic", dict(cell_target=1)), ("gas7", dict()), ("gas40", dict()),
          ("gas700", dict()), ("gas40", dict(cell_target=60)), ("solid", dict()), ("solid", dict(cell_target=40)),
-         ("solid-periodic", dict())]
+         ("solid-periodic", dict()), ("pillar", dict(cell_target=9)), ("pillar", dict(cell_target=12))]
 
 
 @pytest.mark.parametrize("prec", ["fp64", "mixed"])
@@ -84,6 +92,8 @@ def test_lists_at_the_limits_of_a_block(R, mp, kind, over, prec):
     tol, pp = (FP64_TOL, PP_FP64_TOL) if prec == "fp64" else (MIXED_TOL, PP_MIXED_TOL)
     if over.get("cell_target") == 1:
         assert (c.debug_array(9) < 0).all()          # more own cells than a stage has bits for
+    if kind == "pillar":
+        assert c.stats()["max_cell_pairs"] > 256     # more than a row's scratch
     for steps in (0, 12):
         if steps:
             c.step(steps, 0.01)
