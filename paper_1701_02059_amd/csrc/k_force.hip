@@ -647,12 +647,14 @@ __device__ __forceinline__ double lipid_coef64(const DevParams &P, double dx, do
     return rep ? eps * (q * q - 2.0 * q) + (1.0 - phi) * eps : -eps * c2z * phi;
 }
 
-// LDS stage per 256-particle block (structure of arrays): FP64 positions, and either
-// FP32 orientations with the type in w (mixed) or FP64 orientations and a type byte.
-// The stage is the block's pruned partner set; entries beyond the LDS part (rare)
-// are read from global memory.  Mixed mode keeps one more entry, a sentinel far
-// from every particle with a padding type, which list padding points to (on periodic
-// axes the wrap may bring it back into range, so periodic systems also test its type).
+// LDS stage per 256-particle block, in 16-byte records at the offsets that the lists hold:
+// FP64 positions, and either FP32 orientations with the type in w (mixed) or FP64
+// orientations and a type byte.  The stage is the block's pruned partner set; entries
+// beyond the LDS part (rare) are read from global memory (1600 entries in LDS instead of
+// 800 made no difference to FP64 mode).  One more entry is a sentinel that list padding
+// points to and that passes no test: its x is NaN (FP64), its kind is NaN (mixed, FAST), or
+// it lies far from every particle with a padding type (mixed otherwise; on periodic axes
+// the wrap may bring it back into range, so those systems also test its type).
 template <int MIXED>
 struct Stage {
     static constexpr int lds = MIXED ? 640 : 800;
@@ -676,6 +678,16 @@ struct alignas(16) D2 {
 //    meets, the exact FP64 test of the neighbour-set definition decides.  The pair
 //    law then runs in FP32.
 //  - FP64 mode: every entry takes the exact FP64 test; the pair law runs in FP64.
+// What bounds it: vector instructions on systems that fill the GPU (mixed: 151 per pair of
+// rows and 2,650 per wavefront, 74% of the issue cycles of a 4M-particle launch, with 0.93 GB
+// of the 1.4 GB it moves counted at the memory; FP64: 209 per pair of rows), and on small
+// systems one wavefront's latency: a chain of descriptor, slot and record loads, a quarter of
+// the rows, the sums of the four wavefronts and the epilogue.  At 4M particles 407 us mixed
+// and 520 FP64 (439 and 677 with the bounds selected by type, checks per entry, spilled
+// orientations and coefficients copied per row); at 125k FP64 27.5 us (31.8 before its rows
+// were rewritten), at 2,704 13.0 mixed (15.6) and 13.4 FP64.  Six wavefronts per SIMD (80 registers, spills)
+// ran 5 to 12% slower than five; loading the first rows and the epilogue's state before the
+// barriers 2 to 4% slower.
 // KICK: 0 stores F and tau; 1 also applies the closing half-kick of the step;
 // 2 applies the closing half-kick and then, with the same force, the opening
 // half-kick and drift of the next step (positions and orientations go to the

@@ -14,6 +14,7 @@ constexpr int MAXNB = 96;             // neighbour-list rows per chunk
 // (the step kernel looks up the bond table only for those)
 constexpr int TYP_MASK = 3;
 constexpr int TYP_BONDED = 0x80;
+constexpr int CELL_LANES = 16;         // lanes per cell in the kernels that go through cells' members
 constexpr int SORT_IPT = 16;          // items per thread in the radix sort
 constexpr int SORT_TILE = BLOCK * SORT_IPT;
 constexpr int MAX_SLOTS = 256;
@@ -96,9 +97,10 @@ __host__ __device__ inline unsigned long long stat_tag(unsigned long long step, 
 // Systems of at most this many 256-particle blocks run the step kernel with each
 // 64-particle chunk's list rows spread over the four waves of a block (four blocks
 // per particle block): too small to fill the GPU, their step time is one wave's walk
-// over its rows, which this cuts by four.
+// over its rows, which this cuts by four.  Each of the four blocks loads the whole stage,
+// so larger systems lose by it (489 blocks: 40 us a step against 32; eight such systems in
+// one launch 132 against 114).
 constexpr int SPLIT_MAX_BLOCKS = 32;
-constexpr int CELL_LANES = 16;          // lanes per cell in the kernels that go through cells' members
 struct alignas(64) StepStat {
     double d2;                        // largest |x - x_build|^2 of this drift
     double v2;                        // largest |v|^2 used in it
