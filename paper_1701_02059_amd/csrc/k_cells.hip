@@ -696,6 +696,7 @@ __device__ __forceinline__ int nearest_seed(const SysDev &S, const SysScal *sc, 
             const int zlo = gap2[2][0] > bestd2 ? 0 : lo[2], zhi = gap2[2][2] > bestd2 ? 0 : hi[2];
             constexpr int NC = 9;
             constexpr int ord[NC] = {4, 1, 3, 5, 7, 0, 2, 6, 8};
+            int qb[NC], qe[NC];
 #pragma unroll
             for (int k = 0; k < NC; ++k) {
                 const int ox = ord[k] / 3 - 1, oy = ord[k] % 3 - 1;
@@ -705,27 +706,34 @@ __device__ __forceinline__ int nearest_seed(const SysDev &S, const SysScal *sc, 
                 if (S.per[0]) gx = gx < 0 ? gx + sc->gdim[0] : (gx >= sc->gdim[0] ? gx - sc->gdim[0] : gx);
                 if (S.per[1]) gy = gy < 0 ? gy + sc->gdim[1] : (gy >= sc->gdim[1] ? gy - sc->gdim[1] : gy);
                 const int base = (gx * sc->gdim[1] + gy) * sc->gdim[2] + cc[2];
-                ranges[k * BLOCK] = in ? make_int2(ldg(S.gstart + base + zlo), ldg(S.gstart + base + zhi + 1)) : make_int2(0, 0);
+                qb[k] = in ? ldg(S.gstart + base + zlo) : 0;
+                qe[k] = in ? ldg(S.gstart + base + zhi + 1) : 0;
             }
+            int nr = 0;
+#pragma unroll
+            for (int k = 0; k < NC; ++k)
+                if (qe[k] > qb[k]) ranges[nr++ * BLOCK] = make_int2(qb[k], qe[k]);
+            // each lane goes through its own ranges, whatever the others' lengths
             auto columns = [&](auto per_tag) {
                 constexpr bool PER = decltype(per_tag)::value;
-                for (int k = 0; k < NC; ++k) {
-                    const int2 r = ranges[k * BLOCK];
-                    constexpr int SB = 2;            // seeds side by side
-                    for (int q0 = r.x; q0 < r.y; q0 += SB) {
-                        D4 c[SB];
+                constexpr int SB = 2;                // seeds side by side
+                int2 r = nr > 0 ? ranges[0] : make_int2(0, 0);
+                int k = 1;
+                while (r.x < r.y) {
+                    D4 c[SB];
 #pragma unroll
-                        for (int h = 0; h < SB; ++h) c[h] = ldg(S.gpos + min(q0 + h, r.y - 1));
+                    for (int h = 0; h < SB; ++h) c[h] = ldg(S.gpos + min(r.x + h, r.y - 1));
+                    r.x += SB;
+                    if (r.x >= r.y && k < nr) r = ranges[k++ * BLOCK];
 #pragma unroll
-                        for (int h = 0; h < SB; ++h) {
-                            const int sd = (int)c[h].w;
-                            const double d2 = PER ? dist2_exact(S, xi, yi, zi, c[h].x, c[h].y, c[h].z, dx, dy, dz)
-                                                  : dist2_open(xi, yi, zi, c[h].x, c[h].y, c[h].z, dx, dy, dz);
-                            // (not the other particle set's cells)
-                            if ((unsigned)(sd - slo) < span && (d2 < bestd2 || (d2 == bestd2 && sd < best))) {
-                                bestd2 = d2;
-                                best = sd;
-                            }
+                    for (int h = 0; h < SB; ++h) {
+                        const int sd = (int)c[h].w;
+                        const double d2 = PER ? dist2_exact(S, xi, yi, zi, c[h].x, c[h].y, c[h].z, dx, dy, dz)
+                                              : dist2_open(xi, yi, zi, c[h].x, c[h].y, c[h].z, dx, dy, dz);
+                        // (not the other particle set's cells)
+                        if ((unsigned)(sd - slo) < span && (d2 < bestd2 || (d2 == bestd2 && sd < best))) {
+                            bestd2 = d2;
+                            best = sd;
                         }
                     }
                 }
@@ -815,8 +823,9 @@ __device__ __forceinline__ Order order_of(const SysDev &S, int it) {
 // The nearest centroid of each particle, and its place among the cell's members: one atomic
 // per run of neighbouring lanes with the same cell.  (Places within a cell are put in order
 // by k_centroids.)  Bound by its chain of dependent loads on small systems (125k particles:
-// 43.6 us with the widening search alone, 26.9 with the nine columns loaded together) and by
-// vector instructions, about 23 per candidate, on large ones (4M: 476 and 359 us).
+// 43.6 us with the widening search alone, 26.9 with the nine columns loaded together, 19.1
+// with each lane on its own ranges) and by vector instructions, about 23 per candidate, on
+// large ones (4M: 476, 359 and 238 us).
 __global__ __launch_bounds__(BLOCK) void k_assign(const SysDev *Sd, Maps L_maps, int it, int warm) {
     SYS_FROM(p);
     if (!S.sc->rebuild) return;
