@@ -1716,7 +1716,7 @@ __device__ __forceinline__ unsigned pack_used(const unsigned char *f) {
 }
 
 // The pruned stage of a block: the used ones of its scnt stage entries, in stage order
-// (slots to istage), and for every 32 entries their bits and rank in bp.  Returns its size.
+// (entries to istage), and for every 32 entries their bits and rank in bp.  Returns its size.
 __device__ int pruned_stage(const SysDev &S, int lb, int scnt, const unsigned char *s_tf, uint2 *s_bp, int *s_w) {
     const int nwords = (scnt + 31) / 32;                 // at most SMAX / 32 = 64: one wavefront's
     static_assert(SMAX / 32 <= WAVE, "the words of a stage");
@@ -1845,7 +1845,7 @@ constexpr int MWORDS = 11;            // words of hit bits per lane (352 candida
 // area in which one of its members can have partners; compact cells have 0.5 to 1.
 constexpr float WIDE = 1.5f;
 
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) void k_nlist(const SysDev *Sd, Maps L_maps, DevParams P, int cells_moved) {
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) void k_nlist(const SysDev *Sd, Maps L_maps, DevParams P) {
     SYS_FROM(p);
     if (!S.sc->rebuild) return;
     // 53 KB of LDS, three blocks per CU.  s_raw: the stage's x, y, z; the union arrays, then
@@ -1881,15 +1881,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
     const D4 ref = ld3(S.pos + first);
     const D4 pi = valid ? ldpos(S, i) : ref;
     if (valid) {
-        // the drift references of the new lists, and after a cell update (the particles have
-        // moved to new slots) the FP32 orientation copies, which the step kernel keeps current
+        // the drift references of the new lists
         const F3 b = {(float)pi.x, (float)pi.y, (float)pi.z};
         S.xb[i] = b;
         S.xp[i] = b;
-        if (cells_moved) {
-            const V3 o = ldg(S.ori + i);
-            S.ori32[i] = F4{(float)o.x, (float)o.y, (float)o.z, __int_as_float((int)pi.w)};
-        }
     }
     if (S.sc->err & ERR_CNBR) {          // no valid cell pairs: publish empty lists (block-uniform)
         if (lane == 0 && chunk_ok) { S.nlk[chunk] = 0; S.ilk[chunk] = 0; }
@@ -2173,7 +2168,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
                     s_uz[rank[k]] = o[k][2];
                     s_tf[rank[k]] = (unsigned char)t[k];
                     s_om[rank[k]] = (uint16_t)om[k];
-                    stg(S.stage + (size_t)lb * SSTRIDE + rank[k], slot[k]);
+                    stg(S.stage + (size_t)lb * SSTRIDE + rank[k], stage_entry(slot[k], t[k]));
                     if ((unsigned)(slot[k] - first) < (unsigned)BLOCK) s_self[slot[k] - first] = (uint16_t)rank[k];
                 }
             }
@@ -2475,8 +2470,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
     }
 }
 
-void launch_nlist(const LaunchCtx &L, bool cells_moved) {
-    hipLaunchKernelGGL(k_nlist, dim3(L.nblk_p), dim3(BLOCK), 0, L.st, L.S, L.maps, L.prm, cells_moved ? 1 : 0);
+void launch_nlist(const LaunchCtx &L) {
+    hipLaunchKernelGGL(k_nlist, dim3(L.nblk_p), dim3(BLOCK), 0, L.st, L.S, L.maps, L.prm);
 }
 
 // ------------------------------------------------------------------ pruned lists
@@ -2533,14 +2528,14 @@ __global__ __launch_bounds__(BLOCK) void k_prune(const SysDev *Sd, Maps L_maps, 
         for (int k = 0; k < 8; ++k) {
             const int q = q0 + k * BLOCK;
             if (slot[k] < 0) break;
-            const D4 pj = ldpos(S, slot[k]);
+            const V3 pj = ldg(S.pos + stage_slot(slot[k]));
             const float ox = (float)minimg1(pj.x - ref.x, S.per[0], S.box[0]);
             const float oy = (float)minimg1(pj.y - ref.y, S.per[1], S.box[1]);
             const float oz = (float)minimg1(pj.z - ref.z, S.per[2], S.box[2]);
             s_x[q] = ox;
             s_y[q] = oy;
             s_z[q] = oz;
-            s_tf[q] = (unsigned char)((int)pj.w & 3);
+            s_tf[q] = (unsigned char)stage_type(slot[k]);
             far = far || !(fabsf(ox) <= LIST_EXTENT && fabsf(oy) <= LIST_EXTENT && fabsf(oz) <= LIST_EXTENT);
         }
     }

@@ -678,16 +678,17 @@ struct alignas(16) D2 {
 //    meets, the exact FP64 test of the neighbour-set definition decides.  The pair
 //    law then runs in FP32.
 //  - FP64 mode: every entry takes the exact FP64 test; the pair law runs in FP64.
-// What bounds it: vector instructions on systems that fill the GPU (mixed: 151 per pair of
-// rows and 2,650 per wavefront, 74% of the issue cycles of a 4M-particle launch, with 0.93 GB
-// of the 1.4 GB it moves counted at the memory; FP64: 209 per pair of rows), and on small
-// systems one wavefront's latency: a chain of descriptor, slot and record loads, a quarter of
-// the rows, the sums of the four wavefronts and the epilogue.  At 4M particles 407 us mixed
-// and 520 FP64 (439 and 677 with the bounds selected by type, checks per entry, spilled
-// orientations and coefficients copied per row); at 125k FP64 27.5 us (31.8 before its rows
-// were rewritten), at 2,704 13.0 mixed (15.6) and 13.4 FP64.  Six wavefronts per SIMD (80 registers, spills)
-// ran 5 to 12% slower than five; loading the first rows and the epilogue's state before the
-// barriers 2 to 4% slower.
+// What bounds it on systems that fill the GPU: vector instructions (mixed: 151 per pair of
+// rows and about 2,650 per wavefront, three quarters of the issue cycles of a 4M-particle
+// launch; FP64: 209 per pair of rows) and, in mixed mode, memory traffic at three quarters of
+// a plain copy's rate; on small systems one wavefront's latency: a chain of descriptor, entry
+// and record loads, a quarter of the rows, the sums of the four wavefronts and the epilogue.
+// At 4M particles 400 us mixed and 512 FP64 (439 and 677 with the bounds selected by type,
+// checks per entry, spilled orientations, coefficients copied per row and FP32 copies of the
+// orientations kept beside the FP64 ones: 32 bytes per particle and step); at 125k FP64 27.2
+// us (31.8 before its rows were rewritten), at 2,704 13.0 mixed (15.6) and 13.4 FP64.  Six
+// wavefronts per SIMD (80 registers, spills) ran 5 to 12% slower than five; loading the first
+// rows and the epilogue's state before the barriers 2 to 4% slower.
 // KICK: 0 stores F and tau; 1 also applies the closing half-kick of the step;
 // 2 applies the closing half-kick and then, with the same force, the opening
 // half-kick and drift of the next step (positions and orientations go to the
@@ -734,47 +735,47 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
     const int scnt = __builtin_amdgcn_readfirstlane(S.iscount[lb]);
     const int nlds = min(scnt, SL);                 // stage entries held in LDS
     const double vpart = P.vol_on ? volume_partial(S) : 0.0;
+    auto narrow = [](const V3 &n) { return F4{(float)n.x, (float)n.y, (float)n.z, 0.0f}; };
     // this lane's own particle, loaded while the stage is read
     const int traw = valid ? ldg(S.typ + i) : 0;
     const D4 pi = valid ? ld3(S.pos + i) : D4{0.0, 0.0, 0.0, 0.0};
-    // (mixed mode's rows take the FP32 copy of the orientation, which the stage reads too; the
-    // FP64 one would be spilled over them and is read in the epilogue)
+    // (mixed mode's rows take the orientation in FP32; the FP64 one would be spilled over them
+    // and is read again in the epilogue)
     D4 ni = {0.0, 0.0, 0.0, 0.0};
     F4 ni32 = {0.0f, 0.0f, 0.0f, 0.0f};
     if (valid) {
-        if constexpr (MIXED) ni32 = ldg(S.ori32 + i);
+        if constexpr (MIXED) ni32 = narrow(ldg(S.ori + i));
         else ni = ld3(S.ori + i);
     }
-    // FP32 orientations carry the type's bits; FAST rows take 0 for a lipid and 1 for a protein
-    // (and NaN, which passes no test, for the sentinel)
-    auto with_kind = [](F4 n) {
-        if constexpr (FAST) n.w = __float_as_int(n.w) == 0 ? 0.0f : 1.0f;
+    // mixed records carry the type's bits; FAST rows take 0 for a lipid and 1 for a protein (and
+    // NaN, which passes no test, for the sentinel)
+    auto with_kind = [](F4 n, int type) {
+        n.w = FAST ? (type == 0 ? 0.0f : 1.0f) : __int_as_float(type);
         return n;
     };
     // the stage: every thread's (at most three) slots first, then their records
     constexpr int SPT = (SL + BLOCK - 1) / BLOCK;
     for (int q0 = tid; q0 < nlds; q0 += SPT * BLOCK) {
-        int slot[SPT];
+        int32_t ent[SPT];
 #pragma unroll
         for (int k = 0; k < SPT; ++k) {
             const int q = q0 + k * BLOCK;
-            slot[k] = q < nlds ? ldg(S.istage + (size_t)lb * SSTRIDE + q) : -1;
+            ent[k] = q < nlds ? ldg(S.istage + (size_t)lb * SSTRIDE + q) : -1;
         }
 #pragma unroll
         for (int k = 0; k < SPT; ++k) {
             const int q = q0 + k * BLOCK;
-            if (slot[k] < 0) break;
-            const V3 p = ldg(S.pos + slot[k]);
+            if (ent[k] < 0) break;
+            const V3 p = ldg(S.pos + stage_slot(ent[k]));
+            const V3 o = ldg(S.ori + stage_slot(ent[k]));
+            s_xy[q] = D2{p.x, p.y};
             if constexpr (MIXED) {
-                s_xy[q] = D2{p.x, p.y};
                 s_zm[q] = p.z;
-                s_n4[q] = with_kind(ldg(S.ori32 + slot[k]));
+                s_n4[q] = with_kind(narrow(o), stage_type(ent[k]));
             } else {
-                const V3 o = ldg(S.ori + slot[k]);
-                s_xy[q] = D2{p.x, p.y};
                 s_zn[q] = D2{p.z, o.x};
                 s_nn[q] = D2{o.y, o.z};
-                s_t[q] = ldg(S.typ + slot[k]) & TYP_MASK;
+                s_t[q] = (unsigned char)stage_type(ent[k]);
             }
         }
     }
@@ -840,9 +841,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
             if constexpr (PARTIAL) {
                 const int k = (int)(e >> 4);
                 if (k >= nlds && k < scnt) {            // stage entry beyond the LDS part
-                    const int slot = ldg(S.istage + (size_t)lb * SSTRIDE + k);
-                    const V3 p = ldg(S.pos + slot);
-                    const F4 o = with_kind(ldg(S.ori32 + slot));
+                    const int32_t ent = ldg(S.istage + (size_t)lb * SSTRIDE + k);
+                    const V3 p = ldg(S.pos + stage_slot(ent));
+                    const F4 o = with_kind(narrow(ldg(S.ori + stage_slot(ent))), stage_type(ent));
                     c.x = p.x; c.y = p.y; c.z = p.z;
                     c.nx = o.x; c.ny = o.y; c.nz = o.z; c.w = o.w;
                     return c;
@@ -998,12 +999,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
             if constexpr (PARTIAL) {
                 const int k = (int)(e >> 4);
                 if (k >= nlds && k < scnt) {
-                    const int slot = ldg(S.istage + (size_t)lb * SSTRIDE + k);
-                    const V3 p = ldg(S.pos + slot);
-                    const V3 o = ldg(S.ori + slot);
+                    const int32_t ent = ldg(S.istage + (size_t)lb * SSTRIDE + k);
+                    const V3 p = ldg(S.pos + stage_slot(ent));
+                    const V3 o = ldg(S.ori + stage_slot(ent));
                     c.x = p.x; c.y = p.y; c.z = p.z;
                     c.nx = o.x; c.ny = o.y; c.nz = o.z;
-                    c.t = ldg(S.typ + slot) & TYP_MASK;
+                    c.t = stage_type(ent);
                     return c;
                 }
             }
@@ -1242,7 +1243,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
                     on = rotor_drift(ni, wn, dt);
                 }
                 st3(S.ori2 + i, on);
-                S.ori32b[i] = F4{(float)on.x, (float)on.y, (float)on.z, __int_as_float(ti)};
                 drift_measures(xn, vn, xb, xp, disp2, disp2p, vmax2, bad);
                 if (P.vol_on && ti == 0) volume_terms(xn, on, vsum);
             }
@@ -1343,7 +1343,6 @@ __global__ __launch_bounds__(BLOCK) void k_kick_drift(const SysDev *Sd, Maps L_m
             const D4 n = rotor_drift(ld3(S.ori + i), w, dt);
             st3(S.angv + i, w);
             st3(S.ori + i, n);
-            S.ori32[i] = F4{(float)n.x, (float)n.y, (float)n.z, __int_as_float(t)};
             if (P.vol_on) volume_terms(p, n, vsum);
         }
         drift_measures(p, v, S.xb[i], S.xp[i], disp2, disp2p, v2, bad);
@@ -1525,7 +1524,7 @@ __device__ __forceinline__ int entry_slot(const SysDev &S, int blk, int scnt, in
     const size_t base = (size_t)chunk * MAXNB * CHUNK;
     if (scnt >= 0) {
         const int e = S.il16[base + il_at(r, lane)] >> 4;
-        return e < scnt ? S.istage[(size_t)blk * SSTRIDE + e] : -1;
+        return e < scnt ? stage_slot(S.istage[(size_t)blk * SSTRIDE + e]) : -1;
     }
     return S.nl[base + r * CHUNK + lane];
 }

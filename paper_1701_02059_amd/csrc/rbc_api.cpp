@@ -296,8 +296,6 @@ size_t layout(HostSys &s, char *base) {
     d.nl = c.take<int32_t>((size_t)s.nchunk * MAXNB * CHUNK); d.nlk = c.take<int32_t>(s.nchunk);
     d.nl16 = c.take<uint16_t>((size_t)s.nchunk * MAXNB * CHUNK);
     d.typ = c.take<uint8_t>(n); d.typ2 = c.take<uint8_t>(n);
-    d.ori32 = c.take<F4>(n);
-    d.ori32b = c.take<F4>(n);
     d.bstart = c.take<int32_t>(n + 1); d.bpart = c.take<int32_t>(2 * s.nbond); d.br0 = c.take<double>(2 * s.nbond);
     d.epart = c.take<double>((size_t)s.nchunk * 9);
     d.vpart = c.take<double>((size_t)s.nchunk * 8);
@@ -337,7 +335,6 @@ void size_system(const rbc_ctx *h, HostSys &s, int64_t n, int64_t nlip, int64_t 
 void swap_drift(SysDev &d) {
     std::swap(d.pos, d.pos2);
     std::swap(d.ori, d.ori2);
-    std::swap(d.ori32, d.ori32b);
     std::swap(d.bred, d.bred2);
 }
 
@@ -519,7 +516,7 @@ void lists_body(rbc_ctx *h, const LaunchCtx &L, bool cells_moved) {
     launch_cell_pairs(L);
     const bool t = h->timing && h->ncount < (int)h->nb.size();
     if (t) hipEventRecord(h->nb[h->ncount], L.st);
-    launch_nlist(L, cells_moved);
+    launch_nlist(L);
     if (t) hipEventRecord(h->ne[h->ncount++], L.st);
 }
 

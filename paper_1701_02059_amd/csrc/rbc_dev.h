@@ -138,14 +138,12 @@ struct SysDev {
     D4 *gpos;                                       // centroids in grid order, w = seed index (k)
     int32_t *nl, *nlk;                              // neighbour lists (nchunk x MAXNB x 64), rows
     uint16_t *nl16;                                 // the same lists as stage indices (staged blocks; nl_at)
-    F4 *ori32;                                      // FP32 copy of the orientations, w = type bits (staging)
-    F4 *ori32b;                                     // its second buffer (fused drift target; pos2 / ori2 likewise)
     int32_t *bstart, *bpart;                        // bonds by caller id (n+1, 2 nbond)
     double *br0;
     double *epart;                                  // per-chunk energy partials (nchunk x 9)
     double *vpart;                                  // per-chunk lipid sums for the volume (8 x nchunk)
     double *vred;                                   // their first-level reduction (32 x 8)
-    int32_t *stage, *scount;                        // per 256-particle block: staged slots (SMAX), count (-1: none)
+    int32_t *stage, *scount;                        // per 256-particle block: staged entries (SMAX), count (-1: none)
     uint16_t *il16;                                 // pruned lists of the pruned stage's entries (il_at, il_entry; 0xffff pads)
     int32_t *ilk;                                   // per chunk: rows of the pruned list
     int32_t *istage, *iscount;                      // per block: the pruned stage (SMAX), count (-1: use nl)
@@ -204,6 +202,12 @@ struct DevParams {
     int32_t pad2;
     double quench_max;
 };
+
+// A stage's entry: the particle's slot (below 2^29) and its type, which spares the kernels
+// that load the stage a one-byte access per entry.
+__device__ __forceinline__ int32_t stage_entry(int slot, int type) { return slot | type << 29; }
+__device__ __forceinline__ int stage_slot(int32_t e) { return e & ((1 << 29) - 1); }
+__device__ __forceinline__ int stage_type(int32_t e) { return e >> 29; }
 
 // Places in the lists of a 64-particle chunk.  The full lists keep eight rows of a lane
 // together (the build and the prune read and write them 16 bytes at a time), the pruned
@@ -411,7 +415,7 @@ void launch_iteration(const LaunchCtx &L, int it, bool warm, bool last);
 void launch_renumber(const LaunchCtx &L, int iters);
 void launch_cell_bounds(const LaunchCtx &L);
 void launch_cell_pairs(const LaunchCtx &L);
-void launch_nlist(const LaunchCtx &L, bool cells_moved);
+void launch_nlist(const LaunchCtx &L);
 void launch_prune(const LaunchCtx &L);                    // pruned lists of the systems in L's particle map
 void launch_mask_maps(const LaunchCtx &L, const unsigned long long m[4], int32_t *out);   // particle map of a mask
 void launch_pack(const LaunchCtx &L, int sys, const double *x, const double *n, const int32_t *type,
