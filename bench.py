@@ -36,10 +36,10 @@ DT = 0.01
 FLOPS_LIPID_PAIR = 139      # per unordered lipid pair: F_i, F_j, tau_i, tau_j and the distance test
 FLOPS_WCA_PAIR = 29         # per unordered pair with a protein bead
 FLOPS_BOND = 19             # per bond
-# Bytes: the state read and written once per step.  Lipid: read x (24) + type (1) + FP32 n
-# for the partner stage (12) + v, omega, n (72); write x, v, n, omega (96) + FP32 n (12).
-# Protein bead: read x (24) + type (1) + v (24); write x, v (48).
-BYTES_LIPID_STEP = 217
+# Bytes: the state read and written once per step.  Lipid: read x (24) + type (1) + v, omega,
+# n (72); write x, v, n, omega (96).  Protein bead: read x (24) + type (1) + v (24); write x,
+# v (48).
+BYTES_LIPID_STEP = 193
 BYTES_PROTEIN_STEP = 97
 PEAK_FP32 = 157.3           # TFLOP/s, MI355X FP32 vector (published; counts packed FP32)
 PEAK_FP64 = 78.6            # TFLOP/s, MI355X FP64 vector
@@ -47,9 +47,9 @@ PEAK_HBM = 8000.0           # GB/s
 # HBM traffic of that kernel per launch at the whole-cell workload, mixed precision,
 # skins 0.65 and 0.15: rocprofv3 FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 (KiB -> bytes; factors from a
 # plain 512 MiB device copy), valid only for the kernel sources whose digest is given.
-FORCE_TRAFFIC = {"sources_sha256": "f735d1ee4833da80", "skin": 0.65, "inner_skin": 0.15,
-                 "bytes": 1512659236, "fetch_kib": 504500, "write_kib": 468206,
-                 "valu_insts": 181583857}   # SQ_INSTS_VALU per launch (wavefront instructions)
+FORCE_TRAFFIC = {"sources_sha256": "87d6d07e7776bbfc", "skin": 0.65, "inner_skin": 0.15,
+                 "bytes": 1417161784, "fetch_kib": 504491, "write_kib": 374964,
+                 "valu_insts": 165817830}   # SQ_INSTS_VALU per launch (wavefront instructions)
 BYTES_BUILD_READ = 25       # list build: position (3 x 8 B) and type (1 B) of every particle, read once
 CU_COUNT, SIMDS_PER_CU, CLOCK_GHZ = 256, 4, 2.4
 KERNEL_SOURCES = ("paper_1701_02059_amd/csrc/k_force.hip", "paper_1701_02059_amd/csrc/k_cells.hip",

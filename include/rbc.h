@@ -225,12 +225,12 @@ rbc_status rbc_step_times(rbc_handle h, int32_t enable, int64_t cap, double *ms,
  * pointer may be NULL; both read -1 before the first call.  No device work. */
 rbc_status rbc_host_times(rbc_handle h, double *host_us, double *wait_us);
 
-/* Replay the step's fixed launch sequence (the force kernel with its fused drift
- * and the drift statistics) as a HIP graph captured once per system table and time
- * step (enable = 1), or launch every kernel directly (0).  Cell updates always
+/* Replay the step's fixed launch sequence (the force kernel with its fused drift,
+ * and the volume reduction where it is needed) as a HIP graph captured once per system
+ * table and time step (enable = 1), or launch every kernel directly (0).  Cell updates always
  * launch directly, with grids covering only the systems that rebuild.  Results are
- * identical either way.  Default: off (the step is two launches, and a graph launch
- * costs the host more than the two direct ones).  Graphs are not used while force
+ * identical either way.  Default: off (the step is one launch, and a graph launch
+ * costs the host more than the direct one).  Graphs are not used while force
  * timing is enabled.  Synchronises the library stream. */
 rbc_status rbc_set_graphs(rbc_handle h, int32_t enable);
 
