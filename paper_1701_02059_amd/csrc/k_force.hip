@@ -652,9 +652,10 @@ __device__ __forceinline__ double lipid_coef64(const DevParams &P, double dx, do
 // orientations and a type byte.  The stage is the block's pruned partner set; entries
 // beyond the LDS part (rare) are read from global memory (1600 entries in LDS instead of
 // 800 made no difference to FP64 mode).  One more entry is a sentinel that list padding
-// points to and that passes no test: its x is NaN (FP64), its kind is NaN (mixed, FAST), or
-// it lies far from every particle with a padding type (mixed otherwise; on periodic axes
-// the wrap may bring it back into range, so those systems also test its type).
+// points to and that passes no test: its x is NaN (FP64), or it lies at finite far
+// coordinates (mixed, whose branch-free rows would spread a NaN) with a NaN kind (FAST) or a
+// padding type.  On periodic axes the wrap may bring it back into range, so those systems
+// also test its type and give masked rows a separation that is not zero.
 template <int MIXED>
 struct Stage {
     static constexpr int lds = MIXED ? 640 : 800;
@@ -917,9 +918,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
             float ex[UNR], ey[UNR], ez[UNR], A[UNR], bi[UNR], bj[UNR], cn[UNR], ce[UNR], u[UNR];
             unsigned long long anywca = 0ull;
             for (int q = 0; q < UNR; ++q) {
-                u[q] = lipid_coef<FAST>(P, fdx[q], fdy[q], fdz[q], r2[q], nix, niy, niz, c[q].nx, c[q].ny, c[q].nz,
-                                        __builtin_amdgcn_inverse_ballot_w64(in[q] & lip[q]), ex[q], ey[q], ez[q], A[q],
-                                        bi[q], bj[q], cn[q], ce[q]);
+                const bool on = __builtin_amdgcn_inverse_ballot_w64(in[q] & lip[q]);
+                // a masked row needs a root too: the wrapped sentinel may lie on the particle itself
+                // (the origin of a box whose length divides the sentinel's coordinate)
+                const float rr = PER && !on ? 1.0f : r2[q];
+                u[q] = lipid_coef<FAST>(P, fdx[q], fdy[q], fdz[q], rr, nix, niy, niz, c[q].nx, c[q].ny, c[q].nz, on, ex[q],
+                                        ey[q], ez[q], A[q], bi[q], bj[q], cn[q], ce[q]);
                 anywca |= in[q] & ~lip[q];
             }
             for (int q = 0; q < UNR; ++q) {
