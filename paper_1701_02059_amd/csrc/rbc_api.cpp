@@ -53,8 +53,9 @@ struct HostSys {
     bool have_stats = false, rebuilt_last = false, refreshed_last = false;
     double disp2 = 0.0, v2 = 0.0, disp2p = 0.0;
     double cur_d2 = 0.0, cur_v2 = 0.0, cur_d2p = 0.0;   // the latest drift statistics read
-    int cur_err = 0;                 // the error bits published with them
     uint64_t drifts = 0;             // statistics passes since loading (the device's step counter)
+    uint64_t call_drift0 = 0;        // ... when the running step call began
+    int call_err = 0;                // the error bits of all of that call's force evaluations
     bool pending = false;            // staged: uploaded, cells not built yet
     rbc_status failed = RBC_OK;      // ensemble slot frozen by an error (held until retired)
     std::string why;                 // its message
@@ -555,7 +556,7 @@ rbc_status freeze_failed(rbc_ctx *h, const std::vector<std::pair<int, std::strin
     };
     for (int s = 0; s < h->nsys; ++s) {
         if (!runs(h->sys[s])) continue;
-        const rbc_status r = slot_error(h, s, h->sys[s].cur_err);
+        const rbc_status r = slot_error(h, s, h->sys[s].call_err);
         if (r != RBC_OK) freeze(s, r, h->err);
     }
     for (const auto &e : host_err) freeze(e.first, RBC_ERR_SKIN, e.second);
@@ -716,6 +717,21 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
     bool exact_any = false;
     for (const auto &hs : h->sys)
         if (runs(hs) && hs.n >= EXACT_MIN_N) exact_any = true;
+    for (auto &hs : h->sys) {
+        hs.call_err = 0;
+        hs.call_drift0 = hs.drifts;
+    }
+    // The error bits of the latest step whose force has run.  Each step counts, not the last
+    // alone: a build clears the list errors that the steps before it ran with.  They are read
+    // once the next step has published (or the stream is idle): a step that waited for its
+    // statistics publishes twice, before its list work and with its force.
+    auto settle = [&](int s) {
+        HostSys &hs = h->sys[s];
+        if (hs.drifts == hs.call_drift0) return;
+        StepStat e;
+        if (ring_entry(h, s, hs.drifts, e)) hs.call_err |= (int)e.err;
+        else if (out == RBC_OK) out = fail(h, RBC_ERR_HIP, "drift statistics out of sequence (slot " + std::to_string(s) + ")");
+    };
     // the statistics of the latest drift of every running system, from the pinned ring
     auto read_stats = [&]() {
         for (int s = 0; s < h->nsys; ++s) {
@@ -723,13 +739,13 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
             if (!runs(hs)) continue;
             hs.cur_d2 = hs.cur_v2 = hs.cur_d2p = 0.0;
             if (hs.n == 0) continue;
+            settle(s);
             StepStat e;
             if (!ring_entry(h, s, hs.drifts + 1, e) && out == RBC_OK)
                 out = fail(h, RBC_ERR_HIP, "drift statistics out of sequence (slot " + std::to_string(s) + ")");
             hs.cur_d2 = e.d2;
             hs.cur_v2 = e.v2;
             hs.cur_d2p = e.d2p;
-            hs.cur_err = (int)e.err;
             hs.drifts++;
         }
     };
@@ -876,22 +892,19 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
     }
     h->ens_steps += nsteps;
     if (timed) hipEventRecord(h->ev_prev_end, h->st);
-    // the last published error bits cover the call's drifts and list builds (the closing
-    // force raises none): nothing is copied back
+    // the published error bits cover the call's drifts and list builds (the closing force
+    // raises none): nothing is copied back
     const hipError_t le = hipGetLastError();
     if (le != hipSuccess) return fail(h, RBC_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(le));
     HIPCHK(hipStreamSynchronize(h->st));
-    for (int s = 0; s < h->nsys; ++s) {
-        HostSys &hs = h->sys[s];
-        StepStat last;
-        if (runs(hs) && hs.n > 0 && hs.drifts > 0 && ring_entry(h, s, hs.drifts, last)) hs.cur_err = (int)last.err;
-    }
+    for (int s = 0; s < h->nsys; ++s)
+        if (runs(h->sys[s])) settle(s);
     rbc_status e = RBC_OK;
     if (h->ensemble) {
         e = freeze_failed(h, slot_err);       // one slot's error freezes that slot only; the others have advanced nsteps
     } else {
         for (int s = 0; s < h->nsys && e == RBC_OK; ++s)
-            if (runs(h->sys[s])) e = slot_error(h, s, h->sys[s].cur_err);
+            if (runs(h->sys[s])) e = slot_error(h, s, h->sys[s].call_err);
     }
     harvest_timing(h);
     if (timed) {
