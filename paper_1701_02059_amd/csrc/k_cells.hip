@@ -1861,7 +1861,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
     __shared__ int s_lofs[GROUPS + 1];
     __shared__ uint16_t s_nl[GROUPS], s_np[GROUPS];         // lipid and protein candidates of each list
     __shared__ int s_w[16];
-    __shared__ int s_rows, s_big, s_nfit;
+    __shared__ int s_rows[BLOCK / WAVE], s_big, s_nfit;
     uint16_t *s_qpos = s_q, *s_om = s_q;
     static_assert(CANDMAX <= USTAGE && GROUPS <= 16, "list bits");
     float *s_ux = reinterpret_cast<float *>(s_raw), *s_uy = s_ux + USTAGE, *s_uz = s_uy + USTAGE;
@@ -1891,7 +1891,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
         if (tid == 0) { S.scount[lb] = 0; S.iscount[lb] = 0; }
         return;
     }
-    if (tid == 0) { s_rows = 0; s_big = 0; }
+    if (tid == 0) s_big = 0;             // raised after the union's barriers
     reinterpret_cast<uint2 *>(s_tf)[tid] = make_uint2(0u, 0u);
     static_assert(USTAGE == 8 * BLOCK, "type bytes");
     // ---- candidate cells and the union position of every cell-pair entry
@@ -2445,7 +2445,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
         rows = MAXNB;
     }
     if (chunk_ok && lane == 0) S.nlk[chunk] = rows;
-    if (lane == 0) atomicMax(&s_rows, rows);
+    if (lane == 0) s_rows[wv] = rows;
     int nkept = -1;
     if (staged) {
         // pad every lane to the chunk's groups of rows, then the pruned stage and lists
@@ -2466,7 +2466,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
     if (tid == 0) {
         S.scount[lb] = staged ? kept : -1;
         S.iscount[lb] = nkept;
-        if (s_rows > 0) max_if_larger(&S.sc->nlrows, s_rows);   // the build's longest list
+        const int m = max(max(s_rows[0], s_rows[1]), max(s_rows[2], s_rows[3]));
+        if (m > 0) max_if_larger(&S.sc->nlrows, m);             // the build's longest list
     }
 }
 
@@ -2497,7 +2498,7 @@ __global__ __launch_bounds__(BLOCK) void k_prune(const SysDev *Sd, Maps L_maps, 
     __shared__ __align__(16) unsigned char s_raw[3 * SMAX * 4];
     __shared__ __align__(16) unsigned char s_tf[SMAX];     // type | STAGE_USED
     __shared__ int s_w[4];
-    __shared__ int s_big;
+    __shared__ int s_far[BLOCK / WAVE];
     float *s_x = reinterpret_cast<float *>(s_raw), *s_y = s_x + SMAX, *s_z = s_y + SMAX;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int chunk = lb * (BLOCK / WAVE) + wv;
@@ -2513,7 +2514,6 @@ __global__ __launch_bounds__(BLOCK) void k_prune(const SysDev *Sd, Maps L_maps, 
         if (tid == 0) S.iscount[lb] = -1;
         return;
     }
-    if (tid == 0) s_big = 0;
     const D4 ref = ld3(S.pos + (size_t)lb * BLOCK);
     bool far = false;
     // eight entries per thread in flight: their slots, then their positions
@@ -2541,9 +2541,10 @@ __global__ __launch_bounds__(BLOCK) void k_prune(const SysDev *Sd, Maps L_maps, 
     }
     // the bytes up to the next whole word of flags
     if (tid < 32 && scnt + tid < ((scnt + 31) & ~31)) s_tf[scnt + tid] = 0;
-    if (far) s_big = 1;                              // offsets out of range or not finite
+    const bool any_far = __ballot(far) != 0ull;      // offsets out of range or not finite
+    if (lane == 0) s_far[wv] = any_far;
     __syncthreads();
-    const bool keep_all = s_big != 0;
+    const bool keep_all = (s_far[0] | s_far[1] | s_far[2] | s_far[3]) != 0;
     const v4u *src = reinterpret_cast<const v4u *>(S.nl16 + (size_t)(chunk_ok ? chunk : 0) * MAXNB * CHUNK) + lane;
     unsigned pm0 = 0u, pm1 = 0u, pm2 = 0u;           // the rows that stay
     static_assert(MAXNB == 96, "row bits in three words");
