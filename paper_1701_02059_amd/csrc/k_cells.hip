@@ -876,6 +876,7 @@ __global__ __launch_bounds__(BLOCK) void k_cell_place(const SysDev *Sd, Maps L_m
 // 12.5 us, with 8 for the counts' scan and placing, instead of 104 at 125k particles.
 //  A cell of more than CMEM members is left to the whole block: up to BIGS members are
 // counted in LDS; the members of a larger one are collected by going through all particles.
+// Where cells are that large on average (LaunchCtx::wide), each has a block of its own.
 constexpr int CB_BLOCKS = CELL_LANES;
 constexpr int CPB = BLOCK / CELL_LANES;            // cells per block
 constexpr int CMEM = 64;
@@ -887,17 +888,111 @@ __device__ __forceinline__ void wave_fence() {
     __builtin_amdgcn_wave_barrier();
 }
 
+// Particle j, member `at` of cell `cell` in the new order: its offset from the centroid, 0 if
+// it does not count.
+__device__ __forceinline__ int centroid_member(const SysDev &S, const Order &o, const Order &w, int last, uint32_t j, int at,
+                                               int cell, const D4 &sd, double (&d)[3]) {
+    const V3 p = ldg(o.pos + j);
+    const uint8_t t = ldg(o.typ + j);
+    w.idx[at] = o.idx ? o.idx[j] : j;
+    if (!last) {
+        w.pos[at] = p;
+        w.typ[at] = t;
+    }
+    S.owner[at] = cell;
+    const bool use = ((t & TYP_MASK) == 0) == (cell < S.kl);
+    (void)dist2_exact(S, p.x, p.y, p.z, sd.x, sd.y, sd.z, d[0], d[1], d[2]);
+    if (!use) d[0] = d[1] = d[2] = 0.0;
+    return use ? 1 : 0;
+}
+
+// The centroid's coordinate a from the sum of the offsets.
+__device__ __forceinline__ double centroid_moved(const SysDev &S, double x, double sum, int cnt, int a) {
+#pragma clang fp contract(off)
+    if (cnt > 0) {
+        x = x + sum / (double)cnt;
+        if (S.per[a]) x = x - S.box[a] * floor(x / S.box[a]);
+    }
+    return x;
+}
+
+// A cell's centroid by the whole block, into `out` (LDS) and the system's record.
+typedef double CentroidLds[3][CPB * CMEM];         // offsets; a big cell's members, then its offsets
+__device__ void centroid_by_block(const SysDev &S, const Order &o, const Order &w, int last, int c, CentroidLds &s_d, int *s_w,
+                                  int *s_cnt, double *out, int stride) {
+    static_assert(sizeof(s_d) >= 2 * BIGS * sizeof(uint32_t), "a big cell's members");
+    const int tid = threadIdx.x, b = S.cstart[c], m = S.ccount[c];
+    const D4 sd = S.seed[c];
+    if (tid == 0) *s_cnt = 0;
+    if (m <= BIGS) {
+        uint32_t *s_v = reinterpret_cast<uint32_t *>(s_d);
+        for (int q = tid; q < m; q += BLOCK) s_v[q] = S.val[b + q];
+        __syncthreads();
+        for (int q = tid; q < m; q += BLOCK) {
+            const uint32_t v = s_v[q];
+            int r = 0;
+#pragma unroll 8
+            for (int x = 0; x < m; ++x) r += s_v[x] < v ? 1 : 0;
+            s_v[BIGS + r] = v;
+        }
+        __syncthreads();
+        for (int q = tid; q < m; q += BLOCK) S.val[b + q] = s_v[BIGS + q];
+    } else {
+        // the low words of the keys are the cells; each thread takes KP consecutive particles
+        constexpr int KP = 8;
+        const uint32_t *cell = reinterpret_cast<const uint32_t *>(S.key);
+        int at = b;
+        for (int j0 = 0; j0 < S.n; j0 += KP * BLOCK) {
+            const int jb = j0 + tid * KP;
+            unsigned in = 0u;
+#pragma unroll
+            for (int q = 0; q < KP; ++q)
+                if (jb + q < S.n && ldg(cell + 2 * (size_t)(jb + q)) == (uint32_t)c) in |= 1u << q;
+            int tot;
+            int e = at + block_excl_scan(__popc(in), s_w, tot);
+            for (; in; in &= in - 1u) S.val[e++] = (uint32_t)(jb + __ffs(in) - 1);
+            at += tot;
+        }
+    }
+    __syncthreads();
+    double sum = 0.0;
+    int cnt = 0;
+    for (int q0 = 0; q0 < m; q0 += BLOCK) {
+        if (q0 + tid < m) {
+            double d[3];
+            cnt += centroid_member(S, o, w, last, S.val[b + q0 + tid], b + q0 + tid, c, sd, d);
+            for (int a = 0; a < 3; ++a) s_d[a][tid] = d[a];
+        }
+        __syncthreads();
+        if (tid < 3) {
+            const int e = min(BLOCK, m - q0);
+#pragma unroll 8
+            for (int q = 0; q < e; ++q) sum += s_d[tid][q];
+        }
+        __syncthreads();
+    }
+    atomicAdd(s_cnt, cnt);
+    __syncthreads();
+    if (tid < 3) {
+        const double v = centroid_moved(S, tid == 0 ? sd.x : (tid == 1 ? sd.y : sd.z), sum, *s_cnt, tid);
+        out[tid * stride] = v;
+        reinterpret_cast<double *>(S.seed + c)[tid] = v;
+    }
+    __syncthreads();
+}
+
 __global__ __launch_bounds__(BLOCK) void k_centroids(const SysDev *Sd, Maps L_maps, int it, int last) {
 #pragma clang fp contract(off)
     const int cbk = blockIdx.x / CB_BLOCKS;
     const int s = find_sys(L_maps.c, L_maps.nsys, cbk);
     const SysDev &S = Sd[s];
     if (!S.sc->rebuild) return;
-    __shared__ double s_d[3][CPB * CMEM];           // offsets; a big cell's members, then its offsets
+    __shared__ CentroidLds s_d;
     __shared__ uint32_t s_j[CPB][CMEM];
     __shared__ int s_big[CPB];
     __shared__ double s_c[3][CPB];
-    static_assert(sizeof(s_d) >= 2 * BIGS * sizeof(uint32_t), "a big cell's members");
+    __shared__ int s_w[16];
+    __shared__ int s_cnt;
     const int tid = threadIdx.x, g = tid / CELL_LANES, l = tid % CELL_LANES;
     const int sb = (cbk - L_maps.c[s]) * CB_BLOCKS + blockIdx.x % CB_BLOCKS;     // this block among its system's
     const int c = sb * CPB + g;
@@ -905,29 +1000,6 @@ __global__ __launch_bounds__(BLOCK) void k_centroids(const SysDev *Sd, Maps L_ma
     const Order o = order_of(S, it), w = order_of(S, it + 1);
     const int b = have ? S.cstart[c] : 0, m = have ? S.ccount[c] : 0;
     const D4 sd = S.seed[have ? c : 0];
-    // member j in place q of cell `cell`: its offset from the centroid, 0 if it does not count
-    auto member = [&](uint32_t j, int at, int cell, const D4 &sdc, double (&d)[3]) {
-        const V3 p = ldg(o.pos + j);
-        const uint8_t t = ldg(o.typ + j);
-        w.idx[at] = o.idx ? o.idx[j] : j;
-        if (!last) {
-            w.pos[at] = p;
-            w.typ[at] = t;
-        }
-        S.owner[at] = cell;
-        const bool use = ((t & TYP_MASK) == 0) == (cell < S.kl);
-        (void)dist2_exact(S, p.x, p.y, p.z, sdc.x, sdc.y, sdc.z, d[0], d[1], d[2]);
-        if (!use) d[0] = d[1] = d[2] = 0.0;
-        return use ? 1 : 0;
-    };
-    // the centroid's coordinate a from the sum
-    auto moved = [&](double x, double sum, int cnt, int a) {
-        if (cnt > 0) {
-            x = x + sum / (double)cnt;
-            if (S.per[a]) x = x - S.box[a] * floor(x / S.box[a]);
-        }
-        return x;
-    };
     if (l == 0) s_big[g] = m > CMEM ? m : 0;
     double mine = l == 0 ? sd.x : (l == 1 ? sd.y : sd.z);      // lanes 0 to 2: the centroid
     if (m <= CMEM) {
@@ -950,7 +1022,7 @@ __global__ __launch_bounds__(BLOCK) void k_centroids(const SysDev *Sd, Maps L_ma
         for (int r = 0; r < R; ++r)
             if (l + r * CELL_LANES < m) {
                 double d[3];
-                cnt += member(j[r], b + rk[r], c, sd, d);
+                cnt += centroid_member(S, o, w, last, j[r], b + rk[r], c, sd, d);
                 for (int a = 0; a < 3; ++a) s_d[a][g * CMEM + rk[r]] = d[a];
             }
         wave_fence();
@@ -959,7 +1031,7 @@ __global__ __launch_bounds__(BLOCK) void k_centroids(const SysDev *Sd, Maps L_ma
             double sum = 0.0;
 #pragma unroll 4
             for (int q = 0; q < m; ++q) sum += s_d[l][g * CMEM + q];
-            mine = moved(mine, sum, cnt, l);
+            mine = centroid_moved(S, mine, sum, cnt, l);
         }
     }
     if (l < 3) {
@@ -967,60 +1039,8 @@ __global__ __launch_bounds__(BLOCK) void k_centroids(const SysDev *Sd, Maps L_ma
         if (have && m <= CMEM) reinterpret_cast<double *>(S.seed + c)[l] = mine;
     }
     __syncthreads();
-    for (int h = 0; h < CPB; ++h) {
-        const int mb = s_big[h];
-        if (mb == 0) continue;                      // block-uniform
-        __shared__ int s_w[16];
-        __shared__ int s_cnt;
-        const int cb = sb * CPB + h, bb = S.cstart[cb];
-        const D4 sdb = S.seed[cb];
-        if (tid == 0) s_cnt = 0;
-        if (mb <= BIGS) {
-            uint32_t *s_v = reinterpret_cast<uint32_t *>(s_d);
-            for (int q = tid; q < mb; q += BLOCK) s_v[q] = S.val[bb + q];
-            __syncthreads();
-            for (int q = tid; q < mb; q += BLOCK) {
-                const uint32_t v = s_v[q];
-                int r = 0;
-                for (int x = 0; x < mb; ++x) r += s_v[x] < v ? 1 : 0;
-                s_v[BIGS + r] = v;
-            }
-            __syncthreads();
-            for (int q = tid; q < mb; q += BLOCK) S.val[bb + q] = s_v[BIGS + q];
-        } else {
-            int at = bb;
-            for (int j0 = 0; j0 < S.n; j0 += BLOCK) {
-                const int j = j0 + tid;
-                const int in = j < S.n && (int)(S.key[j] & 0xffffffffu) == cb ? 1 : 0;
-                int tot;
-                const int ex = block_excl_scan(in, s_w, tot);
-                if (in) S.val[at + ex] = (uint32_t)j;
-                at += tot;
-            }
-        }
-        __syncthreads();
-        double sum = 0.0;
-        int cnt = 0;
-        for (int q0 = 0; q0 < mb; q0 += BLOCK) {
-            if (q0 + tid < mb) {
-                double d[3];
-                cnt += member(S.val[bb + q0 + tid], bb + q0 + tid, cb, sdb, d);
-                for (int a = 0; a < 3; ++a) s_d[a][tid] = d[a];
-            }
-            __syncthreads();
-            if (tid < 3)
-                for (int q = 0; q < min(BLOCK, mb - q0); ++q) sum += s_d[tid][q];
-            __syncthreads();
-        }
-        atomicAdd(&s_cnt, cnt);
-        __syncthreads();
-        if (tid < 3) {
-            const double v = moved(tid == 0 ? sdb.x : (tid == 1 ? sdb.y : sdb.z), sum, s_cnt, tid);
-            s_c[tid][h] = v;
-            reinterpret_cast<double *>(S.seed + cb)[tid] = v;
-        }
-        __syncthreads();
-    }
+    for (int h = 0; h < CPB; ++h)
+        if (s_big[h]) centroid_by_block(S, o, w, last, sb * CPB + h, s_d, s_w, &s_cnt, &s_c[0][h], CPB);   // block-uniform
     // the block's box (16 centroids: the first row of lanes)
     if (tid < WAVE) {
         const bool in = sb * CPB + (tid & 15) < S.k;
@@ -1034,14 +1054,38 @@ __global__ __launch_bounds__(BLOCK) void k_centroids(const SysDev *Sd, Maps L_ma
     }
 }
 
+// The same with a block per cell (BLOCK of them to a block of the cell map), for large cells.
+// The centroids' boxes are taken by k_seed_bbox_partial.
+__global__ __launch_bounds__(BLOCK) void k_centroids_wide(const SysDev *Sd, Maps L_maps, int it, int last) {
+    const int cbk = blockIdx.x / BLOCK;
+    const int s = find_sys(L_maps.c, L_maps.nsys, cbk);
+    const SysDev &S = Sd[s];
+    if (!S.sc->rebuild) return;
+    __shared__ CentroidLds s_d;
+    __shared__ double s_c[3];
+    __shared__ int s_w[16];
+    __shared__ int s_cnt;
+    const int c = (cbk - L_maps.c[s]) * BLOCK + blockIdx.x % BLOCK;
+    if (c >= S.k) return;
+    centroid_by_block(S, order_of(S, it), order_of(S, it + 1), last, c, s_d, s_w, &s_cnt, s_c, 1);
+}
+
+// Boxes of the moved centroids to a 256-cell block of the cell map.
+static int seed_boxes(const LaunchCtx &L) { return L.wide ? 1 : CB_BLOCKS; }
+
 // One k-means iteration: the seed grid (unless it stands), the particles' cells and the
 // centroids' means.
 void launch_iteration(const LaunchCtx &L, int it, bool warm, bool last) {
-    if (it > 0) grid_build(L, CB_BLOCKS);
+    if (it > 0) grid_build(L, seed_boxes(L));
     hipLaunchKernelGGL(k_assign, dim3(L.nblk_p), dim3(BLOCK), 0, L.st, L.S, L.maps, it, warm ? 1 : 0);
     launch_scan(L, 2);
     hipLaunchKernelGGL(k_cell_place, dim3(L.nblk_p), dim3(BLOCK), 0, L.st, L.S, L.maps);
-    hipLaunchKernelGGL(k_centroids, dim3(CB_BLOCKS * L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps, it, last ? 1 : 0);
+    if (L.wide) {
+        hipLaunchKernelGGL(k_centroids_wide, dim3(BLOCK * L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps, it, last ? 1 : 0);
+        hipLaunchKernelGGL(k_seed_bbox_partial, dim3(L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps);
+    } else {
+        hipLaunchKernelGGL(k_centroids, dim3(CB_BLOCKS * L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps, it, last ? 1 : 0);
+    }
 }
 
 // ------------------------------------------------------------------ Morton order of centroids
@@ -1154,14 +1198,13 @@ static void radix_sort_seeds(const LaunchCtx &L) {
     }
 }
 
-// The seeds' boxes into the Morton keys' frame (the centroid kernel leaves one box per
-// CELL_LANES-lane block).
-__global__ void k_seed_bbox(const SysDev *Sd, int nsys) {
+// The seeds' boxes, sper to a 256-cell block of the cell map, into the Morton keys' frame.
+__global__ void k_seed_bbox(const SysDev *Sd, int sper) {
     const SysDev &S = Sd[blockIdx.x];
     if (!S.sc->rebuild) return;
     __shared__ double s_mn[3][16], s_mx[3][16];
     double mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
-    const int nsb = CB_BLOCKS * ((S.k + BLOCK - 1) / BLOCK);
+    const int nsb = sper * ((S.k + BLOCK - 1) / BLOCK);
     for (int b = threadIdx.x; b < nsb; b += blockDim.x) {
         const double *r = S.sbox + (size_t)b * 6;
         for (int a = 0; a < 3; ++a) { mn[a] = fmin(mn[a], r[a]); mx[a] = fmax(mx[a], r[3 + a]); }
@@ -1263,19 +1306,21 @@ __global__ void k_seed_permute(const SysDev *Sd, Maps L_maps, int ranks) {
 }
 
 // The particles move to their renumbered cells, in the last iteration's order within a cell,
-// CELL_LANES lanes per cell (the whole block for cells of more than CMEM members).  With the
+// CELL_LANES lanes per cell (the whole block for cells of more than CMEM members; with `wide`
+// each cell has a block of its own, as in k_centroids_wide).  With the
 // members at hand, each cell's radius about its new centroid.  Bound by its scattered reads
 // of whole records (333 us for 0.8 GB at 4M particles).
-__global__ __launch_bounds__(BLOCK) void k_move(const SysDev *Sd, Maps L_maps, int iters) {
-    const int cbk = blockIdx.x / CB_BLOCKS;
+__global__ __launch_bounds__(BLOCK) void k_move(const SysDev *Sd, Maps L_maps, int iters, int wide) {
+    const int per = wide ? BLOCK : CB_BLOCKS;       // blocks to one of the cell map
+    const int cbk = blockIdx.x / per;
     const int s = find_sys(L_maps.c, L_maps.nsys, cbk);
     const SysDev &S = Sd[s];
     if (!S.sc->rebuild) return;
     __shared__ int s_big[CPB];
     __shared__ double s_r[BLOCK / WAVE];
     const int tid = threadIdx.x, g = tid / CELL_LANES, l = tid % CELL_LANES;
-    const int c0 = ((cbk - L_maps.c[s]) * CB_BLOCKS + blockIdx.x % CB_BLOCKS) * CPB, c = c0 + g;
-    const bool have = c < S.k;
+    const int c0 = ((cbk - L_maps.c[s]) * per + blockIdx.x % per) * (wide ? 1 : CPB), c = c0 + g;
+    const bool have = c < S.k && (!wide || g == 0);
     const uint32_t *idx = order_of(S, iters).idx;
     auto one = [&](int from, int to, int cn, const D4 &sd) {
         const uint32_t i = ldg(idx + from);
@@ -1295,9 +1340,10 @@ __global__ __launch_bounds__(BLOCK) void k_move(const SysDev *Sd, Maps L_maps, i
     };
     const int b = have ? S.cstart[c] : 0, m = have ? S.ccount[c] : 0;
     const int cn = have ? S.cmap[c] : 0;
-    if (l == 0) s_big[g] = m > CMEM ? m : 0;
+    const bool big = have && (wide || m > CMEM);
+    if (l == 0) s_big[g] = big ? m : -1;
     double r2 = 0.0;
-    if (m <= CMEM && have) {
+    if (have && !big) {
         const D4 sd = S.seed[c];
         const int to = S.cstart2[cn];
         for (int q = l; q < m; q += CELL_LANES) r2 = fmax(r2, one(b + q, to + q, cn, sd));
@@ -1307,7 +1353,7 @@ __global__ __launch_bounds__(BLOCK) void k_move(const SysDev *Sd, Maps L_maps, i
     __syncthreads();
     for (int h = 0; h < CPB; ++h) {
         const int mb = s_big[h];
-        if (mb == 0) continue;                      // block-uniform
+        if (mb < 0) continue;                       // block-uniform
         const int cb = c0 + h, cnb = S.cmap[cb], from = S.cstart[cb], to = S.cstart2[cnb];
         const D4 sd = S.seed[cb];
         double rb = 0.0;
@@ -1347,15 +1393,16 @@ __global__ void k_cell_commit(const SysDev *Sd, Maps L_maps, SysDev *t0, SysDev 
 // the new centroids' grid.
 void launch_renumber(const LaunchCtx &L, int iters) {
     const bool ranks = L.kmax <= RANK_MAX;
-    hipLaunchKernelGGL(k_seed_bbox, dim3(L.nsys), dim3(1024), 0, L.st, L.S, L.nsys);
+    hipLaunchKernelGGL(k_seed_bbox, dim3(L.nsys), dim3(1024), 0, L.st, L.S, seed_boxes(L));
     hipLaunchKernelGGL(k_morton, dim3(L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps);
     if (ranks) hipLaunchKernelGGL(k_rank_seeds, dim3(RANK_SEGS * L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps);
     else radix_sort_seeds(L);
     hipLaunchKernelGGL(k_seed_permute, dim3(L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps, ranks ? 1 : 0);
     launch_scan(L, 1);
-    hipLaunchKernelGGL(k_move, dim3(CB_BLOCKS * L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps, iters);
+    hipLaunchKernelGGL(k_move, dim3((L.wide ? BLOCK : CB_BLOCKS) * L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps, iters,
+                       L.wide ? 1 : 0);
     hipLaunchKernelGGL(k_cell_commit, dim3(L.nblk_c), dim3(BLOCK), 0, L.st, L.S, L.maps, L.tables[0], L.tables[1]);
-    grid_build(L, CB_BLOCKS);
+    grid_build(L, seed_boxes(L));
 }
 
 // ------------------------------------------------------------------ cell radii and cell pairs

@@ -401,6 +401,7 @@ rbc_status refresh_tables(rbc_ctx *h) {
     L.kmin = kmin;
     L.kmax = kmax;
     L.gmax = gmax;
+    L.wide = h->prm.cell_target >= WIDE_CELLS;
     L.nblk_p = mp[ns];
     L.nblk_c = mc[ns];
     L.nblk_ts = mts[ns];

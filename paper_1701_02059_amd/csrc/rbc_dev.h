@@ -15,6 +15,11 @@ constexpr int MAXNB = 96;             // neighbour-list rows per chunk
 constexpr int TYP_MASK = 3;
 constexpr int TYP_BONDED = 0x80;
 constexpr int CELL_LANES = 16;         // lanes per cell in the kernels that go through cells' members
+// Cells that hold this many particles on average get a block each in the update: CELL_LANES lanes
+// hold at most 64 members, and one block took the larger cells among its sixteen in turn (loading
+// 125 thousand particles 2.6 ms at 56 and 27 at 1000; with a block each 1.8 and 9.0; at 40 the
+// lanes 1.7 and the blocks 1.8, at 1M particles 7.5 and 8.5).
+constexpr int WIDE_CELLS = 56;
 constexpr int SORT_IPT = 16;          // items per thread in the radix sort
 constexpr int SORT_TILE = BLOCK * SORT_IPT;
 constexpr int MAX_SLOTS = 256;
@@ -386,6 +391,7 @@ struct LaunchCtx {
     int32_t nsys;
     int32_t kmin, kmax;      // fewest and most cells of a system in the launch
     int32_t gmax;            // most seed-grid cells (capacity) of one
+    int32_t wide;            // cells hold many particles on average: a block per cell (WIDE_CELLS)
     DevParams prm;
     hipStream_t st;
 };
