@@ -1861,7 +1861,9 @@ __device__ __forceinline__ int union_cell(const int *ofs, int nsc, int u) {
 //    thousands of particles that are near none of its members: it is tested as one small
 //    sphere per member instead, where the block's spheres still fit 64 in all.  (One such
 //    cell had left its block of a deformed 125k-particle vesicle without a stage: 6.4 ms
-//    instead of 1.5 ms per 20 steps.)
+//    instead of 1.5 ms per 20 steps.)  Blocks of more than 64 own cells take runs of them as
+//    one sphere each.  Where large cells, of which the block holds a part, pass more than the
+//    stage holds, a second pass keeps only what is also near the boxes of the block's chunks.
 //  - Candidate lists: for each own cell the stage entries with its bit, compacted by one
 //    wavefront's ballots as 16-bit LDS offsets, lipids from the front, proteins from the
 //    back (neighbouring cells share a list where a block has more than 16).  Every
@@ -1881,10 +1883,10 @@ __device__ __forceinline__ int union_cell(const int *ofs, int nsc, int u) {
 // What bounds it is latency: three blocks of four wavefronts share a CU, and every phase is
 // a chain of loads, barriers and LDS reads, so each is written with as many of them side
 // by side as it has (four union particles, eight candidates, eight rows at a time).
-// Blocks whose stage does not fit, or with more than 64 own cells, keep 32-bit lists of
+// Blocks whose stage does not fit, or with more than CANDMAX cell pairs, keep 32-bit lists of
 // global slots (stage count -1), built on FP64 positions by a slow serial scan.
-constexpr int UCELLS = 512;           // candidate (union) cells per block
-constexpr int OWNMAX = 64;            // own cells of a staged block
+constexpr int UCELLS = CANDMAX;       // candidate (union) cells per block
+constexpr int OWNMAX = 64;            // spheres of a block's own cells
 constexpr int GROUPS = 16;            // candidate lists of a block
 constexpr int CLIST = 5120;           // candidate-list entries of those cells
 constexpr int MWORDS = 11;            // words of hit bits per lane (352 candidates)
@@ -1904,7 +1906,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
     __shared__ uint16_t s_q[USTAGE];                        // union position of every cell-pair entry; then the
                                                             // stage entries' own-list bits
     __shared__ F4 s_sph[OWNMAX];                            // spheres of the own cells: offset and widened radius
-    __shared__ uint16_t s_ibeg[OWNMAX];                     // an own cell's first sphere and their number
+    __shared__ uint16_t s_ibeg[OWNMAX];                     // the first sphere of an own cell (or run) and their number
+    __shared__ float s_box[BLOCK / WAVE][6];                // boxes of the chunks: centre, half width
     __shared__ int s_lofs[GROUPS + 1];
     __shared__ uint16_t s_nl[GROUPS], s_np[GROUPS];         // lipid and protein candidates of each list
     __shared__ int s_w[16];
@@ -1915,9 +1918,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
     int *s_cand = reinterpret_cast<int *>(s_raw + RX);
     int *s_ofs = s_cand + UCELLS;
     unsigned long long *s_mask = reinterpret_cast<unsigned long long *>(s_ofs + UCELLS + 2);
-    static_assert(RL >= (2 * UCELLS + 2) * (int)sizeof(int) + UCELLS * (int)sizeof(unsigned long long), "union arrays");
     uint16_t *s_list = reinterpret_cast<uint16_t *>(s_raw + RX);
-    uint16_t *s_self = reinterpret_cast<uint16_t *>(s_raw + RX + RL);
+    uint16_t *s_self = reinterpret_cast<uint16_t *>(s_raw + RX + RL + RM) - BLOCK;
+    static_assert(RL + RM - 2 * BLOCK >= (2 * UCELLS + 2) * (int)sizeof(int) + UCELLS * (int)sizeof(unsigned long long), "union arrays");
     unsigned *s_m = reinterpret_cast<unsigned *>(s_raw + RX + RL);
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int chunk = lb * (BLOCK / WAVE) + wv;
@@ -1948,7 +1951,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
     const int q0 = S.cnbr_start[c0];
     const int ncand = S.cnbr_start[c1 + 1] - q0;
     const int nown = c1 - c0 + 1;
-    bool have_union = !(ncand <= 0 || ncand > CANDMAX || c1 < c0 || nown > OWNMAX);
+    const bool have_union = !(ncand <= 0 || ncand > CANDMAX || c1 < c0);
+    // own cells to a sphere, 1 << rs (a cell pairs with itself: nown is at most CANDMAX)
+    int rs = 0;
+    while (have_union && (nown - 1) >> rs >= OWNMAX) ++rs;
+    const int nsph = ((nown - 1) >> rs) + 1;
     const bool periodic = (S.per[0] | S.per[1] | S.per[2]) != 0;
     const float Lx = S.per[0] ? (float)S.box[0] : 0.0f, Ly = S.per[1] ? (float)S.box[1] : 0.0f,
                 Lz = S.per[2] ? (float)S.box[2] : 0.0f;
@@ -2007,8 +2014,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
                 unsigned b = bm[w];
                 wpre[w] = r;
                 while (b) {
-                    if (r < UCELLS) s_cand[r] = mn + (w << 5) + (__ffs(b) - 1);
-                    ++r;
+                    s_cand[r++] = mn + (w << 5) + (__ffs(b) - 1);
                     b &= b - 1u;
                 }
             }
@@ -2048,16 +2054,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
             }
             int p = block_excl_scan(loc, s_w, nsc);
             for (int q = 0; q < CANDMAX / BLOCK; ++q)
-                if (fl[q]) {
-                    if (p < UCELLS) s_cand[p] = vals[q];
-                    ++p;
-                }
+                if (fl[q]) s_cand[p++] = vals[q];
             __syncthreads();
 #pragma unroll
             for (int k = 0; k < CANDMAX / BLOCK; ++k)
-                if (cv[k] >= 0) s_qpos[tid + k * BLOCK] = (uint16_t)lds_lower_bound(s_cand, min(nsc, UCELLS), cv[k]);
+                if (cv[k] >= 0) s_qpos[tid + k * BLOCK] = (uint16_t)lds_lower_bound(s_cand, nsc, cv[k]);
         }
-        have_union = nsc <= UCELLS;                  // block-uniform
         __syncthreads();
     }
     // ---- the stage
@@ -2089,7 +2091,22 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
         s.w = __int_as_float(((__float_as_int(s.w) + 16) & ~15) | g);
         return s;
     };
-    auto group_of = [&](int a) { return nown <= GROUPS ? a : a * GROUPS / nown; };
+    // candidate list of sphere a's own cells
+    auto group_of = [&](int a) { return nsph <= GROUPS ? a : a * GROUPS / nsph; };
+    // one sphere about own cells [a, e): centred on the middle one, round all that hold particles
+    auto run_sphere = [&](int a, int e) {
+        const D4 m = ldg(S.seed + c0 + ((a + e) >> 1));
+        double r = 0.0;
+        for (int c = a; c < e; ++c)
+            if (ldg(S.ccount + c0 + c) > 0) {
+                const D4 q = ldg(S.seed + c0 + c);
+                double dx, dy, dz;
+                r = fmax(r, q.w + sqrt(dist2_exact(S, m.x, m.y, m.z, q.x, q.y, q.z, dx, dy, dz)));
+            }
+        const float o[3] = {offset(0, m.x, ref.x), offset(1, m.y, ref.y), offset(2, m.z, ref.z)};
+        if (far(o)) s_big = 1;
+        return F4{o[0], o[1], o[2], (float)r + 2e-3f};
+    };
     // list radius of a candidate by its type (the largest over the own types)
     const float rlm0 = P.rlmaxf[0], rlm1 = P.rlmaxf[1], rlm2 = P.rlmaxf[2];
     int kept = 0;
@@ -2097,39 +2114,41 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
         constexpr int PER = UCELLS / BLOCK;
         static_assert(UCELLS == PER * BLOCK, "cells per thread");
         int ccnt[PER], loc = 0;
+#pragma unroll
         for (int q = 0; q < PER; ++q) {
             const int c = tid * PER + q;
             ccnt[q] = c < nsc ? ldg(S.ccount + s_cand[c]) : 0;
             loc += ccnt[q];
-            s_mask[c] = 0ull;
+            if (c < nsc) s_mask[c] = 0ull;
         }
         if (wv == 0) {
             // own cell `lane`: its first sphere, the number beyond one, and whether they are
             // its members'
             F4 sp = {0.0f, 0.0f, 0.0f, 0.0f};
             int m = 0;
-            if (lane < nown) {
-                sp = own_sphere(lane);
-                if (sp.w > WIDE * fmaxf(fmaxf(rlm0, rlm1), rlm2)) {
+            if (lane < nsph) {
+                sp = rs == 0 ? own_sphere(lane) : run_sphere(lane << rs, min(nown, (lane + 1) << rs));
+                if (rs == 0 && sp.w > WIDE * fmaxf(fmaxf(rlm0, rlm1), rlm2)) {
                     const int b = ldg(S.cstart + c0 + lane), e = b + ldg(S.ccount + c0 + lane);
                     m = max(min(e, last + 1) - max(b, first), 0);
                 }
             }
             const int room = wave_incl_scan(max(m - 1, 0));
-            const bool wide = m > 0 && room <= OWNMAX - nown;
+            const bool wide = m > 0 && room <= OWNMAX - nsph;
             const int more = wide ? m - 1 : 0;
             const int at = wave_incl_scan(more) - more + lane;
-            if (lane < nown) {
+            if (lane < nsph) {
                 s_ibeg[lane] = (uint16_t)(at | (more << 8) | (wide ? 0x8000 : 0));
                 if (!wide) s_sph[at] = tagged(sp, group_of(lane));
             }
         }
         int ex = block_excl_scan(loc, s_w, ss);
         if (valid) {
-            const int v = s_ibeg[A - c0];
+            const int v = s_ibeg[(A - c0) >> rs];
             if (v & 0x8000)
                 s_sph[(v & 255) + i - max(ldg(S.cstart + A), first)] = tagged(F4{oi[0], oi[1], oi[2], 2e-3f}, group_of(A - c0));
         }
+#pragma unroll
         for (int q = 0; q < PER; ++q) {
             const int c = tid * PER + q;
             if (c <= nsc) s_ofs[c] = ex;
@@ -2138,88 +2157,131 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
         if (tid == 0 && nsc == UCELLS) s_ofs[nsc] = ss;
         for (int a = wv; a < nown; a += BLOCK / WAVE) {
             const int b = ldg(S.cnbr_start + c0 + a) - q0, e = ldg(S.cnbr_start + c0 + a + 1) - q0;
-            const int v = s_ibeg[a];
+            const int v = s_ibeg[a >> rs];
             const unsigned long long bits = (~0ull >> (63 - ((v >> 8) & 127))) << (v & 255);
             for (int q = b + lane; q < e; q += WAVE) atomicOr(&s_mask[s_qpos[q]], bits);
         }
         __syncthreads();
         constexpr int SB = 4;                       // union particles per thread in flight
-        for (int u0 = 0; u0 < ss; u0 += SB * BLOCK) {
-            int c[SB], slot[SB];
-            float o[SB][3], rm[SB];
-            int t[SB];
-            D4 pj[SB];
-            unsigned lo[SB], hi[SB], om[SB], any = 0u, anyhi = 0u;
+        // whether an offset lies within the largest list radius of a chunk's box (a periodic axis
+        // of which the box spans a quarter or more counts as within)
+        const float rb = fmaxf(rlm0, fmaxf(rlm1, rlm2)) + 1e-3f;
+        auto near_boxes = [&](const float (&q)[3]) {
+            float best = INFINITY;
+            for (int w = 0; w < BLOCK / WAVE; ++w) {
+                float e2 = 0.0f;
 #pragma unroll
-            for (int k = 0; k < SB; ++k) {
-                const int u = u0 + k * BLOCK + tid;
-                c[k] = u < ss ? union_cell(s_ofs, nsc + 1, u) : -1;
-                slot[k] = c[k] >= 0 ? ldg(S.cstart + s_cand[c[k]]) + (u - s_ofs[c[k]]) : first;
+                for (int a = 0; a < 3; ++a) {
+                    const float L = a == 0 ? Lx : (a == 1 ? Ly : Lz), iL1 = a == 0 ? iLx : (a == 1 ? iLy : iLz);
+                    float d = q[a] - s_box[w][a];
+                    if (periodic) d -= L * rintf(d * iL1);
+                    const float e = fmaxf(fabsf(d) - s_box[w][3 + a], 0.0f);
+                    e2 += e * e;
+                }
+                best = fminf(best, e2);
             }
+            return best <= rb * rb;
+        };
+        for (bool boxes = false;; boxes = true) {
+            kept = 0;
+            for (int u0 = 0; u0 < ss; u0 += SB * BLOCK) {
+                int c[SB], slot[SB];
+                float o[SB][3], rm[SB];
+                int t[SB];
+                D4 pj[SB];
+                unsigned lo[SB], hi[SB], om[SB], any = 0u, anyhi = 0u;
 #pragma unroll
-            for (int k = 0; k < SB; ++k) pj[k] = ldpos(S, slot[k]);
+                for (int k = 0; k < SB; ++k) {
+                    const int u = u0 + k * BLOCK + tid;
+                    c[k] = u < ss ? union_cell(s_ofs, nsc + 1, u) : -1;
+                    slot[k] = c[k] >= 0 ? ldg(S.cstart + s_cand[c[k]]) + (u - s_ofs[c[k]]) : first;
+                }
 #pragma unroll
-            for (int k = 0; k < SB; ++k) {
-                o[k][0] = offset(0, pj[k].x, ref.x);
-                o[k][1] = offset(1, pj[k].y, ref.y);
-                o[k][2] = offset(2, pj[k].z, ref.z);
-                if (c[k] >= 0 && far(o[k])) s_big = 1;
-                t[k] = (int)pj[k].w & 3;
-                rm[k] = sel3f(t[k], rlm0, rlm1, rlm2);
-                const unsigned long long m = c[k] >= 0 ? s_mask[c[k]] : 0ull;
-                lo[k] = (unsigned)m;
-                hi[k] = (unsigned)(m >> 32);
-                om[k] = 0u;
-                any |= lo[k];
-                anyhi |= hi[k];
-            }
-            // the own cells' spheres, the four particles' next ones side by side
-            auto spheres = [&](unsigned (&m)[SB], unsigned more, int base) {
-                while (more) {
-                    more = 0u;
+                for (int k = 0; k < SB; ++k) pj[k] = ldpos(S, slot[k]);
 #pragma unroll
-                    for (int k = 0; k < SB; ++k) {
-                        const int a = base + (m[k] ? __ffs(m[k]) - 1 : 0);
-                        const F4 sp = s_sph[a];
-                        const float rr = sp.w + rm[k];
-                        if (m[k] && dist2f(sp.x, sp.y, sp.z, o[k][0], o[k][1], o[k][2]) <= rr * rr)
-                            om[k] |= 1u << (__float_as_int(sp.w) & 15);
-                        m[k] &= m[k] - 1u;
-                        more |= m[k];
+                for (int k = 0; k < SB; ++k) {
+                    o[k][0] = offset(0, pj[k].x, ref.x);
+                    o[k][1] = offset(1, pj[k].y, ref.y);
+                    o[k][2] = offset(2, pj[k].z, ref.z);
+                    if (c[k] >= 0 && far(o[k])) s_big = 1;
+                    t[k] = (int)pj[k].w & 3;
+                    rm[k] = sel3f(t[k], rlm0, rlm1, rlm2);
+                    const unsigned long long m = c[k] >= 0 ? s_mask[c[k]] : 0ull;
+                    lo[k] = (unsigned)m;
+                    hi[k] = (unsigned)(m >> 32);
+                    om[k] = 0u;
+                    any |= lo[k];
+                    anyhi |= hi[k];
+                }
+                // the own cells' spheres, the four particles' next ones side by side
+                auto spheres = [&](unsigned (&m)[SB], unsigned more, int base) {
+                    while (more) {
+                        more = 0u;
+#pragma unroll
+                        for (int k = 0; k < SB; ++k) {
+                            const int a = base + (m[k] ? __ffs(m[k]) - 1 : 0);
+                            const F4 sp = s_sph[a];
+                            const float rr = sp.w + rm[k];
+                            if (m[k] && dist2f(sp.x, sp.y, sp.z, o[k][0], o[k][1], o[k][2]) <= rr * rr)
+                                om[k] |= 1u << (__float_as_int(sp.w) & 15);
+                            m[k] &= m[k] - 1u;
+                            more |= m[k];
+                        }
+                    }
+                };
+                spheres(lo, any, 0);
+                spheres(hi, anyhi, 32);
+                if (boxes) {
+#pragma unroll
+                    for (int k = 0; k < SB; ++k)
+                        if (!near_boxes(o[k])) om[k] = 0u;
+                }
+                // places: by round, wavefront and lane (the union's order)
+                int rank[SB];
+#pragma unroll
+                for (int k = 0; k < SB; ++k) {
+                    const unsigned long long b = __ballot(om[k] != 0u);
+                    rank[k] = __popcll(b & ((1ull << lane) - 1ull));
+                    if (lane == 0) s_w[k * (BLOCK / WAVE) + wv] = __popcll(b);
+                }
+                static_assert(SB * (BLOCK / WAVE) == 16, "counts of a pass");
+                __syncthreads();
+                int run = kept;
+#pragma unroll
+                for (int k = 0; k < SB; ++k) {
+#pragma unroll
+                    for (int w = 0; w < BLOCK / WAVE; ++w) {
+                        if (w == wv) rank[k] += run;
+                        run += s_w[k * (BLOCK / WAVE) + w];
+                    }
+                    if (om[k] && rank[k] < USTAGE) {
+                        s_ux[rank[k]] = o[k][0];
+                        s_uy[rank[k]] = o[k][1];
+                        s_uz[rank[k]] = o[k][2];
+                        s_tf[rank[k]] = (unsigned char)t[k];
+                        s_om[rank[k]] = (uint16_t)om[k];
+                        stg(S.stage + (size_t)lb * SSTRIDE + rank[k], stage_entry(slot[k], t[k]));
+                        if ((unsigned)(slot[k] - first) < (unsigned)BLOCK) s_self[slot[k] - first] = (uint16_t)rank[k];
                     }
                 }
-            };
-            spheres(lo, any, 0);
-            spheres(hi, anyhi, 32);
-            // places: by round, wavefront and lane (the union's order)
-            int rank[SB];
-#pragma unroll
-            for (int k = 0; k < SB; ++k) {
-                const unsigned long long b = __ballot(om[k] != 0u);
-                rank[k] = __popcll(b & ((1ull << lane) - 1ull));
-                if (lane == 0) s_w[k * (BLOCK / WAVE) + wv] = __popcll(b);
+                kept = run;                              // (beyond USTAGE: no stage)
+                __syncthreads();
             }
-            static_assert(SB * (BLOCK / WAVE) == 16, "counts of a pass");
-            __syncthreads();
-            int run = kept;
+            if (kept <= USTAGE || boxes) break;     // block-uniform
+            // the chunks' boxes, and the stage once more
 #pragma unroll
-            for (int k = 0; k < SB; ++k) {
-#pragma unroll
-                for (int w = 0; w < BLOCK / WAVE; ++w) {
-                    if (w == wv) rank[k] += run;
-                    run += s_w[k * (BLOCK / WAVE) + w];
+            for (int a = 0; a < 3; ++a) {
+                float mn = valid ? oi[a] : INFINITY, mx = valid ? oi[a] : -INFINITY;
+                for (int x = 32; x > 0; x >>= 1) {
+                    mn = fminf(mn, __shfl_xor(mn, x));
+                    mx = fmaxf(mx, __shfl_xor(mx, x));
                 }
-                if (om[k] && rank[k] < USTAGE) {
-                    s_ux[rank[k]] = o[k][0];
-                    s_uy[rank[k]] = o[k][1];
-                    s_uz[rank[k]] = o[k][2];
-                    s_tf[rank[k]] = (unsigned char)t[k];
-                    s_om[rank[k]] = (uint16_t)om[k];
-                    stg(S.stage + (size_t)lb * SSTRIDE + rank[k], stage_entry(slot[k], t[k]));
-                    if ((unsigned)(slot[k] - first) < (unsigned)BLOCK) s_self[slot[k] - first] = (uint16_t)rank[k];
+                const float L = a == 0 ? Lx : (a == 1 ? Ly : Lz), half = 0.5f * (mx - mn) + 1e-3f;
+                if (lane == 0) {
+                    s_box[wv][a] = mn <= mx ? 0.5f * (mn + mx) : 0.0f;
+                    s_box[wv][3 + a] = !(mn <= mx) ? -INFINITY : (L > 0.0f && !(4.0f * (half + rb) < L) ? INFINITY : half);
                 }
             }
-            kept = run;                              // (beyond USTAGE: no stage)
             __syncthreads();
         }
     }
@@ -2236,7 +2298,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
         const float rlA = P.rl2f[ti][0], rlB = P.rl2f[ti][1], rlC = P.rl2f[ti][2];
         const float riA = P.rin2f[ti][0], riB = P.rin2f[ti][1], riC = P.rin2f[ti][2];
         const int oself = valid ? 4 * (int)s_self[tid] : -1;     // this particle's own stage entry (LDS offset)
-        const int G = min(nown, GROUPS), mygrp = group_of(A - c0);
+        const int G = min(nsph, GROUPS), mygrp = group_of((A - c0) >> rs);
         auto ux = [&](int o) { return *reinterpret_cast<const float *>(s_raw + o); };
         auto uy = [&](int o) { return *reinterpret_cast<const float *>(s_raw + 4 * USTAGE + o); };
         auto uz = [&](int o) { return *reinterpret_cast<const float *>(s_raw + 8 * USTAGE + o); };
