@@ -1476,48 +1476,62 @@ void launch_volume_reduce(const LaunchCtx &L, bool record) {
 
 // ------------------------------------------------------------------ outputs in caller order
 
-// The state in the caller's order, a thread per caller id: scattered reads of whole records
-// and coalesced writes.  (A thread per slot scattered the writes, and lines written in parts
-// went to memory more than once: 733 MB for 384 and 640 us at 4M particles.)
-__global__ void k_gather_state(const SysDev *Sd, int s, double *x, double *n, double *v, double *w) {
+// The state and forces in the caller's order: a thread per slot (coalesced reads, scattered
+// writes) or a thread per caller id (scattered reads, coalesced writes).  Scattered writes are
+// complete lines by the time they leave the caches as long as the frame stays there: 35 us
+// against 45 for the state of 500k particles, 67 against 90 at 1M, 81 against 109 at 1.2M, but
+// 198 against 133 at 1.5M and 679 against 327 at 4M (forces: 19, 35, 44 against 23, 45, 55; 86
+// against 78 at 1.8M).  Below 60 thousand particles the reads by id are the shorter chain (5.4
+// and 6.8 us at 56 thousand).
+constexpr int OUT_SCATTER_MIN = 1 << 16, OUT_SCATTER_MAX = 5 << 18;
+static bool scatters(int count) { return count >= OUT_SCATTER_MIN && count <= OUT_SCATTER_MAX; }
+
+// N arrays of 3-vectors from slot i to caller id g, the loads side by side
+template <int N>
+__device__ __forceinline__ void copy_out(const V3 *const (&src)[N], double *const (&dst)[N], int i, int g) {
+    V3 r[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+        if (dst[k]) r[k] = ldg(src[k] + i);
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+        if (dst[k]) st3(reinterpret_cast<V3 *>(dst[k]) + g, D4{r[k].x, r[k].y, r[k].z, 0.0});
+}
+
+template <int SCATTER>
+__global__ void k_out_state(const SysDev *Sd, int s, double *x, double *n, double *v, double *w) {
     const SysDev &S = Sd[s];
-    const int g = blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= S.n) return;
-    const int i = ldg(S.slot + g);
-    V3 p{}, o{}, u{}, a{};
-    if (x) p = ldg(S.pos + i);
-    if (n) o = ldg(S.ori + i);
-    if (v) u = ldg(S.vel + i);
-    if (w) a = ldg(S.angv + i);
-    auto put = [&](double *out, const V3 &q) {
-        if (out) st3(reinterpret_cast<V3 *>(out) + g, D4{q.x, q.y, q.z, 0.0});
-    };
-    put(x, p);
-    put(n, o);
-    put(v, u);
-    put(w, a);
+    const int q = blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= S.n) return;
+    const int p = ldg((SCATTER ? S.gid : S.slot) + q);
+    const V3 *const src[4] = {S.pos, S.ori, S.vel, S.angv};
+    double *const dst[4] = {x, n, v, w};
+    copy_out(src, dst, SCATTER ? q : p, SCATTER ? p : q);
 }
 
-void launch_gather_state(const LaunchCtx &L, int sys, double *x, double *n, double *v, double *w, int count) {
+void launch_out_state(const LaunchCtx &L, int sys, double *x, double *n, double *v, double *w, int count) {
     if (count <= 0) return;
-    hipLaunchKernelGGL(k_gather_state, dim3((count + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, L.st, L.S, sys, x, n, v, w);
+    const dim3 grid((count + BLOCK - 1) / BLOCK);
+    if (scatters(count)) hipLaunchKernelGGL(k_out_state<1>, grid, dim3(BLOCK), 0, L.st, L.S, sys, x, n, v, w);
+    else hipLaunchKernelGGL(k_out_state<0>, grid, dim3(BLOCK), 0, L.st, L.S, sys, x, n, v, w);
 }
 
-__global__ void k_gather_forces(const SysDev *Sd, int s, double *F, double *T) {
+template <int SCATTER>
+__global__ void k_out_forces(const SysDev *Sd, int s, double *F, double *T) {
     const SysDev &S = Sd[s];
-    const int g = blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= S.n) return;
-    const int i = ldg(S.slot + g);
-    V3 f{}, t{};
-    if (F) f = ldg(S.frc + i);
-    if (T) t = ldg(S.trq + i);
-    if (F) st3(reinterpret_cast<V3 *>(F) + g, D4{f.x, f.y, f.z, 0.0});
-    if (T) st3(reinterpret_cast<V3 *>(T) + g, D4{t.x, t.y, t.z, 0.0});
+    const int q = blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= S.n) return;
+    const int p = ldg((SCATTER ? S.gid : S.slot) + q);
+    const V3 *const src[2] = {S.frc, S.trq};
+    double *const dst[2] = {F, T};
+    copy_out(src, dst, SCATTER ? q : p, SCATTER ? p : q);
 }
 
-void launch_gather_forces(const LaunchCtx &L, int sys, double *F, double *T, int count) {
+void launch_out_forces(const LaunchCtx &L, int sys, double *F, double *T, int count) {
     if (count <= 0) return;
-    hipLaunchKernelGGL(k_gather_forces, dim3((count + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, L.st, L.S, sys, F, T);
+    const dim3 grid((count + BLOCK - 1) / BLOCK);
+    if (scatters(count)) hipLaunchKernelGGL(k_out_forces<1>, grid, dim3(BLOCK), 0, L.st, L.S, sys, F, T);
+    else hipLaunchKernelGGL(k_out_forces<0>, grid, dim3(BLOCK), 0, L.st, L.S, sys, F, T);
 }
 
 // ------------------------------------------------------------------ neighbour-set export

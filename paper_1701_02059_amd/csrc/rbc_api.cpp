@@ -1334,7 +1334,7 @@ static rbc_status forces_slot(rbc_handle h, int32_t slot, double *F, double *T, 
         Scope sc(h);
         force_launch(h, energy != nullptr, 0, 0.0);
         h->forces_valid = true;
-        launch_gather_forces(h->L, slot, F, T, (int)hs.n);
+        launch_out_forces(h->L, slot, F, T, (int)hs.n);
         if (energy) {
             launch_reduce_energy(h->L);
             // U and W are the first two entries of the system's energy record
@@ -1378,7 +1378,7 @@ static rbc_status state_slot(rbc_handle h, int32_t slot, double *x, double *nrm,
     if (slot < 0 || slot >= h->max_slots || !h->sys[slot].live) return fail(h, RBC_ERR_NOT_READY, "slot not live");
     if (h->sys[slot].failed != RBC_OK) return fail(h, h->sys[slot].failed, "slot failed: " + h->sys[slot].why);
     Scope sc(h);
-    launch_gather_state(h->L, slot, x, nrm, v, w, (int)h->sys[slot].n);
+    launch_out_state(h->L, slot, x, nrm, v, w, (int)h->sys[slot].n);
     return RBC_OK;
 }
 

@@ -403,8 +403,8 @@ void launch_force(const LaunchCtx &L, int mixed, int energy, int kick, double dt
 void launch_reduce_energy(const LaunchCtx &L);
 void launch_volume_partials(const LaunchCtx &L);          // lipid sums of the current state, per chunk
 void launch_volume_reduce(const LaunchCtx &L, bool record);   // lipid sums -> V (record: into the system's record)
-void launch_gather_state(const LaunchCtx &L, int sys, double *x, double *n, double *v, double *w, int count);
-void launch_gather_forces(const LaunchCtx &L, int sys, double *F, double *T, int count);
+void launch_out_state(const LaunchCtx &L, int sys, double *x, double *n, double *v, double *w, int count);
+void launch_out_forces(const LaunchCtx &L, int sys, double *F, double *T, int count);
 // the sorted pairs of a system: count them (the number ends in its hist, as 64 bits, at
 // the index returned), then write the first cap of them
 int64_t launch_pair_count(const LaunchCtx &L, int sys, int count);
