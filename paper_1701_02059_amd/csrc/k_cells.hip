@@ -2267,8 +2267,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
                 kept = run;                              // (beyond USTAGE: no stage)
                 __syncthreads();
             }
-            if (kept <= USTAGE || boxes) break;     // block-uniform
-            // the chunks' boxes, and the stage once more
+            // the chunks' boxes, and the stage once more, where the own cells have at least as many
+            // members outside the block (a block that holds its cells whole gains nothing: 20
+            // thousand vesicle particles with protein cells, an update 544 us, 612 with it)
+            if (kept <= USTAGE || boxes) break;     // block-uniform, as is what follows
+            if (ldg(S.cstart + c1) + ldg(S.ccount + c1) - ldg(S.cstart + c0) < 2 * BLOCK) break;
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 float mn = valid ? oi[a] : INFINITY, mx = valid ? oi[a] : -INFINITY;
