@@ -133,7 +133,7 @@ rbc_status rbc_create(const rbc_params *params, void *hip_stream, rbc_handle *ou
  * particle ids; r0: nbond rest lengths.  [host] box[3] lengths and periodic[3]
  * flags (1 = periodic axis; box ignored on open axes).  Periodic lengths must
  * exceed twice the largest cutoff plus skin.  0 <= n <= 2^29; n = 0 clears the
- * context and returns its memory (otherwise kept for a next system of the same size).
+ * context.
  * Builds the initial Voronoi cells (params.lloyd_iters k-means iterations). */
 rbc_status rbc_set_system(rbc_handle h, int64_t n, const double *x, const double *nrm,
                           const int32_t *type, const double *v, const double *w,
@@ -290,9 +290,7 @@ rbc_status rbc_ensemble_step(rbc_handle h, int64_t nsteps, double dt);
 rbc_status rbc_ensemble_get_state(rbc_handle h, int32_t slot, double *x, double *nrm, double *v, double *w);
 /* Energies of one slot ([host] out[7] as rbc_energy). */
 rbc_status rbc_ensemble_energy(rbc_handle h, int32_t slot, double *out);
-/* Free a slot.  Its memory serves later systems of the same size on this handle, which
- * never holds more than its live systems held at one time (nor more than the budget);
- * rbc_destroy returns it. */
+/* Free a slot and its memory. */
 rbc_status rbc_ensemble_retire(rbc_handle h, int32_t slot);
 /* Slots frozen by an error (ensemble contexts).  When a slot's lists overflow
  * (RBC_ERR_CAPACITY), its state turns non-finite (RBC_ERR_NONFINITE) or a particle

@@ -97,13 +97,9 @@ struct rbc_ctx {
     const int32_t **d_lip = nullptr;
     char *h_tab = nullptr;            // pinned copy of d_sys, d_maps and d_lip, which are one allocation
     size_t tab_bytes = 0;
-    // memory of released systems, kept for the next ones (keep_block)
-    struct Block {
-        void *mem;
-        size_t bytes;
-    };
-    std::vector<Block> spare;
-    size_t spare_bytes = 0, held = 0, peak = 0;      // in blocks: kept, of live systems, the most of live systems
+    // the memory of the system that the running rbc_set_system replaces (else none)
+    void *spare = nullptr;
+    size_t spare_bytes = 0;
     SysScal *h_sc = nullptr;          // pinned mirror of the per-system scalars (read after a sync)
     StepStat *h_stat = nullptr, *d_stat = nullptr;   // published drift statistics: host / device view
     int par = 0;                      // the current descriptor table
@@ -111,7 +107,6 @@ struct rbc_ctx {
     int32_t nsys = 0;                 // descriptors in use (highest live slot + 1)
     bool forces_valid = false;
     bool vol_fresh = false;          // the per-chunk lipid sums describe the current state of every system
-    int sticky = RBC_OK;
     std::string err;
     int64_t ens_steps = 0;
     // captured launch sequences (replayed while the system table and dt are unchanged)
@@ -931,66 +926,30 @@ size_t footprint(const rbc_ctx *h, int64_t n, int64_t nlip, int64_t nbond) {
     return layout(tmp, nullptr);
 }
 
-void release(rbc_ctx *h, int32_t slot, bool refresh = true);
+void release(rbc_ctx *h, int32_t slot, bool replaced = false);
 
-// Systems come and go (frames of one system loaded in turn, requests served in bursts), and
-// an allocation and its release take 350 us of the host's time for a 125k-particle system,
-// most of it the release.  The memory of a released system is kept for the next one of the
-// same size: the driver hands memory out in units of BLOCK_UNIT, so a block is used again by
-// systems whose footprint rounds to the same number of units, and nothing is wasted in it.
-// The handle never holds more in all than its live systems held at one time, nor more than
-// SPARE_MAX beside them, nor more than the admission budget; rbc_destroy returns it, and
-// rbc_set_system without particles.  A block is kept only after the handle's stream, which
-// alone uses it, is idle.
-constexpr size_t BLOCK_UNIT = size_t(2) << 20;
-constexpr size_t SPARE_MAX = size_t(16) << 30;
-size_t block_bytes(size_t bytes) { return (bytes + BLOCK_UNIT - 1) / BLOCK_UNIT * BLOCK_UNIT; }
-
-// Free kept blocks, the oldest first, until `room` bytes of them remain at most.
-void trim_spare(rbc_ctx *h, size_t room) {
-    size_t q = 0;
-    for (; q < h->spare.size() && h->spare_bytes > room; ++q) {
-        hipFree(h->spare[q].mem);
-        h->spare_bytes -= h->spare[q].bytes;
-    }
-    h->spare.erase(h->spare.begin(), h->spare.begin() + (ptrdiff_t)q);
+// Frames of one system are loaded in turn, and an allocation and its release take 310 us of the
+// host's time from 128 MB on (125 thousand particles; 25 us up to 64 MB), nearly all of it the
+// release.  rbc_set_system hands the memory of the system it replaces to the new one where
+// both need the same number of bytes, and frees it before the new one's allocation otherwise.
+// Nothing is kept beyond the call: the handle holds its live systems' memory and no more.
+void drop_spare(rbc_ctx *h) {
+    if (h->spare) hipFree(h->spare);
+    h->spare = nullptr;
+    h->spare_bytes = 0;
 }
 
-size_t spare_room(const rbc_ctx *h) {
-    size_t room = std::min(SPARE_MAX, h->peak > h->held ? h->peak - h->held : 0);
-    if (h->budget > 0) room = std::min(room, (size_t)std::max<int64_t>(0, h->budget - (int64_t)h->held));
-    return room;
-}
-
-// Memory for a system of `bytes`: a kept block of its size, or a new one (nullptr: none left).
-void *take_block(rbc_ctx *h, size_t bytes) {
-    const size_t want = block_bytes(bytes);
+void *take_memory(rbc_ctx *h, size_t bytes) {
     void *mem = nullptr;
-    for (size_t q = h->spare.size(); q-- > 0 && !mem;)
-        if (h->spare[q].bytes == want) {
-            mem = h->spare[q].mem;
-            h->spare_bytes -= want;
-            h->spare.erase(h->spare.begin() + (ptrdiff_t)q);
-        }
-    h->held += want;
-    h->peak = std::max(h->peak, h->held);
-    if (mem) return mem;
-    trim_spare(h, spare_room(h));
-    if (hipMalloc(&mem, want) == hipSuccess) return mem;
-    hipGetLastError();
-    trim_spare(h, 0);
-    if (hipMalloc(&mem, want) == hipSuccess) return mem;
-    hipGetLastError();
-    h->held -= want;
+    if (h->spare && h->spare_bytes == bytes) {
+        std::swap(mem, h->spare);
+        h->spare_bytes = 0;
+        return mem;
+    }
+    drop_spare(h);
+    if (hipMalloc(&mem, bytes) == hipSuccess) return mem;
+    hipGetLastError();                     // reported by the caller's status, not by a later launch's check
     return nullptr;
-}
-
-void keep_block(rbc_ctx *h, void *mem, size_t bytes) {
-    const size_t want = block_bytes(bytes);
-    h->held -= want;
-    h->spare.push_back({mem, want});
-    h->spare_bytes += want;
-    trim_spare(h, spare_room(h));
 }
 
 // Everything of an admission but the cell build: validation, allocation, uploads and
@@ -1046,19 +1005,18 @@ rbc_status stage(rbc_ctx *h, int32_t slot, int64_t n, const double *x, const dou
     const size_t bytes = layout(fresh, nullptr);
     if (h->budget > 0 && h->used + (int64_t)bytes > h->budget)
         return fail(h, RBC_ERR_CAPACITY, "footprint exceeds the remaining device-memory budget");
-    void *mem = take_block(h, bytes);
+    void *mem = take_memory(h, bytes);
     if (!mem) return fail(h, RBC_ERR_OUT_OF_MEMORY, "device allocation failed");
-    // from here on every error path must give the allocation back: the slot does not own it yet
-    struct ReturnOnError {
+    // from here on every error path must free the allocation: the slot does not own it yet
+    struct FreeOnError {
         rbc_ctx *h;
         void *p;
-        size_t bytes;
-        ~ReturnOnError() {
+        ~FreeOnError() {
             if (!p) return;
             hipStreamSynchronize(h->st);
-            keep_block(h, p, bytes);
+            hipFree(p);
         }
-    } guard{h, mem, bytes};
+    } guard{h, mem};
     if (hipMemsetAsync(mem, 0, bytes, h->st) != hipSuccess)
         return fail(h, RBC_ERR_HIP, "hipMemset of a new system failed");
     fresh.mem = mem;
@@ -1102,7 +1060,7 @@ rbc_status stage(rbc_ctx *h, int32_t slot, int64_t n, const double *x, const dou
     HIPCHK(hipMemsetAsync(h->d_sc + slot, 0, sizeof(SysScal), h->st));
     std::memset(h->h_stat + (size_t)slot * STAT_RING, 0, sizeof(StepStat) * STAT_RING);
     hs = fresh;
-    guard.p = nullptr;                     // the slot owns the allocation now (release() takes it back)
+    guard.p = nullptr;                     // the slot owns the allocation now (release() frees it)
     h->vol_fresh = false;
     h->used += (int64_t)bytes;
     hs.pending = true;
@@ -1167,15 +1125,22 @@ rbc_status admit(rbc_ctx *h, int32_t slot, int64_t n, const double *x, const dou
     return build_pending(h, std::vector<int>{slot}, failed);
 }
 
-void release(rbc_ctx *h, int32_t slot, bool refresh) {
+// Free a slot.  `replaced`: the system about to take its place may take its memory, and the
+// tables are refreshed then.
+void release(rbc_ctx *h, int32_t slot, bool replaced) {
     HostSys &hs = h->sys[slot];
     if (!hs.live) return;
     hipStreamSynchronize(h->st);
-    if (hs.mem) keep_block(h, hs.mem, hs.bytes);
+    if (hs.mem && replaced) {
+        h->spare = hs.mem;
+        h->spare_bytes = hs.bytes;
+    } else if (hs.mem) {
+        hipFree(hs.mem);
+    }
     if (hs.pairs_mem) hipFree(hs.pairs_mem);
     h->used -= (int64_t)hs.bytes;
     hs = HostSys{};
-    if (refresh) refresh_tables(h);
+    if (!replaced) refresh_tables(h);
 }
 
 rbc_status create(const rbc_params *params, void *stream, int32_t max_slots, int64_t budget, bool ensemble,
@@ -1274,7 +1239,6 @@ rbc_status rbc_destroy(rbc_handle h) {
         if (h->sys[s].mem) hipFree(h->sys[s].mem);
         if (h->sys[s].pairs_mem) hipFree(h->sys[s].pairs_mem);
     }
-    trim_spare(h, 0);
     for (auto e : h->tb) hipEventDestroy(e);
     for (auto e : h->te) hipEventDestroy(e);
     for (auto e : h->nb) hipEventDestroy(e);
@@ -1301,12 +1265,11 @@ rbc_status rbc_set_system(rbc_handle h, int64_t n, const double *x, const double
                           const double *box, const int32_t *periodic) {
     if (!h) return RBC_ERR_INVALID_ARG;
     if (h->ensemble) return fail(h, RBC_ERR_INVALID_ARG, "use rbc_ensemble_admit on an ensemble context");
-    release(h, 0, false);
+    release(h, 0, true);
     h->forces_valid = false;
-    h->sticky = RBC_OK;
     rbc_status r = RBC_OK;
-    if (n == 0) trim_spare(h, 0);
-    else r = admit(h, 0, n, x, nrm, type, v, w, nbond, bonds, r0, box, periodic);
+    if (n != 0) r = admit(h, 0, n, x, nrm, type, v, w, nbond, bonds, r0, box, periodic);
+    drop_spare(h);
     if (!h->sys[0].live) refresh_tables(h);       // nothing took the released system's place
     return r;
 }
