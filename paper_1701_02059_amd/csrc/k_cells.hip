@@ -26,8 +26,6 @@ namespace rbc {
 
 // ------------------------------------------------------------------ helpers
 
-__device__ __forceinline__ int lane_id() { return threadIdx.x & (WAVE - 1); }
-
 // A running maximum that many waves raise: the atomic is issued only when the value
 // read (never above the true running maximum) is smaller, so that most waves skip the
 // serialised same-address atomic.
@@ -1707,27 +1705,6 @@ void launch_cell_pairs(const LaunchCtx &L) {
 }
 
 // ------------------------------------------------------------------ neighbour lists
-
-// In-place exclusive scan of a[0..n), n <= 8 * BLOCK, by the whole block; returns the total.
-__device__ int block_scan_lds(int *a, int n, int *s_w) {
-    int v[8];
-    int loc = 0;
-    const int base = threadIdx.x * 8;
-    for (int q = 0; q < 8; ++q) {
-        const int idx = base + q;
-        v[q] = idx < n ? a[idx] : 0;
-        loc += v[q];
-    }
-    int tot;
-    int ex = block_excl_scan(loc, s_w, tot);
-    for (int q = 0; q < 8; ++q) {
-        const int idx = base + q;
-        if (idx < n) a[idx] = ex;
-        ex += v[q];
-    }
-    __syncthreads();
-    return tot;
-}
 
 __device__ __forceinline__ int lds_lower_bound(const int *a, int n, int v) {
     int lo = 0, hi = n;
