@@ -1597,9 +1597,10 @@ __device__ int cell_query_wave(const SysDev &S, const SysScal *sc, int A, double
 }
 
 // Cell-pair kernels.  Systems of at least CQ_SERIAL_MIN cells take one thread per
-// cell (there are enough threads to hide the serial walk's latency: 231 us at 225 thousand
-// cells, by wavefronts 251); smaller ones give each cell a wavefront (28 thousand: 115 and
-// 40 us), CQ_BLOCKS blocks per 256-cell block of the cell map.  Both find the same rows.
+// cell (there are enough threads to hide the serial walk's latency: 233 us at 225 thousand
+// cells, by wavefronts 247); smaller ones give each cell a wavefront (150 thousand: 185 and
+// 164 us, 28 thousand: 117 and 42), CQ_BLOCKS blocks per 256-cell block of the cell map.  Both
+// find the same rows.
 // The query writes a cell's first CROW hits to a scratch row (in the memory of the 32-bit
 // fallback lists, idle until the list build) and its row's length; once a scan has placed the
 // rows they are copied, and only a longer row (a cell with a far member reaches many) is
@@ -1607,7 +1608,7 @@ __device__ int cell_query_wave(const SysDev &S, const SysScal *sc, int A, double
 // second time to fill its row took longer than the first time: 41 after 32 us at 6250 cells;
 // the copy takes 4 us.)
 constexpr int CQ_BLOCKS = BLOCK / (BLOCK / WAVE);
-constexpr int CQ_SERIAL_MIN = 150000;
+constexpr int CQ_SERIAL_MIN = 200000;
 constexpr int CROW = 256;             // (less where cells hold fewer than three particles on average)
 __device__ __forceinline__ int crow_of(const SysDev &S) {
     return (int)min((long long)CROW, (long long)S.nchunk * (MAXNB * CHUNK) / S.k);
