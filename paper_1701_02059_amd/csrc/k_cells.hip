@@ -162,7 +162,8 @@ __global__ __launch_bounds__(MAX_SLOTS) void k_set_rebuild(const SysDev *Sd, int
             sc->rmax = 0ull;
             sc->nlrows = 0;
             sc->cnbr_maxrow = 0;
-            sc->err &= ~(ERR_NLIST | ERR_CNBR | ERR_ASSIGN);
+            sc->level = 0;
+            sc->err &= ~(ERR_NLIST | ERR_NPAIRS | ERR_CNBR | ERR_ASSIGN);
             if (S.n > 0) {
                 cnt[0] = (S.n + BLOCK - 1) / BLOCK;
                 cnt[1] = (S.k + BLOCK - 1) / BLOCK;
@@ -1857,7 +1858,8 @@ __device__ __forceinline__ int union_cell(const int *ofs, int nsc, int u) {
 //  - Lists: the lanes take their next set bit row by row together, eight rows to a
 //    16-byte store.  The same pass tests the pruned radius (rc + 2 inner skin), marks the
 //    stage entries that pass and keeps a bit per row; emit_pruned then writes the pruned
-//    lists.  Hits beyond the words that fit are appended one by one.
+//    lists.  Hits beyond the words that fit are appended one by one.  A lane with more than
+//    MAXNB hits starts again at a shorter radius (NL_LEVELS).
 // What bounds it is latency: three blocks of four wavefronts share a CU, and every phase is
 // a chain of loads, barriers and LDS reads, so each is written with as many of them side
 // by side as it has (four union particles, eight candidates, eight rows at a time).
@@ -2268,7 +2270,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
     }
     const bool staged = have_union && kept <= USTAGE && s_big == 0;
     // ---- the lists, and the bits of the rows that the pruned lists keep
-    int cnt = 0, mygroups = 0;                       // this lane's partners, and groups of eight rows written
+    int cnt = 0, mygroups = 0, level = 0;            // this lane's partners, groups of eight rows written, radius
     unsigned pm0 = 0u, pm1 = 0u, pm2 = 0u;
     static_assert(MAXNB == 96, "row bits in three words");
     const int ti = (int)pi.w & 3;
@@ -2276,7 +2278,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
     v4u *row8 = reinterpret_cast<v4u *>(row) + lane;
     if (staged) {
         const float oix = oi[0], oiy = oi[1], oiz = oi[2];
-        const float rlA = P.rl2f[ti][0], rlB = P.rl2f[ti][1], rlC = P.rl2f[ti][2];
+        float rlA = P.rl2f[ti][0], rlB = P.rl2f[ti][1], rlC = P.rl2f[ti][2];
         const float riA = P.rin2f[ti][0], riB = P.rin2f[ti][1], riC = P.rin2f[ti][2];
         const int oself = valid ? 4 * (int)s_self[tid] : -1;     // this particle's own stage entry (LDS offset)
         const int G = min(nsph, GROUPS), mygrp = group_of((A - c0) >> rs);
@@ -2402,87 +2404,101 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
                     auto at = [&](int w, int b) { return w < wl ? pf + 32 * w + b : pb - 1 - 32 * (w - wl) - b; };
                     // a row's test against the pruned radius
                     auto inner = [&](int o, int t) { return dist2(o) < sel3f(t, riA, riB, riC); };
-                    // hit words, the empty ones left out; their numbers, five bits each, in wix
-                    const int nw = wl + ((np + 31) >> 5);
-                    int w = 0, slots = 0;
-                    unsigned long long wix = 0ull;
-                    for (; w < nw && w < 32 && slots < MWORDS; ++w) {
-                        const unsigned m = w < wl ? word(std::true_type{}, 32 * w, nl) : word(std::false_type{}, 32 * (w - wl), np);
-                        if (m) {
-                            s_m[slots * BLOCK + tid] = m;
-                            wix |= (unsigned long long)w << (5 * slots);
-                            ++slots;
-                            cnt += __popc(m);
-                        }
-                    }
-                    // rows: every lane's next hit, eight rows to a store
-                    const int n = min(cnt, MAXNB);
-                    // (the next three words wait in registers; a group that uses up more reads on)
-                    int slot = 0;
-                    unsigned cur = n > 0 ? s_m[tid] : 0u;
-                    for (int g = 0; __ballot(8 * g < n) != 0ull; ++g) {
-                        int o[8], t[8];
-                        bool have[8];
-                        unsigned e[8], pbits = 0u;
-                        unsigned n1 = s_m[min(slot + 1, MWORDS - 1) * BLOCK + tid], n2 = s_m[min(slot + 2, MWORDS - 1) * BLOCK + tid],
-                                 n3 = s_m[min(slot + 3, MWORDS - 1) * BLOCK + tid];
-                        const int last3 = slot + 3;
-#pragma unroll
-                        for (int q = 0; q < 8; ++q) {
-                            have[q] = 8 * g + q < n;
-                            const bool next = have[q] && cur == 0u;
-                            slot += next ? 1 : 0;
-                            cur = next ? n1 : cur;
-                            n1 = next ? n2 : n1;
-                            n2 = next ? n3 : n2;
-                            if (__builtin_expect(__ballot(next && slot > last3) != 0ull, 0))
-                                if (next && slot > last3) cur = s_m[slot * BLOCK + tid];
-                            const int cw = (int)(wix >> (5 * slot)) & 31;
-                            o[q] = have[q] ? at(cw, __ffs(cur) - 1) : pf;
-                            cur &= cur - 1u;
-                        }
-#pragma unroll
-                        for (int q = 0; q < 8; ++q) o[q] = s_list[o[q]];
-#pragma unroll
-                        for (int q = 0; q < 8; ++q) t[q] = s_tf[o[q] >> 2] & 3;
-                        bool in[8];
-#pragma unroll
-                        for (int q = 0; q < 8; ++q) in[q] = have[q] && inner(o[q], t[q]);
-#pragma unroll
-                        for (int q = 0; q < 8; ++q) {
-                            e[q] = have[q] ? (unsigned)(o[q] >> 2) : 0xffffu;
-                            if (in[q]) {
-                                pbits |= 1u << q;
-                                s_tf[o[q] >> 2] = (unsigned char)(t[q] | STAGE_USED);
+                    for (;;) {
+                        // hit words, the empty ones left out; their numbers, five bits each, in wix
+                        const int nw = wl + ((np + 31) >> 5);
+                        int w = 0, slots = 0;
+                        unsigned long long wix = 0ull;
+                        for (; w < nw && w < 32 && slots < MWORDS; ++w) {
+                            const unsigned m = w < wl ? word(std::true_type{}, 32 * w, nl) : word(std::false_type{}, 32 * (w - wl), np);
+                            if (m) {
+                                s_m[slots * BLOCK + tid] = m;
+                                wix |= (unsigned long long)w << (5 * slots);
+                                ++slots;
+                                cnt += __popc(m);
                             }
                         }
-                        const v4u out = {e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
-                        stg(row8 + g * CHUNK, out);
-                        const unsigned pw = pbits << (8 * (g & 3));
-                        if (g < 4) pm0 |= pw;
-                        else if (g < 8) pm1 |= pw;
-                        else pm2 |= pw;
-                        mygroups = g + 1;
-                    }
-                    // the words beyond the slots, hit by hit
-                    for (; w < nw; ++w) {
-                        unsigned m = w < wl ? word(std::true_type{}, 32 * w, nl) : word(std::false_type{}, 32 * (w - wl), np);
-                        for (; m; m &= m - 1u, ++cnt) {
-                            if (cnt >= MAXNB) continue;
-                            const int o1 = s_list[at(w, __ffs(m) - 1)], t1 = s_tf[o1 >> 2] & 3;
-                            if ((cnt & 7) == 0) {
-                                stg(row8 + (cnt >> 3) * CHUNK, v4u{~0u, ~0u, ~0u, ~0u});
-                                mygroups = (cnt >> 3) + 1;
+                        // rows: every lane's next hit, eight rows to a store
+                        const int n = min(cnt, MAXNB);
+                        // (the next three words wait in registers; a group that uses up more reads on)
+                        int slot = 0;
+                        unsigned cur = n > 0 ? s_m[tid] : 0u;
+                        for (int g = 0; __ballot(8 * g < n) != 0ull; ++g) {
+                            int o[8], t[8];
+                            bool have[8];
+                            unsigned e[8], pbits = 0u;
+                            unsigned n1 = s_m[min(slot + 1, MWORDS - 1) * BLOCK + tid], n2 = s_m[min(slot + 2, MWORDS - 1) * BLOCK + tid],
+                                     n3 = s_m[min(slot + 3, MWORDS - 1) * BLOCK + tid];
+                            const int last3 = slot + 3;
+#pragma unroll
+                            for (int q = 0; q < 8; ++q) {
+                                have[q] = 8 * g + q < n;
+                                const bool next = have[q] && cur == 0u;
+                                slot += next ? 1 : 0;
+                                cur = next ? n1 : cur;
+                                n1 = next ? n2 : n1;
+                                n2 = next ? n3 : n2;
+                                if (__builtin_expect(__ballot(next && slot > last3) != 0ull, 0))
+                                    if (next && slot > last3) cur = s_m[slot * BLOCK + tid];
+                                const int cw = (int)(wix >> (5 * slot)) & 31;
+                                o[q] = have[q] ? at(cw, __ffs(cur) - 1) : pf;
+                                cur &= cur - 1u;
                             }
-                            stg(row + nl_at(cnt, lane), (uint16_t)(o1 >> 2));
-                            if (inner(o1, t1)) {
-                                const unsigned bit = 1u << (cnt & 31);
-                                if (cnt < 32) pm0 |= bit;
-                                else if (cnt < 64) pm1 |= bit;
-                                else pm2 |= bit;
-                                s_tf[o1 >> 2] = (unsigned char)(t1 | STAGE_USED);
+#pragma unroll
+                            for (int q = 0; q < 8; ++q) o[q] = s_list[o[q]];
+#pragma unroll
+                            for (int q = 0; q < 8; ++q) t[q] = s_tf[o[q] >> 2] & 3;
+                            bool in[8];
+#pragma unroll
+                            for (int q = 0; q < 8; ++q) in[q] = have[q] && inner(o[q], t[q]);
+#pragma unroll
+                            for (int q = 0; q < 8; ++q) {
+                                e[q] = have[q] ? (unsigned)(o[q] >> 2) : 0xffffu;
+                                if (in[q]) {
+                                    pbits |= 1u << q;
+                                    s_tf[o[q] >> 2] = (unsigned char)(t[q] | STAGE_USED);
+                                }
+                            }
+                            const v4u out = {e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
+                            stg(row8 + g * CHUNK, out);
+                            const unsigned pw = pbits << (8 * (g & 3));
+                            if (g < 4) pm0 |= pw;
+                            else if (g < 8) pm1 |= pw;
+                            else pm2 |= pw;
+                            mygroups = g + 1;
+                        }
+                        // the words beyond the slots, hit by hit
+                        for (; w < nw; ++w) {
+                            unsigned m = w < wl ? word(std::true_type{}, 32 * w, nl) : word(std::false_type{}, 32 * (w - wl), np);
+                            for (; m; m &= m - 1u, ++cnt) {
+                                if (cnt >= MAXNB) continue;
+                                const int o1 = s_list[at(w, __ffs(m) - 1)], t1 = s_tf[o1 >> 2] & 3;
+                                if ((cnt & 7) == 0) {
+                                    stg(row8 + (cnt >> 3) * CHUNK, v4u{~0u, ~0u, ~0u, ~0u});
+                                    mygroups = (cnt >> 3) + 1;
+                                }
+                                stg(row + nl_at(cnt, lane), (uint16_t)(o1 >> 2));
+                                if (inner(o1, t1)) {
+                                    const unsigned bit = 1u << (cnt & 31);
+                                    if (cnt < 32) pm0 |= bit;
+                                    else if (cnt < 64) pm1 |= bit;
+                                    else pm2 |= bit;
+                                    s_tf[o1 >> 2] = (unsigned char)(t1 | STAGE_USED);
+                                }
                             }
                         }
+                        if (__builtin_expect(cnt <= MAXNB || level == NL_LEVELS, 1)) break;
+                        // more than a list holds: once more at the next level's radius
+                        ++level;
+                        auto shorter = [&](float r2) {
+                            const float r = sqrtf(r2) - P.nl_step;
+                            return r * r;
+                        };
+                        rlA = shorter(rlA);
+                        rlB = shorter(rlB);
+                        rlC = shorter(rlC);
+                        cnt = mygroups = 0;
+                        pm0 = pm1 = pm2 = 0u;
                     }
                 };
                 if (periodic) scan(std::true_type{});
@@ -2493,47 +2509,61 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
     }
     int32_t *col = S.nl + (size_t)(chunk_ok ? chunk : 0) * MAXNB * CHUNK + lane;
     if (!staged && valid) {
-        cnt = 0;
-        // the paired cells whose sphere reaches this particle, four side by side, and their
-        // members likewise
-        constexpr int SB = 4;
-        const int qe = S.cnbr_start[A + 1];
-        for (int q0 = S.cnbr_start[A]; q0 < qe; q0 += SB) {
-            int b[SB], e[SB];
+        double cut0 = P.rl2[ti][0], cut1 = P.rl2[ti][1], cut2 = P.rl2[ti][2];
+        for (;;) {
+            cnt = 0;
+            // the paired cells whose sphere reaches this particle, four side by side, and their
+            // members likewise
+            constexpr int SB = 4;
+            const int qe = S.cnbr_start[A + 1];
+            for (int q0 = S.cnbr_start[A]; q0 < qe; q0 += SB) {
+                int b[SB], e[SB];
 #pragma unroll
-            for (int k = 0; k < SB; ++k) {
-                const int B = ldg(S.cnbr + min(q0 + k, qe - 1));
-                const D4 c = ldg(S.seed + B);
-                b[k] = ldg(S.cstart + B);
-                e[k] = b[k] + ldg(S.ccount + B);
-                double dx, dy, dz;
-                const double d2 = dist2_exact(S, pi.x, pi.y, pi.z, c.x, c.y, c.z, dx, dy, dz);
-                const double reach = c.w + P.cell_search + 1e-9;
-                if (q0 + k >= qe || d2 > reach * reach) e[k] = b[k];
-            }
-            for (int k = 0; k < SB; ++k)
-                for (int j0 = b[k]; j0 < e[k]; j0 += SB) {
-                    D4 pj[SB];
+                for (int k = 0; k < SB; ++k) {
+                    const int B = ldg(S.cnbr + min(q0 + k, qe - 1));
+                    const D4 c = ldg(S.seed + B);
+                    b[k] = ldg(S.cstart + B);
+                    e[k] = b[k] + ldg(S.ccount + B);
+                    double dx, dy, dz;
+                    const double d2 = dist2_exact(S, pi.x, pi.y, pi.z, c.x, c.y, c.z, dx, dy, dz);
+                    const double reach = c.w + P.cell_search + 1e-9;
+                    if (q0 + k >= qe || d2 > reach * reach) e[k] = b[k];
+                }
+                for (int k = 0; k < SB; ++k)
+                    for (int j0 = b[k]; j0 < e[k]; j0 += SB) {
+                        D4 pj[SB];
 #pragma unroll
-                    for (int h = 0; h < SB; ++h) pj[h] = ldpos(S, min(j0 + h, e[k] - 1));
+                        for (int h = 0; h < SB; ++h) pj[h] = ldpos(S, min(j0 + h, e[k] - 1));
 #pragma unroll
-                    for (int h = 0; h < SB; ++h) {
-                        const int j = j0 + h;
-                        double dx, dy, dz;
-                        const double d2 = dist2_exact(S, pi.x, pi.y, pi.z, pj[h].x, pj[h].y, pj[h].z, dx, dy, dz);
-                        if (j < e[k] && j != i && d2 < P.rl2[ti][(int)pj[h].w]) {
-                            if (cnt < MAXNB) stg(col + cnt * CHUNK, (int32_t)j);
-                            ++cnt;
+                        for (int h = 0; h < SB; ++h) {
+                            const int j = j0 + h;
+                            double dx, dy, dz;
+                            const double d2 = dist2_exact(S, pi.x, pi.y, pi.z, pj[h].x, pj[h].y, pj[h].z, dx, dy, dz);
+                            if (j < e[k] && j != i && d2 < (pj[h].w == 0.0 ? cut0 : (pj[h].w == 1.0 ? cut1 : cut2))) {
+                                if (cnt < MAXNB) stg(col + cnt * CHUNK, (int32_t)j);
+                                ++cnt;
+                            }
                         }
                     }
-                }
+            }
+            if (cnt <= MAXNB || level == NL_LEVELS) break;
+            ++level;
+            auto shorter = [&](double r2) {
+                const double r = sqrt(r2) - (double)P.nl_step;
+                return r * r;
+            };
+            cut0 = shorter(cut0);
+            cut1 = shorter(cut1);
+            cut2 = shorter(cut2);
         }
     }
     int rows = wave_max_int(cnt);
-    if (rows > MAXNB) {
-        if (lane == 0) atomicOr(&S.sc->err, ERR_NLIST);
-        rows = MAXNB;
+    const int wlevel = wave_max_int(level);
+    if (wlevel > 0 && lane == 0) {
+        atomicOr(&S.sc->err, rows > MAXNB ? ERR_NLIST | ERR_NPAIRS : ERR_NLIST);
+        atomicMax(&S.sc->level, wlevel);
     }
+    rows = min(rows, MAXNB);
     if (chunk_ok && lane == 0) S.nlk[chunk] = rows;
     if (lane == 0) s_rows[wv] = rows;
     int nkept = -1;

@@ -478,11 +478,12 @@ __device__ void stats_of(const double *part, int n, double *s_m) {       // into
     }
 }
 
-__device__ void publish_stats(const SysDev &S, const double *part, int n, unsigned long long step, double *s_m) {
+__device__ void publish_stats(const SysDev &S, const double *part, int n, unsigned long long step, double *s_m,
+                              unsigned long long with) {
     stats_of(part, n, s_m);
     if (threadIdx.x == 0) {
         StepStat *e = S.hstat + (step - 1) % STAT_RING;
-        const unsigned long long err = (unsigned long long)(unsigned)S.sc->err;
+        const unsigned long long err = (unsigned long long)(unsigned)S.sc->err | (unsigned long long)S.sc->level << STAT_LEVEL | with;
         const unsigned long long d2 = dbits(s_m[0]), v2 = dbits(s_m[1]), d2p = dbits(s_m[2]);
         auto put = [](void *p, unsigned long long v) {
             __hip_atomic_store((unsigned long long *)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -716,7 +717,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MIXED ? 5
         if (S.n <= 0) return;
         const unsigned long long step = S.sc->step[par];
         if (KICK == 2 && threadIdx.x == 0) S.sc->step[par ^ 1] = step + 1;       // the fused drift's number
-        publish_stats(S, S.bred, S.nchunk, step, reinterpret_cast<double *>(s_raw));
+        publish_stats(S, S.bred, S.nchunk, step, reinterpret_cast<double *>(s_raw), STAT_FORCE);
         return;
     }
     const int gb = xcd_group_block((int)blockIdx.x - nstat, (int)gridDim.x - nstat);
@@ -1374,7 +1375,7 @@ __global__ __launch_bounds__(WAVE) void k_stats(const SysDev *Sd, int par) {
     const SysDev &S = Sd[blockIdx.x];
     if (S.n <= 0) return;
     __shared__ double s_m[3];
-    publish_stats(S, S.sred, SR1, S.sc->step[par], s_m);
+    publish_stats(S, S.sred, SR1, S.sc->step[par], s_m, 0ull);
 }
 
 void launch_kick_drift(const LaunchCtx &L, double dt) {

@@ -54,8 +54,9 @@ struct HostSys {
     double disp2 = 0.0, v2 = 0.0, disp2p = 0.0;
     double cur_d2 = 0.0, cur_v2 = 0.0, cur_d2p = 0.0;   // the latest drift statistics read
     uint64_t drifts = 0;             // statistics passes since loading (the device's step counter)
-    uint64_t call_drift0 = 0;        // ... when the running step call began
-    int call_err = 0;                // the error bits of all of that call's force evaluations
+    int err = 0;                     // the error bits of the latest force evaluation of a step
+    int lost = 0;                    // ... of any in the running step call that lost pairs
+    int level = 0;                   // the current lists' level (NL_LEVELS)
     bool pending = false;            // staged: uploaded, cells not built yet
     rbc_status failed = RBC_OK;      // ensemble slot frozen by an error (held until retired)
     std::string why;                 // its message
@@ -247,6 +248,7 @@ void make_dev_params(rbc_ctx *h) {
     d.thermo_on = p.gamma > 0.0 || p.gamma_rot > 0.0;
     d.seed_lo = (uint32_t)p.seed;
     d.seed_hi = (uint32_t)(p.seed >> 32);
+    d.nl_step = std::nextafter((float)(2.0 * (p.skin - level_skin(p.skin, 1))), 0.0f);
     d.ou_c = d.ou_cr = 1.0;
     d.ou_a[0] = d.ou_a[1] = d.ou_a[2] = d.ou_ar = 0.0;
     d.quench_on = p.quench;
@@ -520,7 +522,7 @@ void lists_body(rbc_ctx *h, const LaunchCtx &L, bool cells_moved) {
 // The status and message of one slot's error bits.
 rbc_status slot_error(rbc_ctx *h, int s, int e) {
     if (e & ERR_NONFINITE) return fail(h, RBC_ERR_NONFINITE, "non-finite positions or velocities in slot " + std::to_string(s));
-    if (e & ERR_NLIST) return fail(h, RBC_ERR_CAPACITY, "a particle has more than " + std::to_string(MAXNB) + " neighbours within rc + 2 skin (slot " + std::to_string(s) + ")");
+    if (e & (ERR_NLIST | ERR_NPAIRS)) return fail(h, RBC_ERR_CAPACITY, "a particle has more than " + std::to_string(MAXNB) + " neighbours within rc + 2 skin (slot " + std::to_string(s) + ")");
     if (e & ERR_CNBR) return fail(h, RBC_ERR_CAPACITY, "cell-pair list capacity exceeded (slot " + std::to_string(s) + ")");
     if (e & ERR_ASSIGN) return fail(h, RBC_ERR_CAPACITY, "nearest-seed search failed (slot " + std::to_string(s) + ")");
     return RBC_OK;
@@ -552,7 +554,7 @@ rbc_status freeze_failed(rbc_ctx *h, const std::vector<std::pair<int, std::strin
     };
     for (int s = 0; s < h->nsys; ++s) {
         if (!runs(h->sys[s])) continue;
-        const rbc_status r = slot_error(h, s, h->sys[s].call_err);
+        const rbc_status r = slot_error(h, s, h->sys[s].err | h->sys[s].lost);
         if (r != RBC_OK) freeze(s, r, h->err);
     }
     for (const auto &e : host_err) freeze(e.first, RBC_ERR_SKIN, e.second);
@@ -692,8 +694,7 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
     set_step_dt(h, dt);
     const bool graphs = h->graphs && !h->timing && ensure_graphs(h, dt);
     ensure_forces(h);
-    const double skin = h->prm.skin;
-    const double din = inner_skin(h->prm);
+    const double skin_full = h->prm.skin, din_full = inner_skin(h->prm);
     const int64_t K = h->prm.update_every;
     rbc_status out = RBC_OK;
     std::vector<std::pair<int, std::string>> slot_err;   // ensembles: per-slot errors of the host loop
@@ -713,20 +714,19 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
     bool exact_any = false;
     for (const auto &hs : h->sys)
         if (runs(hs) && hs.n >= EXACT_MIN_N) exact_any = true;
-    for (auto &hs : h->sys) {
-        hs.call_err = 0;
-        hs.call_drift0 = hs.drifts;
-    }
-    // The error bits of the latest step whose force has run.  Each step counts, not the last
-    // alone: a build clears the list errors that the steps before it ran with.  They are read
-    // once the next step has published (or the stream is idle): a step that waited for its
-    // statistics publishes twice, before its list work and with its force.
-    auto settle = [&](int s) {
-        HostSys &hs = h->sys[s];
-        if (hs.drifts == hs.call_drift0) return;
-        StepStat e;
-        if (ring_entry(h, s, hs.drifts, e)) hs.call_err |= (int)e.err;
-        else if (out == RBC_OK) out = fail(h, RBC_ERR_HIP, "drift statistics out of sequence (slot " + std::to_string(s) + ")");
+    for (auto &hs : h->sys) hs.err = hs.lost = 0;
+    // The error bits and the level of the lists that the running step's force works with, from
+    // the entries that it published.  Every step's count, not the last one's alone: a build
+    // clears the bits of the one before.
+    auto settle = [&]() {
+        for (int s = 0; s < h->nsys; ++s) {
+            HostSys &hs = h->sys[s];
+            StepStat e;
+            if (!runs(hs) || hs.n == 0 || !ring_entry(h, s, hs.drifts, e)) continue;
+            hs.err = (int)e.err;
+            hs.lost |= hs.err & (ERR_NPAIRS | ERR_CNBR | ERR_NONFINITE);
+            hs.level = (int)(e.err >> STAT_LEVEL) & 0xff;
+        }
     };
     // the statistics of the latest drift of every running system, from the pinned ring
     auto read_stats = [&]() {
@@ -735,7 +735,6 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
             if (!runs(hs)) continue;
             hs.cur_d2 = hs.cur_v2 = hs.cur_d2p = 0.0;
             if (hs.n == 0) continue;
-            settle(s);
             StepStat e;
             if (!ring_entry(h, s, hs.drifts + 1, e) && out == RBC_OK)
                 out = fail(h, RBC_ERR_HIP, "drift statistics out of sequence (slot " + std::to_string(s) + ")");
@@ -749,9 +748,10 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
     const auto t_loop0 = clk::now();
     double wait_s = 0.0;
     // Waiting for a step's drift statistics: poll the ring entries in pinned memory until
-    // their tags match their words.  Polling answers within about a microsecond.  A stream that has ended or failed without them
-    // ends the wait too (looked at every 20 ms: an event recorded per step for this cost
-    // the GPU 6 us between two steps), and read_stats then checks the tags.
+    // their tags match their words.  Polling answers within about a microsecond.  A stream
+    // that has ended or failed without them ends the wait too (looked at every 20 ms: an event
+    // recorded per step for this cost the GPU 6 us between two steps), and read_stats then
+    // checks the tags.
     auto stats_ready = [&]() {
         for (int s = 0; s < h->nsys; ++s) {
             const HostSys &hs = h->sys[s];
@@ -761,10 +761,20 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
         }
         return true;
     };
-    auto wait_stats = [&]() {
+    // the entries already read, published again by the step's force
+    auto force_ready = [&]() {
+        for (int s = 0; s < h->nsys; ++s) {
+            const HostSys &hs = h->sys[s];
+            if (!runs(hs) || hs.n == 0) continue;
+            StepStat e;
+            if (!ring_entry(h, s, hs.drifts, e) || !(e.err & STAT_FORCE)) return false;
+        }
+        return true;
+    };
+    auto wait_for = [&](auto &ready) {
         const auto a = clk::now();
         auto asked = a;
-        for (int k = 1; !stats_ready(); ++k) {
+        for (int k = 1; !ready(); ++k) {
             if (k % 1024) continue;
             const auto b = clk::now();
             if (b - asked < std::chrono::milliseconds(20)) continue;
@@ -790,12 +800,13 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
             for (const auto &hs : h->sys) {
                 if (!runs(hs) || hs.n < EXACT_MIN_N || hs.steps_since + 1 >= K) continue;
                 if (!hs.have_stats) { need = true; break; }
+                const double din = std::min(din_full, level_skin(skin_full, hs.level));
                 const double pred_p = (hs.refreshed_last ? 0.0 : std::sqrt(hs.disp2p)) + 2.0 * dt * std::sqrt(hs.v2);
                 if (pred_p > din - EXACT_MARGIN) { need = true; break; }
             }
             if (need) {
                 launch_stats(h->L);
-                wait_stats();
+                wait_for(stats_ready);
                 read_stats();
                 waited = true;
             }
@@ -815,6 +826,7 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
                 continue;
             }
             bool prune = false, rebuild = false;
+            const double skin = level_skin(skin_full, hs.level), din = std::min(din_full, skin);
             if (hs.n >= EXACT_MIN_N) {
                 // exact displacements at this step's positions (FP32 references: margin);
                 // without them the bound above has ruled out any list work
@@ -851,15 +863,19 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
         if (timed) hipEventRecord(h->ev_step[st], h->st);
         // while the force runs, read this step's drift statistics (unless read above)
         if (!waited) {
-            wait_stats();
+            wait_for(stats_ready);
             read_stats();
+        } else if (!which.empty()) {
+            wait_for(force_ready);      // read before the builds: their bits come with the force
         }
+        settle();
         for (int s = 0; s < h->nsys; ++s) {
             HostSys &hs = h->sys[s];
             if (!runs(hs)) continue;
             const bool rebuilt = std::find(which.begin(), which.end(), s) != which.end();
             const bool was_pruned = std::find(pruned.begin(), pruned.end(), s) != pruned.end();
             const double d2 = hs.cur_d2, v2 = hs.cur_v2, d2p = hs.cur_d2p;
+            const double skin = level_skin(skin_full, hs.level), din = std::min(din_full, skin);
             // the force of this step walked the pruned lists: they had to hold every pair in
             // range, and a prune at this step needed the full lists to hold its radius
             if (!rebuilt && !was_pruned && d2p > din * din)
@@ -893,14 +909,12 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
     const hipError_t le = hipGetLastError();
     if (le != hipSuccess) return fail(h, RBC_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(le));
     HIPCHK(hipStreamSynchronize(h->st));
-    for (int s = 0; s < h->nsys; ++s)
-        if (runs(h->sys[s])) settle(s);
     rbc_status e = RBC_OK;
     if (h->ensemble) {
         e = freeze_failed(h, slot_err);       // one slot's error freezes that slot only; the others have advanced nsteps
     } else {
         for (int s = 0; s < h->nsys && e == RBC_OK; ++s)
-            if (runs(h->sys[s])) e = slot_error(h, s, h->sys[s].call_err);
+            if (runs(h->sys[s])) e = slot_error(h, s, h->sys[s].err | h->sys[s].lost);
     }
     harvest_timing(h);
     if (timed) {
@@ -1288,7 +1302,9 @@ rbc_status rbc_update_cells(rbc_handle h, int32_t lloyd_iters) {
         for (int s : which) h->sys[s].have_stats = false;
         h->forces_valid = false;
     }
-    return sync_and_check(h);
+    const rbc_status r = sync_and_check(h);
+    for (int s : which) h->sys[s].level = h->h_sc[s].level;
+    return r;
 }
 
 static rbc_status forces_slot(rbc_handle h, int32_t slot, double *F, double *T, double *energy) {

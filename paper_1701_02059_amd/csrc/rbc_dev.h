@@ -36,6 +36,7 @@ constexpr int BRED = 12;               // doubles of per-block partial results (
 
 // error bits in SysScal::err
 constexpr int ERR_NLIST = 1;          // a particle had more than MAXNB list neighbours
+constexpr int ERR_NPAIRS = 16;        // ... and its list does not reach far enough even at the last level
 constexpr int ERR_CNBR = 2;           // cell-pair list capacity exceeded
 constexpr int ERR_NONFINITE = 4;      // NaN / Inf in positions or velocities
 constexpr int ERR_ASSIGN = 8;         // nearest-seed search found no seed
@@ -60,6 +61,12 @@ struct F3 {
     float x, y, z;
 };
 
+// A particle with more than MAXNB partners within the list radius takes a list of a shorter one,
+// rc + 2 skin (1 - level / 5) with the first level up to NL_LEVELS that fits.  The system's lists
+// then serve displacements up to the shorter skin of its largest level.
+constexpr int NL_LEVELS = 3;
+__host__ __device__ constexpr double level_skin(double skin, int level) { return skin * (1.0 - 0.2 * level); }
+
 // Per-system scalars living in device memory.
 struct alignas(256) SysScal {
     unsigned long long rmax;          // bits of the largest cell radius
@@ -68,7 +75,8 @@ struct alignas(256) SysScal {
     int32_t nlrows;                   // largest neighbour-list row count of the last build
     int32_t cnbr_total;
     int32_t cnbr_maxrow;
-    int32_t pad0, pad1, pad2;
+    int32_t level;                    // largest level of the last build's lists
+    int32_t pad1, pad2;
     double slo[3], shi[3];            // seed bounding box (Morton quantisation)
     double glo[3], gh[3];             // seed-grid origin and spacing
     int32_t gdim[3];
@@ -86,6 +94,8 @@ struct alignas(256) SysScal {
 // Drift statistics published to pinned host memory, one ring of STAT_RING entries
 // per system indexed by the drift number: the host reads them without a copy.
 constexpr int STAT_RING = 8;
+constexpr int STAT_LEVEL = 32;
+constexpr unsigned long long STAT_FORCE = 1ull << 40;
 // The tag of a published entry: the drift's number (from 1) mixed with the entry's words,
 // so that an entry whose stores have not all arrived does not match.  The device then
 // needs no fence between the words and the tag: a system-scope fence writes the L2 back,
@@ -110,7 +120,8 @@ struct alignas(64) StepStat {
     double d2;                        // largest |x - x_build|^2 of this drift
     double v2;                        // largest |v|^2 used in it
     double d2p;                       // largest |x - x_prune|^2
-    unsigned long long err;           // the system's error bits when this was published
+    unsigned long long err;           // the system's error bits when this was published, its lists'
+                                      // level from STAT_LEVEL on, and STAT_FORCE with its step's force
     unsigned long long tag;           // stat_tag of the drift's number and the words above
 };
 
@@ -199,7 +210,7 @@ struct DevParams {
     // thermostat: v <- c v + a (r - (2^32 - 1)/2) per component, r a Philox word
     int32_t thermo_on;
     uint32_t seed_lo, seed_hi;
-    int32_t pad;
+    float nl_step;         // list radius given up per level
     double ou_c, ou_a[3];  // translation: c = exp(-gamma dt), a per type
     double ou_cr, ou_ar;   // lipid rotation
     // velocity quenching: projection on the force after the closing kick, move cap
