@@ -2146,8 +2146,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
         // whether an offset lies within the largest list radius of a chunk's box (a periodic axis
         // of which the box spans a quarter or more counts as within)
         const float rb = fmaxf(rlm0, fmaxf(rlm1, rlm2)) + 1e-3f;
-        auto near_boxes = [&](const float (&q)[3]) {
+        auto near_boxes = [&](const float (&q)[3]) __attribute__((always_inline)) {
             float best = INFINITY;
+#pragma unroll 1
             for (int w = 0; w < BLOCK / WAVE; ++w) {
                 float e2 = 0.0f;
 #pragma unroll
@@ -2278,13 +2279,28 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
     v4u *row8 = reinterpret_cast<v4u *>(row) + lane;
     if (staged) {
         const float oix = oi[0], oiy = oi[1], oiz = oi[2];
-        float rlA = P.rl2f[ti][0], rlB = P.rl2f[ti][1], rlC = P.rl2f[ti][2];
+        const float rlA = P.rl2f[ti][0], rlB = P.rl2f[ti][1], rlC = P.rl2f[ti][2];
         const float riA = P.rin2f[ti][0], riB = P.rin2f[ti][1], riC = P.rin2f[ti][2];
         const int oself = valid ? 4 * (int)s_self[tid] : -1;     // this particle's own stage entry (LDS offset)
         const int G = min(nsph, GROUPS), mygrp = group_of((A - c0) >> rs);
         auto ux = [&](int o) { return *reinterpret_cast<const float *>(s_raw + o); };
         auto uy = [&](int o) { return *reinterpret_cast<const float *>(s_raw + 4 * USTAGE + o); };
         auto uz = [&](int o) { return *reinterpret_cast<const float *>(s_raw + 8 * USTAGE + o); };
+        // one entry (LDS offset o, type t) as row r of this lane, with its bit of the pruned rows
+        auto append = [&](int r, int o, int t, bool in) __attribute__((always_inline)) {
+            if ((r & 7) == 0) {
+                stg(row8 + (r >> 3) * CHUNK, v4u{~0u, ~0u, ~0u, ~0u});
+                mygroups = (r >> 3) + 1;
+            }
+            stg(row + nl_at(r, lane), (uint16_t)(o >> 2));
+            if (in) {
+                const unsigned bit = 1u << (r & 31);
+                if (r < 32) pm0 |= bit;
+                else if (r < 64) pm1 |= bit;
+                else pm2 |= bit;
+                s_tf[o >> 2] = (unsigned char)(t | STAGE_USED);
+            }
+        };
         // a wavefront's lists (every fourth): one sweep over the stage entries' bits counts
         // them, a second one writes those that fit
         constexpr int LPW = GROUPS / (BLOCK / WAVE);
@@ -2404,105 +2420,128 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 3))) v
                     auto at = [&](int w, int b) { return w < wl ? pf + 32 * w + b : pb - 1 - 32 * (w - wl) - b; };
                     // a row's test against the pruned radius
                     auto inner = [&](int o, int t) { return dist2(o) < sel3f(t, riA, riB, riC); };
-                    for (;;) {
-                        // hit words, the empty ones left out; their numbers, five bits each, in wix
-                        const int nw = wl + ((np + 31) >> 5);
-                        int w = 0, slots = 0;
-                        unsigned long long wix = 0ull;
-                        for (; w < nw && w < 32 && slots < MWORDS; ++w) {
-                            const unsigned m = w < wl ? word(std::true_type{}, 32 * w, nl) : word(std::false_type{}, 32 * (w - wl), np);
-                            if (m) {
-                                s_m[slots * BLOCK + tid] = m;
-                                wix |= (unsigned long long)w << (5 * slots);
-                                ++slots;
-                                cnt += __popc(m);
+                    // hit words, the empty ones left out; their numbers, five bits each, in wix
+                    const int nw = wl + ((np + 31) >> 5);
+                    int w = 0, slots = 0;
+                    unsigned long long wix = 0ull;
+                    for (; w < nw && w < 32 && slots < MWORDS; ++w) {
+                        const unsigned m = w < wl ? word(std::true_type{}, 32 * w, nl) : word(std::false_type{}, 32 * (w - wl), np);
+                        if (m) {
+                            s_m[slots * BLOCK + tid] = m;
+                            wix |= (unsigned long long)w << (5 * slots);
+                            ++slots;
+                            cnt += __popc(m);
+                        }
+                    }
+                    // rows: every lane's next hit, eight rows to a store
+                    const int n = min(cnt, MAXNB);
+                    // (the next three words wait in registers; a group that uses up more reads on)
+                    int slot = 0;
+                    unsigned cur = n > 0 ? s_m[tid] : 0u;
+                    for (int g = 0; __ballot(8 * g < n) != 0ull; ++g) {
+                        int o[8], t[8];
+                        bool have[8];
+                        unsigned e[8], pbits = 0u;
+                        unsigned n1 = s_m[min(slot + 1, MWORDS - 1) * BLOCK + tid], n2 = s_m[min(slot + 2, MWORDS - 1) * BLOCK + tid],
+                                 n3 = s_m[min(slot + 3, MWORDS - 1) * BLOCK + tid];
+                        const int last3 = slot + 3;
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) {
+                            have[q] = 8 * g + q < n;
+                            const bool next = have[q] && cur == 0u;
+                            slot += next ? 1 : 0;
+                            cur = next ? n1 : cur;
+                            n1 = next ? n2 : n1;
+                            n2 = next ? n3 : n2;
+                            if (__builtin_expect(__ballot(next && slot > last3) != 0ull, 0))
+                                if (next && slot > last3) cur = s_m[slot * BLOCK + tid];
+                            const int cw = (int)(wix >> (5 * slot)) & 31;
+                            o[q] = have[q] ? at(cw, __ffs(cur) - 1) : pf;
+                            cur &= cur - 1u;
+                        }
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) o[q] = s_list[o[q]];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) t[q] = s_tf[o[q] >> 2] & 3;
+                        bool in[8];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) in[q] = have[q] && inner(o[q], t[q]);
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) {
+                            e[q] = have[q] ? (unsigned)(o[q] >> 2) : 0xffffu;
+                            if (in[q]) {
+                                pbits |= 1u << q;
+                                s_tf[o[q] >> 2] = (unsigned char)(t[q] | STAGE_USED);
                             }
                         }
-                        // rows: every lane's next hit, eight rows to a store
-                        const int n = min(cnt, MAXNB);
-                        // (the next three words wait in registers; a group that uses up more reads on)
-                        int slot = 0;
-                        unsigned cur = n > 0 ? s_m[tid] : 0u;
-                        for (int g = 0; __ballot(8 * g < n) != 0ull; ++g) {
-                            int o[8], t[8];
-                            bool have[8];
-                            unsigned e[8], pbits = 0u;
-                            unsigned n1 = s_m[min(slot + 1, MWORDS - 1) * BLOCK + tid], n2 = s_m[min(slot + 2, MWORDS - 1) * BLOCK + tid],
-                                     n3 = s_m[min(slot + 3, MWORDS - 1) * BLOCK + tid];
-                            const int last3 = slot + 3;
-#pragma unroll
-                            for (int q = 0; q < 8; ++q) {
-                                have[q] = 8 * g + q < n;
-                                const bool next = have[q] && cur == 0u;
-                                slot += next ? 1 : 0;
-                                cur = next ? n1 : cur;
-                                n1 = next ? n2 : n1;
-                                n2 = next ? n3 : n2;
-                                if (__builtin_expect(__ballot(next && slot > last3) != 0ull, 0))
-                                    if (next && slot > last3) cur = s_m[slot * BLOCK + tid];
-                                const int cw = (int)(wix >> (5 * slot)) & 31;
-                                o[q] = have[q] ? at(cw, __ffs(cur) - 1) : pf;
-                                cur &= cur - 1u;
+                        const v4u out = {e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
+                        stg(row8 + g * CHUNK, out);
+                        const unsigned pw = pbits << (8 * (g & 3));
+                        if (g < 4) pm0 |= pw;
+                        else if (g < 8) pm1 |= pw;
+                        else pm2 |= pw;
+                        mygroups = g + 1;
+                    }
+                    // the words beyond the slots, hit by hit
+                    for (; w < nw; ++w) {
+                        unsigned m = w < wl ? word(std::true_type{}, 32 * w, nl) : word(std::false_type{}, 32 * (w - wl), np);
+                        for (; m; m &= m - 1u, ++cnt) {
+                            if (cnt >= MAXNB) continue;
+                            const int o1 = s_list[at(w, __ffs(m) - 1)], t1 = s_tf[o1 >> 2] & 3;
+                            if ((cnt & 7) == 0) {
+                                stg(row8 + (cnt >> 3) * CHUNK, v4u{~0u, ~0u, ~0u, ~0u});
+                                mygroups = (cnt >> 3) + 1;
                             }
-#pragma unroll
-                            for (int q = 0; q < 8; ++q) o[q] = s_list[o[q]];
-#pragma unroll
-                            for (int q = 0; q < 8; ++q) t[q] = s_tf[o[q] >> 2] & 3;
-                            bool in[8];
-#pragma unroll
-                            for (int q = 0; q < 8; ++q) in[q] = have[q] && inner(o[q], t[q]);
-#pragma unroll
-                            for (int q = 0; q < 8; ++q) {
-                                e[q] = have[q] ? (unsigned)(o[q] >> 2) : 0xffffu;
-                                if (in[q]) {
-                                    pbits |= 1u << q;
-                                    s_tf[o[q] >> 2] = (unsigned char)(t[q] | STAGE_USED);
-                                }
-                            }
-                            const v4u out = {e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
-                            stg(row8 + g * CHUNK, out);
-                            const unsigned pw = pbits << (8 * (g & 3));
-                            if (g < 4) pm0 |= pw;
-                            else if (g < 8) pm1 |= pw;
-                            else pm2 |= pw;
-                            mygroups = g + 1;
-                        }
-                        // the words beyond the slots, hit by hit
-                        for (; w < nw; ++w) {
-                            unsigned m = w < wl ? word(std::true_type{}, 32 * w, nl) : word(std::false_type{}, 32 * (w - wl), np);
-                            for (; m; m &= m - 1u, ++cnt) {
-                                if (cnt >= MAXNB) continue;
-                                const int o1 = s_list[at(w, __ffs(m) - 1)], t1 = s_tf[o1 >> 2] & 3;
-                                if ((cnt & 7) == 0) {
-                                    stg(row8 + (cnt >> 3) * CHUNK, v4u{~0u, ~0u, ~0u, ~0u});
-                                    mygroups = (cnt >> 3) + 1;
-                                }
-                                stg(row + nl_at(cnt, lane), (uint16_t)(o1 >> 2));
-                                if (inner(o1, t1)) {
-                                    const unsigned bit = 1u << (cnt & 31);
-                                    if (cnt < 32) pm0 |= bit;
-                                    else if (cnt < 64) pm1 |= bit;
-                                    else pm2 |= bit;
-                                    s_tf[o1 >> 2] = (unsigned char)(t1 | STAGE_USED);
-                                }
+                            stg(row + nl_at(cnt, lane), (uint16_t)(o1 >> 2));
+                            if (inner(o1, t1)) {
+                                const unsigned bit = 1u << (cnt & 31);
+                                if (cnt < 32) pm0 |= bit;
+                                else if (cnt < 64) pm1 |= bit;
+                                else pm2 |= bit;
+                                s_tf[o1 >> 2] = (unsigned char)(t1 | STAGE_USED);
                             }
                         }
-                        if (__builtin_expect(cnt <= MAXNB || level == NL_LEVELS, 1)) break;
-                        // more than a list holds: once more at the next level's radius
-                        ++level;
-                        auto shorter = [&](float r2) {
-                            const float r = sqrtf(r2) - P.nl_step;
-                            return r * r;
-                        };
-                        rlA = shorter(rlA);
-                        rlB = shorter(rlB);
-                        rlC = shorter(rlC);
-                        cnt = mygroups = 0;
-                        pm0 = pm1 = pm2 = 0u;
                     }
                 };
                 if (periodic) scan(std::true_type{});
                 else scan(std::false_type{});
+                // more than a list holds: once more, hit by hit, at the next level's radius (the
+                // code stays small: the kernel's loops run from the instruction cache)
+                float ra = rlA, rb = rlB, rc = rlC;
+#pragma unroll 1
+                while (__builtin_expect(cnt > MAXNB && level < NL_LEVELS, 0)) {
+                    ++level;
+                    auto shorter = [&](float r2) {
+                        const float r = sqrtf(r2) - P.nl_step;
+                        return r * r;
+                    };
+                    ra = shorter(ra);
+                    rb = shorter(rb);
+                    rc = shorter(rc);
+                    cnt = mygroups = 0;
+                    pm0 = pm1 = pm2 = 0u;
+#pragma unroll 1
+                    for (int c = 0; c < nl + np; ++c) {
+                        const int o = s_list[c < nl ? pf + c : pb - 1 - (c - nl)], t = s_tf[o >> 2] & 3;
+                        const float d2 = dist2f(ux(o), uy(o), uz(o), oix, oiy, oiz);
+                        if (!(d2 < sel3f(t, ra, rb, rc)) || o == oself) continue;
+                        if (cnt < MAXNB) {
+                            if ((cnt & 7) == 0) {
+                                stg(row8 + (cnt >> 3) * CHUNK, v4u{~0u, ~0u, ~0u, ~0u});
+                                mygroups = (cnt >> 3) + 1;
+                            }
+                            stg(row + nl_at(cnt, lane), (uint16_t)(o >> 2));
+                            if (d2 < sel3f(t, riA, riB, riC)) {
+                                const unsigned bit = 1u << (cnt & 31);
+                                if (cnt < 32) pm0 |= bit;
+                                else if (cnt < 64) pm1 |= bit;
+                                else pm2 |= bit;
+                                s_tf[o >> 2] = (unsigned char)(t | STAGE_USED);
+                            }
+                        }
+                        ++cnt;
+                    }
+                }
             }
             g0 += nfit;
         }
