@@ -154,7 +154,9 @@ rbc_status rbc_forces(rbc_handle h, double *F, double *T, double *energy);
 
 /* Advance nsteps of NVE velocity Verlet with time step dt (sync at the end).
  * Cells are updated every update_every steps and earlier when a particle
- * could move more than the skin. */
+ * could move more than the skin.  RBC_ERR_CAPACITY: the last list build left a
+ * particle with more list partners than a list holds, or a build of the call did and
+ * no shorter radius made room, so that steps ran without some pairs. */
 rbc_status rbc_step(rbc_handle h, int64_t nsteps, double dt);
 
 /* Copy the state out in caller order.  [device] n x 3 each; any may be NULL. */

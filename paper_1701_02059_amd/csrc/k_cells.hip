@@ -824,7 +824,7 @@ __device__ __forceinline__ Order order_of(const SysDev &S, int it) {
 // by k_centroids.)  Bound by its chain of dependent loads on small systems (125k particles:
 // 43.6 us with the widening search alone, 26.9 with the nine columns loaded together, 19.1
 // with each lane on its own ranges) and by vector instructions, about 23 per candidate, on
-// large ones (4M: 476, 359 and 238 us).
+// large ones (4M, a fresh cell: 476, 359 and 238 us; 213 once it has run).
 __global__ __launch_bounds__(BLOCK) void k_assign(const SysDev *Sd, Maps L_maps, int it, int warm) {
     SYS_FROM(p);
     if (!S.sc->rebuild) return;
@@ -1306,9 +1306,9 @@ __global__ void k_seed_permute(const SysDev *Sd, Maps L_maps, int ranks) {
 
 // The particles move to their renumbered cells, in the last iteration's order within a cell,
 // CELL_LANES lanes per cell (the whole block for cells of more than CMEM members; with `wide`
-// each cell has a block of its own, as in k_centroids_wide).  With the
-// members at hand, each cell's radius about its new centroid.  Bound by its scattered reads
-// of whole records (333 us for 0.8 GB at 4M particles).
+// each cell has a block of its own, as in k_centroids_wide).  With the members at hand, each
+// cell's radius about its new centroid.  Bound by its scattered reads of whole records (286 us
+// at 4M particles, for 0.8 GB of records that make 1.83 GB of traffic).
 __global__ __launch_bounds__(BLOCK) void k_move(const SysDev *Sd, Maps L_maps, int iters, int wide) {
     const int per = wide ? BLOCK : CB_BLOCKS;       // blocks to one of the cell map
     const int cbk = blockIdx.x / per;
@@ -1842,7 +1842,9 @@ __device__ __forceinline__ int union_cell(const int *ofs, int nsc, int u) {
 //    cell had left its block of a deformed 125k-particle vesicle without a stage: 6.4 ms
 //    instead of 1.5 ms per 20 steps.)  Blocks of more than 64 own cells take runs of them as
 //    one sphere each.  Where large cells, of which the block holds a part, pass more than the
-//    stage holds, a second pass keeps only what is also near the boxes of the block's chunks.
+//    stage holds, a second pass keeps only what is also near the boxes of the block's chunks
+//    (1M particles in cells of 1000: 24% of the blocks staged and 14.8 ms without it, 81% and
+//    7.5 ms with it).
 //  - Candidate lists: for each own cell the stage entries with its bit, compacted by one
 //    wavefront's ballots as 16-bit LDS offsets, lipids from the front, proteins from the
 //    back (neighbouring cells share a list where a block has more than 16).  Every
