@@ -47,9 +47,9 @@ PEAK_HBM = 8000.0           # GB/s
 # HBM traffic of that kernel per launch at the whole-cell workload, mixed precision,
 # skins 0.65 and 0.15: rocprofv3 FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 (KiB -> bytes; factors from a
 # plain 512 MiB device copy), valid only for the kernel sources whose digest is given.
-FORCE_TRAFFIC = {"sources_sha256": "87d6d07e7776bbfc", "skin": 0.65, "inner_skin": 0.15,
-                 "bytes": 1417161784, "fetch_kib": 504491, "write_kib": 374964,
-                 "valu_insts": 165817830}   # SQ_INSTS_VALU per launch (wavefront instructions)
+FORCE_TRAFFIC = {"sources_sha256": "389f0cbdaedd7ebf", "skin": 0.65, "inner_skin": 0.15,
+                 "bytes": 1416947073, "fetch_kib": 504389, "write_kib": 374959,
+                 "valu_insts": 165817832}   # SQ_INSTS_VALU per launch (wavefront instructions)
 BYTES_BUILD_READ = 25       # list build: position (3 x 8 B) and type (1 B) of every particle, read once
 CU_COUNT, SIMDS_PER_CU, CLOCK_GHZ = 256, 4, 2.4
 KERNEL_SOURCES = ("paper_1701_02059_amd/csrc/k_force.hip", "paper_1701_02059_amd/csrc/k_cells.hip",
