@@ -909,6 +909,7 @@ rbc_status step_all(rbc_ctx *h, int64_t nsteps, double dt) {
     const hipError_t le = hipGetLastError();
     if (le != hipSuccess) return fail(h, RBC_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(le));
     HIPCHK(hipStreamSynchronize(h->st));
+    settle();                         // the last entries are whole now, whatever was being written when they were read
     rbc_status e = RBC_OK;
     if (h->ensemble) {
         e = freeze_failed(h, slot_err);       // one slot's error freezes that slot only; the others have advanced nsteps
